@@ -33,14 +33,27 @@ size_t ctx_held_bytes(const mag_ctx *c)
     size_t sum = 0;
     for (const DevBuf *b : {&c->factor, &c->dinv, &c->vecs, &c->partial, &c->ints, &c->aux, &c->bfactor,
                             &c->bdinv, &c->bvec, &c->bscal, &c->bpartial, &c->bints, &c->bdesc, &c->barena,
-                            &c->bstage, &c->hodlr, &c->eig, &c->hss})
+                            &c->bstage, &c->hodlr, &c->eig, &c->hss, &c->split})
         sum += b->bytes;
     return sum;
 }
 
-int ctx_may_allocate(const mag_ctx *c, size_t extra)
+// Give up the split image (the factor runs without it), so that it never takes
+// room from a buffer a call cannot do without.
+static bool drop_split(mag_ctx *ctx)
+{
+    if (!ctx->split.p) return false;
+    hipStreamSynchronize(ctx->stream);
+    hipFree(ctx->split.p);
+    ctx->split.p = nullptr;
+    ctx->split.bytes = 0;
+    return true;
+}
+
+int ctx_may_allocate(mag_ctx *c, size_t extra)
 {
     if (c->ws_limit == 0) return MAG_OK;
+    if (ctx_held_bytes(c) + extra > c->ws_limit) drop_split(c);
     return ctx_held_bytes(c) + extra <= c->ws_limit ? MAG_OK : MAG_ENOMEM;
 }
 
@@ -48,21 +61,33 @@ int ensure(mag_ctx *ctx, DevBuf &b, size_t bytes)
 {
     if (bytes <= b.bytes) return MAG_OK;
     // the cap counts the buffer at its new size in place of its old one
-    if (ctx->ws_limit && ctx_held_bytes(ctx) - b.bytes + bytes > ctx->ws_limit) return MAG_ENOMEM;
+    const auto over = [&] { return ctx->ws_limit && ctx_held_bytes(ctx) - b.bytes + bytes > ctx->ws_limit; };
+    if (over() && (&b == &ctx->split || !drop_split(ctx) || over())) return MAG_ENOMEM;
     if (b.p) {
         if (hipStreamSynchronize(ctx->stream) != hipSuccess) return MAG_EHIP;
         hipFree(b.p);
         b.p = nullptr;
         b.bytes = 0;
     }
-    size_t want = bytes;
-    if (hipMalloc(&b.p, want) != hipSuccess) {
+    hipError_t e = hipMalloc(&b.p, bytes);
+    if (e != hipSuccess && &b != &ctx->split && drop_split(ctx)) {
+        (void)hipGetLastError();
+        e = hipMalloc(&b.p, bytes);
+    }
+    if (e != hipSuccess) {
         (void)hipGetLastError();
         b.p = nullptr;
         return MAG_ENOMEM;
     }
-    b.bytes = want;
+    b.bytes = bytes;
     return MAG_OK;
+}
+
+void *chol32_image(mag_ctx *ctx, int64_t npad, int nb)
+{
+    const size_t bytes = chol32_image_bytes(npad, nb);
+    if (bytes == 0) return nullptr;
+    return ensure(ctx, ctx->split, bytes) == MAG_OK ? ctx->split.p : nullptr;
 }
 
 }  // namespace mag
@@ -235,6 +260,8 @@ int factor_fp32(mag_ctx *ctx, const double *X, int64_t n, int m, double t, Facto
     double *hs = ctx->host_scalars;
     F.shift = 0.0;
     F.shifted = 0;
+    const int nb = panel_width(ctx, F.npad);
+    void *img = chol32_image(ctx, F.npad, nb);
     for (int attempt = 0;; ++attempt) {
         launch_fill_ints(s, status, 8, 0);
         // the tile generator also flags coincident points (Z singular)
@@ -244,7 +271,7 @@ int factor_fp32(mag_ctx *ctx, const double *X, int64_t n, int m, double t, Facto
             ft->used = 0;
             ft->flops.clear();
         }
-        chol32_factor(s, F.A, F.npad, n, F.dinv, status, ft, panel_width(ctx, F.npad));
+        chol32_factor(s, F.A, F.npad, n, F.dinv, status, ft, nb, img);
         HIPCHK(hipMemcpyAsync(hs, status, 8 * sizeof(int), hipMemcpyDeviceToHost, s));
         HIPCHK(hipStreamSynchronize(s));
         if (((const int *)hs)[kStDuplicate]) return MAG_ENOTPD;
@@ -1278,7 +1305,7 @@ void mag_destroy(mag_ctx *c)
     if (c->stream) hipStreamSynchronize(c->stream);
     for (DevBuf *b : {&c->factor, &c->dinv, &c->vecs, &c->partial, &c->ints, &c->aux, &c->bfactor,
                       &c->bdinv, &c->bvec, &c->bscal, &c->bpartial, &c->bints, &c->bdesc, &c->barena,
-                      &c->bstage, &c->hodlr, &c->eig, &c->hss})
+                      &c->bstage, &c->hodlr, &c->eig, &c->hss, &c->split})
         if (b->p) hipFree(b->p);
     if (c->bhost) hipHostFree(c->bhost);
     if (c->blas) rocblas_destroy_handle((rocblas_handle)c->blas);
@@ -1348,7 +1375,7 @@ int mag_autotune(mag_ctx *c, const double *X, int64_t n, int32_t m, double t, in
             launch_fill_ints(s, status, 8, 0);
             if (hipEventRecord(e0, s) != hipSuccess) { rc = MAG_EHIP; break; }
             launch_tilegen32(s, X, n, m, t, A, npad, 0.0f);
-            chol32_factor(s, A, npad, n, dinv, status, nullptr, widths[q]);
+            chol32_factor(s, A, npad, n, dinv, status, nullptr, widths[q], chol32_image(c, npad, widths[q]));
             float ms = 0.0f;
             if (hipEventRecord(e1, s) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
                 hipEventElapsedTime(&ms, e0, e1) != hipSuccess) {
@@ -1568,7 +1595,8 @@ int mag_factor32(mag_ctx *c, const double *X, int64_t n, int32_t m, double t, do
     int *status = (int *)c->ints.p;
     launch_fill_ints(c->stream, status, 8, 0);
     launch_tilegen32(c->stream, X, n, m, t, L, npad, (float)shift);
-    chol32_factor(c->stream, L, npad, n, dinv, status, nullptr, panel_width(c, npad));
+    const int nb = panel_width(c, npad);
+    chol32_factor(c->stream, L, npad, n, dinv, status, nullptr, nb, chol32_image(c, npad, nb));
     HIPCHK(hipMemcpyAsync(c->host_scalars, status, 8 * sizeof(int), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(hipStreamSynchronize(c->stream));
     if (breakdown) *breakdown = ((const int *)c->host_scalars)[kStBreakdown];

@@ -63,7 +63,7 @@ void factor_panel(hipStream_t s, float *A, int64_t npad, int64_t k, int64_t nb, 
 // update with K = 2 nb applies both panels to the rest.  Each tile of the large
 // trailing block is read and written once per two panels.
 void chol32_factor(hipStream_t s, float *A, int64_t npad, int64_t n, float *dinv, int *status,
-                   FactorTimer *timer, int nb_max)
+                   FactorTimer *timer, int nb_max, void *img)
 {
     const int64_t kNb = (nb_max == 256) ? 256 : 512;
     int64_t k = 0;
@@ -103,11 +103,22 @@ void chol32_factor(hipStream_t s, float *A, int64_t npad, int64_t n, float *dinv
                 timer->flops.push_back(nt > 0 ? (double)K * (double)nt * (double)(nt + 1) : 0.0);
                 hipEventRecord(e0, s);
             }
-            launch_syrk_lower(s, C, npad, P, npad, trail, K);
+            if (img) {
+                launch_split(s, P, npad, trail, K, img);
+                launch_syrk_split(s, C, npad, img, trail, K);
+            } else {
+                launch_syrk_lower(s, C, npad, P, npad, trail, K);
+            }
             if (timer) hipEventRecord(e1, s);
         }
         k = k3;
     }
+}
+
+size_t chol32_image_bytes(int64_t npad, int nb)
+{
+    const int64_t K = 2 * ((nb == 256) ? 256 : 512);
+    return npad > K ? split_image_bytes(npad - K, K) : 0;
 }
 
 int size_bucket(int64_t npad)

@@ -282,6 +282,7 @@ struct mag_ctx {
     mag::DevBuf hodlr;     // HODLR preconditioner workspace
     mag::DevBuf eig;       // Lanczos bases of the eigenvalue estimator
     mag::DevBuf hss;       // HSS approximation and ULV factor
+    mag::DevBuf split;     // BF16 split image of a panel (optional: given up when memory runs short)
     void *bhost = nullptr;   // pinned host staging for work lists and descriptors
     size_t bhost_bytes = 0;
     double *host_scalars = nullptr;  // pinned host staging (64 doubles)
@@ -308,8 +309,9 @@ namespace mag {
 int ensure(mag_ctx *ctx, DevBuf &b, size_t bytes);
 // Device bytes held by the context's buffers.
 size_t ctx_held_bytes(const mag_ctx *ctx);
-// MAG_OK if `extra` more device bytes stay within the context's cap.
-int ctx_may_allocate(const mag_ctx *ctx, size_t extra);
+// MAG_OK if `extra` more device bytes stay within the context's cap (the split
+// image is given up for them).
+int ctx_may_allocate(mag_ctx *ctx, size_t extra);
 // Coordinates finite and pairwise distinct (else MAG_EINVAL / MAG_ENOTPD); one host sync.
 // pairs = false checks finiteness only (the caller's FP32 tile generator checks the pairs).
 int check_points(mag_ctx *ctx, const double *X, int64_t n, int m, bool pairs = true);
@@ -321,9 +323,15 @@ struct FactorTimer {
     std::vector<double> flops;
     size_t used = 0;
 };
-// nb: panel width, 256 or 512 (npad is a multiple of 256)
+// nb: panel width, 256 or 512 (npad is a multiple of 256).  img: room for
+// chol32_image_bytes(npad, nb) bytes, or NULL: the trailing updates then run on
+// the FP32 matrix instruction.
 void chol32_factor(hipStream_t s, float *A, int64_t npad, int64_t n, float *dinv, int *status,
-                   FactorTimer *timer, int nb);
+                   FactorTimer *timer, int nb, void *img);
+size_t chol32_image_bytes(int64_t npad, int nb);
+// The context's buffer for that image, or NULL when the context's cap or the
+// device has no room for it.
+void *chol32_image(mag_ctx *ctx, int64_t npad, int nb);
 // panel width for npad on this context: the tuned entry of its size bucket, else 512
 int panel_width(const mag_ctx *ctx, int64_t npad);
 int size_bucket(int64_t npad);
@@ -368,6 +376,14 @@ void launch_gemm_rows64(hipStream_t s, float *C, int64_t ldc, const float *P, in
 // C (N x N, lower 128-tiles only) -= P P^T with P N x K; N multiple of 128.
 void launch_syrk_lower(hipStream_t s, float *C, int64_t ldc, const float *P, int64_t ldp,
                        int64_t N, int64_t K);
+
+// gemm_split.hip: the trailing update on the BF16 matrix cores, FP32 entries
+// split into three BF16 components.  The image of rows x K (column-major P)
+// takes split_image_bytes(rows, K); rows a multiple of 128, K of 16.
+size_t split_image_bytes(int64_t rows, int64_t K);
+void launch_split(hipStream_t s, const float *P, int64_t ldp, int64_t rows, int64_t K, void *img);
+// C (rows x rows, lower 128-tiles only) -= P P^T from the image of P
+void launch_syrk_split(hipStream_t s, float *C, int64_t ldc, const void *img, int64_t rows, int64_t K);
 
 // gemm64.hip: the FP64 factor's contractions, C (M x N) -= P Q^T (kGemmSub) or
 // C = P Q^T with C^T into CT (kGemmSetT); operands column-major as for
