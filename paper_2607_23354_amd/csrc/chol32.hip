@@ -29,14 +29,14 @@ namespace {
 
 // Steps 1-3 for the panel of nb columns at k (its trailing rows already updated
 // by every earlier panel).
-void factor_panel(hipStream_t s, float *A, int64_t npad, int64_t k, int64_t nb, float *dinv, int *status)
+void factor_panel(hipStream_t s, float *A, int64_t npad, int64_t n, int64_t k, int64_t nb, float *dinv, int *status)
 {
     const int64_t T = kTile;
     const int64_t nsub = nb / T;
     for (int64_t sub = 0; sub < nsub; ++sub) {
         const int64_t kk = k + sub * T;
         float *Linv = dinv + (kk / T) * T * T;
-        launch_potrf128(s, A, npad, kk, Linv, status);
+        launch_potrf128(s, A, npad, kk, n, Linv, status);
         const int64_t below = npad - kk - T;
         if (below > 0) {
             float *A21 = A + kk * npad + kk + T;
@@ -69,7 +69,7 @@ void chol32_factor(hipStream_t s, float *A, int64_t npad, int64_t n, float *dinv
     int64_t k = 0;
     while (k < npad) {
         const int64_t nb = std::min<int64_t>(kNb, npad - k);
-        factor_panel(s, A, npad, k, nb, dinv, status);
+        factor_panel(s, A, npad, n, k, nb, dinv, status);
         const int64_t k2 = k + nb;
         if (k2 >= npad) break;
         const int64_t nb2 = std::min<int64_t>(kNb, npad - k2);
@@ -80,7 +80,7 @@ void chol32_factor(hipStream_t s, float *A, int64_t npad, int64_t n, float *dinv
             const float *P = A + k * npad + k2;
             launch_gemm_rows64(s, C, npad, P, npad, P, npad, npad - k2, nb2, nb, kGemmSub);
         }
-        factor_panel(s, A, npad, k2, nb2, dinv, status);
+        factor_panel(s, A, npad, n, k2, nb2, dinv, status);
         const int64_t k3 = k2 + nb2;
         const int64_t trail = npad - k3;
         if (trail > 0) {

@@ -405,7 +405,8 @@ void chol64_factor(hipStream_t s, double *A, int64_t npad, int64_t n, double *di
 
 // potrf.hip: factor the 128 x 128 diagonal block at (k0, k0) of A in place and
 // write its inverse to Linv (128 x 128 column-major).  Breakdown -> status.
-void launch_potrf128(hipStream_t s, float *A, int64_t ld, int64_t k0, float *Linv, int *status);
+// n: rows from n on are identity padding (off-diagonal entries zero).
+void launch_potrf128(hipStream_t s, float *A, int64_t ld, int64_t k0, int64_t n, float *Linv, int *status);
 
 // gemv64.hip: FP64 matrix-free products with Z regenerated from X.
 //   mode 0: y = Z v;  mode 1: y = b - Z v (b may be NULL meaning ones) and
