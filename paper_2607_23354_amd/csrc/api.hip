@@ -1801,7 +1801,8 @@ int mag_tplus(mag_ctx *c, const double *X, int64_t n, int32_t m, const mag_tplus
         CHK(tplus_eval(c, X, n, m, tm, o, false, w_cur, cur, solves));
         CHK(take(cur));
         if (halted || (hi.t - lo.t) / hi.t <= to.rtol) break;
-        const double tx = std::exp(ridders_point(sa, ga, sb, gb, cur.minw));
+        const double tx = std::exp(step_past_root(ridders_point(sa, ga, sb, gb, cur.minw), std::log(lo.t),
+                                                  std::log(hi.t), to.rtol));
         if (!(tx > lo.t && tx < hi.t)) continue;
         CHK(tplus_eval(c, X, n, m, tx, o, false, w_cur, cur, solves));
         ++newton_steps;
@@ -1829,14 +1830,9 @@ int mag_tplus(mag_ctx *c, const double *X, int64_t n, int32_t m, const mag_tplus
             const double sn = sl - last.minw / (last.t * last.dmin_dt);
             const double step = std::fabs(sn - sl);
             if (sn > slo && sn < shi && (!prev_newton || step <= 0.5 * prev_step)) {
-                sc = sn;
                 use_newton = true;
                 prev_step = step;
-                // next to a bracket end: step just past the predicted root so
-                // that the bracket closes to rtol
-                const double close = 0.25 * to.rtol;
-                if (sc - slo < close) sc = std::min(slo + 0.75 * to.rtol, mid);
-                if (shi - sc < close) sc = std::max(shi - 0.75 * to.rtol, mid);
+                sc = step_past_root(sn, slo, shi, to.rtol);
             }
         }
         prev_newton = use_newton;

@@ -308,8 +308,8 @@ __global__ void k_search_select_b(BProb *__restrict__ P, SState *__restrict__ S,
         if (prm.ridders) {
             if (q.rid_pending) {
                 const double sx = ridders_point(q.ra, q.rga, q.rb, q.rgb, q.rgm);
-                if (sx > slo && sx < shi) {
-                    sc = sx;
+                if (sx >= slo && sx <= shi) {
+                    sc = step_past_root(sx, slo, shi, prm.rtol);
                     q.cur_kind = 2;
                 }
             }
@@ -326,12 +326,9 @@ __global__ void k_search_select_b(BProb *__restrict__ P, SState *__restrict__ S,
             const double sn = sl - q.last_min / (q.last_t * q.last_d);
             const double stp = fabs(sn - sl);
             if (sn > slo && sn < shi && (!q.prev_newton || stp <= 0.5 * q.prev_step)) {
-                sc = sn;
+                sc = step_past_root(sn, slo, shi, prm.rtol);
                 q.cur_newton = 1;
                 q.prev_step = stp;
-                const double close = 0.25 * prm.rtol;
-                if (sc - slo < close) sc = fmin(slo + 0.75 * prm.rtol, mid);
-                if (shi - sc < close) sc = fmax(shi - 0.75 * prm.rtol, mid);
             }
         }
         q.prev_newton = q.cur_newton;

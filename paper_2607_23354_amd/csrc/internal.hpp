@@ -505,6 +505,17 @@ __host__ __device__ inline double ridders_point(double sa, double ga, double sb,
     return fmin(fmax(sx, sa), sb);
 }
 
+// A predicted root s (in log t) next to an end of the bracket [s_lo, s_hi]: move it
+// just past the root, so that the bracket closes to rtol instead of shrinking from
+// one side only.
+__host__ __device__ inline double step_past_root(double s, double s_lo, double s_hi, double rtol)
+{
+    const double mid = 0.5 * (s_lo + s_hi), close = 0.25 * rtol;
+    if (s - s_lo < close) s = fmin(s_lo + 0.75 * rtol, mid);
+    if (s_hi - s < close) s = fmax(s_hi - 0.75 * rtol, mid);
+    return s;
+}
+
 int hodlr_max_leaf();
 int hodlr_default_leaf();
 int hodlr_max_cols();
