@@ -187,21 +187,27 @@ bool valid_args(const double *X, int64_t n, int32_t m, double t)
     return X != nullptr && n >= 1 && m >= 1 && std::isfinite(t) && t > 0.0;
 }
 
+// ctx->partial for the products over n points and `others` doubles of other
+// reductions; where memory is short, only what the products cannot do without.
+int ensure_partial(mag_ctx *ctx, int64_t n, size_t others)
+{
+    if (ensure(ctx, ctx->partial, sizeof(double) * (std::max(zmv_partial_doubles(n), others) + 64)) == MAG_OK)
+        return MAG_OK;
+    return ensure(ctx, ctx->partial, sizeof(double) * (std::max(zmv_min_partial_doubles(n), others) + 64));
+}
+
 int ensure_common(mag_ctx *ctx, int64_t n, int restart)
 {
     CHK(ensure(ctx, ctx->ints, sizeof(int) * kIntsTotal));
-    const int64_t npad = round_up(n, kPad);
-    size_t part = std::max(zmv_partial_doubles(n), blas1_partial_doubles(restart + 2));
-    part = std::max(part, dmin_partial_doubles(n) + 8);
-    CHK(ensure(ctx, ctx->partial, sizeof(double) * (part + 64)));
-    (void)npad;
-    return MAG_OK;
+    return ensure_partial(ctx, n, std::max(blas1_partial_doubles(restart + 2), dmin_partial_doubles(n) + 8));
 }
 
+size_t partial_cap(const mag_ctx *ctx) { return ctx->partial.bytes / sizeof(double); }
+
 struct Gmres {
-    int restart;
+    int restart = 0;
     std::vector<double> H;  // (restart+1) x restart, column-major
-    std::vector<double> cs, sn, g;
+    std::vector<double> cs, sn, g, hbuf;
 };
 
 // FP32 factor of Z (+ shift I) with its diagonal-block inverses.
@@ -243,96 +249,135 @@ int carve_vecs(mag_ctx *ctx, int64_t npad, int restart, Vecs &v)
 int ensure_solver(mag_ctx *ctx, int64_t n, int m, int restart)
 {
     CHK(ensure_common(ctx, n, restart));
-    size_t part = std::max(zmv_partial_doubles(n), pair_partial_doubles(n, m));
-    part = std::max(part, blas1_partial_doubles(restart + 2));
-    part = std::max(part, dmin_partial_doubles(n) + 8);
-    CHK(ensure(ctx, ctx->partial, sizeof(double) * (part + 64)));
-    return MAG_OK;
+    const size_t others = std::max(pair_partial_doubles(n, m), blas1_partial_doubles(restart + 2));
+    return ensure_partial(ctx, n, std::max(others, dmin_partial_doubles(n) + 8));
 }
 
-// Tile generation + blocked FP32 Cholesky, retried with a growing diagonal
-// shift when the FP32 factorisation meets a non-positive pivot.
+// Enqueue tile generation, the blocked FP32 Cholesky and the substitution's near
+// tiles, with the shift of F.
+void enqueue_factor(mag_ctx *ctx, const double *X, int64_t n, int m, double t, Factor32 &F, FactorTimer *ft,
+                    Timer *tm, int kernel)
+{
+    hipStream_t s = ctx->stream;
+    int *status = (int *)ctx->ints.p + kIntStatus;
+    const int nb = panel_width(ctx, F.npad);
+    void *img = chol32_image(ctx, F.npad, nb);
+    // the tile generator also flags non-finite coordinates and coincident points (Z singular)
+    launch_tilegen32(s, X, n, m, t, F.A, F.npad, (float)F.shift, status, kernel);
+    if (tm) tm->mark(1);
+    if (ft) {
+        ft->used = 0;
+        ft->flops.clear();
+    }
+    chol32_factor(s, F.A, F.npad, n, F.dinv, status, ft, nb, img);
+    launch_near_q(s, F.A, F.npad, F.dinv, F.nq);
+}
+
+// What the factor's status words ask for: MAG_OK, an error, or kRetry after a
+// non-positive pivot, with the next (growing) diagonal shift in F.
+constexpr int kRetry = 1;
+int factor_verdict(const int *st, int64_t n, int attempt, Factor32 &F)
+{
+    if (st[kStNonFinite]) return MAG_EINVAL;
+    if (st[kStDuplicate]) return MAG_ENOTPD;
+    if (st[kStBreakdown] == 0) return MAG_OK;
+    if (attempt >= 6) return MAG_ENOTPD;
+    F.shift = (F.shift == 0.0) ? 1e-6 * std::max<double>(1.0, std::sqrt((double)n)) : F.shift * 10.0;
+    F.shifted = 1;
+    return kRetry;
+}
+
+// The factor by itself, retried with a growing shift; one host round trip per attempt.
 int factor_fp32(mag_ctx *ctx, const double *X, int64_t n, int m, double t, Factor32 &F,
                 FactorTimer *ft, Timer *tm, int kernel = kKernExp)
 {
     hipStream_t s = ctx->stream;
     int *status = (int *)ctx->ints.p + kIntStatus;
-    double *hs = ctx->host_scalars;
     F.shift = 0.0;
     F.shifted = 0;
-    const int nb = panel_width(ctx, F.npad);
-    void *img = chol32_image(ctx, F.npad, nb);
     for (int attempt = 0;; ++attempt) {
-        launch_fill_ints(s, status, 8, 0);
-        // the tile generator also flags coincident points (Z singular)
-        launch_tilegen32(s, X, n, m, t, F.A, F.npad, (float)F.shift, status, kernel);
-        if (tm && attempt == 0) tm->mark(1);
-        if (ft) {
-            ft->used = 0;
-            ft->flops.clear();
-        }
-        chol32_factor(s, F.A, F.npad, n, F.dinv, status, ft, nb, img);
-        HIPCHK(hipMemcpyAsync(hs, status, 8 * sizeof(int), hipMemcpyDeviceToHost, s));
+        launch_fill_ints(s, status, kStCount, 0);
+        enqueue_factor(ctx, X, n, m, t, F, ft, attempt == 0 ? tm : nullptr, kernel);
+        HIPCHK(hipMemcpyAsync(ctx->host_scalars, status, kStCount * sizeof(int), hipMemcpyDeviceToHost, s));
         HIPCHK(hipStreamSynchronize(s));
-        if (((const int *)hs)[kStDuplicate]) return MAG_ENOTPD;
-        if (((const int *)hs)[kStBreakdown] == 0) break;
-        if (attempt >= 6) return MAG_ENOTPD;
-        F.shift = (F.shift == 0.0) ? 1e-6 * std::max<double>(1.0, std::sqrt((double)n)) : F.shift * 10.0;
-        F.shifted = 1;
+        const int rc = factor_verdict((const int *)ctx->host_scalars, n, attempt, F);
+        if (rc != kRetry) return rc;
     }
-    launch_near_q(s, F.A, F.npad, F.dinv, F.nq);
-    return MAG_OK;
 }
 
 struct RefineStats {
     int outer = 0, inner = 0;
     double resid = INFINITY;
+    // sum, min and argmin of the answer, where the solve has them already
+    bool have_sum = false;
+    double sum = 0.0, mn = 0.0;
+    int64_t am = -1;
+    int status[kStCount] = {};  // the status words of the first round trip
 };
 
 // Solve Z x = b (b: device npad vector, zero padded; NULL means the ones
 // vector of eq. weighting) by GMRES-based iterative refinement: FP64
 // residuals b - Z x with Z regenerated from X, corrections from GMRES on the
 // left-preconditioned system (L L^T)^{-1} Z d = (L L^T)^{-1} r.  The best
-// iterate goes to xout (device npad).  Stops when ||b - Z x||_inf <= tol *
-// max(1, ||b||_inf), on stagnation, or at the iteration limits.
+// iterate goes to xout (device, xlen entries: n or npad).  Stops when
+// ||b - Z x||_inf <= tol * max(1, ||b||_inf), on stagnation, or at the iteration
+// limits.
+//
+// x0 = M^{-1} b and one plain step x1 = x0 + M^{-1}(b - Z x0) are enqueued with
+// both residuals before the host looks at either: nearly every solve needs x1,
+// and most need no more, so such a solve is one round trip (the device writes
+// xout itself if x1 is the answer, launch_finish).  kRetry: the factor enqueued
+// before it (begun) broke down or saw bad points; see st.status.
 // prec(in, out, tmp): out = M^{-1} in for device npad vectors (tmp: npad scratch)
 using PrecFn = std::function<void(const double *, double *, double *)>;
 
 int refine_core(mag_ctx *ctx, const double *X, int64_t n, int m, double t, int64_t npad,
-                const PrecFn &prec, const double *b, double bnorm, double *xout, const mag_opts &o,
-                RefineStats &st, int kernel = kKernExp)
+                const PrecFn &prec, const double *b, double bnorm, double *xout, int64_t xlen, const mag_opts &o,
+                RefineStats &st, int kernel = kKernExp, bool begun = false)
 {
     hipStream_t s = ctx->stream;
     const int restart = std::max(1, o.gmres_restart);
     Vecs v;
     CHK(carve_vecs(ctx, npad, restart, v));
     double *partial = (double *)ctx->partial.p;
+    const size_t cap = partial_cap(ctx);
     int *ints = (int *)ctx->ints.p;
     int *status = ints + kIntStatus;
-    double *hs = ctx->host_scalars;
+    const double *rep = ctx->report;
     const double tol = (o.tol > 0 ? o.tol : 1e-12) * std::max(1.0, bnorm);
     // FP32 entries in the inner products: the correction equation is then solved
     // for an operator within ~1e-7 of Z, so asking GMRES for more than 1e-6 is wasted
     const bool f32_inner = o.inner_prec == MAG_INNER_FP32 && m <= 16 && kernel == kKernExp;
     const double inner_tol = std::max(o.inner_tol > 0 ? o.inner_tol : 1e-10, f32_inner ? 1e-6 : 0.0);
     const int max_gmres = o.max_gmres > 0 ? o.max_gmres : 200;
+    const int max_outer = std::max(1, o.max_outer);
 
-    const double *bb = b;
-    if (!bb) {
-        launch_fill(s, v.rhs, npad, 0.0);
-        launch_fill(s, v.rhs, n, 1.0);
-        bb = v.rhs;
+    if (!begun) launch_refine_begin(s, v.ytmp, b ? nullptr : v.rhs, n, npad, ints + kIntCounters, status);
+    const double *bb = b ? b : v.rhs;
+    // the current iterate and a spare buffer (the best iterate is one of the two),
+    // its residual and a work vector
+    double *cur = v.x, *spare = v.best, *best = nullptr;
+    double *r = v.r, *u = v.u;
+    // x0 = M^{-1} b, and the plain step from it
+    prec(bb, cur, v.ytmp);
+    launch_zmv(s, X, n, m, t, cur, r, bb, 1, partial, cap, v.dsc, false, kernel);
+    const bool spec = max_outer >= 2;
+    if (spec) {
+        prec(r, v.z, v.ytmp);
+        launch_add(s, cur, v.z, spare, npad);
+        launch_zmv(s, X, n, m, t, spare, u, bb, 1, partial, cap, v.dsc + 1, false, kernel);
+        launch_finish(s, spare, n, v.dsc, status, tol, partial, xout, xlen, ctx->report_dev);
+    } else {
+        launch_norm_report(s, v.dsc, status, ctx->report_dev);
     }
-    // x0 = M^{-1} b
-    prec(bb, v.x, v.ytmp);
+    HIPCHK(hipStreamSynchronize(s));
+    const double r0 = spec ? rep[3] : rep[0], r1 = rep[4];
+    std::memcpy(st.status, spec ? rep + 5 : rep + 1, sizeof(st.status));
+    if (st.status[kStNonFinite] || st.status[kStDuplicate] || st.status[kStBreakdown]) return kRetry;
+    if (st.status[kStSpinTimeout]) return MAG_EINTERNAL;
+    st.have_sum = false;
 
     Gmres G;
-    G.restart = restart;
-    G.H.assign((size_t)(restart + 1) * restart, 0.0);
-    G.cs.assign(restart, 0.0);
-    G.sn.assign(restart, 0.0);
-    G.g.assign(restart + 1, 0.0);
-    std::vector<double> hbuf(2 * (restart + 2) + 2);
     double rnorm = INFINITY, best_norm = INFINITY;
     int rc = MAG_ENOCONV;
     int outer = 0, inner_total = 0;
@@ -342,52 +387,75 @@ int refine_core(mag_ctx *ctx, const double *X, int64_t n, int m, double t, int64
     // iteration restarts from the best iterate with GMRES corrections.
     bool plain = true, last_plain = false;
     auto residual = [&]() -> int {
-        launch_zmv(s, X, n, m, t, v.x, v.r, bb, 1, partial, v.dsc, false, kernel);
-        HIPCHK(hipMemcpyAsync(hs, v.dsc, sizeof(double), hipMemcpyDeviceToHost, s));
-        HIPCHK(hipMemcpyAsync(hs + 8, status, 8 * sizeof(int), hipMemcpyDeviceToHost, s));
+        launch_zmv(s, X, n, m, t, cur, r, bb, 1, partial, cap, v.dsc, false, kernel);
+        launch_norm_report(s, v.dsc, status, ctx->report_dev);
         HIPCHK(hipStreamSynchronize(s));
-        if (((const int *)(hs + 8))[kStSpinTimeout]) return MAG_EINTERNAL;
+        if (((const int *)(rep + 1))[kStSpinTimeout]) return MAG_EINTERNAL;
+        rnorm = rep[0];
         return MAG_OK;
     };
-    for (outer = 0; outer < std::max(1, o.max_outer); ++outer) {
-        CHK(residual());
+    bool ahead = false;  // the current iterate is x1, its residual in u
+    for (outer = 0; outer < max_outer; ++outer) {
         const double prev = rnorm;
-        rnorm = hs[0];
+        if (outer == 0) {
+            rnorm = r0;
+        } else if (ahead) {
+            rnorm = r1;
+            std::swap(r, u);
+        } else {
+            CHK(residual());
+        }
+        const bool was_ahead = ahead;
+        ahead = false;
         bool reverted = false;
         if (!(rnorm < best_norm)) {
             if (!last_plain) break;  // no progress: keep the best iterate
             // the plain step did not help: back to the best iterate, GMRES from there
             plain = last_plain = false;
             reverted = true;
-            launch_copy(s, v.best, v.x, npad);
-            if (++outer >= std::max(1, o.max_outer)) break;
+            std::swap(cur, spare);
+            if (++outer >= max_outer) break;
             CHK(residual());
-            rnorm = hs[0];
         } else {
             best_norm = rnorm;
-            launch_copy(s, v.x, v.best, npad);
+            best = cur;
         }
         if (rnorm <= tol) {
             rc = MAG_OK;
+            st.have_sum = was_ahead;
             break;
         }
         if (last_plain && rnorm > 1e-2 * prev) plain = false;
         else if (!last_plain && !reverted && outer > 0 && rnorm > 0.5 * prev) break;  // stagnation
         if (inner_total >= max_gmres) break;
         if (plain) {
-            prec(v.r, v.z, v.ytmp);
-            launch_axpy1(s, v.z, v.x, npad);
+            if (outer == 0 && spec) {
+                ahead = true;
+            } else {
+                prec(r, v.z, v.ytmp);
+                launch_add(s, cur, v.z, spare, npad);
+            }
+            std::swap(cur, spare);
             ++inner_total;
             last_plain = true;
             continue;
         }
         last_plain = false;
         // GMRES(restart) on M^{-1} Z d = M^{-1} r, d0 = 0
-        prec(v.r, v.z, v.ytmp);
+        if (G.H.empty()) {
+            G.restart = restart;
+            G.H.resize((size_t)(restart + 1) * restart);
+            G.cs.assign(restart, 0.0);
+            G.sn.assign(restart, 0.0);
+            G.g.resize(restart + 1);
+            G.hbuf.resize(2 * (restart + 2) + 2);
+        }
+        std::vector<double> &hbuf = G.hbuf;
+        prec(r, v.z, v.ytmp);
         launch_nrm2(s, v.z, npad, partial, v.dsc + 1);
-        HIPCHK(hipMemcpyAsync(hs + 1, v.dsc + 1, sizeof(double), hipMemcpyDeviceToHost, s));
+        HIPCHK(hipMemcpyAsync(ctx->host_scalars + 1, v.dsc + 1, sizeof(double), hipMemcpyDeviceToHost, s));
         HIPCHK(hipStreamSynchronize(s));
-        const double beta = hs[1];
+        const double beta = ctx->host_scalars[1];
         if (!(beta > 0.0) || !std::isfinite(beta)) break;
         launch_scale_inv(s, v.z, v.V, npad, v.dsc + 1);
         std::fill(G.H.begin(), G.H.end(), 0.0);
@@ -397,13 +465,13 @@ int refine_core(mag_ctx *ctx, const double *X, int64_t n, int m, double t, int64
         for (int k = 0; k < restart && inner_total < max_gmres; ++k) {
             double *Vk = v.V + (size_t)k * npad;
             double *Vk1 = v.V + (size_t)(k + 1) * npad;
-            launch_zmv(s, X, n, m, t, Vk, v.u, nullptr, 0, partial, nullptr, f32_inner, kernel);
-            prec(v.u, Vk1, v.ytmp);
+            launch_zmv(s, X, n, m, t, Vk, u, nullptr, 0, partial, cap, nullptr, f32_inner, kernel);
+            prec(u, Vk1, v.ytmp);
             // classical Gram-Schmidt, twice
             launch_multidot(s, v.V, npad, k + 1, Vk1, npad, partial, v.hdev);
-            launch_multi_axpy(s, v.V, npad, k + 1, v.hdev, Vk1, npad, -1.0);
+            launch_multi_axpy(s, v.V, npad, k + 1, v.hdev, Vk1, Vk1, npad, -1.0);
             launch_multidot(s, v.V, npad, k + 1, Vk1, npad, partial, v.hdev + (k + 1));
-            launch_multi_axpy(s, v.V, npad, k + 1, v.hdev + (k + 1), Vk1, npad, -1.0);
+            launch_multi_axpy(s, v.V, npad, k + 1, v.hdev + (k + 1), Vk1, Vk1, npad, -1.0);
             launch_nrm2(s, Vk1, npad, partial, v.hdev + 2 * (k + 1));
             HIPCHK(hipMemcpyAsync(hbuf.data(), v.hdev, sizeof(double) * (2 * (k + 1) + 1),
                                   hipMemcpyDeviceToHost, s));
@@ -437,9 +505,17 @@ int refine_core(mag_ctx *ctx, const double *X, int64_t n, int m, double t, int64
             y[i] = acc / G.H[(size_t)i * (restart + 1) + i];
         }
         HIPCHK(hipMemcpyAsync(v.hdev, y.data(), sizeof(double) * kdone, hipMemcpyHostToDevice, s));
-        launch_multi_axpy(s, v.V, npad, kdone, v.hdev, v.x, npad, 1.0);
+        launch_multi_axpy(s, v.V, npad, kdone, v.hdev, cur, spare, npad, 1.0);
+        std::swap(cur, spare);
     }
-    if (xout != v.best) launch_copy(s, v.best, xout, npad);
+    if (!st.have_sum) {
+        launch_copy(s, best ? best : v.x, xout, xlen);
+        HIPCHK(hipStreamSynchronize(s));
+    } else {
+        st.sum = rep[0];
+        st.mn = rep[1];
+        st.am = (int64_t)rep[2];
+    }
     st.outer = outer + (rc == MAG_OK ? 1 : 0);
     st.inner = inner_total;
     st.resid = best_norm;
@@ -448,8 +524,8 @@ int refine_core(mag_ctx *ctx, const double *X, int64_t n, int m, double t, int64
 
 // GMRES-IR with the FP32 Cholesky factor F as the preconditioner (L L^T)^{-1}.
 int refine_solve(mag_ctx *ctx, const double *X, int64_t n, int m, double t, const Factor32 &F,
-                 const double *b, double bnorm, double *xout, const mag_opts &o, RefineStats &st,
-                 int kernel = kKernExp)
+                 const double *b, double bnorm, double *xout, int64_t xlen, const mag_opts &o, RefineStats &st,
+                 int kernel = kKernExp, bool begun = false)
 {
     int *ints = (int *)ctx->ints.p;
     int *status = ints + kIntStatus;
@@ -458,20 +534,52 @@ int refine_solve(mag_ctx *ctx, const double *X, int64_t n, int m, double t, cons
     const PrecFn prec = [&](const double *in, double *out, double *tmp) {
         launch_prec_apply(s, F.A, F.npad, F.dinv, in, tmp, out, counters, status, F.nq, spin_limit_of(ctx));
     };
-    return refine_core(ctx, X, n, m, t, F.npad, prec, b, bnorm, xout, o, st, kernel);
+    const int rc = refine_core(ctx, X, n, m, t, F.npad, prec, b, bnorm, xout, xlen, o, st, kernel, begun);
+    return (rc == kRetry && !begun) ? MAG_EINTERNAL : rc;
+}
+
+// Factor Z(t) into F and solve Z x = 1 with it, without a round trip between the
+// two; retried with a growing diagonal shift after a non-positive pivot.
+// MAG_EINVAL: non-finite coordinates; MAG_ENOTPD: coincident points.
+int factor_and_solve(mag_ctx *ctx, const double *X, int64_t n, int m, double t, Factor32 &F, double *xout,
+                     int64_t xlen, const mag_opts &o, RefineStats &st, FactorTimer *ft = nullptr,
+                     Timer *tm = nullptr)
+{
+    int *ints = (int *)ctx->ints.p;
+    Vecs v;
+    CHK(carve_vecs(ctx, F.npad, std::max(1, o.gmres_restart), v));
+    F.shift = 0.0;
+    F.shifted = 0;
+    for (int attempt = 0;; ++attempt) {
+        launch_refine_begin(ctx->stream, v.ytmp, v.rhs, n, F.npad, ints + kIntCounters, ints + kIntStatus);
+        enqueue_factor(ctx, X, n, m, t, F, ft, attempt == 0 ? tm : nullptr, kKernExp);
+        if (tm) tm->mark(2);
+        int rc = refine_solve(ctx, X, n, m, t, F, nullptr, 1.0, xout, xlen, o, st, kKernExp, true);
+        if (rc != kRetry) return rc;
+        rc = factor_verdict(st.status, n, attempt, F);
+        if (rc != kRetry) return rc;
+    }
 }
 
 // sum, min, argmin of w[0..n) -> host
 int summarize(mag_ctx *ctx, const double *w, int64_t n, double &sum, double &mn, int64_t &am)
 {
     hipStream_t s = ctx->stream;
-    double *dsc = (double *)ctx->partial.p + blas1_partial_doubles(3);
-    launch_sum_min(s, w, n, (double *)ctx->partial.p, dsc);
-    HIPCHK(hipMemcpyAsync(ctx->host_scalars + 32, dsc, 3 * sizeof(double), hipMemcpyDeviceToHost, s));
+    launch_sum_min(s, w, n, (double *)ctx->partial.p, ctx->report_dev);
     HIPCHK(hipStreamSynchronize(s));
-    sum = ctx->host_scalars[32];
-    mn = ctx->host_scalars[33];
-    am = (int64_t)ctx->host_scalars[34];
+    sum = ctx->report[0];
+    mn = ctx->report[1];
+    am = (int64_t)ctx->report[2];
+    return MAG_OK;
+}
+
+// the same of a solve's answer w, which may have it already
+int summarize(mag_ctx *ctx, const RefineStats &st, const double *w, int64_t n, double &sum, double &mn, int64_t &am)
+{
+    if (!st.have_sum) return summarize(ctx, w, n, sum, mn, am);
+    sum = st.sum;
+    mn = st.mn;
+    am = st.am;
     return MAG_OK;
 }
 
@@ -512,7 +620,7 @@ int diag_backward(mag_ctx *ctx, const double *X, int64_t n, int m, double t, con
     double *partial = (double *)ctx->partial.p;
     double *dsc = aux + 4 * npad;
     launch_affine_ones(s, nullptr, 1.0, aux, n, npad);
-    launch_zmv(s, X, n, m, t, aux, aux + npad, nullptr, 0, partial, nullptr);
+    launch_zmv(s, X, n, m, t, aux, aux + npad, nullptr, 0, partial, partial_cap(ctx), nullptr);
     launch_amax(s, aux + npad, npad, partial, dsc);
     launch_amax(s, w, n, partial, dsc + 1);
     HIPCHK(hipMemcpyAsync(ctx->host_scalars + 48, dsc, 2 * sizeof(double), hipMemcpyDeviceToHost, s));
@@ -545,19 +653,17 @@ int solve_fp32_ir(mag_ctx *ctx, const double *X, int64_t n, int m, double t, dou
     tm.start(o.profile != 0, s);
     FactorTimer ft;
     tm.mark(0);
-    CHK(factor_fp32(ctx, X, n, m, t, F, o.profile ? &ft : nullptr, &tm));
-    if (keepF) *keepF = F;
-    tm.mark(2);
-    Vecs v;
-    CHK(carve_vecs(ctx, F.npad, restart, v));
     RefineStats st;
-    int rc = refine_solve(ctx, X, n, m, t, F, nullptr, 1.0, v.best, o, st);
-    if (rc != MAG_OK && rc != MAG_ENOCONV) return rc;
+    int rc = factor_and_solve(ctx, X, n, m, t, F, w, n, o, st, o.profile ? &ft : nullptr, &tm);
+    if (keepF) *keepF = F;
+    if (rc != MAG_OK && rc != MAG_ENOCONV) {
+        for (auto e : ft.ev) hipEventDestroy(e);
+        return rc;
+    }
     tm.mark(3);
-    launch_copy(s, v.best, w, n);
     double sum, mn;
     int64_t am;
-    CHK(summarize(ctx, v.best, n, sum, mn, am));
+    CHK(summarize(ctx, st, w, n, sum, mn, am));
     tm.mark(4);
     if (info) {
         info->outer_iters = st.outer;
@@ -591,7 +697,7 @@ int solve_fp32_ir(mag_ctx *ctx, const double *X, int64_t n, int m, double t, dou
             oi.tol = 1e-6;
             const SolveOp inv = [&](const double *in, double *out) -> int {
                 RefineStats s2;
-                const int r2 = refine_solve(ctx, X, n, m, t, F, in, 1.0, out, oi, s2);
+                const int r2 = refine_solve(ctx, X, n, m, t, F, in, 1.0, out, F.npad, oi, s2);
                 return r2 == MAG_ENOCONV ? MAG_OK : r2;
             };
             CHK(diag_cond(ctx, X, n, m, t, inv, info->cond_est));
@@ -640,7 +746,7 @@ int solve_fp64_dense(mag_ctx *ctx, const double *X, int64_t n, int m, double t, 
     if (*(const int *)(hs + 16) != 0) return MAG_ENOTPD;
     if (info) {
         // diagnostics: residual (FP64 matrix-free) and magnitude
-        launch_zmv(s, X, n, m, t, w, r, nullptr, 1, partial, dsc + 4);
+        launch_zmv(s, X, n, m, t, w, r, nullptr, 1, partial, partial_cap(ctx), dsc + 4);
         HIPCHK(hipMemcpyAsync(hs + 5, dsc + 4, sizeof(double), hipMemcpyDeviceToHost, s));
         launch_sum_min(s, w, n, partial, dsc);
         HIPCHK(hipMemcpyAsync(hs + 2, dsc, 3 * sizeof(double), hipMemcpyDeviceToHost, s));
@@ -705,7 +811,7 @@ int solve_fp64_chol(mag_ctx *ctx, const double *X, int64_t n, int m, double t, d
     tm.mark(1);
     chol64_factor(s, A, npad, n, dinv, status, o.profile ? &ft : nullptr);
     tm.mark(2);
-    launch_affine_ones(s, nullptr, 1.0, rhs, n, npad);
+    launch_refine_begin(s, ytmp, rhs, n, npad, ints + kIntCounters, nullptr);
     launch_chol64_solve(s, A, npad, dinv, rhs, ytmp, z, ints + kIntCounters, status, spin_limit_of(ctx));
     HIPCHK(hipMemcpyAsync(w, z, sizeof(double) * n, hipMemcpyDeviceToDevice, s));
     tm.mark(3);
@@ -719,7 +825,7 @@ int solve_fp64_chol(mag_ctx *ctx, const double *X, int64_t n, int m, double t, d
     }
     if (rc == MAG_OK && info) {
         // diagnostics: residual (FP64 matrix-free) and magnitude
-        launch_zmv(s, X, n, m, t, w, z, nullptr, 1, partial, dsc + 4);
+        launch_zmv(s, X, n, m, t, w, z, nullptr, 1, partial, partial_cap(ctx), dsc + 4);
         HIPCHK(hipMemcpyAsync(hs + 5, dsc + 4, sizeof(double), hipMemcpyDeviceToHost, s));
         launch_sum_min(s, w, n, partial, dsc);
         HIPCHK(hipMemcpyAsync(hs + 2, dsc, 3 * sizeof(double), hipMemcpyDeviceToHost, s));
@@ -781,17 +887,14 @@ int solve_hodlr(mag_ctx *ctx, const double *X, int64_t n, int m, double t, doubl
                      o.seed, H));
     tm.mark(1);
     tm.mark(2);
-    Vecs v;
-    CHK(carve_vecs(ctx, H.npad, restart, v));
     const PrecFn prec = [&](const double *in, double *out, double *) { hodlr_apply(s, H, in, out); };
     RefineStats st;
-    int rc = refine_core(ctx, X, n, m, t, H.npad, prec, nullptr, 1.0, v.best, o, st);
+    int rc = refine_core(ctx, X, n, m, t, H.npad, prec, nullptr, 1.0, w, n, o, st);
     if (rc != MAG_OK && rc != MAG_ENOCONV) return rc;
     tm.mark(3);
-    launch_copy(s, v.best, w, n);
     double sum, mn;
     int64_t am;
-    CHK(summarize(ctx, v.best, n, sum, mn, am));
+    CHK(summarize(ctx, st, w, n, sum, mn, am));
     tm.mark(4);
     if (info) {
         info->outer_iters = st.outer;
@@ -813,7 +916,7 @@ int solve_hodlr(mag_ctx *ctx, const double *X, int64_t n, int m, double t, doubl
             oi.tol = 1e-6;
             const SolveOp inv = [&](const double *in, double *out) -> int {
                 RefineStats s2;
-                const int r2 = refine_core(ctx, X, n, m, t, H.npad, prec, in, 1.0, out, oi, s2);
+                const int r2 = refine_core(ctx, X, n, m, t, H.npad, prec, in, 1.0, out, H.npad, oi, s2);
                 return r2 == MAG_ENOCONV ? MAG_OK : r2;
             };
             CHK(diag_cond(ctx, X, n, m, t, inv, info->cond_est));
@@ -842,22 +945,19 @@ int solve_hss(mag_ctx *ctx, const double *X, int64_t n, int m, double t, double 
     }
     tm.mark(1);
     tm.mark(2);
-    Vecs v;
-    CHK(carve_vecs(ctx, H.npad, restart, v));
     int prc = MAG_OK;
     const PrecFn prec = [&](const double *in, double *out, double *) {
         const int e = hss_apply(s, H, in, out);
         if (e != MAG_OK) prc = e;
     };
     RefineStats st;
-    int rc = refine_core(ctx, X, n, m, t, H.npad, prec, nullptr, 1.0, v.best, o, st);
+    int rc = refine_core(ctx, X, n, m, t, H.npad, prec, nullptr, 1.0, w, n, o, st);
     if (prc != MAG_OK) return prc;
     if (rc != MAG_OK && rc != MAG_ENOCONV) return rc;
     tm.mark(3);
-    launch_copy(s, v.best, w, n);
     double sum, mn;
     int64_t am;
-    CHK(summarize(ctx, v.best, n, sum, mn, am));
+    CHK(summarize(ctx, st, w, n, sum, mn, am));
     tm.mark(4);
     if (info) {
         info->outer_iters = st.outer;
@@ -879,7 +979,7 @@ int solve_hss(mag_ctx *ctx, const double *X, int64_t n, int m, double t, double 
             oi.tol = 1e-6;
             const SolveOp inv = [&](const double *in, double *out) -> int {
                 RefineStats s2;
-                const int r2 = refine_core(ctx, X, n, m, t, H.npad, prec, in, 1.0, out, oi, s2);
+                const int r2 = refine_core(ctx, X, n, m, t, H.npad, prec, in, 1.0, out, H.npad, oi, s2);
                 if (prc != MAG_OK) return prc;
                 return r2 == MAG_ENOCONV ? MAG_OK : r2;
             };
@@ -908,6 +1008,7 @@ bool auto_dense(mag_ctx *ctx, int64_t n)
     const double npad = (double)round_up(n, kPad);
     const double need = 4.0 * npad * npad;
     if (ctx->ws_limit && need > (double)ctx->ws_limit) return false;
+    if ((double)ctx->factor.bytes >= need) return true;
     if (hipMemGetInfo(&fr, &tot) != hipSuccess) return true;
     return need <= 0.75 * ((double)fr + (double)ctx->factor.bytes);
 }
@@ -925,7 +1026,7 @@ int dwdt_with_factor(mag_ctx *ctx, const double *X, int64_t n, int m, double t, 
     launch_amax(s, aux, F.npad, partial, amax);
     HIPCHK(hipMemcpyAsync(ctx->host_scalars + 40, amax, sizeof(double), hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
-    return refine_solve(ctx, X, n, m, t, F, aux, ctx->host_scalars[40], out, o, st);
+    return refine_solve(ctx, X, n, m, t, F, aux, ctx->host_scalars[40], out, F.npad, o, st);
 }
 
 int ensure_aux(mag_ctx *ctx, int64_t npad)
@@ -1053,9 +1154,9 @@ int lanczos_top(mag_ctx *ctx, int64_t npad, const std::function<int(const double
         double *qj1 = Q + (size_t)(j + 1) * npad;
         CHK(op(qj, u));
         launch_multidot(s, Q, npad, j + 1, u, npad, partial, dev);
-        launch_multi_axpy(s, Q, npad, j + 1, dev, u, npad, -1.0);
+        launch_multi_axpy(s, Q, npad, j + 1, dev, u, u, npad, -1.0);
         launch_multidot(s, Q, npad, j + 1, u, npad, partial, dev + (j + 1));
-        launch_multi_axpy(s, Q, npad, j + 1, dev + (j + 1), u, npad, -1.0);
+        launch_multi_axpy(s, Q, npad, j + 1, dev + (j + 1), u, u, npad, -1.0);
         launch_nrm2(s, u, npad, partial, dev + 2 * (j + 1));
         HIPCHK(hipMemcpyAsync(hbuf.data(), dev, sizeof(double) * (2 * (j + 1) + 1), hipMemcpyDeviceToHost, s));
         HIPCHK(hipStreamSynchronize(s));
@@ -1100,7 +1201,7 @@ int diag_cond(mag_ctx *ctx, const double *X, int64_t n, int m, double t, const S
     HIPCHK(hipStreamSynchronize(s));
     const double q0norm = ctx->host_scalars[50];
     const SolveOp zop = [&](const double *in, double *out) -> int {
-        launch_zmv(s, X, n, m, t, in, out, nullptr, 0, partial, nullptr);
+        launch_zmv(s, X, n, m, t, in, out, nullptr, 0, partial, partial_cap(ctx), nullptr);
         return MAG_OK;
     };
     LanczosResult top, bot;
@@ -1156,18 +1257,15 @@ int tplus_deriv(mag_ctx *ctx, const double *X, int64_t n, int m, const mag_opts 
 int tplus_eval(mag_ctx *ctx, const double *X, int64_t n, int m, double t, const mag_opts &o,
                bool deriv, double *dst, TEval &ev, int &solves)
 {
-    const int restart = std::max(1, o.gmres_restart);
     Factor32 F = ctx_factor(ctx, n);
-    CHK(factor_fp32(ctx, X, n, m, t, F, nullptr, nullptr));
     RefineStats st;
-    int rc = refine_solve(ctx, X, n, m, t, F, nullptr, 1.0, dst, o, st);
+    int rc = factor_and_solve(ctx, X, n, m, t, F, dst, F.npad, o, st);
     if (rc != MAG_OK && rc != MAG_ENOCONV) return rc;
     ++solves;
     double sum;
-    CHK(summarize(ctx, dst, n, sum, ev.minw, ev.arg));
+    CHK(summarize(ctx, st, dst, n, sum, ev.minw, ev.arg));
     ev.t = t;
     ev.has_deriv = false;
-    (void)restart;
     if (deriv) return tplus_deriv(ctx, X, n, m, o, dst, ev);
     return MAG_OK;
 }
@@ -1277,11 +1375,18 @@ int mag_create(mag_ctx **out, int device)
         return MAG_EHIP;
     }
     c->stream = c->own_stream;
-    if (hipHostMalloc((void **)&c->host_scalars, 64 * sizeof(double), hipHostMallocDefault) != hipSuccess) {
+    // 64 doubles of copies, then 16 that kernels write (a solve's norms, status words
+    // and summary)
+    void *dev = nullptr;
+    if (hipHostMalloc((void **)&c->host_scalars, 80 * sizeof(double), hipHostMallocDefault) != hipSuccess ||
+        hipHostGetDevicePointer(&dev, c->host_scalars, 0) != hipSuccess) {
+        if (c->host_scalars) hipHostFree(c->host_scalars);
         hipStreamDestroy(c->own_stream);
         delete c;
         return MAG_EHIP;
     }
+    c->report = c->host_scalars + 64;
+    c->report_dev = (double *)dev + 64;
     int cus = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) == hipSuccess && cus > 0)
         c->cu_count = cus;
@@ -1474,9 +1579,10 @@ int mag_weighting(mag_ctx *c, const double *X, int64_t n, int32_t m, double t, d
     // MAG_AUTO: the HODLR preconditioner above the measured crossover, the dense
     // FP32 factor below it or when the HODLR solve does not converge
     const bool auto_hodlr = o.solver == MAG_AUTO && n > kAutoHodlrMinN && m <= 16;
-    // the FP32 path's tile generator checks the pairs itself (no separate O(n^2) pass)
-    const bool fp32 = o.solver == MAG_FP32_IR || (o.solver == MAG_AUTO && !auto_hodlr);
-    int rc = check_points(c, X, n, m, !fp32);
+    // the FP32 path's tile generator checks the points itself (no pass and no round trip
+    // of their own)
+    const bool fp32 = o.solver == MAG_FP32_IR || (o.solver == MAG_AUTO && !auto_hodlr && auto_dense(c, n));
+    int rc = (fp32 && n > 1) ? MAG_OK : check_points(c, X, n, m, o.solver != MAG_AUTO || auto_hodlr);
     if (rc == MAG_OK && n == 1) {
         launch_fill(c->stream, w, 1, 1.0);
         HIPCHK(hipStreamSynchronize(c->stream));
@@ -1502,7 +1608,7 @@ int mag_weighting(mag_ctx *c, const double *X, int64_t n, int32_t m, double t, d
                 CHK(ensure_common(c, n, oh.gmres_restart));
                 rc = solve_hodlr(c, X, n, m, t, w, oh, info);
                 if (rc == MAG_ENOCONV && auto_dense(c, n)) rc = solve_fp32_ir(c, X, n, m, t, w, o, info);
-            } else if (auto_dense(c, n)) {
+            } else if (fp32) {
                 rc = solve_fp32_ir(c, X, n, m, t, w, o, info);
             } else {
                 rc = MAG_ENOMEM;
@@ -1552,7 +1658,7 @@ int mag_zmatvec(mag_ctx *c, const double *X, int64_t n, int32_t m, double t, con
     const int64_t npad = round_up(n, kPad);
     CHK(ensure(c, c->vecs, sizeof(double) * ((size_t)npad + 256)));
     double *ybuf = (double *)c->vecs.p;
-    launch_zmv(c->stream, X, n, m, t, v, ybuf, nullptr, 0, (double *)c->partial.p, nullptr);
+    launch_zmv(c->stream, X, n, m, t, v, ybuf, nullptr, 0, (double *)c->partial.p, partial_cap(c), nullptr);
     HIPCHK(hipMemcpyAsync(y, ybuf, sizeof(double) * n, hipMemcpyDeviceToDevice, c->stream));
     HIPCHK(hipStreamSynchronize(c->stream));
     return MAG_OK;
@@ -1568,7 +1674,7 @@ int mag_residual(mag_ctx *c, const double *X, int64_t n, int32_t m, double t, co
     CHK(ensure(c, c->vecs, sizeof(double) * ((size_t)npad + 256)));
     double *rbuf = (double *)c->vecs.p;
     double *dsc = rbuf + npad;
-    launch_zmv(c->stream, X, n, m, t, w, rbuf, nullptr, 1, (double *)c->partial.p, dsc);
+    launch_zmv(c->stream, X, n, m, t, w, rbuf, nullptr, 1, (double *)c->partial.p, partial_cap(c), dsc);
     HIPCHK(hipMemcpyAsync(r, rbuf, sizeof(double) * n, hipMemcpyDeviceToDevice, c->stream));
     HIPCHK(hipMemcpyAsync(c->host_scalars, dsc, sizeof(double), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(hipStreamSynchronize(c->stream));
@@ -1622,6 +1728,7 @@ int mag_prec_apply(mag_ctx *c, const float *L, const float *dinv, int64_t n, con
     launch_fill(c->stream, rb, npad, 0.0);
     HIPCHK(hipMemcpyAsync(rb, r, sizeof(double) * n, hipMemcpyDeviceToDevice, c->stream));
     launch_near_q(c->stream, L, npad, dinv, nq);
+    launch_refine_begin(c->stream, yt, nullptr, n, npad, ints + kIntCounters, nullptr);
     launch_prec_apply(c->stream, L, npad, dinv, rb, yt, zb, ints + kIntCounters, ints, nq, spin_limit_of(c));
     HIPCHK(hipMemcpyAsync(z, zb, sizeof(double) * n, hipMemcpyDeviceToDevice, c->stream));
     HIPCHK(hipMemcpyAsync(c->host_scalars, ints, 8 * sizeof(int), hipMemcpyDeviceToHost, c->stream));
@@ -1661,6 +1768,7 @@ int mag_chol64_solve(mag_ctx *c, const double *L, const double *dinv, int64_t n,
     launch_fill_ints(c->stream, ints, 8, 0);
     launch_fill(c->stream, rb, npad, 0.0);
     HIPCHK(hipMemcpyAsync(rb, r, sizeof(double) * n, hipMemcpyDeviceToDevice, c->stream));
+    launch_refine_begin(c->stream, yt, nullptr, n, npad, ints + kIntCounters, nullptr);
     launch_chol64_solve(c->stream, L, npad, dinv, rb, yt, zb, ints + kIntCounters, ints, spin_limit_of(c));
     HIPCHK(hipMemcpyAsync(z, zb, sizeof(double) * n, hipMemcpyDeviceToDevice, c->stream));
     HIPCHK(hipMemcpyAsync(c->host_scalars, ints, 8 * sizeof(int), hipMemcpyDeviceToHost, c->stream));
@@ -1702,6 +1810,7 @@ int mag_tplus(mag_ctx *c, const double *X, int64_t n, int32_t m, const mag_tplus
     CHK(ensure_solver(c, n, m, restart));
     int rc = check_points(c, X, n, m);
     if (rc != MAG_OK) return rc;
+    const double dmin = std::sqrt(c->host_scalars[8]);  // left by check_points (n >= 2)
     *t_plus = 0.0;
     if (n <= 2) {
         // one or two points: w > 0 for every t (w_j = 1/(1 + e^{-td}))
@@ -1715,8 +1824,6 @@ int mag_tplus(mag_ctx *c, const double *X, int64_t n, int32_t m, const mag_tplus
     const int64_t npad = round_up(n, kPad);
     CHK(ensure_ctx_factor(c, n));
     CHK(ensure_aux(c, npad));
-    double dmin = 0.0;
-    CHK(mag_dmin(c, X, n, m, &dmin));
     const double tb = std::log((double)(n - 1)) / dmin;
     const double eps = to.eps > 0.0 ? to.eps : (double)n * std::ldexp(1.0, -53);
     double *w_hi = (double *)c->aux.p + 3 * npad;  // weighting at the current upper end
@@ -1880,16 +1987,14 @@ int mag_dwdt(mag_ctx *c, const double *X, int64_t n, int32_t m, double t, double
     else mag_opts_default(&o);
     const int restart = std::max(1, o.gmres_restart);
     CHK(ensure_solver(c, n, m, restart));
-    CHK(check_points(c, X, n, m));
     const int64_t npad = round_up(n, kPad);
     CHK(ensure_ctx_factor(c, n));
     CHK(ensure_aux(c, npad));
     Factor32 F = ctx_factor(c, n);
-    CHK(factor_fp32(c, X, n, m, t, F, nullptr, nullptr));
     double *wv = (double *)c->aux.p + npad;
     double *d = (double *)c->aux.p + 2 * npad;
     RefineStats st;
-    int rc = refine_solve(c, X, n, m, t, F, nullptr, 1.0, wv, o, st);
+    int rc = factor_and_solve(c, X, n, m, t, F, wv, npad, o, st);
     if (rc != MAG_OK) return rc;
     rc = dwdt_with_factor(c, X, n, m, t, F, wv, d, o, st);
     if (rc != MAG_OK) return rc;
@@ -1956,13 +2061,14 @@ int mag_weighting_zero(mag_ctx *c, const double *X, int64_t n, int32_t m, double
     Vecs v;
     CHK(carve_vecs(c, F.npad, restart, v));
     RefineStats st;
-    const int rc = refine_solve(c, X, n, m, cs, F, nullptr, 1.0, v.best, o, st, kKernShiftDist);
+    double *u = v.V;  // the Krylov basis is free once the solve is done
+    const int rc = refine_solve(c, X, n, m, cs, F, nullptr, 1.0, u, n, o, st, kKernShiftDist);
     if (rc != MAG_OK && rc != MAG_ENOCONV) return rc;
     double beta, mn;
     int64_t am;
-    CHK(summarize(c, v.best, n, beta, mn, am));
+    CHK(summarize(c, st, u, n, beta, mn, am));
     if (!(beta != 0.0) || !std::isfinite(beta)) return MAG_EINTERNAL;
-    launch_scale(s, v.best, 1.0 / beta, w, n, n);
+    launch_scale(s, u, 1.0 / beta, w, n, n);
     double sw;
     CHK(summarize(c, w, n, sw, mn, am));
     if (info) {
@@ -2036,7 +2142,7 @@ int mag_eig_extremes(mag_ctx *c, const double *X, int64_t n, int32_t m, double t
     // lambda_max: Lanczos on Z (matrix-free FP64 products)
     LanczosResult top;
     const auto zop = [&](const double *in, double *out) -> int {
-        launch_zmv(s, X, n, m, t, in, out, nullptr, 0, partial, nullptr);
+        launch_zmv(s, X, n, m, t, in, out, nullptr, 0, partial, partial_cap(c), nullptr);
         return MAG_OK;
     };
     launch_scale(s, q0, 1.0 / q0norm, Q, npad, npad);
@@ -2048,7 +2154,7 @@ int mag_eig_extremes(mag_ctx *c, const double *X, int64_t n, int32_t m, double t
     int solve_steps = 0, solve_rc = MAG_OK;
     const auto iop = [&](const double *in, double *out) -> int {
         RefineStats st;
-        const int rc = refine_solve(c, X, n, m, t, F, in, 1.0, out, o, st);
+        const int rc = refine_solve(c, X, n, m, t, F, in, 1.0, out, npad, o, st);
         solve_steps += st.outer;
         if (rc == MAG_ENOCONV) {
             solve_rc = rc;
@@ -2085,7 +2191,7 @@ int mag_weighting_fwd(mag_ctx *c, const double *X, int64_t n, int32_t m, double 
     if (opts) o = *opts;
     else mag_opts_default(&o);
     CHK(ensure_solver(c, n, m, std::max(1, o.gmres_restart)));
-    CHK(check_points(c, X, n, m));
+    if (n == 1) CHK(check_points(c, X, n, m, false));  // else the factor checks the points
     {
         const size_t np = (size_t)round_up(n, kPad);
         CHK(ctx_may_allocate(c, sizeof(float) * (np * np + np * kTile + near_q_floats(np))));
@@ -2156,7 +2262,7 @@ int mag_weighting_vjp(mag_ctx *c, mag_factor *f, const double *X, int64_t n, int
         HIPCHK(hipMemcpyAsync(c->host_scalars + 42, amax, sizeof(double), hipMemcpyDeviceToHost, s));
         HIPCHK(hipStreamSynchronize(s));
         RefineStats st;
-        int rc = refine_solve(c, X, n, m, t, f->F, rhs, c->host_scalars[42], lam, o, st);
+        int rc = refine_solve(c, X, n, m, t, f->F, rhs, c->host_scalars[42], lam, npad, o, st);
         if (rc != MAG_OK) return rc;
     } else {
         launch_scale(s, wv, gM, lam, n, npad);  // lambda = gM w

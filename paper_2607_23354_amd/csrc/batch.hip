@@ -67,6 +67,7 @@ struct Batch {
     std::vector<BProb> h;  // host copy of the descriptors
     BProb *d = nullptr;    // device descriptors
     int64_t maxpad = 0, maxn = 0;
+    int ts = 128;          // edge of the products' symmetric tiles
     // arenas for work lists: persistent (the factorisation schedule) + transient
     char *dev_arena = nullptr, *host_arena = nullptr;
     size_t arena_bytes = 0, persist_used = 0, trans_used = 0;
@@ -157,9 +158,9 @@ struct Batch {
 };
 
 // split-reduction doubles of one problem: products, derivatives, dot products, d_min
-size_t batch_partial_doubles(int64_t n, int restart)
+size_t batch_partial_doubles(int64_t n, int restart, int ts)
 {
-    size_t p = std::max(zmv_partial_doubles(n), pair_partial_doubles(n, 1));
+    size_t p = std::max(zmv_b_partial_doubles(n, ts), pair_partial_doubles(n, 1));
     p = std::max(p, blas1_partial_doubles(restart + 2));
     p = std::max(p, dmin_partial_doubles(n) + 8);
     return p + 64;
@@ -175,14 +176,15 @@ int batch_setup(mag_ctx *c, Batch &bt, const std::vector<const double *> &Xs,
     bt.m = m;
     bt.sl = slots_for(restart);
     const int B = bt.B;
-    size_t fac = 0, dv = 0, vec = 0, part = 0;
+    size_t fac = 0, dv = 0, vec = 0;
+    int64_t tiles = 0;
     std::vector<int64_t> np(B);
     for (int b = 0; b < B; ++b) {
         np[b] = round_up(ns[b], kPad);
         fac += (size_t)np[b] * np[b];
         dv += (size_t)np[b] * kTile;
         vec += (size_t)bt.sl.n * np[b];
-        part += batch_partial_doubles(ns[b], restart);
+        tiles += np[b] / 128 * (np[b] / 128 + 1) / 2;
         bt.maxpad = std::max(bt.maxpad, np[b]);
         bt.maxn = std::max(bt.maxn, ns[b]);
     }
@@ -190,7 +192,16 @@ int batch_setup(mag_ctx *c, Batch &bt, const std::vector<const double *> &Xs,
     BRC(ensure(c, c->bdinv, sizeof(float) * dv));
     BRC(ensure(c, c->bvec, sizeof(double) * vec));
     BRC(ensure(c, c->bscal, sizeof(double) * (size_t)B * SC_COUNT));
-    BRC(ensure(c, c->bpartial, sizeof(double) * part));
+    bt.ts = zmv_b_tile(tiles);
+    const auto part = [&] {
+        size_t p = 0;
+        for (int b = 0; b < B; ++b) p += batch_partial_doubles(ns[b], restart, bt.ts);
+        return sizeof(double) * p;
+    };
+    if (ensure(c, c->bpartial, part()) != MAG_OK) {
+        bt.ts = 128;  // the least they can do with
+        BRC(ensure(c, c->bpartial, part()));
+    }
     BRC(ensure(c, c->bints, sizeof(int) * (size_t)B * kIntsPer));
     BRC(ensure(c, c->bdesc, sizeof(BProb) * B));
     BRC(ensure(c, c->bstage, sizeof(double) * ((size_t)B * 128 + 64)));
@@ -229,7 +240,7 @@ int batch_setup(mag_ctx *c, Batch &bt, const std::vector<const double *> &Xs,
         vp += (size_t)bt.sl.n * np[b];
         q.scal = (double *)c->bscal.p + (size_t)b * SC_COUNT;
         q.partial = pp;
-        pp += batch_partial_doubles(ns[b], restart);
+        pp += batch_partial_doubles(ns[b], restart, bt.ts);
         q.ints = (int *)c->bints.p + (size_t)b * kIntsPer;
         q.m = m;
         q.active = 1;
@@ -237,7 +248,9 @@ int batch_setup(mag_ctx *c, Batch &bt, const std::vector<const double *> &Xs,
     BCHK(hipMemsetAsync(c->bvec.p, 0, sizeof(double) * vec, bt.s));
     BCHK(hipMemsetAsync(c->bscal.p, 0, sizeof(double) * (size_t)B * SC_COUNT, bt.s));
     BCHK(hipMemsetAsync(c->bints.p, 0, sizeof(int) * (size_t)B * kIntsPer, bt.s));
-    return bt.upload_desc();
+    BRC(bt.upload_desc());
+    launch_prec_begin_b(bt.s, bt.d, B, bt.sl.Y);
+    return MAG_OK;
 }
 
 // The factorisation schedule of all problems (work lists in the persistent
@@ -360,8 +373,8 @@ int batch_refine(Batch &bt, const std::vector<int> &ids, int rhs_slot, const std
         st[p].g.assign(R + 1, 0.0);
     }
     auto prec_units = [&](int p) { return prec_b_units(bt.h[p].npad); };
-    auto zmv_units = [&](int p) { return zmv_b_units(bt.h[p].n, bt.m); };
-    auto red_units = [&](int p) { return zmv_b_reduce_units(bt.h[p].n, bt.m); };
+    auto zmv_units = [&](int p) { return zmv_b_units(bt.h[p].n, bt.m, bt.ts); };
+    auto red_units = [&](int p) { return zmv_b_reduce_units(bt.h[p].n, bt.m, bt.ts); };
     auto one = [&](int) { return (int64_t)1; };
 
     // x0 = M^{-1} b
@@ -380,7 +393,7 @@ int batch_refine(Batch &bt, const std::vector<int> &ids, int rhs_slot, const std
         BRC(bt.make_work(L, zmv_units, false, wz));
         BRC(bt.make_work(L, red_units, false, wr));
         BRC(bt.make_work(L, one, false, w1));
-        launch_zmv_b(bt.s, bt.m, bt.d, wz, wr, S.X, S.Rr, rhs_slot, 1, SC_RNORM);
+        launch_zmv_b(bt.s, bt.m, bt.d, wz, wr, S.X, S.Rr, rhs_slot, 1, SC_RNORM, bt.ts);
         BRC(bt.gather(w1.plist, w1.na, SC_RNORM, 1, hv));
         std::vector<int> G;        // problems that improved (>= 0: and take a correction)
         std::vector<int> revert;   // plain step without progress: back to the best iterate
@@ -488,7 +501,7 @@ int batch_refine(Batch &bt, const std::vector<int> &ids, int rhs_slot, const std
             BRC(bt.make_work(act, red_units, false, ar));
             BRC(bt.make_work(act, prec_units, false, ap));
             BRC(bt.make_work(act, one, false, a1));
-            launch_zmv_b(bt.s, bt.m, bt.d, az, ar, S.V0 + k, S.U, -1, 0, 0);
+            launch_zmv_b(bt.s, bt.m, bt.d, az, ar, S.V0 + k, S.U, -1, 0, 0, bt.ts);
             launch_prec_apply_b(bt.s, bt.d, ap, S.U, S.Y, S.V0 + k + 1);
             launch_multidot_b(bt.s, bt.d, a1.plist, a1.na, S.V0, k + 1, S.V0 + k + 1, SC_H);
             launch_multi_axpy_b(bt.s, bt.d, a1.plist, a1.na, bt.maxpad, S.V0, k + 1, SC_H, S.V0 + k + 1, -1.0);
@@ -568,8 +581,8 @@ int make_all_work(Batch &bt, AllWork &A)
 {
     std::vector<int> all(bt.B);
     for (int b = 0; b < bt.B; ++b) all[b] = b;
-    BRC(bt.make_work(all, [&](int p) { return zmv_b_units(bt.h[p].n, bt.m); }, true, A.wz));
-    BRC(bt.make_work(all, [&](int p) { return zmv_b_reduce_units(bt.h[p].n, bt.m); }, true, A.wr));
+    BRC(bt.make_work(all, [&](int p) { return zmv_b_units(bt.h[p].n, bt.m, bt.ts); }, true, A.wz));
+    BRC(bt.make_work(all, [&](int p) { return zmv_b_reduce_units(bt.h[p].n, bt.m, bt.ts); }, true, A.wr));
     BRC(bt.make_work(all, [&](int p) { return prec_b_units(bt.h[p].npad); }, true, A.wp));
     BRC(bt.make_work(all, [&](int p) { return dz_b_units(bt.h[p].n); }, true, A.wdz));
     BRC(bt.make_work(all, [&](int p) { return bt.h[p].npad / 256; }, true, A.wdr));
@@ -600,7 +613,7 @@ void record_refine(Batch &bt, const AllWork &A, int rhs_slot, int64_t bnorm_off,
     for (int round = 0; round <= rp.rounds; ++round) {
         const int final_round = round == rp.rounds ? 1 : 0;
         launch_gate_b(s, P, B, F_REF);
-        launch_zmv_b(s, bt.m, P, A.wz, A.wr, S.X, S.Rr, rhs_slot, 1, SC_RNORM);
+        launch_zmv_b(s, bt.m, P, A.wz, A.wr, S.X, S.Rr, rhs_slot, 1, SC_RNORM, bt.ts);
         launch_ref_decide_b(s, P, B, final_round, rp.max_gmres);
         launch_gate_b(s, P, B, F_COPYBEST);
         launch_copy_b(s, P, A.all, B, mp, S.X, S.Best);
@@ -623,7 +636,7 @@ void record_refine(Batch &bt, const AllWork &A, int rhs_slot, int64_t bnorm_off,
         launch_scale_inv_b(s, P, A.all, B, mp, S.Z, S.V0, SC_BETA);
         for (int k = 0; k < rp.kcycle; ++k) {
             launch_gate_b(s, P, B, F_INNER);
-            launch_zmv_b(s, bt.m, P, A.wz, A.wr, S.V0 + k, S.U, -1, 0, 0);
+            launch_zmv_b(s, bt.m, P, A.wz, A.wr, S.V0 + k, S.U, -1, 0, 0, bt.ts);
             launch_prec_apply_b(s, P, A.wp, S.U, S.Y, S.V0 + k + 1);
             launch_arnoldi_b(s, P, B, k, S.V0, rp.kcycle, rp.inner_tol, rp.max_gmres);
         }

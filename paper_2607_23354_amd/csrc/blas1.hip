@@ -45,11 +45,11 @@ __global__ void k_copy(const double *x, double *y, int64_t len)
         y[i] = x[i];
 }
 
-__global__ void k_axpy1(const double *x, double *y, int64_t len)
+__global__ void k_add(const double *x, const double *y, double *z, int64_t len)
 {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < len;
          i += (int64_t)gridDim.x * blockDim.x)
-        y[i] += x[i];
+        z[i] = x[i] + y[i];
 }
 
 __global__ void k_scale_inv(const double *x, double *y, int64_t len, const double *alpha)
@@ -86,14 +86,14 @@ __global__ void __launch_bounds__(RB) k_rows_sum(const double *partial, int k, d
     }
 }
 
-__global__ void k_multi_axpy(const double *V, int64_t ld, int k, const double *h, double *u,
+__global__ void k_multi_axpy(const double *V, int64_t ld, int k, const double *h, const double *u0, double *u,
                              int64_t len, double sign)
 {
     for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < len;
          e += (int64_t)gridDim.x * blockDim.x) {
         double s = 0.0;
         for (int i = 0; i < k; ++i) s = fma(h[i], V[(int64_t)i * ld + e], s);
-        u[e] = fma(sign, s, u[e]);
+        u[e] = fma(sign, s, u0[e]);
     }
 }
 
@@ -116,12 +116,42 @@ __global__ void __launch_bounds__(RB) k_sqrt_sum(const double *partial, double *
     if (threadIdx.x == 0) out[0] = sqrt(s);
 }
 
-// partial[3g] = sum, [3g+1] = min, [3g+2] = argmin (as double) over chunk g
-__global__ void __launch_bounds__(RB) k_summin_partial(const double *x, int64_t n, double *partial)
+// What a summary's final pass also does for a speculated solve (launch_finish).
+struct Finish {
+    const double *norms;  // max norms of the residuals of x0 and x1 (NULL: no solve)
+    const int *status;    // the solve's status words
+    double tol;
+};
+
+// x1 is the answer: nothing went wrong, x0 did not meet tol and x1 does (and is
+// the better of the two)
+__device__ inline bool accepted(const Finish &f)
+{
+    for (int e = 0; e < kStCount; ++e)
+        if (f.status[e] != 0) return false;
+    const double r0 = f.norms[0], r1 = f.norms[1];
+    return r0 > f.tol && r0 < INFINITY && r1 < r0 && r1 <= f.tol;
+}
+
+// out[0] = norm, out[1..4] the status words (out may be host memory)
+__global__ void k_norm_report(const double *norm, const int *status, double *out)
+{
+    if (threadIdx.x == 0) out[0] = norm[0];
+    if (threadIdx.x < kStCount) reinterpret_cast<int *>(out + 1)[threadIdx.x] = status[threadIdx.x];
+}
+
+// partial[3g] = sum, [3g+1] = min, [3g+2] = argmin (as double) over chunk g.
+// dst (optional): x copied to it if the solve's x1 is accepted; entries [n, len)
+// are zero in x too.
+__global__ void __launch_bounds__(RB)
+k_summin_partial(const double *x, int64_t n, double *partial, Finish f, double *dst, int64_t len)
 {
     __shared__ double red[RB];
     __shared__ double rmin[RB];
     __shared__ int64_t rarg[RB];
+    if (dst && accepted(f)) {
+        for (int64_t e = blockIdx.x * (int64_t)RB + threadIdx.x; e < len; e += (int64_t)gridDim.x * RB) dst[e] = x[e];
+    }
     const int64_t chunk = (n + RG - 1) / RG;
     const int64_t lo = blockIdx.x * chunk, hi = min(n, lo + chunk);
     double s = 0.0, mn = INFINITY;
@@ -152,23 +182,41 @@ __global__ void __launch_bounds__(RB) k_summin_partial(const double *x, int64_t 
     }
 }
 
-__global__ void k_summin_final(const double *partial, double *out)
+// The RG block results to out[0..2]: the sums by a tree of error-free
+// transformations (Knuth's two-sum, the errors summed beside), one block sum per
+// thread (a loop of one thread over them took 22 us).  With f.norms: out[3..4]
+// the norms and out[5..8] the status words, for one read by the host.
+__global__ void __launch_bounds__(RG) k_summin_final(const double *partial, double *out, Finish f)
 {
-    if (threadIdx.x != 0) return;
-    double s = 0.0, c = 0.0, mn = INFINITY, am = -1.0;
-    for (int g = 0; g < RG; ++g) {
-        // Neumaier-compensated accumulation of the block sums
-        const double x = partial[3 * g];
-        const double u = s + x;
-        c += (fabs(s) >= fabs(x)) ? ((s - u) + x) : ((x - u) + s);
-        s = u;
-        const double v = partial[3 * g + 1];
-        const double a = partial[3 * g + 2];
-        if (v < mn || (v == mn && a >= 0 && (am < 0 || a < am))) { mn = v; am = a; }
+    __shared__ double rs[RG], rc[RG], rmin[RG], ram[RG];
+    const int t = threadIdx.x;
+    rs[t] = partial[3 * t];
+    rc[t] = 0.0;
+    rmin[t] = partial[3 * t + 1];
+    ram[t] = partial[3 * t + 2];
+    __syncthreads();
+    for (int w = RG / 2; w > 0; w >>= 1) {
+        if (t < w) {
+            const double a = rs[t], b = rs[t + w], u = a + b, z = u - a;
+            rc[t] = (rc[t] + rc[t + w]) + ((a - (u - z)) + (b - z));
+            rs[t] = u;
+            const double v = rmin[t + w], i = ram[t + w];
+            if (v < rmin[t] || (v == rmin[t] && i >= 0 && (ram[t] < 0 || i < ram[t]))) {
+                rmin[t] = v;
+                ram[t] = i;
+            }
+        }
+        __syncthreads();
     }
-    out[0] = s + c;
-    out[1] = mn;
-    out[2] = am;
+    if (t == 0) {
+        out[0] = rs[0] + rc[0];
+        out[1] = rmin[0];
+        out[2] = ram[0];
+    }
+    if (f.norms) {
+        if (t < 2) out[3 + t] = f.norms[t];
+        if (t < kStCount) reinterpret_cast<int *>(out + 5)[t] = f.status[t];
+    }
 }
 
 __global__ void __launch_bounds__(RB) k_amax_partial(const double *x, int64_t len, double *partial)
@@ -472,9 +520,9 @@ void launch_copy(hipStream_t s, const double *x, double *y, int64_t len)
 {
     hipLaunchKernelGGL(k_copy, dim3(grid_for(len)), dim3(256), 0, s, x, y, len);
 }
-void launch_axpy1(hipStream_t s, const double *x, double *y, int64_t len)
+void launch_add(hipStream_t s, const double *x, const double *y, double *z, int64_t len)
 {
-    hipLaunchKernelGGL(k_axpy1, dim3(grid_for(len)), dim3(256), 0, s, x, y, len);
+    hipLaunchKernelGGL(k_add, dim3(grid_for(len)), dim3(256), 0, s, x, y, z, len);
 }
 void launch_scale_inv(hipStream_t s, const double *x, double *y, int64_t len, const double *alpha)
 {
@@ -487,9 +535,9 @@ void launch_multidot(hipStream_t s, const double *V, int64_t ld, int k, const do
     hipLaunchKernelGGL(k_rows_sum, dim3(1), dim3(RB), 0, s, partial, k, h);
 }
 void launch_multi_axpy(hipStream_t s, const double *V, int64_t ld, int k, const double *h,
-                       double *u, int64_t len, double sign)
+                       const double *u0, double *u, int64_t len, double sign)
 {
-    hipLaunchKernelGGL(k_multi_axpy, dim3(grid_for(len)), dim3(256), 0, s, V, ld, k, h, u, len, sign);
+    hipLaunchKernelGGL(k_multi_axpy, dim3(grid_for(len)), dim3(256), 0, s, V, ld, k, h, u0, u, len, sign);
 }
 void launch_nrm2(hipStream_t s, const double *x, int64_t len, double *partial, double *out)
 {
@@ -498,8 +546,19 @@ void launch_nrm2(hipStream_t s, const double *x, int64_t len, double *partial, d
 }
 void launch_sum_min(hipStream_t s, const double *x, int64_t n, double *partial, double *out)
 {
-    hipLaunchKernelGGL(k_summin_partial, dim3(RG), dim3(RB), 0, s, x, n, partial);
-    hipLaunchKernelGGL(k_summin_final, dim3(1), dim3(64), 0, s, partial, out);
+    hipLaunchKernelGGL(k_summin_partial, dim3(RG), dim3(RB), 0, s, x, n, partial, Finish{}, nullptr, (int64_t)0);
+    hipLaunchKernelGGL(k_summin_final, dim3(1), dim3(RG), 0, s, partial, out, Finish{});
+}
+void launch_finish(hipStream_t s, const double *x, int64_t n, const double *norms, const int *status, double tol,
+                   double *partial, double *dst, int64_t len, double *out)
+{
+    const Finish f{norms, status, tol};
+    hipLaunchKernelGGL(k_summin_partial, dim3(RG), dim3(RB), 0, s, x, n, partial, f, dst, len);
+    hipLaunchKernelGGL(k_summin_final, dim3(1), dim3(RG), 0, s, partial, out, f);
+}
+void launch_norm_report(hipStream_t s, const double *norm, const int *status, double *out)
+{
+    hipLaunchKernelGGL(k_norm_report, dim3(1), dim3(64), 0, s, norm, status, out);
 }
 
 void launch_amax(hipStream_t s, const double *x, int64_t len, double *partial, double *out)

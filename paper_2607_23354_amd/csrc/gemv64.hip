@@ -191,7 +191,8 @@ __device__ __forceinline__ double zexp_tab(double t, double s, const double2 *T)
     return exp_tab(-(t * sqrt_pos(fmin(fmax(s, 1.0e-300), 1.0e300))), T);
 }
 
-constexpr int TS = 128;       // symmetric tile edge
+constexpr int TSB = 128;      // symmetric tile edge
+constexpr int TSS = 64;       // the same for small n, where 128-tiles leave most CUs idle
 constexpr int kEntExp = 0, kEntExp32 = 1, kEntShiftDist = 2;
 constexpr int MMAX_SYM = 16;  // largest dimension of the symmetric product
 
@@ -205,19 +206,20 @@ __device__ inline void tri_tile(int64_t idx, int64_t &I, int64_t &J)
     J = idx - r * (r + 1) / 2;
 }
 
-// One lower tile (I, J) of Z per workgroup; thread (ty, tx) owns rows 8 ty ..
-// and columns 8 tx .. of the tile.  part[tile * 2 TS + p]: row sums
+// One lower tile (I, J) of Z per workgroup; thread (ty, tx) owns the TS / 16
+// rows from TS / 16 ty and as many columns of the tile.  part[tile * 2 TS + p]: row sums
 // sum_c Z(r0 + p, c) v_c over the tile's columns; part[tile * 2 TS + TS + p]:
 // column sums sum_r Z(r, c0 + p) v_r (off-diagonal tiles only; a diagonal
 // tile is summed over its full square as rows).  M > 0: compile-time m.
 // ENT: the entry, kEntExp exp(-t d) in FP64, kEntExp32 the same in FP32 (sums in
 // FP64), kEntShiftDist t - d in FP64 (t carries the shift c of the scale-zero
 // system, diagonal c).
-template <int M, int ENT = kEntExp>
+template <int M, int TS, int ENT = kEntExp>
 __device__ __forceinline__ void zmv_sym_body(const double *__restrict__ X, int64_t n, int m_rt, double t,
                                              const double *__restrict__ v, double *__restrict__ part,
                                              int64_t tile)
 {
+    constexpr int E = TS / 16;  // rows and columns per thread
     constexpr int MM = (M > 0) ? M : MMAX_SYM;
     __shared__ double Xr[MM][TS];
     __shared__ double Xc[MM][TS];
@@ -243,17 +245,17 @@ __device__ __forceinline__ void zmv_sym_body(const double *__restrict__ X, int64
     __syncthreads();
     const int ty = tid >> 4, tx = tid & 15;
     const int nr = (int)min((int64_t)TS, n - r0), nc = (int)min((int64_t)TS, n - c0);
-    double xr[8][(M > 0) ? M : 1];
+    double xr[E][(M > 0) ? M : 1];
     if (M > 0) {
 #pragma unroll
-        for (int ii = 0; ii < 8; ++ii)
+        for (int ii = 0; ii < E; ++ii)
 #pragma unroll
-            for (int l = 0; l < ((M > 0) ? M : 1); ++l) xr[ii][l] = Xr[l][8 * ty + ii];
+            for (int l = 0; l < ((M > 0) ? M : 1); ++l) xr[ii][l] = Xr[l][E * ty + ii];
     }
-    double rowacc[8], colsum[8];
+    double rowacc[E], colsum[E];
 #pragma unroll
-    for (int ii = 0; ii < 8; ++ii) rowacc[ii] = 0.0;
-    // one column at a time: the 8 row entries of a column are independent
+    for (int ii = 0; ii < E; ++ii) rowacc[ii] = 0.0;
+    // one column at a time: the row entries of a column are independent
     // exp evaluations, enough parallelism without unrolling the columns.
     // Every entry is evaluated (padding coordinates are zero, the diagonal's
     // s = 0 is harmless) and, in diagonal and edge tiles only, then selected,
@@ -261,16 +263,16 @@ __device__ __forceinline__ void zmv_sym_body(const double *__restrict__ X, int64
     auto columns = [&](auto full_tile) {
         constexpr bool FULL = decltype(full_tile)::value;
 #pragma unroll 1
-        for (int jj = 0; jj < 8; ++jj) {
-            const int c = 8 * tx + jj;
+        for (int jj = 0; jj < E; ++jj) {
+            const int c = E * tx + jj;
             double xc[MM];
 #pragma unroll
             for (int l = 0; l < MM; ++l) xc[l] = (l < m) ? Xc[l][c] : 0.0;
             const double vcj = vc[c];
             double colacc = 0.0;
 #pragma unroll
-            for (int ii = 0; ii < 8; ++ii) {
-                const int r = 8 * ty + ii;
+            for (int ii = 0; ii < E; ++ii) {
+                const int r = E * ty + ii;
                 double s = 0.0;
 #pragma unroll
                 for (int l = 0; l < MM; ++l) {
@@ -300,7 +302,7 @@ __device__ __forceinline__ void zmv_sym_body(const double *__restrict__ X, int64
     double *pt = part + tile * 2 * TS;
     // rows: sum over the 16 tx lanes (contiguous) by a fixed butterfly
 #pragma unroll
-    for (int ii = 0; ii < 8; ++ii) {
+    for (int ii = 0; ii < E; ++ii) {
         double a = rowacc[ii];
         a += __shfl_xor(a, 1);
         a += __shfl_xor(a, 2);
@@ -310,13 +312,13 @@ __device__ __forceinline__ void zmv_sym_body(const double *__restrict__ X, int64
     }
     if (tx == 0) {
 #pragma unroll
-        for (int ii = 0; ii < 8; ++ii) pt[8 * ty + ii] = rowacc[ii];
+        for (int ii = 0; ii < E; ++ii) pt[E * ty + ii] = rowacc[ii];
     }
     if (diag) return;  // uniform per workgroup
     // columns: sum over the 4 ty of a wave (lanes 16 and 32 apart), then the 4 waves
     const int wave = tid >> 6, tyw = (tid >> 4) & 3;
 #pragma unroll
-    for (int jj = 0; jj < 8; ++jj) {
+    for (int jj = 0; jj < E; ++jj) {
         double a = colsum[jj];
         a += __shfl_xor(a, 16);
         a += __shfl_xor(a, 32);
@@ -324,29 +326,39 @@ __device__ __forceinline__ void zmv_sym_body(const double *__restrict__ X, int64
     }
     if (tyw == 0) {
 #pragma unroll
-        for (int jj = 0; jj < 8; ++jj) red[wave][8 * tx + jj] = colsum[jj];
+        for (int jj = 0; jj < E; ++jj) red[wave][E * tx + jj] = colsum[jj];
     }
     __syncthreads();
     if (tid < TS) pt[TS + tid] = ((red[0][tid] + red[1][tid]) + red[2][tid]) + red[3][tid];
 }
 
-// Block I of y (rows r0 .. r0 + TS): sum of the row sums of tiles (I, 0..I)
-// and the column sums of tiles (I+1..T-1, I), in that order.  mode 0: y = Z v;
-// mode 1: y = b - Z v (b == NULL: ones) and blkmax[I] = max |y| over the block.
 // m <= 3: the entry loop fits 128 VGPRs, so four workgroups share a CU (more
 // waves to hide the FP64 latency); larger m keeps its coordinates in registers.
-template <int M, int ENT = kEntExp>
+// norm (optional) is zeroed for the reduce that follows.
+template <int M, int TS, int ENT = kEntExp>
 __global__ void __launch_bounds__(256, (M >= 1 && M <= 3) ? 4 : 1)
 k_zmv_sym(const double *__restrict__ X, int64_t n, int m_rt, double t, const double *__restrict__ v,
-          double *__restrict__ part)
+          double *__restrict__ part, double *__restrict__ norm)
 {
-    zmv_sym_body<M, ENT>(X, n, m_rt, t, v, part, blockIdx.x);
+    if (norm && blockIdx.x == 0 && threadIdx.x == 0) *norm = 0.0;
+    zmv_sym_body<M, TS, ENT>(X, n, m_rt, t, v, part, blockIdx.x);
 }
 
+// norm = max(norm, v) for v >= 0 (the bit patterns of nonnegative doubles are
+// ordered as their values)
+__device__ inline void atomic_max_nonneg(double *norm, double v)
+{
+    atomicMax(reinterpret_cast<unsigned long long *>(norm), __builtin_bit_cast(unsigned long long, v));
+}
+
+// Block I of y (rows r0 .. r0 + TS): sum of the row sums of tiles (I, 0..I)
+// and the column sums of tiles (I+1..T-1, I), in that order.  mode 0: y = Z v;
+// mode 1: y = b - Z v (b == NULL: ones) and norm = max(norm, |y|).
+template <int TS>
 __device__ __forceinline__ void zmv_sym_reduce_body(const double *__restrict__ part, int64_t T, int64_t n,
                                                     int64_t npad, double *__restrict__ y,
                                                     const double *__restrict__ b, int mode,
-                                                    double *__restrict__ blkmax, int64_t I)
+                                                    double *__restrict__ norm, int64_t I)
 {
     __shared__ double red[TS];
     const int p = threadIdx.x;
@@ -358,80 +370,67 @@ __device__ __forceinline__ void zmv_sym_reduce_body(const double *__restrict__ p
     double val = 0.0;
     if (row < n) val = (mode == 0) ? s : (b ? b[row] : 1.0) - s;
     if (row < npad) y[row] = val;
-    if (mode == 1) {
+    if (mode == 1 && norm) {
         red[p] = fabs(val);
         __syncthreads();
         for (int w = TS / 2; w > 0; w >>= 1) {
             if (p < w) red[p] = fmax(red[p], red[p + w]);
             __syncthreads();
         }
-        if (p == 0) blkmax[I] = red[0];
+        if (p == 0) atomic_max_nonneg(norm, fmax(0.0, red[0]));
     }
 }
 
+template <int TS>
 __global__ void __launch_bounds__(TS)
 k_zmv_sym_reduce(const double *__restrict__ part, int64_t T, int64_t n, int64_t npad, double *__restrict__ y,
-                 const double *__restrict__ b, int mode, double *__restrict__ blkmax)
+                 const double *__restrict__ b, int mode, double *__restrict__ norm)
 {
-    zmv_sym_reduce_body(part, T, n, npad, y, b, mode, blkmax, blockIdx.x);
+    zmv_sym_reduce_body<TS>(part, T, n, npad, y, b, mode, norm, blockIdx.x);
 }
 
 // Batched symmetric Z v: units T(T+1)/2 tiles per problem (T = npad / TS),
-// then the per-block reduce (units T per problem); blkmax after the tiles.
-template <int M>
-__global__ void __launch_bounds__(256, (M >= 1 && M <= 3) ? 4 : 1) k_zmv_sym_b(const BProb *__restrict__ P, BWork w, int v_slot)
+// then the per-block reduce (units T per problem).  norm_off < 0: no norm.
+template <int M, int TS>
+__global__ void __launch_bounds__(256, (M >= 1 && M <= 3) ? 4 : 1)
+k_zmv_sym_b(const BProb *__restrict__ P, BWork w, int v_slot, int64_t norm_off)
 {
     const int i = bfind(w.pref, w.na, blockIdx.x);
     const BProb &q = P[w.plist[i]];
     if (!q.active) return;
-    zmv_sym_body<M>(q.X, q.n, q.m, q.t, q.vec + (int64_t)v_slot * q.npad, q.partial, blockIdx.x - w.pref[i]);
+    const int64_t u = blockIdx.x - w.pref[i];
+    if (norm_off >= 0 && u == 0 && threadIdx.x == 0) q.scal[norm_off] = 0.0;
+    zmv_sym_body<M, TS>(q.X, q.n, q.m, q.t, q.vec + (int64_t)v_slot * q.npad, q.partial, u);
 }
 
+template <int TS>
 __global__ void __launch_bounds__(TS)
-k_zmv_sym_reduce_b(const BProb *__restrict__ P, BWork w, int y_slot, int b_slot, int mode)
+k_zmv_sym_reduce_b(const BProb *__restrict__ P, BWork w, int y_slot, int b_slot, int mode, int64_t norm_off)
 {
     const int i = bfind(w.pref, w.na, blockIdx.x);
     const BProb &q = P[w.plist[i]];
     if (!q.active) return;
-    const int64_t T = q.npad / TS;
-    zmv_sym_reduce_body(q.partial, T, q.n, q.npad, q.vec + (int64_t)y_slot * q.npad,
-                        b_slot >= 0 ? q.vec + (int64_t)b_slot * q.npad : nullptr, mode,
-                        q.partial + T * (T + 1) / 2 * 2 * TS, blockIdx.x - w.pref[i]);
-}
-
-__global__ void __launch_bounds__(256) k_max_final_sym_b(const BProb *__restrict__ P, BWork w, int64_t out_off)
-{
-    __shared__ double red[256];
-    const BProb &q = P[w.plist[blockIdx.x]];
-    if (!q.active) return;
-    const int64_t T = q.npad / TS;
-    const double *blkmax = q.partial + T * (T + 1) / 2 * 2 * TS;
-    double v = 0.0;
-    for (int64_t e = threadIdx.x; e < T; e += 256) v = fmax(v, blkmax[e]);
-    red[threadIdx.x] = v;
-    __syncthreads();
-    for (int s2 = 128; s2 > 0; s2 >>= 1) {
-        if (threadIdx.x < s2) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + s2]);
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) q.scal[out_off] = red[0];
+    zmv_sym_reduce_body<TS>(q.partial, q.npad / TS, q.n, q.npad, q.vec + (int64_t)y_slot * q.npad,
+                            b_slot >= 0 ? q.vec + (int64_t)b_slot * q.npad : nullptr, mode,
+                            norm_off >= 0 ? q.scal + norm_off : nullptr, blockIdx.x - w.pref[i]);
 }
 
 template <int M>
 __global__ void __launch_bounds__(RT)
 k_zmv_partial(const double *__restrict__ X, int64_t n, int m_rt, double t,
               const double *__restrict__ v, double *__restrict__ partial, int64_t cps,
-              int64_t npad)
+              int64_t npad, double *__restrict__ norm)
 {
+    if (norm && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *norm = 0.0;
     zmv_partial_body<M>(X, n, m_rt, t, v, partial, cps, npad, blockIdx.x, blockIdx.y);
 }
 
 // mode 0: y = sum_s partial;  mode 1: y = b - sum_s partial (b == NULL: ones),
-// and per-block max |y| into blkmax.
+// and norm = max(norm, |y|).
 __device__ __forceinline__ void zmv_reduce_body(const double *__restrict__ partial, int64_t npad,
                                                 int64_t n, int splits, double *__restrict__ y,
                                                 const double *__restrict__ b, int mode,
-                                                double *__restrict__ blkmax, int64_t bx)
+                                                double *__restrict__ norm, int64_t bx)
 {
     __shared__ double red[256];
     const int64_t j = bx * 256 + threadIdx.x;
@@ -444,37 +443,23 @@ __device__ __forceinline__ void zmv_reduce_body(const double *__restrict__ parti
         else val = (b ? b[j] : 1.0) - s;
         y[j] = val;
     }
-    if (mode == 1) {
+    if (mode == 1 && norm) {
         red[threadIdx.x] = fabs(val);
         __syncthreads();
         for (int w = 128; w > 0; w >>= 1) {
             if (threadIdx.x < w) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + w]);
             __syncthreads();
         }
-        if (threadIdx.x == 0) blkmax[bx] = red[0];
+        if (threadIdx.x == 0) atomic_max_nonneg(norm, fmax(0.0, red[0]));
     }
 }
 
 __global__ void __launch_bounds__(256)
 k_zmv_reduce(const double *__restrict__ partial, int64_t npad, int64_t n, int splits,
              double *__restrict__ y, const double *__restrict__ b, int mode,
-             double *__restrict__ blkmax)
+             double *__restrict__ norm)
 {
-    zmv_reduce_body(partial, npad, n, splits, y, b, mode, blkmax, blockIdx.x);
-}
-
-__global__ void __launch_bounds__(256) k_max_final(const double *blkmax, int64_t nb, double *out)
-{
-    __shared__ double red[256];
-    double v = 0.0;
-    for (int64_t i = threadIdx.x; i < nb; i += 256) v = fmax(v, blkmax[i]);
-    red[threadIdx.x] = v;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (threadIdx.x < w) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + w]);
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) out[0] = red[0];
+    zmv_reduce_body(partial, npad, n, splits, y, b, mode, norm, blockIdx.x);
 }
 
 struct Plan {
@@ -499,21 +484,22 @@ __host__ __device__ inline Plan plan_for(int64_t n)
 // Batched Z v: work units of problem p = rowblocks * splits (row block major).
 template <int M>
 __global__ void __launch_bounds__(RT)
-k_zmv_partial_b(const BProb *__restrict__ P, BWork w, int v_slot)
+k_zmv_partial_b(const BProb *__restrict__ P, BWork w, int v_slot, int64_t norm_off)
 {
     const int i = bfind(w.pref, w.na, blockIdx.x);
     const BProb &q = P[w.plist[i]];
     if (!q.active) return;
     const Plan pl = plan_for(q.n);
     const int64_t u = blockIdx.x - w.pref[i];
+    if (norm_off >= 0 && u == 0 && threadIdx.x == 0) q.scal[norm_off] = 0.0;
     zmv_partial_body<M>(q.X, q.n, q.m, q.t, q.vec + (int64_t)v_slot * q.npad, q.partial, pl.cps,
                         q.npad, u / pl.splits, u % pl.splits);
 }
 
 // Batched reduce (units = npad/256 per problem); mode 1 writes b - Z v with b
-// from b_slot (b_slot < 0: ones) and per-block maxima after the split partials.
+// from b_slot (b_slot < 0: ones) and its max norm.
 __global__ void __launch_bounds__(256)
-k_zmv_reduce_b(const BProb *__restrict__ P, BWork w, int y_slot, int b_slot, int mode)
+k_zmv_reduce_b(const BProb *__restrict__ P, BWork w, int y_slot, int b_slot, int mode, int64_t norm_off)
 {
     const int i = bfind(w.pref, w.na, blockIdx.x);
     const BProb &q = P[w.plist[i]];
@@ -522,89 +508,93 @@ k_zmv_reduce_b(const BProb *__restrict__ P, BWork w, int y_slot, int b_slot, int
     const int64_t u = blockIdx.x - w.pref[i];
     zmv_reduce_body(q.partial, q.npad, q.n, (int)pl.splits, q.vec + (int64_t)y_slot * q.npad,
                     b_slot >= 0 ? q.vec + (int64_t)b_slot * q.npad : nullptr, mode,
-                    q.partial + pl.splits * q.npad, u);
-}
-
-// Batched max of the block maxima into a scalar slot of each problem.
-__global__ void __launch_bounds__(256) k_max_final_b(const BProb *__restrict__ P, BWork w, int64_t out_off)
-{
-    __shared__ double red[256];
-    const BProb &q = P[w.plist[blockIdx.x]];
-    if (!q.active) return;
-    const Plan pl = plan_for(q.n);
-    const double *blkmax = q.partial + pl.splits * q.npad;
-    const int64_t nb = q.npad / 256;
-    double v = 0.0;
-    for (int64_t e = threadIdx.x; e < nb; e += 256) v = fmax(v, blkmax[e]);
-    red[threadIdx.x] = v;
-    __syncthreads();
-    for (int s2 = 128; s2 > 0; s2 >>= 1) {
-        if (threadIdx.x < s2) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + s2]);
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) q.scal[out_off] = red[0];
+                    norm_off >= 0 ? q.scal + norm_off : nullptr, u);
 }
 
 }  // namespace
 
-size_t zmv_partial_doubles(int64_t n)
+// Largest n on the 64-edged symmetric tiles.  At 128 a size below about 3000 has
+// fewer tiles than the chip has CUs and each runs at its own latency (13 us at
+// n = 100).
+constexpr int64_t kSmallTileN = 3072;
+
+static size_t sym_doubles(int64_t n, int ts)
 {
-    Plan p = plan_for(n);
-    const int64_t T = (p.npad + TS - 1) / TS;
-    const size_t sym = (size_t)(T * (T + 1) / 2) * 2 * TS + (size_t)T + 8;
-    return std::max(sym, (size_t)(p.splits * p.npad + p.npad / 256 + 8));
+    const int64_t T = (n + kPad - 1) / kPad * kPad / ts;
+    return (size_t)(T * (T + 1) / 2) * 2 * ts;
 }
 
-int64_t zmv_b_units(int64_t n, int m)
+// the least a product needs (128-edged tiles, or the row-per-thread form)
+size_t zmv_min_partial_doubles(int64_t n)
+{
+    Plan p = plan_for(n);
+    return std::max(sym_doubles(n, TSB) + (size_t)(p.npad / TSB), (size_t)(p.splits * p.npad + p.npad / 256)) + 8;
+}
+
+size_t zmv_partial_doubles(int64_t n)
+{
+    return n <= kSmallTileN ? std::max(zmv_min_partial_doubles(n), sym_doubles(n, TSS)) : zmv_min_partial_doubles(n);
+}
+
+// Edge of the symmetric tiles of a batch with this many 128-edged ones, and the
+// partial sums of one of its problems.
+int zmv_b_tile(int64_t tiles128) { return tiles128 <= 1024 ? TSS : TSB; }
+
+size_t zmv_b_partial_doubles(int64_t n, int ts)
+{
+    return std::max(zmv_min_partial_doubles(n), sym_doubles(n, ts));
+}
+
+int64_t zmv_b_units(int64_t n, int m, int ts)
 {
     if (m <= MMAX_SYM) {
-        const int64_t T = ((n + kPad - 1) / kPad * kPad) / TS;
+        const int64_t T = ((n + kPad - 1) / kPad * kPad) / ts;
         return T * (T + 1) / 2;
     }
     Plan p = plan_for(n);
     return p.rowblocks * p.splits;
 }
 
-int64_t zmv_b_reduce_units(int64_t n, int m)
+int64_t zmv_b_reduce_units(int64_t n, int m, int ts)
 {
     const int64_t npad = (n + kPad - 1) / kPad * kPad;
-    return m <= MMAX_SYM ? npad / TS : npad / 256;
+    return m <= MMAX_SYM ? npad / ts : npad / 256;
+}
+
+template <int TS>
+void zmv_sym_b(hipStream_t s, int m, const BProb *P, const BWork &wz, const BWork &wr, int v_slot, int y_slot,
+               int b_slot, int mode, int64_t norm_off)
+{
+    const dim3 g((unsigned)wz.total);
+    switch (m) {
+    case 1: hipLaunchKernelGGL((k_zmv_sym_b<1, TS>), g, dim3(256), 0, s, P, wz, v_slot, norm_off); break;
+    case 2: hipLaunchKernelGGL((k_zmv_sym_b<2, TS>), g, dim3(256), 0, s, P, wz, v_slot, norm_off); break;
+    case 3: hipLaunchKernelGGL((k_zmv_sym_b<3, TS>), g, dim3(256), 0, s, P, wz, v_slot, norm_off); break;
+    case 4: hipLaunchKernelGGL((k_zmv_sym_b<4, TS>), g, dim3(256), 0, s, P, wz, v_slot, norm_off); break;
+    case 8: hipLaunchKernelGGL((k_zmv_sym_b<8, TS>), g, dim3(256), 0, s, P, wz, v_slot, norm_off); break;
+    default: hipLaunchKernelGGL((k_zmv_sym_b<0, TS>), g, dim3(256), 0, s, P, wz, v_slot, norm_off); break;
+    }
+    hipLaunchKernelGGL(k_zmv_sym_reduce_b<TS>, dim3((unsigned)wr.total), dim3(TS), 0, s, P, wr, y_slot, b_slot, mode,
+                       norm_off);
 }
 
 // Batched y_slot = Z v_slot (mode 0) or y_slot = b - Z v_slot with its max norm
-// into scal[norm_off] (mode 1).  wz: units zmv_b_units(n, m); wr: units
-// zmv_b_reduce_units(n, m).
+// into scal[norm_off] (mode 1).  wz: units zmv_b_units(n, m, ts); wr: units
+// zmv_b_reduce_units(n, m, ts); ts: the symmetric tiles' edge, 64 or 128.
 void launch_zmv_b(hipStream_t s, int m, const BProb *P, const BWork &wz, const BWork &wr,
-                  int v_slot, int y_slot, int b_slot, int mode, int64_t norm_off)
+                  int v_slot, int y_slot, int b_slot, int mode, int64_t norm_off, int ts)
 {
     if (wz.na <= 0) return;
-    const dim3 g((unsigned)wz.total);
+    if (mode == 0) norm_off = -1;
     if (m <= MMAX_SYM) {
-        switch (m) {
-        case 1: hipLaunchKernelGGL(k_zmv_sym_b<1>, g, dim3(256), 0, s, P, wz, v_slot); break;
-        case 2: hipLaunchKernelGGL(k_zmv_sym_b<2>, g, dim3(256), 0, s, P, wz, v_slot); break;
-        case 3: hipLaunchKernelGGL(k_zmv_sym_b<3>, g, dim3(256), 0, s, P, wz, v_slot); break;
-        case 4: hipLaunchKernelGGL(k_zmv_sym_b<4>, g, dim3(256), 0, s, P, wz, v_slot); break;
-        case 8: hipLaunchKernelGGL(k_zmv_sym_b<8>, g, dim3(256), 0, s, P, wz, v_slot); break;
-        default: hipLaunchKernelGGL(k_zmv_sym_b<0>, g, dim3(256), 0, s, P, wz, v_slot); break;
-        }
-        hipLaunchKernelGGL(k_zmv_sym_reduce_b, dim3((unsigned)wr.total), dim3(TS), 0, s, P, wr, y_slot, b_slot, mode);
-        if (mode == 1)
-            hipLaunchKernelGGL(k_max_final_sym_b, dim3(wz.na), dim3(256), 0, s, P, wz, norm_off);
+        if (ts == TSS) zmv_sym_b<TSS>(s, m, P, wz, wr, v_slot, y_slot, b_slot, mode, norm_off);
+        else zmv_sym_b<TSB>(s, m, P, wz, wr, v_slot, y_slot, b_slot, mode, norm_off);
         return;
     }
-    switch (m) {
-    case 1: hipLaunchKernelGGL(k_zmv_partial_b<1>, g, dim3(RT), 0, s, P, wz, v_slot); break;
-    case 2: hipLaunchKernelGGL(k_zmv_partial_b<2>, g, dim3(RT), 0, s, P, wz, v_slot); break;
-    case 3: hipLaunchKernelGGL(k_zmv_partial_b<3>, g, dim3(RT), 0, s, P, wz, v_slot); break;
-    case 4: hipLaunchKernelGGL(k_zmv_partial_b<4>, g, dim3(RT), 0, s, P, wz, v_slot); break;
-    case 8: hipLaunchKernelGGL(k_zmv_partial_b<8>, g, dim3(RT), 0, s, P, wz, v_slot); break;
-    default: hipLaunchKernelGGL(k_zmv_partial_b<0>, g, dim3(RT), 0, s, P, wz, v_slot); break;
-    }
-    hipLaunchKernelGGL(k_zmv_reduce_b, dim3((unsigned)wr.total), dim3(256), 0, s, P, wr, y_slot,
-                       b_slot, mode);
-    if (mode == 1)
-        hipLaunchKernelGGL(k_max_final_b, dim3(wz.na), dim3(256), 0, s, P, wz, norm_off);
+    // m > MMAX_SYM: the runtime-m row-per-thread form
+    hipLaunchKernelGGL(k_zmv_partial_b<0>, dim3((unsigned)wz.total), dim3(RT), 0, s, P, wz, v_slot, norm_off);
+    hipLaunchKernelGGL(k_zmv_reduce_b, dim3((unsigned)wr.total), dim3(256), 0, s, P, wr, y_slot, b_slot, mode,
+                       norm_off);
 }
 
 size_t zmv_split_partial_doubles(int64_t n)
@@ -619,61 +609,48 @@ void launch_zmv_split(hipStream_t s, const double *X, int64_t n, int m, double t
 {
     Plan p = plan_for(n);
     dim3 grid((unsigned)p.rowblocks, (unsigned)p.splits);
-    hipLaunchKernelGGL(k_zmv_partial<0>, grid, dim3(RT), 0, s, X, n, m, t, v, partial, p.cps, p.npad);
-    const int64_t rb = p.npad / 256;
-    double *blkmax = partial + p.splits * p.npad;
-    hipLaunchKernelGGL(k_zmv_reduce, dim3((unsigned)rb), dim3(256), 0, s, partial, p.npad, n, (int)p.splits, y, b,
-                       mode, blkmax);
-    if (mode == 1 && out_norm)
-        hipLaunchKernelGGL(k_max_final, dim3(1), dim3(256), 0, s, blkmax, rb, out_norm);
+    double *norm = mode == 1 ? out_norm : nullptr;
+    hipLaunchKernelGGL(k_zmv_partial<0>, grid, dim3(RT), 0, s, X, n, m, t, v, partial, p.cps, p.npad, norm);
+    hipLaunchKernelGGL(k_zmv_reduce, dim3((unsigned)(p.npad / 256)), dim3(256), 0, s, partial, p.npad, n,
+                       (int)p.splits, y, b, mode, norm);
+}
+
+template <int ENT, int TS>
+void zmv_sym(hipStream_t s, const double *X, int64_t n, int m, double t, const double *v, double *y, const double *b,
+             int mode, double *partial, double *norm)
+{
+    const int64_t npad = (n + kPad - 1) / kPad * kPad;
+    const int64_t T = npad / TS;
+    const dim3 grid((unsigned)(T * (T + 1) / 2));
+    switch (m) {
+    case 1: hipLaunchKernelGGL((k_zmv_sym<1, TS, ENT>), grid, dim3(256), 0, s, X, n, m, t, v, partial, norm); break;
+    case 2: hipLaunchKernelGGL((k_zmv_sym<2, TS, ENT>), grid, dim3(256), 0, s, X, n, m, t, v, partial, norm); break;
+    case 3: hipLaunchKernelGGL((k_zmv_sym<3, TS, ENT>), grid, dim3(256), 0, s, X, n, m, t, v, partial, norm); break;
+    case 4: hipLaunchKernelGGL((k_zmv_sym<4, TS, ENT>), grid, dim3(256), 0, s, X, n, m, t, v, partial, norm); break;
+    case 8: hipLaunchKernelGGL((k_zmv_sym<8, TS, ENT>), grid, dim3(256), 0, s, X, n, m, t, v, partial, norm); break;
+    default: hipLaunchKernelGGL((k_zmv_sym<0, TS, ENT>), grid, dim3(256), 0, s, X, n, m, t, v, partial, norm); break;
+    }
+    hipLaunchKernelGGL(k_zmv_sym_reduce<TS>, dim3((unsigned)T), dim3(TS), 0, s, partial, T, n, npad, y, b, mode, norm);
 }
 
 template <int ENT>
-void launch_zmv_sym_tiles(hipStream_t s, const double *X, int64_t n, int m, double t, const double *v,
-                          double *partial, const dim3 grid)
+void zmv_sym_any(hipStream_t s, const double *X, int64_t n, int m, double t, const double *v, double *y,
+                 const double *b, int mode, double *partial, size_t cap, double *norm)
 {
-    switch (m) {
-    case 1: hipLaunchKernelGGL((k_zmv_sym<1, ENT>), grid, dim3(256), 0, s, X, n, m, t, v, partial); break;
-    case 2: hipLaunchKernelGGL((k_zmv_sym<2, ENT>), grid, dim3(256), 0, s, X, n, m, t, v, partial); break;
-    case 3: hipLaunchKernelGGL((k_zmv_sym<3, ENT>), grid, dim3(256), 0, s, X, n, m, t, v, partial); break;
-    case 4: hipLaunchKernelGGL((k_zmv_sym<4, ENT>), grid, dim3(256), 0, s, X, n, m, t, v, partial); break;
-    case 8: hipLaunchKernelGGL((k_zmv_sym<8, ENT>), grid, dim3(256), 0, s, X, n, m, t, v, partial); break;
-    default: hipLaunchKernelGGL((k_zmv_sym<0, ENT>), grid, dim3(256), 0, s, X, n, m, t, v, partial); break;
-    }
+    if (n <= kSmallTileN && cap >= sym_doubles(n, TSS)) zmv_sym<ENT, TSS>(s, X, n, m, t, v, y, b, mode, partial, norm);
+    else zmv_sym<ENT, TSB>(s, X, n, m, t, v, y, b, mode, partial, norm);
 }
 
 void launch_zmv(hipStream_t s, const double *X, int64_t n, int m, double t, const double *v,
-                double *y, const double *b, int mode, double *partial, double *out_norm, bool f32_entries,
+                double *y, const double *b, int mode, double *partial, size_t cap, double *out_norm, bool f32_entries,
                 int kernel)
 {
-    if (kernel == kKernShiftDist) {
-        // the scale-zero system (m <= 16 only, checked by the caller)
-        const int64_t npad = (n + kPad - 1) / kPad * kPad;
-        const int64_t T = npad / TS;
-        const int64_t tiles = T * (T + 1) / 2;
-        launch_zmv_sym_tiles<kEntShiftDist>(s, X, n, m, t, v, partial, dim3((unsigned)tiles));
-        double *blkmax = partial + tiles * 2 * TS;
-        hipLaunchKernelGGL(k_zmv_sym_reduce, dim3((unsigned)T), dim3(TS), 0, s, partial, T, n, npad, y, b, mode,
-                           blkmax);
-        if (mode == 1 && out_norm)
-            hipLaunchKernelGGL(k_max_final, dim3(1), dim3(256), 0, s, blkmax, T, out_norm);
-        return;
-    }
-    if (m > MMAX_SYM) {
-        launch_zmv_split(s, X, n, m, t, v, y, b, mode, partial, out_norm);
-        return;
-    }
-    const int64_t npad = (n + kPad - 1) / kPad * kPad;
-    const int64_t T = npad / TS;
-    const int64_t tiles = T * (T + 1) / 2;
-    const dim3 grid((unsigned)tiles);
-    if (f32_entries) launch_zmv_sym_tiles<kEntExp32>(s, X, n, m, t, v, partial, grid);
-    else launch_zmv_sym_tiles<kEntExp>(s, X, n, m, t, v, partial, grid);
-    double *blkmax = partial + tiles * 2 * TS;
-    hipLaunchKernelGGL(k_zmv_sym_reduce, dim3((unsigned)T), dim3(TS), 0, s, partial, T, n, npad, y, b, mode,
-                       blkmax);
-    if (mode == 1 && out_norm)
-        hipLaunchKernelGGL(k_max_final, dim3(1), dim3(256), 0, s, blkmax, T, out_norm);
+    double *norm = mode == 1 ? out_norm : nullptr;
+    // the scale-zero system has m <= 16 only (checked by the caller)
+    if (kernel == kKernShiftDist) zmv_sym_any<kEntShiftDist>(s, X, n, m, t, v, y, b, mode, partial, cap, norm);
+    else if (m > MMAX_SYM) launch_zmv_split(s, X, n, m, t, v, y, b, mode, partial, out_norm);
+    else if (f32_entries) zmv_sym_any<kEntExp32>(s, X, n, m, t, v, y, b, mode, partial, cap, norm);
+    else zmv_sym_any<kEntExp>(s, X, n, m, t, v, y, b, mode, partial, cap, norm);
 }
 
 }  // namespace mag

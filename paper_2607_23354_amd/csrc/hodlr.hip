@@ -1652,7 +1652,7 @@ int hss_factor(mag_ctx *ctx, const double *X, int64_t n, int m, double t, int le
         const int64_t tasks = (int64_t)1 << (l - 1);
         for (int mode = 0; mode < 2; ++mode)
             launch_zblock(s, H.Xp, m, t, H.bnd + boff(l), mode, tasks, rbl[l], Om, Tmp, r, r);
-        launch_axpy1(s, Tmp, S, (int64_t)n * r);
+        launch_add(s, S, Tmp, S, (int64_t)n * r);
     }
     // Bc[l][pair] = U(I_a)^T Z(I_a, I_b) U(I_b) for level l's sibling pairs, U: n x k[l]
     auto couplings = [&](const double *U, int l) {

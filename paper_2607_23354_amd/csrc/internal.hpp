@@ -210,12 +210,17 @@ void launch_potrf128_b(hipStream_t s, const BProb *P, const BWork &w, int64_t k0
 int64_t gemm_b_units(int kind, int64_t npad, int64_t kk);
 void launch_gemm_b(hipStream_t s, int kind, const BProb *P, const BWork &w, int64_t kk);
 int64_t prec_b_units(int64_t npad);
+// tickets zero and tmp_slot unset: once before the first launch_prec_apply_b, which
+// leaves them so; rhs_slot, tmp_slot and x_slot differ
+void launch_prec_begin_b(hipStream_t s, const BProb *P, int B, int tmp_slot);
 void launch_prec_apply_b(hipStream_t s, const BProb *P, const BWork &w, int rhs_slot, int tmp_slot,
                          int x_slot);
-int64_t zmv_b_units(int64_t n, int m);
-int64_t zmv_b_reduce_units(int64_t n, int m);
+int zmv_b_tile(int64_t tiles128);
+size_t zmv_b_partial_doubles(int64_t n, int ts);
+int64_t zmv_b_units(int64_t n, int m, int ts);
+int64_t zmv_b_reduce_units(int64_t n, int m, int ts);
 void launch_zmv_b(hipStream_t s, int m, const BProb *P, const BWork &wz, const BWork &wr, int v_slot,
-                  int y_slot, int b_slot, int mode, int64_t norm_off);
+                  int y_slot, int b_slot, int mode, int64_t norm_off, int ts);
 int64_t dz_b_units(int64_t n);
 void launch_dzmv_b(hipStream_t s, int m, const BProb *P, const BWork &wz, const BWork &wr, int v_slot,
                    int y_slot);
@@ -286,6 +291,8 @@ struct mag_ctx {
     void *bhost = nullptr;   // pinned host staging for work lists and descriptors
     size_t bhost_bytes = 0;
     double *host_scalars = nullptr;  // pinned host staging (64 doubles)
+    double *report = nullptr;        // 16 more that kernels write, and their device address
+    double *report_dev = nullptr;
     void *blas = nullptr;            // rocblas_handle (lazy, FP64 comparator)
     int64_t cu_count = 256;
     // tuned panel width of the single-solve FP32 factor per size bucket
@@ -350,7 +357,8 @@ void launch_gradx(hipStream_t s, const double *X, int64_t n, int m, double t, co
 
 // ---- launchers (all enqueue on ctx->stream) --------------------------------
 // tilegen.hip
-// status (optional): status[kStDuplicate] = 1 if some pair j != k < n has d_jk = 0.
+// status (optional): status[kStDuplicate] = 1 if some pair j != k < n has d_jk = 0,
+// status[kStNonFinite] = 1 if a coordinate is not finite.
 // kernel kKernShiftDist writes t - d_jk (diagonal t + shift) instead of exp(-t d_jk).
 void launch_tilegen32(hipStream_t s, const double *X, int64_t n, int m, double t,
                       float *A, int64_t npad, float shift, int *status = nullptr, int kernel = kKernExp);
@@ -410,15 +418,18 @@ void launch_potrf128(hipStream_t s, float *A, int64_t ld, int64_t k0, int64_t n,
 
 // gemv64.hip: FP64 matrix-free products with Z regenerated from X.
 //   mode 0: y = Z v;  mode 1: y = b - Z v (b may be NULL meaning ones) and
-//   out_norm[0] = ||y||_inf (device scalar).
+//   out_norm[0] = ||y||_inf (device scalar, by an atomic maximum).
 //   f32_entries: each entry exp(-t d) evaluated in FP32 (sums stay FP64); the
 //   inner products of GMRES may take it, residuals never do (m <= 16 only).
 //   kernel: kKernExp the entries exp(-t d) of Z; kKernShiftDist the entries
 //   t - d of the scale-zero system c 1 1^T - d with c passed as t (m <= 16).
 void launch_zmv(hipStream_t s, const double *X, int64_t n, int m, double t,
                 const double *v, double *y, const double *b, int mode,
-                double *partial, double *out_norm, bool f32_entries = false, int kernel = kKernExp);
+                double *partial, size_t cap, double *out_norm, bool f32_entries = false, int kernel = kKernExp);
+// partial holds cap doubles: zmv_partial_doubles(n), or zmv_min_partial_doubles(n)
+// where memory is short (128-edged tiles at every n).
 size_t zmv_partial_doubles(int64_t n);
+size_t zmv_min_partial_doubles(int64_t n);
 // The row-per-thread form of launch_zmv (any m; no symmetric tiles): partial
 // needs zmv_split_partial_doubles(n) doubles, y npad doubles; the max norm of
 // mode 1 goes to out_norm (may be NULL).
@@ -434,13 +445,19 @@ int noalloc_setup(int device);
 constexpr long kSpinLimitDefault = 1L << 26;
 // trsv.hip: z = L^{-T} L^{-1} r with the FP32 factor, FP64 arithmetic, by the
 // one-block-per-workgroup substitution with a composite near step.  Q: the near
-// tiles of launch_near_q for this factor (required).
+// tiles of launch_near_q for this factor (required).  r, y_tmp and z are three
+// vectors; y_tmp and the counters as launch_refine_begin leaves them, which every
+// apply restores.
 void launch_prec_apply(hipStream_t s, const float *L, int64_t npad, const float *dinv,
                        const double *r, double *y_tmp, double *z, int *counters, int *status,
                        const float *Q, long spin_limit);
 // The near tiles D_b T(b, b -/+ 1) of every 128-block of the FP32 factor, both
 // directions (near_q_floats(npad) floats), from the factor and its inverses.
 size_t near_q_floats(int64_t npad);
+// y_tmp unset, counters (and status, if not NULL) zero; rhs (if not NULL): ones on
+// [0, n), zero on [n, npad)
+void launch_refine_begin(hipStream_t s, double *y_tmp, double *rhs, int64_t n, int64_t npad, int *counters,
+                         int *status);
 void launch_near_q(hipStream_t s, const float *A, int64_t npad, const float *dinv, float *Q);
 size_t prec_counter_ints();
 // z = L^{-T} L^{-1} r with the FP64 factor of chol64_factor (64-blocks).
@@ -455,18 +472,26 @@ void launch_copy(hipStream_t s, const double *x, double *y, int64_t len);
 // h[i] = V_i . u for i < k (V rows of stride ld), result in device h (k doubles).
 void launch_multidot(hipStream_t s, const double *V, int64_t ld, int k, const double *u,
                      int64_t len, double *partial, double *h);
-// u -= sum_i h[i] V_i
+// u = u0 + sign * sum_i h[i] V_i (u0 may be u)
 void launch_multi_axpy(hipStream_t s, const double *V, int64_t ld, int k, const double *h,
-                       double *u, int64_t len, double sign);
+                       const double *u0, double *u, int64_t len, double sign);
 // out = ||x||_2 (device scalar)
 void launch_nrm2(hipStream_t s, const double *x, int64_t len, double *partial, double *out);
 // y = x * (1/alpha[0]) with device alpha
 void launch_scale_inv(hipStream_t s, const double *x, double *y, int64_t len, const double *alpha);
-// y += x
-void launch_axpy1(hipStream_t s, const double *x, double *y, int64_t len);
-// sum (block sums combined with Neumaier compensation), min, argmin of x[0..n):
-// out[0]=sum, out[1]=min, out[2]=argmin
+// z = x + y
+void launch_add(hipStream_t s, const double *x, const double *y, double *z, int64_t len);
+// sum (block sums combined with compensation), min, argmin of x[0..n):
+// out[0]=sum, out[1]=min, out[2]=argmin (out may be host memory)
 void launch_sum_min(hipStream_t s, const double *x, int64_t n, double *partial, double *out);
+// The same of the iterate x1 of a speculated solve (see refine_core), whose residuals'
+// norms (x0's and x1's) and status words are on the device: also out[3..4] = norms,
+// out[5..8] = status words, and x1 to dst (len entries) if every word is 0, x0
+// misses tol and x1 meets it.
+void launch_finish(hipStream_t s, const double *x, int64_t n, const double *norms, const int *status, double tol,
+                   double *partial, double *dst, int64_t len, double *out);
+// out[0] = norm, out[1..4] = status words (out may be host memory)
+void launch_norm_report(hipStream_t s, const double *norm, const int *status, double *out);
 // out = max |x_i|
 void launch_amax(hipStream_t s, const double *x, int64_t len, double *partial, double *out);
 // y = a*1 + x on [0, n) (x may be NULL), zero on [n, len)

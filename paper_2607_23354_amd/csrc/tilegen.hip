@@ -22,13 +22,16 @@ constexpr int kPerThread = kRows * kCols / kThreads;  // 32 entries
 // Map a linear block index onto the lower block set {(I, Jc) : Jc <= 2I+1},
 // where I counts 128-row tiles and Jc counts 64-column blocks.  Row tile I
 // owns blocks [I(I+1), (I+1)(I+2)).
+// (for NC-column blocks: Jc < R (I + 1) with R = 128 / NC, from R I (I + 1) / 2 on)
+template <int NC = kCols>
 __device__ inline void lower_block(int64_t idx, int64_t &I, int64_t &Jc)
 {
-    int64_t r = (int64_t)((sqrt(4.0 * (double)idx + 1.0) - 1.0) * 0.5);
-    while (r * (r + 1) > idx) --r;
-    while ((r + 1) * (r + 2) <= idx) ++r;
+    constexpr int64_t R = kRows / NC;
+    int64_t r = (int64_t)((sqrt(8.0 / R * (double)idx + 1.0) - 1.0) * 0.5);
+    while (R * r * (r + 1) / 2 > idx) --r;
+    while (R * (r + 1) * (r + 2) / 2 <= idx) ++r;
     I = r;
-    Jc = idx - r * (r + 1);
+    Jc = idx - R * r * (r + 1) / 2;
 }
 
 __device__ inline double sq_acc(double s, double e)
@@ -40,22 +43,27 @@ __device__ inline double sq_acc(double s, double e)
 
 // Stage coordinates [l0, l0+lc) of `count` consecutive points starting at
 // `first` into S[l][count] (zero beyond n).
+// bad (optional): bad[kStNonFinite] = 1 if one is not finite.
 __device__ inline void stage(double *S, int count, const double *X, int64_t n, int m,
-                             int64_t first, int l0, int lc)
+                             int64_t first, int l0, int lc, int *bad = nullptr)
 {
     for (int e = threadIdx.x; e < lc * count; e += blockDim.x) {
         int l = e / count, p = e % count;
         int64_t j = first + p;
-        S[l * count + p] = (j < n) ? X[j * m + l0 + l] : 0.0;
+        const double x = (j < n) ? X[j * m + l0 + l] : 0.0;
+        if (bad && !isfinite(x)) bad[kStNonFinite] = 1;
+        S[l * count + p] = x;
     }
 }
 
-// Squared distances of the 32 entries (row r, columns c0 + 2*c ... ) of a
-// 128 x 64 block.  Thread layout: r = tid & 127, column parity h = tid >> 7,
+// Squared distances of the NC / 2 entries (row r, columns c0 + 2*c ... ) of a
+// 128 x NC block.  Thread layout: r = tid & 127, column parity h = tid >> 7,
 // entry c covers column 2c + h, so a fixed c is written by 128 consecutive rows.
-__device__ inline void block_sqdist(double (&s)[kPerThread], const double *X, int64_t n, int m,
-                                    int64_t row0, int64_t col0, double *Sr, double *Sc)
+template <int NC = kCols>
+__device__ inline void block_sqdist(double (&s)[NC / 2], const double *X, int64_t n, int m,
+                                    int64_t row0, int64_t col0, double *Sr, double *Sc, int *bad = nullptr)
 {
+    constexpr int kPerThread = NC / 2, kCols = NC;
     const int r = threadIdx.x & (kRows - 1);
     const int h = threadIdx.x >> 7;
 #pragma unroll
@@ -63,7 +71,7 @@ __device__ inline void block_sqdist(double (&s)[kPerThread], const double *X, in
     for (int l0 = 0; l0 < m; l0 += kLC) {
         int lc = min(kLC, m - l0);
         __syncthreads();
-        stage(Sr, kRows, X, n, m, row0, l0, lc);
+        stage(Sr, kRows, X, n, m, row0, l0, lc, bad);
         stage(Sc, kCols, X, n, m, col0, l0, lc);
         __syncthreads();
         for (int l = 0; l < lc; ++l) {
@@ -77,24 +85,24 @@ __device__ inline void block_sqdist(double (&s)[kPerThread], const double *X, in
     }
 }
 
-template <int KERN = kKernExp>
+template <int KERN = kKernExp, int NC = kCols>
 __device__ __forceinline__ void tilegen32_body(const double *__restrict__ X, int64_t n, int m,
                                                double t, float *__restrict__ A, int64_t npad,
                                                float shift, int64_t blk, int *__restrict__ status)
 {
     __shared__ double Sr[kLC * kRows];
-    __shared__ double Sc[kLC * kCols];
+    __shared__ double Sc[kLC * NC];
     int64_t I, Jc;
-    lower_block(blk, I, Jc);
-    const int64_t row0 = I * kRows, col0 = Jc * kCols;
-    double s[kPerThread];
-    block_sqdist(s, X, n, m, row0, col0, Sr, Sc);
+    lower_block<NC>(blk, I, Jc);
+    const int64_t row0 = I * kRows, col0 = Jc * NC;
+    double s[NC / 2];
+    block_sqdist<NC>(s, X, n, m, row0, col0, Sr, Sc, Jc == 0 ? status : nullptr);
     const int r = threadIdx.x & (kRows - 1);
     const int h = threadIdx.x >> 7;
     const int64_t j = row0 + r;
     const float tf = (float)t;
 #pragma unroll
-    for (int c = 0; c < kPerThread; ++c) {
+    for (int c = 0; c < NC / 2; ++c) {
         const int64_t k = col0 + 2 * c + h;
         float v;
         if (j == k)
@@ -112,12 +120,12 @@ __device__ __forceinline__ void tilegen32_body(const double *__restrict__ X, int
     }
 }
 
-template <int KERN>
+template <int KERN, int NC>
 __global__ void __launch_bounds__(kThreads)
 k_tilegen32(const double *__restrict__ X, int64_t n, int m, double t, float *__restrict__ A,
             int64_t npad, float shift, int *__restrict__ status)
 {
-    tilegen32_body<KERN>(X, n, m, t, A, npad, shift, blockIdx.x, status);
+    tilegen32_body<KERN, NC>(X, n, m, t, A, npad, shift, blockIdx.x, status);
 }
 
 // Batched: one launch for every active problem of a batch.
@@ -249,17 +257,26 @@ int64_t lower_blocks(int64_t rows)
     return T * (T + 1);
 }
 
+template <int NC>
+void tilegen32(hipStream_t s, const double *X, int64_t n, int m, double t, float *A, int64_t npad, float shift,
+               int *status, int kernel)
+{
+    const int64_t T = npad / kRows;
+    const dim3 g((unsigned)(kRows / NC * (T * (T + 1) / 2)));
+    if (kernel == kKernShiftDist)
+        hipLaunchKernelGGL((k_tilegen32<kKernShiftDist, NC>), g, dim3(kThreads), 0, s, X, n, m, t, A, npad, shift, status);
+    else
+        hipLaunchKernelGGL((k_tilegen32<kKernExp, NC>), g, dim3(kThreads), 0, s, X, n, m, t, A, npad, shift, status);
+}
+
 }  // namespace
 
 void launch_tilegen32(hipStream_t s, const double *X, int64_t n, int m, double t, float *A,
                       int64_t npad, float shift, int *status, int kernel)
 {
-    if (kernel == kKernShiftDist)
-        hipLaunchKernelGGL(k_tilegen32<kKernShiftDist>, dim3((unsigned)lower_blocks(npad)), dim3(kThreads), 0, s, X,
-                           n, m, t, A, npad, shift, status);
-    else
-        hipLaunchKernelGGL(k_tilegen32<kKernExp>, dim3((unsigned)lower_blocks(npad)), dim3(kThreads), 0, s, X, n,
-                           m, t, A, npad, shift, status);
+    // up to 1024 rows a 128 x 64 block per workgroup would leave most CUs without one
+    if (npad <= 1024) tilegen32<16>(s, X, n, m, t, A, npad, shift, status, kernel);
+    else tilegen32<kCols>(s, X, n, m, t, A, npad, shift, status, kernel);
 }
 
 void launch_tilegen64(hipStream_t s, const double *X, int64_t n, int m, double t, double *A)

@@ -72,6 +72,28 @@ __device__ inline void st_entry(double *x, int64_t i, double v)
                        __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// The next ticket of this direction.  Its first workgroup zeroes the other
+// direction's tickets (that solve is over or not begun), so a pair of solves
+// leaves the counters as it found them but for the backward ticket, which the
+// next forward solve zeroes.
+template <bool BWD>
+__device__ inline int take_ticket(int *counters)
+{
+    const int ticket = atomicAdd(&counters[BWD ? kBwdTicket : kFwdTicket], 1);
+    if (ticket == 0) counters[BWD ? kFwdTicket : kBwdTicket] = 0;
+    return ticket;
+}
+
+// The vectors' "unset" state is kept up by the solves themselves: the forward one
+// unsets the entries of z, which the backward one will write, and the backward
+// one those of its right-hand side y, each once it has read it, for the next
+// forward solve.
+template <bool BWD>
+__device__ inline void unset_after_read(double *rhs, double *z, int64_t i)
+{
+    reinterpret_cast<uint64_t *>(BWD ? rhs : z)[i] = kUnset;
+}
+
 // Wave 0 (lanes 0..63): wait until the BS entries of block j0 (and j1 if two)
 // of x are set, and copy them to xs[0] (xs[1]).  Bounded: after spin_limit
 // polls the status word is set and whatever was read is used.
@@ -144,7 +166,7 @@ __device__ inline void load_quad(const double *p, Quad<double> &q)
 template <bool BWD, typename T, int BS>
 __device__ __forceinline__ void trsv_body(const T *__restrict__ L, int64_t ld,
                                           const T *__restrict__ dinv,
-                                          const double *__restrict__ rhs, double *__restrict__ x,
+                                          double *__restrict__ rhs, double *__restrict__ x, double *__restrict__ z,
                                           int *counters, int nblk, int *status, long spin_limit)
 {
     constexpr int RG = BS / 4;      // row groups of a tile (4 rows each)
@@ -160,7 +182,7 @@ __device__ __forceinline__ void trsv_body(const T *__restrict__ L, int64_t ld,
     const int tid = threadIdx.x;
     const int nband = nblk / 2;
     if (tid == 0) {
-        const int ticket = atomicAdd(&counters[BWD ? kBwdTicket : kFwdTicket], 1);
+        const int ticket = take_ticket<BWD>(counters);
         s_band = BWD ? nband - 1 - ticket : ticket;
     }
     __syncthreads();
@@ -200,6 +222,8 @@ __device__ __forceinline__ void trsv_body(const T *__restrict__ L, int64_t ld,
     if (tid < BS) {
         rhs0 = rhs[(int64_t)b0 * BS + tid];
         rhs1 = rhs[(int64_t)b1 * BS + tid];
+        unset_after_read<BWD>(rhs, z, (int64_t)b0 * BS + tid);
+        unset_after_read<BWD>(rhs, z, (int64_t)b1 * BS + tid);
     }
     Tile ti;
     load(b1, b0, ti);
@@ -323,10 +347,10 @@ __device__ __forceinline__ void trsv_body(const T *__restrict__ L, int64_t ld,
 template <bool BWD, typename T, int BS>
 __global__ void __launch_bounds__(256)
 k_trsv(const T *__restrict__ L, int64_t ld, const T *__restrict__ dinv,
-       const double *__restrict__ rhs, double *__restrict__ x, int *counters, int nblk,
+       double *__restrict__ rhs, double *__restrict__ x, double *__restrict__ z, int *counters, int nblk,
        int *status, long spin_limit)
 {
-    trsv_body<BWD, T, BS>(L, ld, dinv, rhs, x, counters, nblk, status, spin_limit);
+    trsv_body<BWD, T, BS>(L, ld, dinv, rhs, x, z, counters, nblk, status, spin_limit);
 }
 
 // One triangular solve of the FP32 factor with one 128-row block per
@@ -342,9 +366,9 @@ k_trsv(const T *__restrict__ L, int64_t ld, const T *__restrict__ dinv,
 // chain costs one hand-off and one 128 x 128 product per block.
 template <bool BWD>
 __device__ __forceinline__ void trsv1_body(const float *__restrict__ L, int64_t ld, const float *__restrict__ dinv,
-                                           const float *__restrict__ Qb, const double *__restrict__ rhs,
-                                           double *__restrict__ x, int *counters, int nblk, int *status,
-                                           long spin_limit)
+                                           const float *__restrict__ Qb, double *__restrict__ rhs,
+                                           double *__restrict__ x, double *__restrict__ z, int *counters, int nblk,
+                                           int *status, long spin_limit)
 {
     constexpr int BS = 128;
     __shared__ float Dl[BS * (BS + 1)];  // D_b, row-major, padded stride
@@ -353,7 +377,7 @@ __device__ __forceinline__ void trsv1_body(const float *__restrict__ L, int64_t 
     __shared__ int s_blk;
     const int tid = threadIdx.x;
     if (tid == 0) {
-        const int ticket = atomicAdd(&counters[BWD ? kBwdTicket : kFwdTicket], 1);
+        const int ticket = take_ticket<BWD>(counters);
         s_blk = BWD ? nblk - 1 - ticket : ticket;
     }
     __syncthreads();
@@ -384,7 +408,10 @@ __device__ __forceinline__ void trsv1_body(const float *__restrict__ L, int64_t 
 
     // resident from the start: the right-hand side, D_b and the near tile Q_b
     double r0 = 0.0;
-    if (tid < BS) r0 = rhs[(int64_t)b * BS + tid];
+    if (tid < BS) {
+        r0 = rhs[(int64_t)b * BS + tid];
+        unset_after_read<BWD>(rhs, z, (int64_t)b * BS + tid);
+    }
     Tile tq;
     if (has_near) load(Qb + (int64_t)b * BS * BS, BS, tq);
     {
@@ -454,93 +481,112 @@ __device__ __forceinline__ void trsv1_body(const float *__restrict__ L, int64_t 
 template <bool BWD>
 __global__ void __launch_bounds__(256)
 k_trsv1(const float *__restrict__ L, int64_t ld, const float *__restrict__ dinv, const float *__restrict__ Qb,
-        const double *__restrict__ rhs, double *__restrict__ x, int *counters, int nblk, int *status,
+        double *__restrict__ rhs, double *__restrict__ x, double *__restrict__ z, int *counters, int nblk, int *status,
         long spin_limit)
 {
-    trsv1_body<BWD>(L, ld, dinv, Qb, rhs, x, counters, nblk, status, spin_limit);
+    trsv1_body<BWD>(L, ld, dinv, Qb, rhs, x, z, counters, nblk, status, spin_limit);
 }
 
 // The near tiles of k_trsv1 for every 128-block of the FP32 factor, both
-// directions: workgroup (b, d) forms Q = D_b T(b, n) (forward: D_b L(b, b - 1);
-// backward: D_b^T L^T(b, b + 1)) with FP64 accumulation of the FP32 entries,
-// stored in FP32, column-major, at Q + (d nblk + b) 128^2.  The first block in
-// solve order has none.
+// directions: Q = D_b T(b, n) (forward: D_b L(b, b - 1); backward: D_b^T L^T(b, b + 1))
+// with FP64 accumulation of the FP32 entries, stored in FP32, column-major, at
+// Q + (d nblk + b) 128^2.  The first block in solve order has none.
+// A workgroup forms one 64 x 64 quadrant on the FP64 matrix cores (at small sizes the
+// launch is one block's latency: 44 us for a whole block per workgroup on the
+// vector unit); K in two stages of 64, of which the triangular D leaves one empty
+// for half of the quadrants.  v_mfma_f64_16x16x4: lane 16 kq + q supplies A(q, kq) and
+// B(kq, q) and holds D(kq + 4 v, q); A from the tile's columns and B from D's rows,
+// so sixteen lanes store sixteen consecutive rows.
 __global__ void __launch_bounds__(256)
 k_near_q(const float *__restrict__ A, int64_t npad, const float *__restrict__ dinv, float *__restrict__ Q, int nblk)
 {
-    constexpr int B = 128;
-    __shared__ float Xs[B * B];  // X(i, k) at Xs[k B + i]
-    __shared__ float Ys[B * B];  // Y(k, j) at Ys[k B + j]
+    typedef double v4d __attribute__((ext_vector_type(4)));
+    constexpr int B = 128, H = 64, SL = 80;  // stage stride: the four k-rows of a read on disjoint banks
+    __shared__ float Xs[H * SL];  // X(i, k) at Xs[k SL + i]
+    __shared__ float Ys[H * SL];  // Y(k, j) at Ys[k SL + j]
     const int b = blockIdx.x, d = blockIdx.y;
     const bool bwd = d == 1;
     if (bwd ? (b >= nblk - 1) : (b == 0)) return;  // uniform per workgroup
     const int jn = bwd ? b + 1 : b - 1;
-    const int tid = threadIdx.x;
-    const int ti = tid & 15, tj = tid >> 4;  // output rows 8 ti .., columns 8 tj ..
+    const int i0 = H * (blockIdx.z & 1), j0 = H * (blockIdx.z >> 1);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int q = lane & 15, kq = lane >> 4;
     const float *D = dinv + (int64_t)b * B * B;  // column-major inverse
-    for (int e = tid; e < B * B; e += 256) {
-        const int i = e & (B - 1), k = e >> 7;
-        Xs[k * B + i] = bwd ? D[i * B + k] : D[k * B + i];
-        // tile T(b, jn): element (r, c) at A[(jn B + c) npad + b B + r], as Y(k = r, j = c)
-        Ys[i * B + k] = A[((int64_t)jn * B + k) * npad + (int64_t)b * B + i];
-    }
-    __syncthreads();
-    double acc[8][8];
+    v4d acc[4];
 #pragma unroll
-    for (int a = 0; a < 8; ++a)
+    for (int t = 0; t < 4; ++t)
 #pragma unroll
-        for (int c = 0; c < 8; ++c) acc[a][c] = 0.0;
-    for (int k = 0; k < B; ++k) {
-        const float4 xa = *reinterpret_cast<const float4 *>(&Xs[k * B + 8 * ti]);
-        const float4 xb = *reinterpret_cast<const float4 *>(&Xs[k * B + 8 * ti + 4]);
-        const float4 ya = *reinterpret_cast<const float4 *>(&Ys[k * B + 8 * tj]);
-        const float4 yb = *reinterpret_cast<const float4 *>(&Ys[k * B + 8 * tj + 4]);
-        const double xv[8] = {xa.x, xa.y, xa.z, xa.w, xb.x, xb.y, xb.z, xb.w};
-        const double yv[8] = {ya.x, ya.y, ya.z, ya.w, yb.x, yb.y, yb.z, yb.w};
+        for (int v = 0; v < 4; ++v) acc[t][v] = 0.0;
+    for (int k0 = 0; k0 < B; k0 += H) {
+        if (bwd ? (k0 < i0) : (k0 > i0)) continue;  // D(i, k) = 0 for k > i, D(k, i) for k < i
+        // every load in flight before the first LDS store
+        float xv[H * H / 256], yv[H * H / 256];
+        const int u = tid & (H - 1), v0 = tid >> 6;
 #pragma unroll
-        for (int a = 0; a < 8; ++a)
+        for (int e = 0; e < H * H / 256; ++e) {
+            const int v = v0 + 4 * e;
+            xv[e] = bwd ? D[(i0 + v) * B + k0 + u] : D[(k0 + v) * B + i0 + u];
+            // tile T(b, jn): element (r, c) at A[(jn B + c) npad + b B + r], as Y(k = r, j = c)
+            yv[e] = A[((int64_t)jn * B + j0 + v) * npad + (int64_t)b * B + k0 + u];
+        }
+        __syncthreads();
 #pragma unroll
-            for (int c = 0; c < 8; ++c) acc[a][c] = fma(xv[a], yv[c], acc[a][c]);
+        for (int e = 0; e < H * H / 256; ++e) {
+            const int v = v0 + 4 * e;
+            Xs[bwd ? u * SL + v : v * SL + u] = xv[e];
+            Ys[u * SL + v] = yv[e];
+        }
+        __syncthreads();
+#pragma unroll 4
+        for (int k = 0; k < H; k += 4) {
+            const double x = (double)Xs[(k + kq) * SL + 16 * wave + q];
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)Ys[(k + kq) * SL + 16 * t + q], x, acc[t], 0, 0, 0);
+        }
     }
     float *dst = Q + ((int64_t)d * nblk + b) * B * B;
 #pragma unroll
-    for (int c = 0; c < 8; ++c)
+    for (int t = 0; t < 4; ++t)
 #pragma unroll
-        for (int a = 0; a < 8; ++a) dst[(8 * tj + c) * B + 8 * ti + a] = (float)acc[a][c];
+        for (int v = 0; v < 4; ++v) dst[(j0 + 16 * t + kq + 4 * v) * B + i0 + 16 * wave + q] = (float)acc[t][v];
 }
 
 // Batched: workgroups of problem p take tickets from p's own counters, so the
 // forward-progress argument holds per problem; problems never wait on each other.
 template <bool BWD>
 __global__ void __launch_bounds__(256)
-k_trsv_b(const BProb *__restrict__ P, BWork w, int rhs_slot, int x_slot)
+k_trsv_b(const BProb *__restrict__ P, BWork w, int rhs_slot, int x_slot, int z_slot)
 {
     const int i = bfind(w.pref, w.na, blockIdx.x);
     const BProb &q = P[w.plist[i]];
     if (!q.active) return;
     trsv_body<BWD, float, 128>(q.A, q.npad, q.dinv, q.vec + (int64_t)rhs_slot * q.npad,
-                               q.vec + (int64_t)x_slot * q.npad, q.ints + 64, (int)(q.npad / 128), q.ints,
-                               kSpinLimitDefault);
+                               q.vec + (int64_t)x_slot * q.npad, q.vec + (int64_t)z_slot * q.npad, q.ints + 64,
+                               (int)(q.npad / 128), q.ints, kSpinLimitDefault);
 }
 
-// Tickets to zero and the vector in `slot` unset, one workgroup per problem
-// (tickets: only when `tickets`).
-__global__ void k_unset_b(const BProb *__restrict__ P, BWork w, int slot, int tickets)
+// Tickets zero and the vector in `slot` unset, one workgroup per problem.
+__global__ void k_prec_begin_b(const BProb *__restrict__ P, int slot)
 {
-    const BProb &q = P[w.plist[blockIdx.x]];
-    if (!q.active) return;
-    if (tickets)
-        for (int e = threadIdx.x; e < kCounterInts; e += blockDim.x) q.ints[64 + e] = 0;
+    const BProb &q = P[blockIdx.x];
+    for (int e = threadIdx.x; e < kCounterInts; e += blockDim.x) q.ints[64 + e] = 0;
     uint64_t *a = reinterpret_cast<uint64_t *>(q.vec + (int64_t)slot * q.npad);
     for (int64_t e = threadIdx.x; e < q.npad; e += blockDim.x) a[e] = kUnset;
 }
 
-// Every entry of a (n entries) unset.
-__global__ void k_unset(double *__restrict__ a, int64_t n)
+// Start of a refinement: status words (optional) and tickets zero, y unset, ones
+// on [0, n) and zero on [n, npad) into rhs (optional).
+__global__ void k_refine_begin(double *__restrict__ y, double *__restrict__ rhs, int64_t n, int64_t npad,
+                               int *counters, int *status)
 {
-    uint64_t *u = reinterpret_cast<uint64_t *>(a);
-    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x)
-        u[e] = kUnset;
+    const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (e < kCounterInts) counters[e] = 0;
+    if (status && e < kStCount) status[e] = 0;
+    if (e < npad) {
+        reinterpret_cast<uint64_t *>(y)[e] = kUnset;
+        if (rhs) rhs[e] = e < n ? 1.0 : 0.0;
+    }
 }
 
 }  // namespace
@@ -549,15 +595,25 @@ size_t prec_counter_ints() { return kCounterInts; }
 
 int64_t prec_b_units(int64_t npad) { return npad / 256; }
 
+void launch_prec_begin_b(hipStream_t s, const BProb *P, int B, int tmp_slot)
+{
+    if (B > 0) hipLaunchKernelGGL(k_prec_begin_b, dim3(B), dim3(256), 0, s, P, tmp_slot);
+}
+
 // x_slot = (L L^T)^{-1} rhs_slot for every problem of the work list (units = npad/128 each)
 void launch_prec_apply_b(hipStream_t s, const BProb *P, const BWork &w, int rhs_slot, int tmp_slot,
                          int x_slot)
 {
     if (w.na <= 0) return;
-    hipLaunchKernelGGL(k_unset_b, dim3(w.na), dim3(256), 0, s, P, w, tmp_slot, 1);
-    hipLaunchKernelGGL(k_trsv_b<false>, dim3((unsigned)w.total), dim3(256), 0, s, P, w, rhs_slot, tmp_slot);
-    hipLaunchKernelGGL(k_unset_b, dim3(w.na), dim3(256), 0, s, P, w, x_slot, 0);
-    hipLaunchKernelGGL(k_trsv_b<true>, dim3((unsigned)w.total), dim3(256), 0, s, P, w, tmp_slot, x_slot);
+    hipLaunchKernelGGL(k_trsv_b<false>, dim3((unsigned)w.total), dim3(256), 0, s, P, w, rhs_slot, tmp_slot, x_slot);
+    hipLaunchKernelGGL(k_trsv_b<true>, dim3((unsigned)w.total), dim3(256), 0, s, P, w, tmp_slot, x_slot, tmp_slot);
+}
+
+void launch_refine_begin(hipStream_t s, double *y_tmp, double *rhs, int64_t n, int64_t npad, int *counters,
+                         int *status)
+{
+    hipLaunchKernelGGL(k_refine_begin, dim3((unsigned)((npad + 255) / 256)), dim3(256), 0, s, y_tmp, rhs, n, npad,
+                       counters, status);
 }
 
 template <typename T, int BS>
@@ -565,15 +621,11 @@ void prec_apply(hipStream_t s, const T *L, int64_t npad, const T *dinv, const do
                 int *counters, int *status, long spin_limit)
 {
     const int nblk = (int)(npad / BS);  // even: npad is a multiple of 256
-    const unsigned gu = (unsigned)std::min<int64_t>((npad + 255) / 256, 1024);
-    launch_fill_ints(s, counters, kCounterInts, 0);
-    hipLaunchKernelGGL(k_unset, dim3(gu), dim3(256), 0, s, y_tmp, npad);
-    hipLaunchKernelGGL((k_trsv<false, T, BS>), dim3(nblk / 2), dim3(256), 0, s, L, npad, dinv, r, y_tmp, counters,
+    double *rhs = const_cast<double *>(r);  // the forward solve only reads it
+    hipLaunchKernelGGL((k_trsv<false, T, BS>), dim3(nblk / 2), dim3(256), 0, s, L, npad, dinv, rhs, y_tmp, z, counters,
                        nblk, status, spin_limit);
-    // z may be the caller's r: unset it only once the forward solve has read r
-    hipLaunchKernelGGL(k_unset, dim3(gu), dim3(256), 0, s, z, npad);
-    hipLaunchKernelGGL((k_trsv<true, T, BS>), dim3(nblk / 2), dim3(256), 0, s, L, npad, dinv, y_tmp, z, counters,
-                       nblk, status, spin_limit);
+    hipLaunchKernelGGL((k_trsv<true, T, BS>), dim3(nblk / 2), dim3(256), 0, s, L, npad, dinv, y_tmp, z,
+                       (double *)nullptr, counters, nblk, status, spin_limit);
 }
 
 void launch_prec_apply(hipStream_t s, const float *L, int64_t npad, const float *dinv,
@@ -582,15 +634,11 @@ void launch_prec_apply(hipStream_t s, const float *L, int64_t npad, const float 
 {
     const int nblk = (int)(npad / 128);
     const float *Qb = Q + (int64_t)nblk * 128 * 128;  // the backward direction's tiles
-    const unsigned gu = (unsigned)std::min<int64_t>((npad + 255) / 256, 1024);
-    launch_fill_ints(s, counters, kCounterInts, 0);
-    hipLaunchKernelGGL(k_unset, dim3(gu), dim3(256), 0, s, y_tmp, npad);
-    hipLaunchKernelGGL(k_trsv1<false>, dim3(nblk), dim3(256), 0, s, L, npad, dinv, Q, r, y_tmp, counters, nblk,
+    double *rhs = const_cast<double *>(r);  // the forward solve only reads it
+    hipLaunchKernelGGL(k_trsv1<false>, dim3(nblk), dim3(256), 0, s, L, npad, dinv, Q, rhs, y_tmp, z, counters, nblk,
                        status, spin_limit);
-    // z may be the caller's r: unset it only once the forward solve has read r
-    hipLaunchKernelGGL(k_unset, dim3(gu), dim3(256), 0, s, z, npad);
-    hipLaunchKernelGGL(k_trsv1<true>, dim3(nblk), dim3(256), 0, s, L, npad, dinv, Qb, y_tmp, z, counters, nblk,
-                       status, spin_limit);
+    hipLaunchKernelGGL(k_trsv1<true>, dim3(nblk), dim3(256), 0, s, L, npad, dinv, Qb, y_tmp, z, (double *)nullptr,
+                       counters, nblk, status, spin_limit);
 }
 
 size_t near_q_floats(int64_t npad) { return (size_t)npad * 256; }
@@ -599,7 +647,7 @@ void launch_near_q(hipStream_t s, const float *A, int64_t npad, const float *din
 {
     const int nblk = (int)(npad / 128);
     if (nblk < 2) return;
-    hipLaunchKernelGGL(k_near_q, dim3((unsigned)nblk, 2), dim3(256), 0, s, A, npad, dinv, Q, nblk);
+    hipLaunchKernelGGL(k_near_q, dim3((unsigned)nblk, 2, 4), dim3(256), 0, s, A, npad, dinv, Q, nblk);
 }
 
 void launch_chol64_solve(hipStream_t s, const double *L, int64_t npad, const double *dinv, const double *r,
