@@ -221,6 +221,16 @@ int batch_setup(mag_ctx *c, Batch &bt, const std::vector<const double *> &Xs,
     bt.d = (BProb *)c->bdesc.p;
     bt.dstage = (double *)c->bstage.p;
     bt.h.resize(B);
+    // the split images of the trailing updates (after pairs of panels or single ones),
+    // if there is room for them
+    const auto image = [](int64_t npad) {
+        return std::max(split_image_bytes(std::max<int64_t>(0, npad - 2 * kPanel), 2 * kPanel),
+                        split_image_bytes(std::max<int64_t>(0, npad - kPanel), kPanel));
+    };
+    size_t img = 0;
+    for (int b = 0; b < B; ++b) img += image(np[b]);
+    const bool split = img > 0 && ensure(c, c->split, img) == MAG_OK;
+    char *ip = (char *)c->split.p;
     float *fp = (float *)c->bfactor.p;
     float *dp = (float *)c->bdinv.p;
     double *vp = (double *)c->bvec.p;
@@ -244,6 +254,8 @@ int batch_setup(mag_ctx *c, Batch &bt, const std::vector<const double *> &Xs,
         q.ints = (int *)c->bints.p + (size_t)b * kIntsPer;
         q.m = m;
         q.active = 1;
+        q.img = split ? ip : nullptr;
+        ip += image(np[b]);
     }
     BCHK(hipMemsetAsync(c->bvec.p, 0, sizeof(double) * vec, bt.s));
     BCHK(hipMemsetAsync(c->bscal.p, 0, sizeof(double) * (size_t)B * SC_COUNT, bt.s));
@@ -257,10 +269,35 @@ int batch_setup(mag_ctx *c, Batch &bt, const std::vector<const double *> &Xs,
 // arena), launched inside the step graph's capture; every kernel skips problems
 // whose descriptor is inactive.
 struct FLaunch {
-    int kind;  // 0 trsm, 1 subupdate, 2 syrk (pair), 3 potrf, 4 tilegen, 5 zero status, 6 strip, 7 syrk (single)
+    // 0 trsm, 1 subupdate, 2 syrk (pair), 3 potrf, 4 tilegen, 5 zero status, 6 strip, 7 syrk
+    // (single); on the split image: 8 split, 9 syrk
+    int kind;
     int64_t kk;
     BWork w;
+    int64_t K = 0;
+    int tm = 0;
 };
+
+// The trailing update after the K columns at k.
+int schedule_trailing(Batch &bt, std::vector<FLaunch> &seq, const std::vector<int> &all, int64_t k, int64_t K)
+{
+    BWork w;
+    const auto rows = [&](int p) { return bt.h[p].npad - k - K; };
+    if (!bt.h[0].img) {
+        const int kind = K == 2 * kPanel ? 2 : 4;
+        BRC(bt.make_work(all, [&](int p) { return rows(p) > 0 ? gemm_b_units(kind, bt.h[p].npad, k) : 0; }, true, w));
+        seq.push_back({K == 2 * kPanel ? 2 : 7, k, w});
+        return MAG_OK;
+    }
+    int64_t tiles = 0;
+    for (int p : all) tiles += syrk_split_b_units(rows(p), 256);
+    const int tm = syrk_split_tile(tiles);
+    BRC(bt.make_work(all, [&](int p) { return split_b_units(rows(p), K); }, true, w));
+    seq.push_back({8, k, w, K});
+    BRC(bt.make_work(all, [&](int p) { return syrk_split_b_units(rows(p), tm); }, true, w));
+    seq.push_back({9, k, w, K, tm});
+    return MAG_OK;
+}
 
 // group: 0 the context's tuned choice for this batch's largest npad, 1 single
 // panels, 2 pairs.
@@ -293,9 +330,7 @@ int batch_factor_schedule(Batch &bt, std::vector<FLaunch> &seq, int group = 0)
                     seq.push_back({1, kk, w1});
                 }
             }
-            BWork w4;
-            BRC(bt.make_work(all, [&](int p) { return k < bt.h[p].npad ? gemm_b_units(4, bt.h[p].npad, k) : 0; }, true, w4));
-            seq.push_back({7, k, w4});
+            BRC(schedule_trailing(bt, seq, all, k, kPanel));
         }
         return MAG_OK;
     }
@@ -324,9 +359,7 @@ int batch_factor_schedule(Batch &bt, std::vector<FLaunch> &seq, int group = 0)
                 }
             }
         }
-        BWork w2;
-        BRC(bt.make_work(all, [&](int p) { return k < bt.h[p].npad ? gemm_b_units(2, bt.h[p].npad, k) : 0; }, true, w2));
-        seq.push_back({2, k, w2});
+        BRC(schedule_trailing(bt, seq, all, k, 2 * kPanel));
     }
     return MAG_OK;
 }
@@ -340,6 +373,8 @@ void record_factor(Batch &bt, const std::vector<FLaunch> &seq)
         case 3: launch_potrf128_b(bt.s, bt.d, L.w, L.kk); break;
         case 6: launch_gemm_b(bt.s, 3, bt.d, L.w, L.kk); break;
         case 7: launch_gemm_b(bt.s, 4, bt.d, L.w, L.kk); break;
+        case 8: launch_split_b(bt.s, bt.d, L.w, L.kk, L.K); break;
+        case 9: launch_syrk_split_b(bt.s, bt.d, L.w, L.kk, L.K, L.tm); break;
         default: launch_gemm_b(bt.s, L.kind, bt.d, L.w, L.kk); break;
         }
     }

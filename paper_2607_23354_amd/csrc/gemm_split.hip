@@ -58,13 +58,10 @@ __device__ __forceinline__ void split8(const float (&x)[8], v8bf (&c)[NS])
     }
 }
 
-// rows [0, rows) of the columns at P (column-major, K of them) into img
-__global__ void __launch_bounds__(NT)
-k_split(const float *__restrict__ P, int64_t ldp, int64_t rows, v8bf *__restrict__ img, int64_t stride)
+// row r of column group g of the columns at P (column-major) into img
+__device__ __forceinline__ void split_unit(const float *__restrict__ P, int64_t ldp, int64_t r, int64_t g,
+                                           v8bf *__restrict__ img, int64_t stride)
 {
-    const int64_t r = blockIdx.x * (int64_t)NT + threadIdx.x;
-    const int64_t g = blockIdx.y;
-    if (r >= rows) return;
     float x[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) x[j] = P[(8 * g + j) * ldp + r];
@@ -72,6 +69,14 @@ k_split(const float *__restrict__ P, int64_t ldp, int64_t rows, v8bf *__restrict
     split8(x, c);
 #pragma unroll
     for (int s = 0; s < NS; ++s) img[(g * NS + s) * stride + r] = c[s];
+}
+
+// rows [0, rows) of the columns at P into img
+__global__ void __launch_bounds__(NT)
+k_split(const float *__restrict__ P, int64_t ldp, int64_t rows, v8bf *__restrict__ img, int64_t stride)
+{
+    const int64_t r = blockIdx.x * (int64_t)NT + threadIdx.x;
+    if (r < rows) split_unit(P, ldp, r, blockIdx.y, img, stride);
 }
 
 // ---- the update ---------------------------------------------------------------
@@ -233,6 +238,34 @@ k_syrk_split(float *__restrict__ C, int64_t ldc, const v8bf *__restrict__ img, i
     split_tile_body<TM>(C, ldc, img, stride, i0, j0, rows, K);
 }
 
+// Batched: the trailing rows of every active problem after the K columns at kk.
+// Units of the split: (rows / 256) x (K / 8); of the update, tiles of TM x 128 by
+// rows of tiles.
+__global__ void __launch_bounds__(NT)
+k_split_b(const BProb *__restrict__ Pr, BWork w, int64_t kk, int64_t K)
+{
+    const int i = bfind(w.pref, w.na, blockIdx.x);
+    const BProb &q = Pr[w.plist[i]];
+    if (!q.active) return;
+    const int64_t u = blockIdx.x - w.pref[i], rows = q.npad - kk - K, rb = rows / NT;
+    split_unit(q.A + kk * q.npad + kk + K, q.npad, (u % rb) * NT + threadIdx.x, u / rb, (v8bf *)q.img, rows);
+}
+
+template <int TM>
+__global__ void __launch_bounds__(NT, 2)
+k_syrk_split_b(const BProb *__restrict__ Pr, BWork w, int64_t kk, int64_t K)
+{
+    constexpr int64_t R = TM / TN;  // tile row ti has R (ti + 1) tiles
+    const int i = bfind(w.pref, w.na, blockIdx.x);
+    const BProb &q = Pr[w.plist[i]];
+    if (!q.active) return;
+    const int64_t u = blockIdx.x - w.pref[i], rows = q.npad - kk - K;
+    int64_t ti, tj;
+    tri_index(u / R, ti, tj);
+    tj = u - R * (ti * (ti + 1) / 2);
+    split_tile_body<TM>(q.A + (kk + K) * q.npad + kk + K, q.npad, (const v8bf *)q.img, rows, ti * TM, tj * TN, rows, K);
+}
+
 }  // namespace
 
 size_t split_image_bytes(int64_t rows, int64_t K) { return (size_t)round_up(rows, 256) * (size_t)(K / 8) * NS * 16; }
@@ -244,6 +277,28 @@ void launch_split(hipStream_t s, const float *P, int64_t ldp, int64_t rows, int6
                        (v8bf *)img, round_up(rows, 256));
 }
 
+// Units of one problem of the batched split and update (rows: a multiple of 256).
+int64_t split_b_units(int64_t rows, int64_t K) { return rows > 0 ? rows / NT * (K / 8) : 0; }
+int64_t syrk_split_b_units(int64_t rows, int tm)
+{
+    const int64_t T = rows > 0 ? rows / tm : 0;
+    return T * (T + 1) / 2 * (tm / TN);
+}
+// row tile of the batched update, from its number of 256-row tiles (see launch_syrk_split)
+int syrk_split_tile(int64_t tiles256) { return tiles256 >= 400 ? 256 : 128; }
+
+void launch_split_b(hipStream_t s, const BProb *P, const BWork &w, int64_t kk, int64_t K)
+{
+    if (w.total > 0) hipLaunchKernelGGL(k_split_b, dim3((unsigned)w.total), dim3(NT), 0, s, P, w, kk, K);
+}
+
+void launch_syrk_split_b(hipStream_t s, const BProb *P, const BWork &w, int64_t kk, int64_t K, int tm)
+{
+    if (w.total <= 0) return;
+    if (tm == 256) hipLaunchKernelGGL(k_syrk_split_b<256>, dim3((unsigned)w.total), dim3(NT), 0, s, P, w, kk, K);
+    else hipLaunchKernelGGL(k_syrk_split_b<128>, dim3((unsigned)w.total), dim3(NT), 0, s, P, w, kk, K);
+}
+
 void launch_syrk_split(hipStream_t s, float *C, int64_t ldc, const void *img, int64_t rows, int64_t K)
 {
     if (rows <= 0 || K <= 0) return;
@@ -252,7 +307,7 @@ void launch_syrk_split(hipStream_t s, float *C, int64_t ldc, const void *img, in
     const int64_t blocks = (nsup + kXcds - 1) / kXcds * kXcds * (kSup / TN);
     // 256-row tiles read a quarter less through L2 per product; below about 400 of
     // them (two per CU hold 512) the 128-row ones spread the work better
-    if ((rows / 256) * (rows / 256 + 1) >= 400)
+    if (syrk_split_tile((rows / 256) * (rows / 256 + 1)) == 256)
         hipLaunchKernelGGL(k_syrk_split<256>, dim3((unsigned)(blocks * (kSup / 256))), dim3(NT), 0, s, C, ldc,
                            (const v8bf *)img, round_up(rows, 256), rows, K);
     else

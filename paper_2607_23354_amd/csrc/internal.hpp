@@ -67,6 +67,7 @@ struct BProb {
     int *ints;        // status [0, 64) and preconditioner counters [64, ...)
     int32_t m;
     int32_t active;   // 0: skip (finished)
+    void *img;        // BF16 split image of a panel pair (NULL: FP32 trailing updates)
 };
 
 struct BWork {
@@ -209,6 +210,12 @@ void launch_tilegen32_b(hipStream_t s, const BProb *P, const BWork &w);
 void launch_potrf128_b(hipStream_t s, const BProb *P, const BWork &w, int64_t k0);
 int64_t gemm_b_units(int kind, int64_t npad, int64_t kk);
 void launch_gemm_b(hipStream_t s, int kind, const BProb *P, const BWork &w, int64_t kk);
+// gemm_split.hip: the trailing updates on the BF16 matrix cores
+int64_t split_b_units(int64_t rows, int64_t K);
+int64_t syrk_split_b_units(int64_t rows, int tm);
+int syrk_split_tile(int64_t tiles256);
+void launch_split_b(hipStream_t s, const BProb *P, const BWork &w, int64_t kk, int64_t K);
+void launch_syrk_split_b(hipStream_t s, const BProb *P, const BWork &w, int64_t kk, int64_t K, int tm);
 int64_t prec_b_units(int64_t npad);
 // tickets zero and tmp_slot unset: once before the first launch_prec_apply_b, which
 // leaves them so; rhs_slot, tmp_slot and x_slot differ

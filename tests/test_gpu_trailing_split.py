@@ -76,3 +76,32 @@ def test_cap_without_room_for_the_image(mag):
         assert torch.isfinite(d).all()
     finally:
         ctx.close()
+
+
+# clouds whose trailing updates fall on the 128-row tiles (few) and on the 256-row
+# ones (many), in both groupings, beside clouds with no trailing update at all
+@pytest.mark.parametrize("group", [1, 2])
+@pytest.mark.parametrize("sizes", [(200, 300, 513, 1025), (3000,) * 6 + (257, 767, 2049)])
+def test_batched_split_update(mag, sizes, group):
+    clouds = [W.gaussian(n, 3, seed=n + b) for b, n in enumerate(sizes)]
+    X, offs = W.pack_clouds(clouds)
+    ts = [W.gaussian_cutoff_estimate(n, 3) for n in sizes]
+    ctx = mag.Context(0)
+    try:
+        mag.tune_batch_group(max(sizes), group, ctx=ctx)
+        w, _, infos = mag.weighting_batch(dev(X), offs, ts, ctx=ctx)
+        w = w.cpu().numpy()
+        held = ctx.workspace_bytes()
+        for b, (Xb, t) in enumerate(zip(clouds, ts)):
+            assert infos[b]["status"] == 0
+            assert np.abs(oracle.residual(Xb, t, w[offs[b]:offs[b + 1]])).max() <= 1e-12
+        # the same without room for the images: the FP32 updates
+        ctx.close()
+        ctx = mag.Context(0)
+        mag.tune_batch_group(max(sizes), group, ctx=ctx)
+        ctx.set_workspace_limit(held - 1)
+        wc, _, infos = mag.weighting_batch(dev(X), offs, ts, ctx=ctx)
+        assert ctx.workspace_bytes() < held and all(i["status"] == 0 for i in infos)
+        assert np.abs(wc.cpu().numpy() - w).max() <= 1e-10 * np.abs(w).max()
+    finally:
+        ctx.close()
