@@ -36,7 +36,7 @@ void factor_panel(hipStream_t s, float *A, int64_t npad, int64_t n, int64_t k, i
     for (int64_t sub = 0; sub < nsub; ++sub) {
         const int64_t kk = k + sub * T;
         float *Linv = dinv + (kk / T) * T * T;
-        launch_potrf128(s, A, npad, kk, n, Linv, status);
+        if (sub == 0) launch_potrf128(s, A, npad, kk, n, Linv, status);
         const int64_t below = npad - kk - T;
         if (below > 0) {
             float *A21 = A + kk * npad + kk + T;
@@ -44,11 +44,8 @@ void factor_panel(hipStream_t s, float *A, int64_t npad, int64_t n, int64_t k, i
             launch_gemm_rows64(s, A21, npad, A21, npad, Linv, T, below, T, T, kGemmSetT, A12);
         }
         if (sub + 1 < nsub) {
-            // the panel's remaining sub-panels (rows kk+T ..) by this sub-panel;
-            // tiles above their diagonal are rewritten later by their own trsm
-            float *C = A + (kk + T) * npad + kk + T;
-            const float *P = A + kk * npad + kk + T;
-            launch_gemm_rows64(s, C, npad, P, npad, P, npad, below, (nsub - sub - 1) * T, T, kGemmSub);
+            // the panel's remaining sub-panels by this one, and the next diagonal block
+            launch_update_potrf(s, A, npad, kk, n, (int)(nsub - sub - 1), Linv + T * T, status);
         }
     }
 }

@@ -422,6 +422,10 @@ void chol64_factor(hipStream_t s, double *A, int64_t npad, int64_t n, double *di
 // write its inverse to Linv (128 x 128 column-major).  Breakdown -> status.
 // n: rows from n on are identity padding (off-diagonal entries zero).
 void launch_potrf128(hipStream_t s, float *A, int64_t ld, int64_t k0, int64_t n, float *Linv, int *status);
+// The ncol 128-column blocks right of the sub-panel at kk updated by it (lower 128-tiles of
+// the rows below it), and launch_potrf128 of the first of them, at kk + 128.
+void launch_update_potrf(hipStream_t s, float *A, int64_t ld, int64_t kk, int64_t n, int ncol, float *Linv,
+                         int *status);
 
 // gemv64.hip: FP64 matrix-free products with Z regenerated from X.
 //   mode 0: y = Z v;  mode 1: y = b - Z v (b may be NULL meaning ones) and

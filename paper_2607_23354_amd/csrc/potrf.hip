@@ -148,15 +148,22 @@ __device__ __forceinline__ void block_updates(v4f (&Q)[NBLK], const v4f &x, cons
     for (int m = M0; m < M1; ++m) Q[m] = Q[m + 1] - acc[m - M0];
 }
 
+// FUSED: the block is first updated by the 128 columns of the sub-panel left of it
+// (its rows of that sub-panel's L21), A -= L21 L21^T; Us holds the row blocks of 64
+// of those columns at a time.
+template <bool FUSED>
 __device__ __forceinline__ void potrf128_body(float *__restrict__ A, int64_t ld, int64_t k0, int64_t n,
-                                              float *__restrict__ Linv, int *__restrict__ status)
+                                              float *__restrict__ Linv, int *__restrict__ status, v4f (*Us)[NBLK][64])
 {
     __shared__ v4f Lx[NBLK][64];   // the blocks L_Kj of a step, row layout
     __shared__ float Yd[SB * SB];  // the inverse of its diagonal block, Yd[k * SB + c]
     __shared__ int bad;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int I = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // the row block of a wave: waves w and w + 4 share a SIMD, and a long row block goes
+    // with a short one
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int I = wave < NBLK / 2 ? wave : 3 * NBLK / 2 - 1 - wave;
     const int g = lane >> 4, i = lane & 15;
     float *Ab = A + k0 * ld + k0;
 
@@ -197,6 +204,45 @@ __device__ __forceinline__ void potrf128_body(float *__restrict__ A, int64_t ld,
             for (int r = 0; r < 4; ++r) Q[K][r] = K < I ? Q[K][r] : (K == I ? dg[r] : 0.0f);
     }
     if (tid == 0) bad = 0;
+    if (FUSED) {
+        const unsigned off = 4 * g * (unsigned)ld + SB * I + i;
+        v4f x[2][4];
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) x[h][c][r] = (Ab - (NB - 64 * h - SB * c - r) * ld)[off];
+        v4f acc[NBLK];
+#pragma unroll
+        for (int K = 0; K < NBLK; ++K)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[K][r] = 0.0f;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            if (h > 0) __syncthreads();
+#pragma unroll
+            for (int c = 0; c < 4; ++c) Us[c][I][lane] = x[h][c];
+            __syncthreads();
+#pragma unroll
+            for (int K = 0; K < NBLK; ++K) {
+                if (K > I) continue;  // uniform per wave
+                v4f y[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) y[c] = Us[c][K][lane];
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        acc[K] = __builtin_amdgcn_mfma_f32_16x16x4f32(y[c][r], x[h][c][r], acc[K], 0, 0, 0);
+            }
+        }
+#pragma unroll
+        for (int K = 0; K < NBLK; ++K) {
+            Q[K] -= acc[K];
+            if (K == I) dg = Q[K];
+        }
+    }
     __syncthreads();
 
     v4f P = dg, P0, X;
@@ -284,7 +330,7 @@ __global__ void __launch_bounds__(NTP)
 k_potrf128(float *__restrict__ A, int64_t ld, int64_t k0, int64_t n, float *__restrict__ Linv,
            int *__restrict__ status)
 {
-    potrf128_body(A, ld, k0, n, Linv, status);
+    potrf128_body<false>(A, ld, k0, n, Linv, status, nullptr);
 }
 
 // Batched: one workgroup per problem whose padded size exceeds k0.
@@ -293,7 +339,93 @@ k_potrf128_b(const BProb *__restrict__ P, BWork w, int64_t k0)
 {
     const BProb &q = P[w.plist[blockIdx.x]];
     if (!q.active || k0 >= q.npad) return;
-    potrf128_body(q.A, q.npad, k0, q.n, q.dinv + (k0 / NB) * NB * NB, q.ints);
+    potrf128_body<false>(q.A, q.npad, k0, q.n, q.dinv + (k0 / NB) * NB * NB, q.ints, nullptr);
+}
+
+// ---- sub-panel update and the next diagonal block in one launch ------------------
+// C (i, j) -= P P^T for one 128 x 128 tile (rows i0.., columns j0..) by the 128
+// columns at P, on eight waves of 32 x 64 each; K staged through LDS in
+// double-buffered chunks of 16 by direct loads (see gemm_mfma.hip).
+typedef float v16f __attribute__((ext_vector_type(16)));
+typedef const __attribute__((address_space(1))) void *gptr;
+typedef __attribute__((address_space(3))) void *lptr;
+constexpr int KC = 16;
+
+__device__ __forceinline__ void update_tile(float *__restrict__ C, int64_t ldc, const float *__restrict__ P,
+                                            int64_t ldp, int64_t i0, int64_t j0, float *lds)
+{
+    float (*Ps)[KC][NB] = reinterpret_cast<float (*)[KC][NB]>(lds);
+    float (*Qs)[KC][NB] = reinterpret_cast<float (*)[KC][NB]>(lds + 2 * KC * NB);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wi = (wave & 3) * 32, wj = (wave >> 2) * 64;
+    const int l32 = lane & 31, hi = lane >> 5;
+    v16f acc[2];
+#pragma unroll
+    for (int jb = 0; jb < 2; ++jb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[jb][r] = 0.0f;
+    // wave w stages k-rows 2 w and 2 w + 1 of P and of Q
+    const int64_t off = (int64_t)(threadIdx.x >> 5) * ldp + 4 * (threadIdx.x & 31);
+    const float *pg = P + off + i0, *qg = P + off + j0;
+    auto stage_in = [&](int b) {
+        __builtin_amdgcn_global_load_lds((gptr)pg, (lptr)&Ps[b][2 * wave][0], 16, 0, 0);
+        __builtin_amdgcn_global_load_lds((gptr)qg, (lptr)&Qs[b][2 * wave][0], 16, 0, 0);
+        pg += KC * ldp;
+        qg += KC * ldp;
+    };
+    stage_in(0);
+    __syncthreads();
+    constexpr int nst = NB / KC;
+    for (int st = 0; st < nst; ++st) {
+        const int buf = st & 1;
+        if (st + 1 < nst) stage_in(buf ^ 1);
+#pragma unroll
+        for (int kp = 0; kp < KC / 2; ++kp) {
+            const int p = 2 * kp + hi;
+            const float pv = Ps[buf][p][wi + l32];
+            acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(Qs[buf][p][wj + l32], pv, acc[0], 0, 0, 0);
+            acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(Qs[buf][p][wj + 32 + l32], pv, acc[1], 0, 0, 0);
+        }
+        __syncthreads();  // waits for the direct loads of the next stage too
+    }
+    float cv[2][16];
+    float *c0 = C + (j0 + wj) * ldc + i0 + wi + l32;
+#pragma unroll
+    for (int jb = 0; jb < 2; ++jb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) cv[jb][r] = c0[(jb * 32 + 8 * (r >> 2) + 4 * hi + (r & 3)) * ldc];
+#pragma unroll
+    for (int jb = 0; jb < 2; ++jb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            c0[(jb * 32 + 8 * (r >> 2) + 4 * hi + (r & 3)) * ldc] = cv[jb][r] - acc[jb][r];
+}
+
+// The columns kk + 128 .. kk + 128 (1 + ncol) of the trailing rows (from kk + 128) updated
+// by the sub-panel at kk, lower 128-tiles only; workgroup 0 takes the first tile,
+// the next diagonal block, and goes on to factor it while the others update
+// theirs: its 12 us of pivots run beside the update instead of after it, and it
+// needs no load of its own.
+constexpr int kUpdateLds = 4 * KC * NB * 4;  // bytes: two buffers of P and Q stages
+static_assert(kUpdateLds >= (int)(4 * NBLK * 64 * sizeof(v4f)), "the row blocks of the fused update fit the stages");
+
+__global__ void __launch_bounds__(NTP, 4)
+k_update_potrf(float *__restrict__ A, int64_t ld, int64_t kk, int64_t n, int ncol, float *__restrict__ Linv,
+               int *__restrict__ status)
+{
+    __shared__ v4f lds[kUpdateLds / sizeof(v4f)];
+    if (blockIdx.x == 0) {
+        potrf128_body<true>(A, ld, kk + NB, n, Linv, status, reinterpret_cast<v4f (*)[NBLK][64]>(lds));
+        return;
+    }
+    const int64_t T = (ld - kk - NB) / NB;  // tile rows
+    int64_t u = blockIdx.x, tj = 0;
+    while (u >= T - tj) {  // column tj has T - tj tiles
+        u -= T - tj;
+        ++tj;
+    }
+    update_tile(A + (kk + NB) * ld + kk + NB, ld, A + kk * ld + kk + NB, ld, (tj + u) * NB, tj * NB,
+                reinterpret_cast<float *>(lds));
 }
 
 }  // namespace
@@ -306,6 +438,15 @@ void launch_potrf128_b(hipStream_t s, const BProb *P, const BWork &w, int64_t k0
 void launch_potrf128(hipStream_t s, float *A, int64_t ld, int64_t k0, int64_t n, float *Linv, int *status)
 {
     hipLaunchKernelGGL(k_potrf128, dim3(1), dim3(NTP), 0, s, A, ld, k0, n, Linv, status);
+}
+
+void launch_update_potrf(hipStream_t s, float *A, int64_t ld, int64_t kk, int64_t n, int ncol, float *Linv, int *status)
+{
+    const int64_t T = (ld - kk - NB) / NB;
+    if (T <= 0 || ncol <= 0) return;
+    const int64_t nc = ncol < T ? ncol : T;
+    const int64_t tiles = nc * T - nc * (nc - 1) / 2;
+    hipLaunchKernelGGL(k_update_potrf, dim3((unsigned)tiles), dim3(NTP), 0, s, A, ld, kk, n, (int)nc, Linv, status);
 }
 
 }  // namespace mag
