@@ -40,13 +40,19 @@ size_t ctx_held_bytes(const mag_ctx *c)
 
 // Give up the split image (the factor runs without it), so that it never takes
 // room from a buffer a call cannot do without.
+static void release(mag_ctx *ctx, DevBuf &b)
+{
+    if (!b.p) return;
+    hipStreamSynchronize(ctx->stream);
+    hipFree(b.p);
+    b.p = nullptr;
+    b.bytes = 0;
+}
+
 static bool drop_split(mag_ctx *ctx)
 {
     if (!ctx->split.p) return false;
-    hipStreamSynchronize(ctx->stream);
-    hipFree(ctx->split.p);
-    ctx->split.p = nullptr;
-    ctx->split.bytes = 0;
+    release(ctx, ctx->split);
     return true;
 }
 
@@ -990,14 +996,17 @@ int solve_hss(mag_ctx *ctx, const double *X, int64_t n, int m, double t, double 
 }
 
 // MAG_AUTO takes the HODLR preconditioner above this size.  Measured on the
-// MI355X, whole solves (noisy torus at t = 0.5, 2, 8; Gaussian cloud at its
-// cutoff scale; mixture of five Gaussians at t = 30, 100): n = 49152: dense
-// FP32 factor + refinement 330-376 ms, HODLR 272-455 ms; n = 65536: 767-828 ms
-// against 425-647 ms (HODLR with max_rank 512 and one subspace iteration);
-// n = 98304: 2.47-2.62 s against 0.82-1.45 s.  The clustered clouds compress
-// worst and put the crossover near the upper sizes; without the subspace
-// iteration the HODLR solve of the mixture at t = 30 stalls at n = 131072.
-constexpr int64_t kAutoHodlrMinN = 49152;
+// MI355X, whole solves, dense FP32 factor + refinement against the HODLR with
+// max_rank 512 and one subspace iteration (noisy torus at t = 0.5, 2, 8; Gaussian
+// cloud at its cutoff scale; mixture of five Gaussians at t = 30, 100): n = 52000:
+// 274-316 ms against 365-402 ms; n = 57344: 357-405 against 389-508 (the torus at t = 0.5
+// alone 405 against 393); n = 60001: 410-461 against 408-466; n = 65536: 522-583
+// against 443-583.  Without the subspace iteration the HODLR solve of the mixture
+// at t = 30 stalls at n = 131072.
+constexpr int64_t kAutoHodlrMinN = 57344;
+// Up to here the dense factor is the only choice; between the two the HODLR still
+// takes what the dense path has no memory for or does not converge on.
+constexpr int64_t kAutoDenseOnlyN = 49152;
 
 // Whether the dense FP32 factor's npad^2 floats fit in three quarters of the
 // device memory (counting what this context already holds for it) and in the
@@ -1578,11 +1587,23 @@ int mag_weighting(mag_ctx *c, const double *X, int64_t n, int32_t m, double t, d
     CHK(ensure_common(c, n, std::max(1, o.gmres_restart)));
     // MAG_AUTO: the HODLR preconditioner above the measured crossover, the dense
     // FP32 factor below it or when the HODLR solve does not converge
-    const bool auto_hodlr = o.solver == MAG_AUTO && n > kAutoHodlrMinN && m <= 16;
+    const bool may_hodlr = o.solver == MAG_AUTO && n > kAutoDenseOnlyN && m <= 16;
+    const bool fits = o.solver == MAG_AUTO && auto_dense(c, n);
+    const bool auto_hodlr = may_hodlr && (n > kAutoHodlrMinN || !fits);
     // the FP32 path's tile generator checks the points itself (no pass and no round trip
     // of their own)
-    const bool fp32 = o.solver == MAG_FP32_IR || (o.solver == MAG_AUTO && !auto_hodlr && auto_dense(c, n));
+    const bool fp32 = o.solver == MAG_FP32_IR || (o.solver == MAG_AUTO && !auto_hodlr && fits);
     int rc = (fp32 && n > 1) ? MAG_OK : check_points(c, X, n, m, o.solver != MAG_AUTO || auto_hodlr);
+    const auto hodlr = [&]() -> int {
+        mag_opts oh = o;
+        oh.max_rank = std::max(oh.max_rank, 512);
+        oh.power_iters = std::max(oh.power_iters, 1);
+        oh.gmres_restart = std::max(oh.gmres_restart, 100);
+        oh.max_gmres = std::max(oh.max_gmres, 400);
+        oh.max_outer = std::max(oh.max_outer, 30);
+        CHK(ensure_common(c, n, oh.gmres_restart));
+        return solve_hodlr(c, X, n, m, t, w, oh, info);
+    };
     if (rc == MAG_OK && n == 1) {
         launch_fill(c->stream, w, 1, 1.0);
         HIPCHK(hipStreamSynchronize(c->stream));
@@ -1599,17 +1620,16 @@ int mag_weighting(mag_ctx *c, const double *X, int64_t n, int32_t m, double t, d
         case MAG_HSS: rc = solve_hss(c, X, n, m, t, w, o, info); break;
         case MAG_AUTO:
             if (auto_hodlr) {
-                mag_opts oh = o;
-                oh.max_rank = std::max(oh.max_rank, 512);
-                oh.power_iters = std::max(oh.power_iters, 1);
-                oh.gmres_restart = std::max(oh.gmres_restart, 100);
-                oh.max_gmres = std::max(oh.max_gmres, 400);
-                oh.max_outer = std::max(oh.max_outer, 30);
-                CHK(ensure_common(c, n, oh.gmres_restart));
-                rc = solve_hodlr(c, X, n, m, t, w, oh, info);
+                rc = hodlr();
                 if (rc == MAG_ENOCONV && auto_dense(c, n)) rc = solve_fp32_ir(c, X, n, m, t, w, o, info);
             } else if (fp32) {
                 rc = solve_fp32_ir(c, X, n, m, t, w, o, info);
+                if (may_hodlr && (rc == MAG_ENOMEM || rc == MAG_ENOCONV)) {
+                    // the HODLR needs less than the factor, whose memory it may need
+                    release(c, c->factor);
+                    release(c, c->dinv);
+                    rc = hodlr();
+                }
             } else {
                 rc = MAG_ENOMEM;
             }
