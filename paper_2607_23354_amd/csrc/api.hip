@@ -38,8 +38,6 @@ size_t ctx_held_bytes(const mag_ctx *c)
     return sum;
 }
 
-// Give up the split image (the factor runs without it), so that it never takes
-// room from a buffer a call cannot do without.
 static void release(mag_ctx *ctx, DevBuf &b)
 {
     if (!b.p) return;
@@ -49,6 +47,8 @@ static void release(mag_ctx *ctx, DevBuf &b)
     b.bytes = 0;
 }
 
+// Give up the split image (the factor runs without it), so that it never takes
+// room from a buffer a call cannot do without.
 static bool drop_split(mag_ctx *ctx)
 {
     if (!ctx->split.p) return false;
@@ -1624,8 +1624,10 @@ int mag_weighting(mag_ctx *c, const double *X, int64_t n, int32_t m, double t, d
                 if (rc == MAG_ENOCONV && auto_dense(c, n)) rc = solve_fp32_ir(c, X, n, m, t, w, o, info);
             } else if (fp32) {
                 rc = solve_fp32_ir(c, X, n, m, t, w, o, info);
-                if (may_hodlr && (rc == MAG_ENOMEM || rc == MAG_ENOCONV)) {
-                    // the HODLR needs less than the factor, whose memory it may need
+                // the HODLR takes what the factor cannot (a singular Z stays refused)
+                if (may_hodlr && (rc == MAG_ENOMEM || rc == MAG_ENOCONV ||
+                                  (rc == MAG_ENOTPD && check_points(c, X, n, m) == MAG_OK))) {
+                    // it needs less than the factor, whose memory it may need
                     release(c, c->factor);
                     release(c, c->dinv);
                     rc = hodlr();
