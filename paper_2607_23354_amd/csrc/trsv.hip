@@ -11,7 +11,7 @@
 //     (whose FP64 inverses fit LDS); the figures below are those of the FP32
 //     factor at n = 32768;
 //   * k_trsv1 (one workgroup per block, composite near step, further down)
-//     serves the single FP32 solves: 0.58 ms per direction at n = 32768
+//     serves the single FP32 solves: 0.52 ms per direction at n = 32768
 //     against the band kernel's 0.97 ms.
 //
 // Each triangular solve is ONE launch and no host round trips ("sync-free"
@@ -364,41 +364,83 @@ k_trsv(const T *__restrict__ L, int64_t ld, const T *__restrict__ dinv,
 // formed once the far blocks are in, so after its predecessor's block arrives
 // a workgroup applies one resident tile and one reduction: the dependency
 // chain costs one hand-off and one 128 x 128 product per block.
+//
+// Bound by that chain: the hand-off (a store becoming visible to a poll, about
+// 1 us) and the product after it, 1.6 us a block together.  Hence eight waves that
+// own 16 columns of every tile each: a wave polls its own 16 entries of a block
+// and multiplies by them with no workgroup barrier between, Q_b is converted to
+// FP64 before the wait, and one barrier is left, at the sum over the waves.  With
+// one polling wave, two barriers and 256 threads a direction took 55 us at
+// n = 3001 and 0.58 ms at n = 32768, now 40 us and 0.52 ms.
 template <bool BWD>
 __device__ __forceinline__ void trsv1_body(const float *__restrict__ L, int64_t ld, const float *__restrict__ dinv,
                                            const float *__restrict__ Qb, double *__restrict__ rhs,
                                            double *__restrict__ x, double *__restrict__ z, int *counters, int nblk,
                                            int *status, long spin_limit)
 {
-    constexpr int BS = 128;
+    constexpr int BS = 128, NW = 8, NT = 64 * NW;
+    constexpr int WC = BS / NW;          // columns of a wave
+    constexpr int TC = WC / 2;           // and of a thread (half waves take half each)
+    constexpr int NP = NT / BS, PC = BS / NP;  // parts of the block product's sums
     __shared__ float Dl[BS * (BS + 1)];  // D_b, row-major, padded stride
-    __shared__ double xs[2][BS];
-    __shared__ double part[8][BS];
+    __shared__ double xs[NW][2][WC];
+    __shared__ double part[NW][BS];
+    __shared__ double rb[BS];
     __shared__ int s_blk;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (tid == 0) {
         const int ticket = take_ticket<BWD>(counters);
         s_blk = BWD ? nblk - 1 - ticket : ticket;
     }
     __syncthreads();
     const int b = s_blk;
-    const int rg = tid & 31, cg = tid >> 5;     // tile products: rows 4 rg .., columns 16 cg ..
-    const int row = tid & (BS - 1), h = tid >> 7;  // block product: half h of row's sum
-    using Tile = Quad<float>[16];
+    const int rg = lane & 31, ch = lane >> 5;     // tile products: rows 4 rg .., columns TC ch .. of the wave's
+    const int row = tid & (BS - 1), h = tid >> 7;  // block product: part h of row's sum
+    using Tile = Quad<float>[TC];
     auto load = [&](const float *base, int64_t ldb, Tile &t) {
-        const float *p = base + (int64_t)(16 * cg) * ldb + 4 * rg;
+        const float *p = base + (int64_t)(WC * wave + TC * ch) * ldb + 4 * rg;
 #pragma unroll
-        for (int c = 0; c < 16; ++c) load_quad(p + (int64_t)c * ldb, t[c]);
+        for (int c = 0; c < TC; ++c) load_quad(p + (int64_t)c * ldb, t[c]);
     };
     auto tile = [&](int j) { return L + (int64_t)j * BS * ld + (int64_t)b * BS; };
     auto gemv = [&](const Tile &t, const double *xv, double (&acc)[4]) {
 #pragma unroll
-        for (int c = 0; c < 16; ++c) {
-            const double v = xv[16 * cg + c];
+        for (int c = 0; c < TC; ++c) {
+            const double v = xv[TC * ch + c];
             acc[0] += (double)t[c].v[0] * v;
             acc[1] += (double)t[c].v[1] * v;
             acc[2] += (double)t[c].v[2] * v;
             acc[3] += (double)t[c].v[3] * v;
+        }
+    };
+    // the wave's entries of block j0 (lanes 0..15) and j1 (16..31) into xs[wave]
+    auto wait = [&](int j0, int j1, bool two, bool nap) {
+        const int e = lane & (WC - 1);
+        const bool mine = lane < WC || (two && lane < 2 * WC);
+        const int64_t at = (int64_t)(lane < WC ? j0 : j1) * BS + WC * wave + e;
+        uint64_t a = 0;
+        long spins = 0;
+        for (;;) {
+            if (mine) a = ld_entry(x, at);
+            if (__ballot(mine && a == kUnset) == 0) break;
+            if (++spins > spin_limit) {
+                if (lane == 0) status[kStSpinTimeout] = 1;
+                break;
+            }
+            if (nap) __builtin_amdgcn_s_sleep(1);
+        }
+        if (mine) xs[wave][lane < WC ? 0 : 1][e] = __builtin_bit_cast(double, a);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // read back by this wave only
+        __builtin_amdgcn_wave_barrier();
+    };
+    // sums of the wave's two half-wave column groups, then of the waves (part)
+    auto to_part = [&](double (&acc)[4]) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[i] += __shfl_xor(acc[i], 32);
+        if (ch == 0) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) part[wave][4 * rg + i] = acc[i];
         }
     };
     auto jof = [&](int st) { return BWD ? (nblk - 1 - st) : st; };
@@ -414,72 +456,83 @@ __device__ __forceinline__ void trsv1_body(const float *__restrict__ L, int64_t 
     }
     Tile tq;
     if (has_near) load(Qb + (int64_t)b * BS * BS, BS, tq);
-    {
-        const float *src = dinv + (int64_t)b * BS * BS;
-        for (int e = tid; e < BS * BS; e += 256) {
-            const int rr = e & (BS - 1), cc = e >> 7;
-            Dl[rr * (BS + 1) + cc] = src[e];
-        }
-    }
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
     Tile ta, tb;
     if (nfar > 0) load(tile(jof(0)), ld, ta);
     if (nfar > 1) load(tile(jof(1)), ld, tb);
+    {
+        const float *src = dinv + (int64_t)b * BS * BS;
+        float d[BS * BS / NT];
+#pragma unroll
+        for (int e = 0; e < BS * BS / NT; ++e) d[e] = src[tid + NT * e];
+#pragma unroll
+        for (int e = 0; e < BS * BS / NT; ++e) Dl[row * (BS + 1) + h + NP * e] = d[e];
+    }
+    double q[TC][4];
+#pragma unroll
+    for (int c = 0; c < TC; ++c)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) q[c][i] = has_near ? (double)tq[c].v[i] : 0.0;
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
     for (int st = 0; st < nfar; st += 2) {
         const bool two = st + 1 < nfar;
-        if (tid < 64) wait_blocks<BS>(x, jof(st), two ? jof(st + 1) : 0, two, xs, status, spin_limit);
-        __syncthreads();
-        gemv(ta, xs[0], acc);
-        if (two) gemv(tb, xs[1], acc);
-        __syncthreads();  // xs is rewritten by the next wait (or the block product below)
+        wait(jof(st), two ? jof(st + 1) : 0, two, true);
+        gemv(ta, xs[wave][0], acc);
+        if (two) gemv(tb, xs[wave][1], acc);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // xs is rewritten by the next wait
+        __builtin_amdgcn_wave_barrier();
         if (st + 2 < nfar) load(tile(jof(st + 2)), ld, ta);
         if (st + 3 < nfar) load(tile(jof(st + 3)), ld, tb);
     }
     // y = D_b (rhs_b - acc)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) part[cg][4 * rg + i] = acc[i];
+    to_part(acc);
     __syncthreads();
     if (tid < BS) {
         double sacc = 0.0;
 #pragma unroll
-        for (int g = 0; g < 8; ++g) sacc += part[g][tid];
-        xs[0][tid] = r0 - sacc;
+        for (int g = 0; g < NW; ++g) sacc += part[g][tid];
+        rb[tid] = r0 - sacc;
     }
     __syncthreads();
     double v = 0.0;
 #pragma unroll 16
-    for (int c = 0; c < 64; ++c) {
-        const int cc = h * 64 + c;
+    for (int c = 0; c < PC; ++c) {
+        const int cc = h * PC + c;
         const float d = BWD ? Dl[cc * (BS + 1) + row] : Dl[row * (BS + 1) + cc];
-        v += (double)d * xs[0][cc];
+        v += (double)d * rb[cc];
     }
     part[h][row] = v;
     __syncthreads();
     double y = 0.0;
-    if (tid < BS) y = part[0][tid] + part[1][tid];
+    if (tid < BS) {
+#pragma unroll
+        for (int g = 0; g < NP; ++g) y += part[g][tid];
+    }
     if (!has_near) {
         if (tid < BS) st_entry(x, (int64_t)b * BS + tid, y);
         return;
     }
-    // the predecessor's block: x_b = y - Q_b x_n
     __syncthreads();  // part is rewritten below
-    if (tid < 64) wait_blocks<BS>(x, jof(nsteps - 1), 0, false, xs, status, spin_limit);
-    __syncthreads();
+    // the predecessor's block: x_b = y - Q_b x_n
+    wait(jof(nsteps - 1), 0, false, false);
     double aq[4] = {0.0, 0.0, 0.0, 0.0};
-    gemv(tq, xs[0], aq);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) part[cg][4 * rg + i] = aq[i];
+    for (int c = 0; c < TC; ++c) {
+        const double xv = xs[wave][0][TC * ch + c];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) aq[i] += q[c][i] * xv;
+    }
+    to_part(aq);
     __syncthreads();
     if (tid < BS) {
         double sq = 0.0;
 #pragma unroll
-        for (int g = 0; g < 8; ++g) sq += part[g][tid];
+        for (int g = 0; g < NW; ++g) sq += part[g][tid];
         st_entry(x, (int64_t)b * BS + tid, y - sq);
     }
 }
 
 template <bool BWD>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(512)
 k_trsv1(const float *__restrict__ L, int64_t ld, const float *__restrict__ dinv, const float *__restrict__ Qb,
         double *__restrict__ rhs, double *__restrict__ x, double *__restrict__ z, int *counters, int nblk, int *status,
         long spin_limit)
@@ -635,9 +688,9 @@ void launch_prec_apply(hipStream_t s, const float *L, int64_t npad, const float 
     const int nblk = (int)(npad / 128);
     const float *Qb = Q + (int64_t)nblk * 128 * 128;  // the backward direction's tiles
     double *rhs = const_cast<double *>(r);  // the forward solve only reads it
-    hipLaunchKernelGGL(k_trsv1<false>, dim3(nblk), dim3(256), 0, s, L, npad, dinv, Q, rhs, y_tmp, z, counters, nblk,
+    hipLaunchKernelGGL(k_trsv1<false>, dim3(nblk), dim3(512), 0, s, L, npad, dinv, Q, rhs, y_tmp, z, counters, nblk,
                        status, spin_limit);
-    hipLaunchKernelGGL(k_trsv1<true>, dim3(nblk), dim3(256), 0, s, L, npad, dinv, Qb, y_tmp, z, (double *)nullptr,
+    hipLaunchKernelGGL(k_trsv1<true>, dim3(nblk), dim3(512), 0, s, L, npad, dinv, Qb, y_tmp, z, (double *)nullptr,
                        counters, nblk, status, spin_limit);
 }
 
