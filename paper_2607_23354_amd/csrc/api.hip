@@ -275,7 +275,7 @@ void enqueue_factor(mag_ctx *ctx, const double *X, int64_t n, int m, double t, F
         ft->used = 0;
         ft->flops.clear();
     }
-    chol32_factor(s, F.A, F.npad, n, F.dinv, status, ft, nb, img);
+    chol32_factor(s, F.A, F.npad, n, F.dinv, status, ft, nb, img, ctx->panel);
     launch_near_q(s, F.A, F.npad, F.dinv, F.nq);
 }
 
@@ -1404,9 +1404,16 @@ int mag_create(mag_ctx **out, int device)
         mag_destroy(c);
         return MAG_EHIP;
     }
-    if (ensure(c, c->ints, sizeof(int) * kIntsTotal) != MAG_OK) {
+    // the panel hand-off is a fixed part of a context, like its pinned words: no cap counts it
+    if (ensure(c, c->ints, sizeof(int) * kIntsTotal) != MAG_OK ||
+        hipMalloc(&c->panel, panel_work_bytes()) != hipSuccess) {
         mag_destroy(c);
         return MAG_ENOMEM;
+    }
+    launch_fill_ints(c->stream, (int *)c->panel, (int64_t)(panel_work_bytes() / sizeof(int)), 0);
+    if (hipStreamSynchronize(c->stream) != hipSuccess) {
+        mag_destroy(c);
+        return MAG_EHIP;
     }
     *out = c;
     return MAG_OK;
@@ -1421,6 +1428,7 @@ void mag_destroy(mag_ctx *c)
                       &c->bdinv, &c->bvec, &c->bscal, &c->bpartial, &c->bints, &c->bdesc, &c->barena,
                       &c->bstage, &c->hodlr, &c->eig, &c->hss, &c->split})
         if (b->p) hipFree(b->p);
+    if (c->panel) hipFree(c->panel);
     if (c->bhost) hipHostFree(c->bhost);
     if (c->blas) rocblas_destroy_handle((rocblas_handle)c->blas);
     if (c->host_scalars) hipHostFree(c->host_scalars);
@@ -1489,7 +1497,7 @@ int mag_autotune(mag_ctx *c, const double *X, int64_t n, int32_t m, double t, in
             launch_fill_ints(s, status, 8, 0);
             if (hipEventRecord(e0, s) != hipSuccess) { rc = MAG_EHIP; break; }
             launch_tilegen32(s, X, n, m, t, A, npad, 0.0f);
-            chol32_factor(s, A, npad, n, dinv, status, nullptr, widths[q], chol32_image(c, npad, widths[q]));
+            chol32_factor(s, A, npad, n, dinv, status, nullptr, widths[q], chol32_image(c, npad, widths[q]), c->panel);
             float ms = 0.0f;
             if (hipEventRecord(e1, s) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
                 hipEventElapsedTime(&ms, e0, e1) != hipSuccess) {
@@ -1724,7 +1732,7 @@ int mag_factor32(mag_ctx *c, const double *X, int64_t n, int32_t m, double t, do
     launch_fill_ints(c->stream, status, 8, 0);
     launch_tilegen32(c->stream, X, n, m, t, L, npad, (float)shift);
     const int nb = panel_width(c, npad);
-    chol32_factor(c->stream, L, npad, n, dinv, status, nullptr, nb, chol32_image(c, npad, nb));
+    chol32_factor(c->stream, L, npad, n, dinv, status, nullptr, nb, chol32_image(c, npad, nb), c->panel);
     HIPCHK(hipMemcpyAsync(c->host_scalars, status, 8 * sizeof(int), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(hipStreamSynchronize(c->stream));
     if (breakdown) *breakdown = ((const int *)c->host_scalars)[kStBreakdown];

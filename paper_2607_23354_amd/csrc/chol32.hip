@@ -2,55 +2,22 @@
 //
 // Z is symmetric positive definite for distinct Euclidean points (Sections 2
 // and 3.2), so Z = L L^T exists; this factor is computed in FP32 and used as
-// the preconditioner of the FP64 refinement.  For each panel of nb = 512
-// columns (or 256, the tunable choice) starting at k (256 for a last,
-// narrower panel), made of 128-column sub-panels s:
-//   1. potrf128   factor of the 128 x 128 diagonal block and its inverse
-//   2. trsm       rows below:  L21 = A21 * inv(L11)^T     (MFMA, in place),
-//                 with L21^T written into the upper triangle
-//   3. update     the panel's later sub-panels by this one (K = 128)
-// and, panels taken in pairs, 4. the trailing update A22 -= L21 L21^T of both
-// panels at once (K = 2 nb, lower tiles only), after a strip update of the
-// second panel's columns by the first.  A deep K in step 4 amortises the load
-// and store of each C tile over more MFMA work; steps 2, 3 and the strip run
-// on 64-row tiles (twice the workgroups of 128-row ones, which keeps more CUs
-// busy in the late panels, where a 128-row tiling leaves most of them idle).
-// The inverses of the diagonal 128-blocks are kept (dinv) for the
-// preconditioner's triangular solves.
+// the preconditioner of the FP64 refinement.  Panels of 512 columns (or 256, the
+// tunable choice; 256 for a last, narrower one) are factored by one launch each
+// (potrf.hip: 128 x 128 diagonal blocks, their inverses, the rows below, and L^T
+// in the upper triangle).  They go in pairs: after the first panel a strip update
+// brings the second one's columns up to date; after the second, one trailing
+// update A22 -= L21 L21^T of both panels (K = 2 nb, lower tiles only) applies the
+// pair to the rest.  A deep K amortises the load and store of each C tile over more
+// matrix work; the strip runs on 64-row tiles (twice the workgroups of 128-row
+// ones, which keeps more CUs busy in the late panels).  The inverses of the diagonal
+// 128-blocks are kept (dinv) for the preconditioner's triangular solves.
 #include "internal.hpp"
 
 #include <algorithm>
 #include <vector>
 
 namespace mag {
-
-
-namespace {
-
-// Steps 1-3 for the panel of nb columns at k (its trailing rows already updated
-// by every earlier panel).
-void factor_panel(hipStream_t s, float *A, int64_t npad, int64_t n, int64_t k, int64_t nb, float *dinv, int *status)
-{
-    const int64_t T = kTile;
-    const int64_t nsub = nb / T;
-    for (int64_t sub = 0; sub < nsub; ++sub) {
-        const int64_t kk = k + sub * T;
-        float *Linv = dinv + (kk / T) * T * T;
-        if (sub == 0) launch_potrf128(s, A, npad, kk, n, Linv, status);
-        const int64_t below = npad - kk - T;
-        if (below > 0) {
-            float *A21 = A + kk * npad + kk + T;
-            float *A12 = A + (kk + T) * npad + kk;  // upper triangle: L21^T
-            launch_gemm_rows64(s, A21, npad, A21, npad, Linv, T, below, T, T, kGemmSetT, A12);
-        }
-        if (sub + 1 < nsub) {
-            // the panel's remaining sub-panels by this one, and the next diagonal block
-            launch_update_potrf(s, A, npad, kk, n, (int)(nsub - sub - 1), Linv + T * T, status);
-        }
-    }
-}
-
-}  // namespace
 
 // Factor the padded npad x npad FP32 matrix A (column-major, ld = npad) in place.
 // timer (optional) records an event pair around every trailing update.
@@ -60,24 +27,26 @@ void factor_panel(hipStream_t s, float *A, int64_t npad, int64_t n, int64_t k, i
 // update with K = 2 nb applies both panels to the rest.  Each tile of the large
 // trailing block is read and written once per two panels.
 void chol32_factor(hipStream_t s, float *A, int64_t npad, int64_t n, float *dinv, int *status,
-                   FactorTimer *timer, int nb_max, void *img)
+                   FactorTimer *timer, int nb_max, void *img, void *work)
 {
     const int64_t kNb = (nb_max == 256) ? 256 : 512;
     int64_t k = 0;
+    int panels = 0;
+    launch_panel_begin(s, work);
     while (k < npad) {
         const int64_t nb = std::min<int64_t>(kNb, npad - k);
-        factor_panel(s, A, npad, n, k, nb, dinv, status);
+        launch_panel(s, A, npad, k, nb, n, dinv, status, work, panels++);
         const int64_t k2 = k + nb;
         if (k2 >= npad) break;
         const int64_t nb2 = std::min<int64_t>(kNb, npad - k2);
         {
             // strip: panel p+1's columns (all rows from k2) by panel p; the tiles above
-            // the 128-diagonal of its diagonal block are rewritten by its own trsm
+            // the 128-diagonal of its diagonal block are rewritten by its own panel launch
             float *C = A + k2 * npad + k2;
             const float *P = A + k * npad + k2;
-            launch_gemm_rows64(s, C, npad, P, npad, P, npad, npad - k2, nb2, nb, kGemmSub);
+            launch_gemm_rows64(s, C, npad, P, npad, P, npad, npad - k2, nb2, nb);
         }
-        factor_panel(s, A, npad, n, k2, nb2, dinv, status);
+        launch_panel(s, A, npad, k2, nb2, n, dinv, status, work, panels++);
         const int64_t k3 = k2 + nb2;
         const int64_t trail = npad - k3;
         if (trail > 0) {

@@ -1,11 +1,10 @@
 // gemm_mfma.hip -- FP32 MFMA kernel for the Cholesky's dense contractions.
 //
 //   C (M x N)  <-  C - P Q^T      (kGemmSub: trailing SYRK/GEMM updates)
-//   C (M x N)  <-  P Q^T          (kGemmSet: panel TRSM against an explicit
-//                                   inverse of the diagonal block)
-//   kGemmSetT: as kGemmSet and also C^T into CT (CT(j, i) = CT[i * ldc + j]),
-//   staged through LDS so both stores are coalesced; the factorisation uses
-//   it to keep L^T in the upper triangle for the backward substitution.
+//   C (M x N)  <-  P Q^T          (kGemmSetT: the batched panel TRSM against an
+//                                   explicit inverse of the diagonal block), with
+//   C^T into CT (CT(j, i) = CT[i * ldc + j]) staged through LDS so both stores are
+//   coalesced: L^T in the upper triangle, for the backward substitution.
 //
 // All operands are column-major FP32: P(i, p) = P[p * ldp + i],
 // Q(j, p) = Q[p * ldq + j], C(i, j) = C[j * ldc + i].  Accumulation is FP32
@@ -206,22 +205,18 @@ __device__ __forceinline__ void gemm_tile_body(float *__restrict__ C, int64_t ld
     }
 }
 
-// The panel path's short-K contractions (K = 128: the panel solve against the
-// diagonal block's inverse and the sub-panel updates) on tiles of 64 rows x 128
-// columns: twice the workgroups of the 128 x 128 tile for the same rows, so the
-// later panels, whose few row tiles leave most CUs idle, finish in about half
-// the MFMA time per workgroup.  A workgroup still owns whole 128-column rows of
-// C, so the in-place panel solve (C = P) reads its rows before it rewrites them.
-// Waves in 2 x 2: rows wi .. wi + 31, columns wj .. wj + 63 (two 32 x 32
-// accumulators).  K staged through LDS in double-buffered chunks of 16 by direct
-// loads, as in gemm_tile_body.
+// The strip update of a panel pair (its second panel's columns by the first) on
+// tiles of 64 rows x 128 columns: twice the workgroups of the 128 x 128 tile for the
+// same rows, so the later strips, whose few row tiles leave most CUs idle, finish in
+// about half the MFMA time per workgroup.  Waves in 2 x 2: rows wi .. wi + 31,
+// columns wj .. wj + 63 (two 32 x 32 accumulators).  K staged through LDS in
+// double-buffered chunks of 16 by direct loads, as in gemm_tile_body.
 constexpr int BR = 64;
 constexpr int LDS_R64 = 2 * KC * BR + 2 * KC * BT;  // P and Q stages (24 KB)
 
-template <int MODE>
 __global__ void __launch_bounds__(NT, 2)
 k_gemm_rows64(float *__restrict__ C, int64_t ldc, const float *__restrict__ P, int64_t ldp,
-              const float *__restrict__ Q, int64_t ldq, int64_t tilesM, int64_t K, float *__restrict__ CT)
+              const float *__restrict__ Q, int64_t ldq, int64_t tilesM, int64_t K)
 {
     __shared__ float lds[LDS_R64];
     float (*Ps)[KC][BR] = reinterpret_cast<float (*)[KC][BR]>(lds);
@@ -282,45 +277,16 @@ k_gemm_rows64(float *__restrict__ C, int64_t ldc, const float *__restrict__ P, i
     const int64_t i = i0 + wi + l32;
 #pragma unroll
     for (int jb = 0; jb < 2; ++jb) {
-        if (MODE == kGemmSub) {
-            float cv[16];
+        float cv[16];
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int64_t j = j0 + wj + jb * 32 + 8 * (r >> 2) + 4 * hi + (r & 3);
-                cv[r] = C[j * ldc + i];
-            }
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int64_t j = j0 + wj + jb * 32 + 8 * (r >> 2) + 4 * hi + (r & 3);
-                C[j * ldc + i] = cv[r] - acc[jb][r];
-            }
-        } else {
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int64_t j = j0 + wj + jb * 32 + 8 * (r >> 2) + 4 * hi + (r & 3);
-                C[j * ldc + i] = acc[jb][r];
-            }
+        for (int r = 0; r < 16; ++r) {
+            const int64_t j = j0 + wj + jb * 32 + 8 * (r >> 2) + 4 * hi + (r & 3);
+            cv[r] = C[j * ldc + i];
         }
-    }
-    if (MODE == kGemmSetT) {
-        // transposed copy, 64 columns of the tile at a time through LDS (T[jl][il])
-        float *T = lds;
 #pragma unroll
-        for (int half = 0; half < 2; ++half) {
-            __syncthreads();
-            if ((wave >> 1) == half) {
-#pragma unroll
-                for (int jb = 0; jb < 2; ++jb)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const int jl = jb * 32 + 8 * (r >> 2) + 4 * hi + (r & 3);
-                        T[jl * (BR + 1) + wi + l32] = acc[jb][r];
-                    }
-            }
-            __syncthreads();
-            const int jl = threadIdx.x & 63;
-            for (int il = threadIdx.x >> 6; il < BR; il += NT / 64)
-                CT[(i0 + il) * ldc + j0 + half * 64 + jl] = T[jl * (BR + 1) + il];
+        for (int r = 0; r < 16; ++r) {
+            const int64_t j = j0 + wj + jb * 32 + 8 * (r >> 2) + 4 * hi + (r & 3);
+            C[j * ldc + i] = cv[r] - acc[jb][r];
         }
     }
 }
@@ -435,17 +401,11 @@ void launch_gemm_b(hipStream_t s, int kind, const BProb *P, const BWork &w, int6
 }
 
 void launch_gemm_rows64(hipStream_t s, float *C, int64_t ldc, const float *P, int64_t ldp, const float *Q,
-                        int64_t ldq, int64_t M, int64_t N, int64_t K, GemmMode mode, float *CT)
+                        int64_t ldq, int64_t M, int64_t N, int64_t K)
 {
     const int64_t tm = M / BR, tn = N / BT;
     if (tm <= 0 || tn <= 0 || K <= 0) return;
-    const dim3 g((unsigned)(tm * tn));
-    if (mode == kGemmSub)
-        hipLaunchKernelGGL(k_gemm_rows64<kGemmSub>, g, dim3(NT), 0, s, C, ldc, P, ldp, Q, ldq, tm, K, CT);
-    else if (mode == kGemmSet)
-        hipLaunchKernelGGL(k_gemm_rows64<kGemmSet>, g, dim3(NT), 0, s, C, ldc, P, ldp, Q, ldq, tm, K, CT);
-    else
-        hipLaunchKernelGGL(k_gemm_rows64<kGemmSetT>, g, dim3(NT), 0, s, C, ldc, P, ldp, Q, ldq, tm, K, CT);
+    hipLaunchKernelGGL(k_gemm_rows64, dim3((unsigned)(tm * tn)), dim3(NT), 0, s, C, ldc, P, ldp, Q, ldq, tm, K);
 }
 
 void launch_syrk_lower(hipStream_t s, float *C, int64_t ldc, const float *P, int64_t ldp,

@@ -295,6 +295,7 @@ struct mag_ctx {
     mag::DevBuf eig;       // Lanczos bases of the eigenvalue estimator
     mag::DevBuf hss;       // HSS approximation and ULV factor
     mag::DevBuf split;     // BF16 split image of a panel (optional: given up when memory runs short)
+    void *panel = nullptr;   // exchange of the FP32 factor's panel kernel (panel_work_bytes)
     void *bhost = nullptr;   // pinned host staging for work lists and descriptors
     size_t bhost_bytes = 0;
     double *host_scalars = nullptr;  // pinned host staging (64 doubles)
@@ -339,9 +340,9 @@ struct FactorTimer {
 };
 // nb: panel width, 256 or 512 (npad is a multiple of 256).  img: room for
 // chol32_image_bytes(npad, nb) bytes, or NULL: the trailing updates then run on
-// the FP32 matrix instruction.
+// the FP32 matrix instruction.  work: the context's panel buffer.
 void chol32_factor(hipStream_t s, float *A, int64_t npad, int64_t n, float *dinv, int *status,
-                   FactorTimer *timer, int nb, void *img);
+                   FactorTimer *timer, int nb, void *img, void *work);
 size_t chol32_image_bytes(int64_t npad, int nb);
 // The context's buffer for that image, or NULL when the context's cap or the
 // device has no room for it.
@@ -379,15 +380,12 @@ void launch_dmin2(hipStream_t s, const double *X, int64_t n, int m, double *part
                   int64_t *np, double *out_min2);
 void launch_check_finite(hipStream_t s, const double *X, int64_t count, int *status);
 
-// gemm_mfma.hip: C (M x N) = [C] - P * Q^T (kGemmSub) or C = P * Q^T (kGemmSet),
-// column-major operands: P is M x K (P[p*ldp + i]), Q is N x K (Q[p*ldq + j]).
-// kGemmSetT also writes C^T to CT (CT(j, i) at CT[i * ldc + j]).
-enum GemmMode { kGemmSub = 0, kGemmSet = 1, kGemmSetT = 2 };
-// The panel path's contractions on 64-row x 128-column tiles: M a multiple of
-// 64, N of 128, K of 16.  A workgroup owns whole 128-column row blocks of C, so
-// C may alias P when N = 128 (the in-place panel solve).
+// C - P Q^T into C, or P Q^T into C with its transpose (the GEMM kernels' modes)
+enum GemmMode { kGemmSub = 0, kGemmSetT = 2 };
+// gemm_mfma.hip: C (M x N) -= P Q^T, column-major operands: P is M x K (P[p*ldp + i]), Q
+// is N x K (Q[p*ldq + j]); M a multiple of 64, N of 128, K of 16.
 void launch_gemm_rows64(hipStream_t s, float *C, int64_t ldc, const float *P, int64_t ldp, const float *Q,
-                        int64_t ldq, int64_t M, int64_t N, int64_t K, GemmMode mode, float *CT = nullptr);
+                        int64_t ldq, int64_t M, int64_t N, int64_t K);
 // C (N x N, lower 128-tiles only) -= P P^T with P N x K; N multiple of 128.
 void launch_syrk_lower(hipStream_t s, float *C, int64_t ldc, const float *P, int64_t ldp,
                        int64_t N, int64_t K);
@@ -418,14 +416,15 @@ void launch_potrf64(hipStream_t s, double *A, int64_t ld, int64_t k0, double *Li
 // (npad / 64 blocks of 64 x 64).
 void chol64_factor(hipStream_t s, double *A, int64_t npad, int64_t n, double *dinv, int *status, FactorTimer *timer);
 
-// potrf.hip: factor the 128 x 128 diagonal block at (k0, k0) of A in place and
-// write its inverse to Linv (128 x 128 column-major).  Breakdown -> status.
-// n: rows from n on are identity padding (off-diagonal entries zero).
-void launch_potrf128(hipStream_t s, float *A, int64_t ld, int64_t k0, int64_t n, float *Linv, int *status);
-// The ncol 128-column blocks right of the sub-panel at kk updated by it (lower 128-tiles of
-// the rows below it), and launch_potrf128 of the first of them, at kk + 128.
-void launch_update_potrf(hipStream_t s, float *A, int64_t ld, int64_t kk, int64_t n, int ncol, float *Linv,
-                         int *status);
+// potrf.hip: the FP32 factor's panel of nb (256 or 512) columns at k in one launch: L in
+// place, L^T in the upper triangle, the inverses of its 128 x 128 diagonal blocks
+// (column-major) into dinv.  Rows from n on are identity padding.  Breakdown ->
+// status.  work: panel_work_bytes() of the context; launch_panel_begin before
+// the first panel of a factor, whose panels count index up from 0.
+size_t panel_work_bytes();
+void launch_panel_begin(hipStream_t s, void *work);
+void launch_panel(hipStream_t s, float *A, int64_t ld, int64_t k, int64_t nb, int64_t n, float *dinv, int *status,
+                  void *work, int index);
 
 // gemv64.hip: FP64 matrix-free products with Z regenerated from X.
 //   mode 0: y = Z v;  mode 1: y = b - Z v (b may be NULL meaning ones) and

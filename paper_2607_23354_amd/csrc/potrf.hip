@@ -1,11 +1,11 @@
-// potrf.hip -- Cholesky factor and inverse of one 128 x 128 diagonal block.
+// potrf.hip -- Cholesky factor and inverse of the 128 x 128 diagonal blocks, and the
+// panels of the single FP32 factor around them.
 //
 // The blocked right-looking Cholesky (factor of Z, which is symmetric
 // positive definite for distinct Euclidean points, Section 3.2) needs at each
-// panel step the factor L11 of the diagonal block and, to turn the panel's
-// triangular solve into an MFMA contraction, the explicit inverse L11^{-1}.
-// One workgroup of eight waves does both, in eight steps of 16 columns, with
-// every 16 x 16 block in the registers of one wave:
+// panel step the factor L11 of the diagonal block and its explicit inverse (for the
+// substitutions, and for the batched panel solve).  Eight waves do both (factor128),
+// in eight steps of 16 columns, with every 16 x 16 block in the registers of one wave:
 //   * row layout: lane 16 g + i, register r of a block hold entry (i, 4 g + r), so a
 //     block is four registers, the accumulator of v_mfma_f32_16x16x4 (of the
 //     transposed block) and, register by register, either of its operands;
@@ -27,6 +27,18 @@
 // instruction's accumulator the diagonal's backward error was twice as large, and
 // biased (rms 2.1e-7 against 1.0e-7; 1.4e-7 with the 32-column sweeps; m = 8, n = 5000).
 //
+// k_panel factors a panel of up to 512 columns in one launch, a workgroup per 128 rows:
+// the top block's workgroups factor the diagonal blocks one after another, and
+// every 16-column step of theirs goes to all workgroups below through a small exchange
+// in memory the moment it is done, where it is applied to their rows at once.  The
+// chain is then four diagonal blocks and the hand-offs between them, instead of
+// those and seven launches that each wait for the last workgroup of the one before
+// (a panel of 512 columns: 88 us instead of 112 us at n = 3001 and 8192, 105 us instead of
+// 160 us at n = 32768).  Every workgroup keeps its rows of the sub-panel and the sums for
+// the later ones in registers, so each entry is loaded, updated by a subtraction
+// per 128 columns' sum, and stored once; the backward error went down by up to 40 %
+// (2.0e-7 instead of 3.4e-7, m = 8, n = 5000).
+//
 // A pivot that is not positive (or not finite) marks status[0] with the
 // global pivot index + 1 (its column turns into NaNs; the kernel still finishes);
 // the host then refactors with a diagonal shift.
@@ -41,6 +53,8 @@ constexpr int NB = 128;
 constexpr int SB = 16;            // block edge
 constexpr int NBLK = NB / SB;     // blocks per row = waves
 constexpr int NTP = 64 * NBLK;    // threads
+constexpr int kPanelSteps = 32;   // 16-column steps of the widest panel (512 columns)
+constexpr long kPanelSpinLimit = 1L << 22;  // polls of one wait (seconds: never reached by a running panel)
 
 __device__ inline float bcast(float v, int src_lane)
 {
@@ -148,103 +162,144 @@ __device__ __forceinline__ void block_updates(v4f (&Q)[NBLK], const v4f &x, cons
     for (int m = M0; m < M1; ++m) Q[m] = Q[m + 1] - acc[m - M0];
 }
 
-// FUSED: the block is first updated by the 128 columns of the sub-panel left of it
-// (its rows of that sub-panel's L21), A -= L21 L21^T; Us holds the row blocks of 64
-// of those columns at a time.
-template <bool FUSED>
-__device__ __forceinline__ void potrf128_body(float *__restrict__ A, int64_t ld, int64_t k0, int64_t n,
-                                              float *__restrict__ Linv, int *__restrict__ status, v4f (*Us)[NBLK][64])
+// Below the diagonal block the products run on the BF16 matrix cores, each FP32 operand
+// as the exact sum of three BF16 components h, m, l (8 bits of the significand each)
+// and all products but m l, l m and l l, below FP32's own rounding: per 16 x 16 x 16 block
+// three instructions of 16 cycles (two products each) in place of four of 32.
+typedef unsigned int v4u __attribute__((ext_vector_type(4)));
+typedef unsigned int v2u __attribute__((ext_vector_type(2)));
+typedef unsigned int v8u __attribute__((ext_vector_type(8)));
+typedef __bf16 v8b __attribute__((ext_vector_type(8)));
+
+// A block's rows in components: words 0, 1: columns 4 g .. 4 g + 3 of l; 2, 3: of h; 4, 5: of
+// m.  Words 0-3 and 2-5 are the two K = 32 operands.
+struct Split {
+    v2u c[3];
+};
+
+__device__ __forceinline__ Split split_rows(const v4f &x)
 {
-    __shared__ v4f Lx[NBLK][64];   // the blocks L_Kj of a step, row layout
-    __shared__ float Yd[SB * SB];  // the inverse of its diagonal block, Yd[k * SB + c]
-    __shared__ int bad;
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    // the row block of a wave: waves w and w + 4 share a SIMD, and a long row block goes
-    // with a short one
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int I = wave < NBLK / 2 ? wave : 3 * NBLK / 2 - 1 - wave;
-    const int g = lane >> 4, i = lane & 15;
-    float *Ab = A + k0 * ld + k0;
-
-    if (k0 >= n) {
-        // a block of the identity padding (uniform): its diagonal entries alone
-        for (int e = tid; e < NB * NB; e += NTP) {
-            const int c = e >> 7, r = e & (NB - 1);
-            float l = 0.0f, v = 0.0f;
-            if (r == c) {
-                const float d = Ab[(int64_t)c * ld + r];
-                v = __builtin_amdgcn_rsqf(d);
-                l = d * v;
-            }
-            Ab[(int64_t)c * ld + r] = l;
-            Linv[e] = v;
-        }
-        return;
+    typedef float v2f __attribute__((ext_vector_type(2)));
+    typedef __bf16 v2b __attribute__((ext_vector_type(2)));
+    const auto pack = [](const v2f &v) { return __builtin_bit_cast(unsigned, __builtin_convertvector(v, v2b)); };
+    const auto rest = [](const v2f &v, unsigned u) {
+        v2f d;
+        d[0] = v[0] - __int_as_float((int)(u << 16));
+        d[1] = v[1] - __int_as_float((int)(u & 0xffff0000u));
+        return d;
+    };
+    Split s;
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+        v2f v;
+        v[0] = x[2 * p];
+        v[1] = x[2 * p + 1];
+        s.c[1][p] = pack(v);
+        v = rest(v, s.c[1][p]);
+        s.c[2][p] = pack(v);
+        s.c[0][p] = pack(rest(v, s.c[2][p]));
     }
+    return s;
+}
 
-    // Q[m] at step j: block (I, j + m) of A while j + m <= I; from step I on, of the
-    // eliminated identity.  All loads first; the diagonal block from its lower
-    // triangle, mirrored.
-    v4f Q[NBLK], dg;
+struct SplitX {  // the operand every block of a row is multiplied by: (h, h), (m, m), (h, l)
+    v4u hh, mm, hl;
+};
+
+__device__ __forceinline__ v4u join(const v2u &a, const v2u &b)
+{
+    return __builtin_shufflevector(a, b, 0, 1, 2, 3);
+}
+
+__device__ __forceinline__ SplitX widen(const Split &s)
+{
+    SplitX x;
+    x.hh = join(s.c[1], s.c[1]);
+    x.mm = join(s.c[2], s.c[2]);
+    x.hl = join(s.c[1], s.c[0]);
+    return x;
+}
+
+__device__ __forceinline__ v4f mfma_b(const v4u &y, const v4u &x, const v4f &c)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8b, y), __builtin_bit_cast(v8b, x), c, 0, 0, 0);
+}
+
+// A block of a step in LDS, lane by lane.
+struct SplitBlock {
+    v2u l[64];
+    v4u hm[64];
+    __device__ __forceinline__ void put(int lane, const Split &s)
     {
-        const unsigned off = 4 * g * (unsigned)ld + SB * I + i;
-#pragma unroll
-        for (int K = 0; K < NBLK; ++K)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) Q[K][r] = (Ab + (SB * K + r) * ld)[off];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int k = 4 * g + r, lo = k < i ? k : i, hi = k < i ? i : k;
-            dg[r] = Ab[(SB * I + lo) * ld + SB * I + hi];
-        }
-#pragma unroll
-        for (int K = 0; K < NBLK; ++K)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) Q[K][r] = K < I ? Q[K][r] : (K == I ? dg[r] : 0.0f);
+        l[lane] = s.c[0];
+        hm[lane] = join(s.c[1], s.c[2]);
     }
-    if (tid == 0) bad = 0;
-    if (FUSED) {
-        const unsigned off = 4 * g * (unsigned)ld + SB * I + i;
-        v4f x[2][4];
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-            for (int c = 0; c < 4; ++c)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) x[h][c][r] = (Ab - (NB - 64 * h - SB * c - r) * ld)[off];
-        v4f acc[NBLK];
-#pragma unroll
-        for (int K = 0; K < NBLK; ++K)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) acc[K][r] = 0.0f;
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            if (h > 0) __syncthreads();
-#pragma unroll
-            for (int c = 0; c < 4; ++c) Us[c][I][lane] = x[h][c];
-            __syncthreads();
-#pragma unroll
-            for (int K = 0; K < NBLK; ++K) {
-                if (K > I) continue;  // uniform per wave
-                v4f y[4];
-#pragma unroll
-                for (int c = 0; c < 4; ++c) y[c] = Us[c][K][lane];
-#pragma unroll
-                for (int c = 0; c < 4; ++c)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        acc[K] = __builtin_amdgcn_mfma_f32_16x16x4f32(y[c][r], x[h][c][r], acc[K], 0, 0, 0);
-            }
-        }
-#pragma unroll
-        for (int K = 0; K < NBLK; ++K) {
-            Q[K] -= acc[K];
-            if (K == I) dg = Q[K];
-        }
-    }
-    __syncthreads();
+};
 
+// acc[m] += X L_K^T, K = (K0 + m) mod 8, for four blocks of L in LDS.
+__device__ __forceinline__ void four_blocks(v4f *acc, const SplitX &x, const SplitBlock *L, int K0, int lane)
+{
+    v4u hm[4], lh[4];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+        const SplitBlock &b = L[(K0 + m) & (NBLK - 1)];
+        const v2u l = b.l[lane];
+        const v4u h = b.hm[lane];
+        const v8u w = __builtin_shufflevector(join(l, l), h, 0, 1, 4, 5, 6, 7, -1, -1);
+        lh[m] = __builtin_shufflevector(w, w, 0, 1, 2, 3);
+        hm[m] = __builtin_shufflevector(w, w, 2, 3, 4, 5);
+    }
+#pragma unroll
+    for (int m = 0; m < 4; ++m) acc[m] = mfma_b(lh[m], x.hl, acc[m]);
+#pragma unroll
+    for (int m = 0; m < 4; ++m) acc[m] = mfma_b(hm[m], x.mm, acc[m]);
+#pragma unroll
+    for (int m = 0; m < 4; ++m) acc[m] = mfma_b(hm[m], x.hh, acc[m]);
+}
+
+// ---- hand-off of a panel's top block between workgroups ---------------------------
+// A block passes in its components, a plane of 512 bytes each (an inverse in FP32: two),
+// by relaxed atomics of 8 bytes past the L2s; kUnset in a word marks what is not
+// there yet.
+constexpr uint32_t kUnset = 0x7fa5f00du;  // a signalling NaN, in BF16 too (arithmetic yields quiet ones)
+constexpr int kBlockWords = 192;          // 8-byte words
+constexpr int kPanelBlocks = kPanelSteps * (kPanelSteps + 1) / 2;
+
+// Block of 16-row block row R >= g at 16-column step g of the panel's top block.
+__device__ __forceinline__ uint64_t *xblock(uint64_t *xch, int g, int R)
+{
+    return xch + (g * kPanelSteps - g * (g + 1) / 2 + R) * kBlockWords;
+}
+
+__device__ __forceinline__ v2u ld_plane(const uint64_t *p, int c, int lane)
+{
+    return __builtin_bit_cast(v2u, __hip_atomic_load(p + 64 * c + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+
+__device__ __forceinline__ void st_plane(uint64_t *p, int c, int lane, v2u v)
+{
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+        if (v[r] == kUnset) v[r] = 0x7fc07fc0u;
+    __hip_atomic_store(p + 64 * c + lane, __builtin_bit_cast(uint64_t, v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ __forceinline__ void st_split(uint64_t *p, int lane, const Split &s)
+{
+#pragma unroll
+    for (int c = 0; c < 3; ++c) st_plane(p, c, lane, s.c[c]);
+}
+
+// Factor of the 128 x 128 block at Ab (global pivot index k0) whose row block I is in
+// the wave's registers: Q[m], block (I, m) for m <= I and zero beyond, and dg = Q[I].
+// PUB: the blocks L_Kj and the inverses of the 16 x 16 diagonal blocks go to the exchange,
+// steps g0 .. g0 + 7.
+template <bool PUB>
+__device__ __forceinline__ void factor128(v4f (&Q)[NBLK], const v4f &dg, float *__restrict__ Ab, int64_t ld, int64_t k0,
+                                          float *__restrict__ Linv, int *__restrict__ status, v4f (*Lx)[64], float *Yd,
+                                          int &bad, int I, int lane, uint64_t *xch, int g0)
+{
+    const int g = lane >> 4, i = lane & 15;
     v4f P = dg, P0, X;
     // wave j: factor its diagonal block P and put the inverse in LDS
     auto diagonal = [&]() {
@@ -264,13 +319,24 @@ __device__ __forceinline__ void potrf128_body(float *__restrict__ A, int64_t ld,
     for (int j = 0; j < NBLK; ++j) {
         if (I != j) {
             const v4f y = *reinterpret_cast<const v4f *>(Yd + i * SB + 4 * g);
+            if (PUB && I == ((j + 2) & (NBLK - 1))) {
+                uint64_t *p = xblock(xch, g0 + j, g0 + j);
+                st_plane(p, 0, lane, __builtin_bit_cast(v4u, y).xy);
+                st_plane(p, 1, lane, __builtin_bit_cast(v4u, y).zw);
+            }
 #pragma unroll
             for (int r = 0; r < 4; ++r) X[r] = 0.0f;
 #pragma unroll
             for (int r = 0; r < 4; ++r) X = __builtin_amdgcn_mfma_f32_16x16x4f32(y[r], Q[0][r], X, 0, 0, 0);
         }
-        if (I > j) Lx[I][lane] = X;
+        if (I > j) {
+            Lx[I][lane] = X;
+            if (PUB && I != j + 1) st_split(xblock(xch, g0 + j, g0 + I), lane, split_rows(X));
+        }
         __syncthreads();
+        // for wave j + 1, which goes on with the pivots
+        if (PUB && j + 1 < NBLK && I == ((j + 3) & (NBLK - 1)))
+            st_split(xblock(xch, g0 + j, g0 + j + 1), lane, split_rows(Lx[j + 1][lane]));
         // out: L and L^T of this block column, rows of the inverse
         if (I == j) {
             float d = 1.0f;
@@ -323,14 +389,54 @@ __device__ __forceinline__ void potrf128_body(float *__restrict__ A, int64_t ld,
         }
         __syncthreads();
     }
-    if (tid == 0 && bad != 0) atomicCAS(&status[kStBreakdown], 0, bad);
+    if (threadIdx.x == 0 && bad != 0) atomicCAS(&status[kStBreakdown], 0, bad);
 }
 
-__global__ void __launch_bounds__(NTP)
-k_potrf128(float *__restrict__ A, int64_t ld, int64_t k0, int64_t n, float *__restrict__ Linv,
-           int *__restrict__ status)
+// A diagonal block of the identity padding: its diagonal entries alone.
+__device__ __forceinline__ void factor_padding(float *__restrict__ Ab, int64_t ld, float *__restrict__ Linv)
 {
-    potrf128_body<false>(A, ld, k0, n, Linv, status, nullptr);
+    for (int e = threadIdx.x; e < NB * NB; e += NTP) {
+        const int c = e >> 7, r = e & (NB - 1);
+        float l = 0.0f, v = 0.0f;
+        if (r == c) {
+            const float d = Ab[(int64_t)c * ld + r];
+            v = __builtin_amdgcn_rsqf(d);
+            l = d * v;
+        }
+        Ab[(int64_t)c * ld + r] = l;
+        Linv[e] = v;
+    }
+}
+
+// The row block of a wave: waves w and w + 4 share a SIMD, and a long row block goes
+// with a short one.
+__device__ __forceinline__ int row_block()
+{
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    return wave < NBLK / 2 ? wave : 3 * NBLK / 2 - 1 - wave;
+}
+
+// Row block I of the 128 x 128 tile at At.
+__device__ __forceinline__ void load_rows(v4f (&Q)[NBLK], const float *__restrict__ At, int64_t ld, int I, int lane)
+{
+    const unsigned off = 4 * (lane >> 4) * (unsigned)ld + SB * I + (lane & 15);
+#pragma unroll
+    for (int K = 0; K < NBLK; ++K)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) Q[K][r] = (At + (SB * K + r) * ld)[off];
+}
+
+// Diagonal block I of the 128 x 128 block at Ab, from its lower triangle.
+__device__ __forceinline__ v4f load_diagonal(const float *__restrict__ Ab, int64_t ld, int I, int lane)
+{
+    const int g = lane >> 4, i = lane & 15;
+    v4f d;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int k = 4 * g + r, lo = k < i ? k : i, hi = k < i ? i : k;
+        d[r] = Ab[(SB * I + lo) * ld + SB * I + hi];
+    }
+    return d;
 }
 
 // Batched: one workgroup per problem whose padded size exceeds k0.
@@ -339,93 +445,297 @@ k_potrf128_b(const BProb *__restrict__ P, BWork w, int64_t k0)
 {
     const BProb &q = P[w.plist[blockIdx.x]];
     if (!q.active || k0 >= q.npad) return;
-    potrf128_body<false>(q.A, q.npad, k0, q.n, q.dinv + (k0 / NB) * NB * NB, q.ints, nullptr);
-}
-
-// ---- sub-panel update and the next diagonal block in one launch ------------------
-// C (i, j) -= P P^T for one 128 x 128 tile (rows i0.., columns j0..) by the 128
-// columns at P, on eight waves of 32 x 64 each; K staged through LDS in
-// double-buffered chunks of 16 by direct loads (see gemm_mfma.hip).
-typedef float v16f __attribute__((ext_vector_type(16)));
-typedef const __attribute__((address_space(1))) void *gptr;
-typedef __attribute__((address_space(3))) void *lptr;
-constexpr int KC = 16;
-
-__device__ __forceinline__ void update_tile(float *__restrict__ C, int64_t ldc, const float *__restrict__ P,
-                                            int64_t ldp, int64_t i0, int64_t j0, float *lds)
-{
-    float (*Ps)[KC][NB] = reinterpret_cast<float (*)[KC][NB]>(lds);
-    float (*Qs)[KC][NB] = reinterpret_cast<float (*)[KC][NB]>(lds + 2 * KC * NB);
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int wi = (wave & 3) * 32, wj = (wave >> 2) * 64;
-    const int l32 = lane & 31, hi = lane >> 5;
-    v16f acc[2];
-#pragma unroll
-    for (int jb = 0; jb < 2; ++jb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[jb][r] = 0.0f;
-    // wave w stages k-rows 2 w and 2 w + 1 of P and of Q
-    const int64_t off = (int64_t)(threadIdx.x >> 5) * ldp + 4 * (threadIdx.x & 31);
-    const float *pg = P + off + i0, *qg = P + off + j0;
-    auto stage_in = [&](int b) {
-        __builtin_amdgcn_global_load_lds((gptr)pg, (lptr)&Ps[b][2 * wave][0], 16, 0, 0);
-        __builtin_amdgcn_global_load_lds((gptr)qg, (lptr)&Qs[b][2 * wave][0], 16, 0, 0);
-        pg += KC * ldp;
-        qg += KC * ldp;
-    };
-    stage_in(0);
-    __syncthreads();
-    constexpr int nst = NB / KC;
-    for (int st = 0; st < nst; ++st) {
-        const int buf = st & 1;
-        if (st + 1 < nst) stage_in(buf ^ 1);
-#pragma unroll
-        for (int kp = 0; kp < KC / 2; ++kp) {
-            const int p = 2 * kp + hi;
-            const float pv = Ps[buf][p][wi + l32];
-            acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(Qs[buf][p][wj + l32], pv, acc[0], 0, 0, 0);
-            acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(Qs[buf][p][wj + 32 + l32], pv, acc[1], 0, 0, 0);
-        }
-        __syncthreads();  // waits for the direct loads of the next stage too
-    }
-    float cv[2][16];
-    float *c0 = C + (j0 + wj) * ldc + i0 + wi + l32;
-#pragma unroll
-    for (int jb = 0; jb < 2; ++jb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) cv[jb][r] = c0[(jb * 32 + 8 * (r >> 2) + 4 * hi + (r & 3)) * ldc];
-#pragma unroll
-    for (int jb = 0; jb < 2; ++jb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-            c0[(jb * 32 + 8 * (r >> 2) + 4 * hi + (r & 3)) * ldc] = cv[jb][r] - acc[jb][r];
-}
-
-// The columns kk + 128 .. kk + 128 (1 + ncol) of the trailing rows (from kk + 128) updated
-// by the sub-panel at kk, lower 128-tiles only; workgroup 0 takes the first tile,
-// the next diagonal block, and goes on to factor it while the others update
-// theirs: its 12 us of pivots run beside the update instead of after it, and it
-// needs no load of its own.
-constexpr int kUpdateLds = 4 * KC * NB * 4;  // bytes: two buffers of P and Q stages
-static_assert(kUpdateLds >= (int)(4 * NBLK * 64 * sizeof(v4f)), "the row blocks of the fused update fit the stages");
-
-__global__ void __launch_bounds__(NTP, 4)
-k_update_potrf(float *__restrict__ A, int64_t ld, int64_t kk, int64_t n, int ncol, float *__restrict__ Linv,
-               int *__restrict__ status)
-{
-    __shared__ v4f lds[kUpdateLds / sizeof(v4f)];
-    if (blockIdx.x == 0) {
-        potrf128_body<true>(A, ld, kk + NB, n, Linv, status, reinterpret_cast<v4f (*)[NBLK][64]>(lds));
+    __shared__ v4f Lx[NBLK][64];   // the blocks L_Kj of a step, row layout
+    __shared__ float Yd[SB * SB];  // the inverse of its diagonal block, Yd[k * SB + c]
+    __shared__ int bad;
+    const int lane = threadIdx.x & 63, I = row_block();
+    float *Ab = q.A + k0 * q.npad + k0, *Linv = q.dinv + (k0 / NB) * NB * NB;
+    if (k0 >= q.n) {
+        factor_padding(Ab, q.npad, Linv);
         return;
     }
-    const int64_t T = (ld - kk - NB) / NB;  // tile rows
-    int64_t u = blockIdx.x, tj = 0;
-    while (u >= T - tj) {  // column tj has T - tj tiles
-        u -= T - tj;
-        ++tj;
+    // Q[m] at step j: block (I, j + m) of A while j + m <= I; from step I on, of the
+    // eliminated identity
+    v4f Q[NBLK];
+    load_rows(Q, Ab, q.npad, I, lane);
+    const v4f dg = load_diagonal(Ab, q.npad, I, lane);
+#pragma unroll
+    for (int K = 0; K < NBLK; ++K)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) Q[K][r] = K < I ? Q[K][r] : (K == I ? dg[r] : 0.0f);
+    if (threadIdx.x == 0) bad = 0;
+    __syncthreads();
+    factor128<false>(Q, dg, Ab, q.npad, k0, Linv, q.ints, Lx, Yd, bad, I, lane, nullptr, 0);
+}
+
+// ---- one panel in one launch -------------------------------------------------------
+struct PanelArgs {
+    float *A;         // the matrix
+    int64_t ld, k, n;
+    int nsub;         // 128-column sub-panels
+    float *dinv;      // inverse of the panel's first diagonal block, the others behind it
+    int *status, *ticket;
+    uint64_t *xch, *xnext;  // this launch's exchange and the next one's
+    long spin_limit;
+};
+
+constexpr int MT = kPanelSteps / NBLK;  // most tiles (128-column sub-panels) of a panel
+
+struct PanelShared {
+    SplitBlock B[2][MT][NBLK];  // a step's blocks: of the sub-panel's own rows, of the later tiles'
+    SplitBlock O[2][NBLK];      // and of the workgroup's own rows
+    v4f Y[2][64];               // the inverse of the step's diagonal block
+    float Yd[SB * SB];
+    int bad, ib;
+};
+
+// Sub-panel S of the rows below its diagonal block: tile Q (updated by the earlier
+// sub-panels) into L, acc[t - 1] += L L_t^T for the panel's later tiles t.
+template <int S>
+__device__ __forceinline__ void below(const PanelArgs &a, PanelShared &sh, v4f (&Q)[NBLK], v4f (&acc)[MT - 1][NBLK],
+                                      Split (&pf)[MT], int ib, int I, int lane, long &limit)
+{
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int g4 = lane >> 4, i = lane & 15;
+    const bool top = ib < a.nsub;
+    const int lim = top ? ib : a.nsub;  // tiles whose blocks come from other workgroups
+    // block `wave` of tile S + q at step g: the wave's share of a step's blocks
+    auto need = [&](int g, int q) {
+        return q == 0 ? wave >= (g & (NBLK - 1)) : (g >> 3) + q < lim;
+    };
+    auto fetch = [&](int g) {
+#pragma unroll
+        for (int q = 0; q < MT; ++q)
+            if (need(g, q)) {
+                const uint64_t *p = xblock(a.xch, g, NBLK * ((g >> 3) + q) + wave);
+#pragma unroll
+                for (int c = 0; c < 3; ++c)
+                    if (c < 2 || q > 0 || wave != (g & (NBLK - 1))) pf[q].c[c] = ld_plane(p, c, lane);
+            }
+    };
+    auto missing = [&](int g) {
+        bool u = false;
+#pragma unroll
+        for (int q = 0; q < MT; ++q)
+            if (need(g, q)) {
+                // (the two words of an atomic come together)
+                u = u || pf[q].c[0][0] == kUnset || pf[q].c[1][0] == kUnset;
+                if (q > 0 || wave != (g & (NBLK - 1))) u = u || pf[q].c[2][0] == kUnset;
+            }
+        return __ballot(u) != 0;
+    };
+    // until the step's blocks are there: the top block's workgroups poll the data, the
+    // others one entry of each block, now and then
+    auto wait = [&](int g) {
+        long spins = 0;
+        while (missing(g)) {
+            if (++spins > limit) {
+                if (lane == 0) a.status[kStSpinTimeout] = 1;
+                limit = 0;
+                return;
+            }
+            if (!top) {
+                const int s = g >> 3;
+                bool mine = false;
+                if (lane == 0) mine = need(g, 0);
+#pragma unroll
+                for (int q = 1; q < MT; ++q)
+                    if (lane == q) mine = need(g, q);
+                const uint64_t *e = xblock(a.xch, g, NBLK * (s + (lane & (MT - 1))) + wave) + 127;
+                for (;;) {
+                    uint64_t v = 0;
+                    if (mine) v = __hip_atomic_load(e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (__ballot(mine && (uint32_t)(v >> 32) == kUnset) == 0 || ++spins > limit) break;
+                    __builtin_amdgcn_s_sleep(8);
+                }
+            }
+            fetch(g);
+        }
+    };
+    float *low = a.A + (a.k + NB * S + 4 * g4) * a.ld + a.k + NB * ib + SB * I + i;
+    float *up = a.A + (a.k + NB * ib + SB * I + i) * a.ld + a.k + NB * S + 4 * g4;
+    if (S == 0) fetch(0);
+#pragma unroll 1
+    for (int j = 0; j < NBLK + (top ? 1 : 0); ++j) {
+        const int g = NBLK * S + j, cur = j & 1;
+        SplitX x;
+        if (j < NBLK) {
+            wait(g);
+#pragma unroll
+            for (int q = 0; q < MT - S; ++q)
+                if (need(g, q)) {
+                    if (q == 0 && wave == j)
+                        sh.Y[cur][lane] = __builtin_bit_cast(v4f, join(pf[0].c[0], pf[0].c[1]));
+                    else
+                        sh.B[cur][q][wave].put(lane, pf[q]);
+                }
+            if (g + 1 < NBLK * lim) fetch(g + 1);
+            __syncthreads();
+            v4f X;
+            {
+                const v4f y = sh.Y[cur][lane];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) X[r] = 0.0f;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) X = __builtin_amdgcn_mfma_f32_16x16x4f32(y[r], Q[0][r], X, 0, 0, 0);
+            }
+            const Split xs = split_rows(X);
+            if (top) {
+                st_split(xblock(a.xch, g, NBLK * ib + I), lane, xs);
+                sh.O[cur][I].put(lane, xs);
+            }
+            x = widen(xs);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) low[r * a.ld] = X[r];
+            *reinterpret_cast<v4f *>(up) = X;
+            low += SB * a.ld;
+            up += SB;
+            // the blocks right of this one in the sub-panel
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                if (j < NBLK - 1 - 4 * h) {
+                    v4f u[4];
+#pragma unroll
+                    for (int m = 0; m < 4; ++m)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) u[m][r] = 0.0f;
+                    four_blocks(u, x, sh.B[cur][0], j + 1 + 4 * h, lane);
+#pragma unroll
+                    for (int m = 0; m < 4; ++m)
+                        if (4 * h + m < NBLK - 1) Q[4 * h + m] = Q[4 * h + m + 1] - u[m];
+                }
+        } else {
+            __syncthreads();
+        }
+        // the later tiles; the workgroup's own (its diagonal block's) one step behind, when
+        // every wave's block is in LDS
+#pragma unroll
+        for (int t = S + 1; t < MT; ++t) {
+            const bool own = top && t == ib;
+            if ((j < NBLK && t < lim) || (own && j > 0)) {
+                const SplitBlock *L = sh.B[cur][t - S];
+                if (own) {
+                    L = sh.O[cur ^ 1];
+                    Split xs;
+                    xs.c[0] = L[I].l[lane];
+                    const v4u hm = L[I].hm[lane];
+                    xs.c[1] = hm.xy;
+                    xs.c[2] = hm.zw;
+                    x = widen(xs);
+                }
+                __builtin_amdgcn_sched_barrier(0);  // keeps the tiles' operands from being live together
+#pragma unroll
+                for (int h = 0; h < 2; ++h) four_blocks(acc[t - 1] + 4 * h, x, L, 4 * h, lane);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
     }
-    update_tile(A + (kk + NB) * ld + kk + NB, ld, A + kk * ld + kk + NB, ld, (tj + u) * NB, tj * NB,
-                reinterpret_cast<float *>(lds));
+}
+
+// The workgroup's part in sub-panel S: its tile below the diagonal block, or (true) that
+// block's rows into Q and dg for the factorisation.
+template <int S>
+__device__ __forceinline__ bool panel_step(const PanelArgs &a, PanelShared &sh, v4f (&Q)[NBLK], v4f &dg,
+                                           v4f (&acc)[MT - 1][NBLK], Split (&pf)[MT], int ib, int I, int lane, long &limit)
+{
+    const int64_t k0 = a.k + NB * S;
+    float *At = a.A + k0 * a.ld + a.k + NB * ib;  // tile (ib, S)
+    if (k0 >= a.n) {
+        // the identity padding (uniform)
+        if (ib == S) return true;
+        float *Up = a.A + (a.k + NB * ib) * a.ld + k0;
+        for (int e = threadIdx.x; e < NB * NB; e += NTP) {
+            At[(int64_t)(e >> 7) * a.ld + (e & (NB - 1))] = 0.0f;
+            Up[(int64_t)(e >> 7) * a.ld + (e & (NB - 1))] = 0.0f;
+        }
+        return false;
+    }
+    load_rows(Q, At, a.ld, I, lane);
+    if (ib == S) dg = load_diagonal(At, a.ld, I, lane);
+    if (S > 0) {
+#pragma unroll
+        for (int K = 0; K < NBLK; ++K) {
+            const v4f u = acc[S > 0 ? S - 1 : 0][K];
+            Q[K] -= u;
+            if (K == I) dg -= u;
+        }
+    }
+    if (ib == S) return true;
+    below<S>(a, sh, Q, acc, pf, ib, I, lane, limit);
+    return false;
+}
+
+__global__ void __launch_bounds__(NTP)
+k_panel(PanelArgs a)
+{
+    __shared__ PanelShared sh;
+    const int lane = threadIdx.x & 63, I = row_block();
+    // the panel's rows of (most likely) this workgroup on their way to the L2 meanwhile, a
+    // line per thread and tile
+    float warm = 0.0f;
+    for (int t = 0; t < a.nsub; ++t)
+        warm += a.A[(a.k + NB * t + (threadIdx.x >> 2)) * a.ld + a.k + NB * (int64_t)blockIdx.x + 32 * (threadIdx.x & 3)];
+    if (threadIdx.x == 0) {
+        // tickets: a workgroup waits only for earlier ones, which are running
+        sh.ib = atomicAdd(a.ticket, 1);
+        if (sh.ib == (int)gridDim.x - 1) *a.ticket = 0;
+        sh.bad = 0;
+    }
+    __syncthreads();
+    const int ib = __builtin_amdgcn_readfirstlane(sh.ib);
+    asm volatile("" ::"v"(warm));
+    v4f Q[NBLK], dg, acc[MT - 1][NBLK];
+    Split pf[MT];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) dg[r] = 0.0f;
+#pragma unroll
+    for (int t = 0; t < MT - 1; ++t)
+#pragma unroll
+        for (int K = 0; K < NBLK; ++K)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[t][K][r] = 0.0f;
+#pragma unroll
+    for (int q = 0; q < MT; ++q)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) pf[q].c[c][0] = pf[q].c[c][1] = 0;
+    long limit = a.spin_limit;
+    if (!panel_step<0>(a, sh, Q, dg, acc, pf, ib, I, lane, limit) &&
+        !panel_step<1>(a, sh, Q, dg, acc, pf, ib, I, lane, limit)) {
+        if (a.nsub == 2) return;
+        if (!panel_step<2>(a, sh, Q, dg, acc, pf, ib, I, lane, limit) &&
+            !panel_step<3>(a, sh, Q, dg, acc, pf, ib, I, lane, limit))
+            return;
+    }
+    // block ib of the diagonal
+    {
+        const int64_t k0 = a.k + NB * ib;
+        float *Ab = a.A + k0 * a.ld + k0, *Linv = a.dinv + ib * NB * NB;
+        if (k0 >= a.n) {
+            factor_padding(Ab, a.ld, Linv);
+        } else {
+#pragma unroll
+            for (int K = 0; K < NBLK; ++K)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) Q[K][r] = K < I ? Q[K][r] : (K == I ? dg[r] : 0.0f);
+            factor128<true>(Q, dg, Ab, a.ld, k0, Linv, a.status, reinterpret_cast<v4f (*)[64]>(sh.B), sh.Yd, sh.bad, I, lane, a.xch, NBLK * ib);
+        }
+    }
+    if (ib == 0) {
+        // done early: unset the next launch's exchange
+        v4u u;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) u[r] = kUnset;
+        for (int e = threadIdx.x; e < kPanelBlocks * kBlockWords / 2; e += NTP) reinterpret_cast<v4u *>(a.xnext)[e] = u;
+    }
+}
+
+__global__ void __launch_bounds__(256)
+k_unset(v4u *__restrict__ x)
+{
+    v4u u;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) u[r] = kUnset;
+    x[blockIdx.x * 256 + threadIdx.x] = u;
 }
 
 }  // namespace
@@ -435,18 +745,32 @@ void launch_potrf128_b(hipStream_t s, const BProb *P, const BWork &w, int64_t k0
     if (w.na > 0) hipLaunchKernelGGL(k_potrf128_b, dim3(w.na), dim3(NTP), 0, s, P, w, k0);
 }
 
-void launch_potrf128(hipStream_t s, float *A, int64_t ld, int64_t k0, int64_t n, float *Linv, int *status)
+constexpr size_t kExchangeBytes = (size_t)kPanelBlocks * kBlockWords * 8;
+static_assert(kExchangeBytes % 4096 == 0, "whole workgroups of k_unset");
+size_t panel_work_bytes() { return 2 * kExchangeBytes + 64; }
+
+void launch_panel_begin(hipStream_t s, void *work)
 {
-    hipLaunchKernelGGL(k_potrf128, dim3(1), dim3(NTP), 0, s, A, ld, k0, n, Linv, status);
+    hipLaunchKernelGGL(k_unset, dim3(kExchangeBytes / 4096), dim3(256), 0, s, (v4u *)work);
 }
 
-void launch_update_potrf(hipStream_t s, float *A, int64_t ld, int64_t kk, int64_t n, int ncol, float *Linv, int *status)
+void launch_panel(hipStream_t s, float *A, int64_t ld, int64_t k, int64_t nb, int64_t n, float *dinv, int *status,
+                  void *work, int index)
 {
-    const int64_t T = (ld - kk - NB) / NB;
-    if (T <= 0 || ncol <= 0) return;
-    const int64_t nc = ncol < T ? ncol : T;
-    const int64_t tiles = nc * T - nc * (nc - 1) / 2;
-    hipLaunchKernelGGL(k_update_potrf, dim3((unsigned)tiles), dim3(NTP), 0, s, A, ld, kk, n, (int)nc, Linv, status);
+    char *w = (char *)work;
+    PanelArgs a;
+    a.A = A;
+    a.ld = ld;
+    a.k = k;
+    a.n = n;
+    a.nsub = (int)(nb / NB);
+    a.dinv = dinv + (k / NB) * NB * NB;
+    a.status = status;
+    a.ticket = (int *)(w + 2 * kExchangeBytes);
+    a.xch = (uint64_t *)(w + (index & 1) * kExchangeBytes);
+    a.xnext = (uint64_t *)(w + (~index & 1) * kExchangeBytes);
+    a.spin_limit = kPanelSpinLimit;
+    hipLaunchKernelGGL(k_panel, dim3((unsigned)((ld - k) / NB)), dim3(NTP), 0, s, a);
 }
 
 }  // namespace mag
