@@ -9,12 +9,12 @@
 // small clouds costs about as many launches as one cloud.
 //
 // The factorisation's launch sequence depends only on the problems' padded
-// sizes, so its work lists are uploaded once per batch and the sequence is
-// captured in a hipGraph that is replayed for every t-step; the per-step data
-// (scale t, active flag, diagonal shift) live in the device descriptor array
-// that the kernels read at run time.  The refinement (GMRES) keeps one
-// Hessenberg per problem on the host and runs its iterations in lockstep over
-// the problems that have not yet converged.
+// sizes, so its work lists are uploaded once per batch and, in a search, the
+// sequence is captured in a hipGraph that is replayed for every t-step; the per-step
+// data (scale t, active flag, diagonal shift) live in the device descriptor array
+// that the kernels read at run time.  The refinement is controlled on the device
+// (bctl.hip); problems that its rounds leave short of tol are retaken with one
+// Hessenberg per problem on the host, in lockstep over those not yet converged.
 #include "internal.hpp"
 
 #include <algorithm>
@@ -71,15 +71,17 @@ struct Batch {
     // arenas for work lists: persistent (the factorisation schedule) + transient
     char *dev_arena = nullptr, *host_arena = nullptr;
     size_t arena_bytes = 0, persist_used = 0, trans_used = 0;
-    hipGraphExec_t graph = nullptr;
-    hipGraph_t graph_def = nullptr;
+    hipGraphExec_t graph[2] = {nullptr, nullptr};  // a step's two parts
+    hipGraph_t graph_def[2] = {nullptr, nullptr};
     std::vector<double> hostbuf;
     double *dstage = nullptr;  // device staging for gathered scalars
 
     ~Batch()
     {
-        if (graph) hipGraphExecDestroy(graph);
-        if (graph_def) hipGraphDestroy(graph_def);
+        for (auto g : graph)
+            if (g) hipGraphExecDestroy(g);
+        for (auto g : graph_def)
+            if (g) hipGraphDestroy(g);
     }
 
     // Append bytes to an arena region.  Transient data: the host copy is made
@@ -157,12 +159,11 @@ struct Batch {
     }
 };
 
-// split-reduction doubles of one problem: products, derivatives, dot products, d_min
+// split-reduction doubles of one problem: products, derivatives, dot products
 size_t batch_partial_doubles(int64_t n, int restart, int ts)
 {
     size_t p = std::max(zmv_b_partial_doubles(n, ts), pair_partial_doubles(n, 1));
     p = std::max(p, blas1_partial_doubles(restart + 2));
-    p = std::max(p, dmin_partial_doubles(n) + 8);
     return p + 64;
 }
 
@@ -634,25 +635,30 @@ struct RefPlan {
 
 // Record the device-controlled refinement of Z x = b (b in rhs_slot, zero
 // padded) for the problems active on entry; the best iterate lands in slot
-// Best.  bnorm_off: scalar slot of ||b||_inf (tol scales with it), or -1.
-void record_refine(Batch &bt, const AllWork &A, int rhs_slot, int64_t bnorm_off, const RefPlan &rp)
+// Best.  bnorm_off: scalar slot of ||b||_inf (tol scales with it), or -1.  The first part
+// (rest = false) ends with round 1's residual and decision, the second takes it up there.
+void record_refine(Batch &bt, const AllWork &A, int rhs_slot, int64_t bnorm_off, const RefPlan &rp, bool rest)
 {
     const Slots &S = bt.sl;
     hipStream_t s = bt.s;
     BProb *P = bt.d;
     const int B = bt.B;
     const int64_t mp = bt.maxpad;
-    launch_ref_init_b(s, P, B, bnorm_off, rp.tol);
-    launch_gate_b(s, P, B, F_REF);
-    launch_prec_apply_b(s, P, A.wp, rhs_slot, S.Y, S.X);  // x0 = M^{-1} b
-    for (int round = 0; round <= rp.rounds; ++round) {
-        const int final_round = round == rp.rounds ? 1 : 0;
+    if (!rest) {
+        launch_ref_init_b(s, P, B, bnorm_off, rp.tol);
         launch_gate_b(s, P, B, F_REF);
-        launch_zmv_b(s, bt.m, P, A.wz, A.wr, S.X, S.Rr, rhs_slot, 1, SC_RNORM, bt.ts);
-        launch_ref_decide_b(s, P, B, final_round, rp.max_gmres);
-        launch_gate_b(s, P, B, F_COPYBEST);
-        launch_copy_b(s, P, A.all, B, mp, S.X, S.Best);
-        if (final_round) break;
+        launch_prec_apply_b(s, P, A.wp, rhs_slot, S.Y, S.X);  // x0 = M^{-1} b
+    }
+    for (int round = rest ? 1 : 0; round <= rp.rounds; ++round) {
+        const int final_round = round == rp.rounds ? 1 : 0;
+        if (!rest || round > 1) {
+            launch_gate_b(s, P, B, F_REF);
+            launch_zmv_b(s, bt.m, P, A.wz, A.wr, S.X, S.Rr, rhs_slot, 1, SC_RNORM, bt.ts);
+            launch_ref_decide_b(s, P, B, final_round, rp.max_gmres);
+            launch_gate_b(s, P, B, F_COPYBEST);
+            launch_copy_b(s, P, A.all, B, mp, S.X, S.Best);
+        }
+        if (final_round || (!rest && round == 1)) break;
         if (round > 0) {  // the first round cannot revert (no best iterate before it)
             launch_gate_b(s, P, B, F_REVERT);
             launch_copy_b(s, P, A.all, B, mp, S.Best, S.X);
@@ -681,61 +687,108 @@ void record_refine(Batch &bt, const AllWork &A, int rhs_slot, int64_t bnorm_off,
     }
 }
 
-// Capture one step of the batched search (or of the fixed-scale solves) as a
-// graph: each cloud's next scale, the factorisation, the refinement, min w,
-// the bracket update and, for Newton steps, d(min w)/dt; then the count of
-// clouds still searching into dcount[0..2).
-int build_step_graph(Batch &bt, const std::vector<FLaunch> &fseq, const AllWork &A, SState *S, const SParams &prm,
-                     const RefPlan &rp, const RefPlan &dp, int *dcount)
+// One step of the batched search or of the fixed-scale solves: everything its launches need.
+struct Step {
+    std::vector<FLaunch> fseq;
+    AllWork A;
+    SState *S = nullptr;
+    SParams prm{};
+    RefPlan rp, dp;         // the solve's refinement and the Newton derivative's
+    int *dcount = nullptr;  // clouds still searching, breakdown at every shift, refinements parked
+};
+
+// min w, the bracket update and, for Newton steps, the first part of d(min w)/dt = (dw/dt) at
+// argmin w, dw/dt = Z^{-1} (D o Z) w with this step's factor.
+void record_update(Batch &bt, const Step &st)
 {
     const Slots &SL = bt.sl;
     hipStream_t s = bt.s;
     BProb *P = bt.d;
     const int B = bt.B;
-    const int64_t mp = bt.maxpad;
-    BRC(bt.flush_persistent());     // work lists and states, in one copy
-    BCHK(hipStreamSynchronize(s));
-    BCHK(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
-    launch_search_select_b(s, P, S, B, prm);
-    record_factor(bt, fseq);
-    launch_breakdown_b(s, P, S, B);
     launch_gate_b(s, P, B, F_SEARCH);
-    launch_fill_b(s, P, A.all, B, mp, SL.Rhs, 1.0, true);
-    record_refine(bt, A, SL.Rhs, -1, rp);
-    launch_gate_b(s, P, B, F_SEARCH);
-    launch_summin_b(s, P, A.all, B, SL.Best, SC_SUM);
-    launch_search_update_b(s, P, S, B, prm);
+    launch_summin_b(s, P, st.A.all, B, SL.Best, SC_SUM);
+    launch_search_update_b(s, P, st.S, B, st.prm);
     launch_gate_b(s, P, B, F_HI);
-    launch_copy_b(s, P, A.all, B, mp, SL.Best, SL.W);
-    if (prm.newton) {
-        // dw/dt = Z^{-1} (D o Z) w with this step's factor; its entry at argmin w
-        launch_gate_b(s, P, B, F_NEEDD);
-        launch_copy_b(s, P, A.all, B, mp, SL.Best, SL.DZ);
-        launch_dzmv_b(s, bt.m, P, A.wdz, A.wdr, SL.DZ, SL.Rhs);
-        launch_amax_b(s, P, A.all, B, SL.Rhs, SC_AMAX);
-        record_refine(bt, A, SL.Rhs, SC_AMAX, dp);
-        launch_gate_b(s, P, B, F_NEEDD);
-        launch_pick_b(s, P, A.all, B, SL.Best, SC_SUM + 2, SC_PICK);
-        launch_search_deriv_b(s, P, S, B);
-    }
-    launch_search_count_b(s, S, B, dcount);
-    hipGraph_t g = nullptr;
-    if (hipStreamEndCapture(s, &g) != hipSuccess) return MAG_EHIP;
-    bt.graph_def = g;
-    BCHK(hipGraphInstantiate(&bt.graph, g, nullptr, nullptr, 0));
-    return MAG_OK;
+    launch_copy_b(s, P, st.A.all, B, bt.maxpad, SL.Best, SL.W);
+    if (!st.prm.newton) return;
+    launch_gate_b(s, P, B, F_NEEDD);
+    launch_copy_b(s, P, st.A.all, B, bt.maxpad, SL.Best, SL.DZ);
+    launch_dzmv_b(s, bt.m, P, st.A.wdz, st.A.wdr, SL.DZ, SL.Rhs);
+    launch_amax_b(s, P, st.A.all, B, SL.Rhs, SC_AMAX);
+    record_refine(bt, st.A, SL.Rhs, SC_AMAX, st.dp, false);
 }
 
-// Run step graphs until no cloud is searching (one count read per step).
+void record_derivative(Batch &bt, const Step &st)
+{
+    launch_gate_b(bt.s, bt.d, bt.B, F_NEEDD);
+    launch_pick_b(bt.s, bt.d, st.A.all, bt.B, bt.sl.Best, SC_SUM + 2, SC_PICK);
+    launch_search_deriv_b(bt.s, bt.d, st.S, bt.B);
+}
+
+// Each cloud's next scale, the factorisation, the refinement as far as the residual after its
+// first correction; for clouds that met tol there, the rest of the step.
+void record_step(Batch &bt, const Step &st)
+{
+    hipStream_t s = bt.s;
+    BProb *P = bt.d;
+    launch_search_select_b(s, P, st.S, bt.B, st.prm);
+    record_factor(bt, st.fseq);
+    launch_breakdown_b(s, P, st.S, bt.B);
+    launch_gate_b(s, P, bt.B, F_SEARCH);
+    launch_fill_b(s, P, st.A.all, bt.B, bt.maxpad, bt.sl.Rhs, 1.0, true);
+    record_refine(bt, st.A, bt.sl.Rhs, -1, st.rp, false);
+    launch_park_b(s, P, bt.B, F_SEARCH);
+    record_update(bt, st);
+    if (st.prm.newton) {
+        launch_park_b(s, P, bt.B, F_NEEDD);
+        record_derivative(bt, st);
+    }
+    launch_search_count_b(s, P, st.S, bt.B, st.dcount);
+}
+
+// The rest of the step for the parked clouds.
+void record_rest(Batch &bt, const Step &st)
+{
+    launch_unpark_b(bt.s, bt.d, bt.B, F_SEARCH);
+    record_refine(bt, st.A, bt.sl.Rhs, -1, st.rp, true);
+    record_update(bt, st);
+    if (st.prm.newton) {
+        launch_unpark_b(bt.s, bt.d, bt.B, F_NEEDD);
+        record_refine(bt, st.A, bt.sl.Rhs, SC_AMAX, st.dp, true);
+        record_derivative(bt, st);
+    }
+    launch_search_count_b(bt.s, bt.d, st.S, bt.B, st.dcount);
+}
+
+// Run steps until no cloud is searching (one count read per step, and one more if
+// refinements go on).  captured: as graphs, for searches that repeat the step some
+// thirty times; a fixed-scale batch takes it once, which a capture does not pay for.
 // Returns the number of steps, or a negative error code.
-int run_steps(Batch &bt, const int *dcount, int max_steps)
+int run_steps(Batch &bt, const Step &st, bool captured, int max_steps)
 {
     int *hc = reinterpret_cast<int *>(bt.c->host_scalars + 60);
-    for (int step = 0; step < max_steps; ++step) {
-        BCHK(hipGraphLaunch(bt.graph, bt.s));
-        BCHK(hipMemcpyAsync(hc, dcount, 2 * sizeof(int), hipMemcpyDeviceToHost, bt.s));
+    BRC(bt.flush_persistent());  // work lists and states, in one copy
+    if (captured) BCHK(hipStreamSynchronize(bt.s));
+    const auto part = [&](int which) -> int {
+        if (!captured) {
+            which == 0 ? record_step(bt, st) : record_rest(bt, st);
+        } else {
+            if (!bt.graph[which]) {
+                BCHK(hipStreamBeginCapture(bt.s, hipStreamCaptureModeThreadLocal));
+                which == 0 ? record_step(bt, st) : record_rest(bt, st);
+                if (hipStreamEndCapture(bt.s, &bt.graph_def[which]) != hipSuccess) return MAG_EHIP;
+                BCHK(hipGraphInstantiate(&bt.graph[which], bt.graph_def[which], nullptr, nullptr, 0));
+            }
+            BCHK(hipGraphLaunch(bt.graph[which], bt.s));
+        }
+        BCHK(hipMemcpyAsync(hc, st.dcount, 3 * sizeof(int), hipMemcpyDeviceToHost, bt.s));
         BCHK(hipStreamSynchronize(bt.s));
+        return MAG_OK;
+    };
+    for (int step = 0; step < max_steps; ++step) {
+        BRC(part(0));
         if (hc[1]) return MAG_ENOTPD;  // the FP32 factor broke down at every shift
+        if (hc[2] > 0) BRC(part(1));
         if (hc[0] == 0) return step + 1;
     }
     return MAG_ENOCONV;
@@ -746,30 +799,25 @@ int run_steps(Batch &bt, const int *dcount, int max_steps)
 // returned in dmin2.  One host sync.
 int batch_validate(Batch &bt, std::vector<double> &dmin2)
 {
-    mag_ctx *c = bt.c;
-    int *status = (int *)c->ints.p;
-    launch_fill_ints(bt.s, status, 8, 0);
-    std::vector<int> pl;
-    for (int b = 0; b < bt.B; ++b) {
-        const BProb &q = bt.h[b];
-        launch_check_finite(bt.s, q.X, q.n * (int64_t)bt.m, status);
-        if (q.n >= 2) {
-            launch_dmin2(bt.s, q.X, q.n, bt.m, q.partial, nullptr, q.scal + SC_PICK);
-            pl.push_back(b);
-        }
-    }
-    BCHK(hipMemcpyAsync(c->host_scalars + 56, status, 8 * sizeof(int), hipMemcpyDeviceToHost, bt.s));
+    std::vector<int> all(bt.B);
+    for (int b = 0; b < bt.B; ++b) all[b] = b;
+    BWork w;
+    BRC(bt.make_work(all, [&](int p) { return validate_b_units(bt.h[p].n); }, false, w));
+    launch_validate_b(bt.s, bt.d, bt.B, w);
+    std::vector<double> v;
+    BRC(bt.gather(w.plist, bt.B, SC_PICK, 2, v));
     dmin2.assign(bt.B, INFINITY);
-    if (!pl.empty()) {
-        const int *pd = bt.put(pl, false);
-        if (!pd) return MAG_ENOMEM;
-        std::vector<double> v;
-        BRC(bt.gather(pd, (int)pl.size(), SC_PICK, 1, v));
-        for (size_t i = 0; i < pl.size(); ++i) dmin2[pl[i]] = v[i];
-    } else {
-        BRC(bt.sync());
+    bool finite = true;
+    for (int b = 0; b < bt.B; ++b) {
+        uint64_t bits;
+        std::memcpy(&bits, &v[2 * b], sizeof bits);
+        if (bits != 0) {
+            bits = ~bits;
+            std::memcpy(&dmin2[b], &bits, sizeof bits);
+        }
+        finite = finite && v[2 * b + 1] == 0.0;
     }
-    if (((const int *)(c->host_scalars + 56))[kStNonFinite]) return MAG_EINVAL;
+    if (!finite) return MAG_EINVAL;
     for (int b = 0; b < bt.B; ++b)
         if (!(dmin2[b] > 0.0)) return MAG_ENOTPD;
     return MAG_OK;
@@ -819,18 +867,15 @@ int mag_weighting_batch(mag_ctx *c, int32_t B, const double *X, const int64_t *o
     // one fixed-scale solve per problem, retried with a shift after an FP32 breakdown
     std::vector<SState> st0(B);
     std::memset(st0.data(), 0, sizeof(SState) * B);
-    SState *Sd = bt.put(st0, true);
+    Step step;
+    SState *Sd = step.S = bt.put(st0, true);
     if (!Sd) return MAG_ENOMEM;
-    std::vector<FLaunch> fseq;
-    BRC(batch_factor_schedule(bt, fseq));
-    AllWork A;
-    BRC(make_all_work(bt, A));
-    SParams prm{};
-    prm.fixed = 1;
-    int *dcount = reinterpret_cast<int *>(bt.dstage + (size_t)B * 128);
-    const RefPlan rp = main_plan(o, restart);
-    BRC(build_step_graph(bt, fseq, A, Sd, prm, rp, rp, dcount));
-    const int steps = run_steps(bt, dcount, 8);
+    BRC(batch_factor_schedule(bt, step.fseq));
+    BRC(make_all_work(bt, step.A));
+    step.prm.fixed = 1;
+    step.dcount = reinterpret_cast<int *>(bt.dstage + (size_t)B * 128);
+    step.rp = step.dp = main_plan(o, restart);
+    const int steps = run_steps(bt, step, false, 8);
     if (steps < 0) return steps;
     std::vector<SState> st(B);
     BCHK(hipMemcpyAsync(st.data(), Sd, sizeof(SState) * B, hipMemcpyDeviceToHost, bt.s));
@@ -1017,13 +1062,12 @@ int mag_tplus_batch(mag_ctx *c, int32_t B, const double *X, const int64_t *offs,
         q.gi = to.grid - 1;
         q.prev_step = INFINITY;
     }
-    SState *Sd = bt.put(st0, true);
+    Step step;
+    SState *Sd = step.S = bt.put(st0, true);
     if (!Sd) return MAG_ENOMEM;
-    std::vector<FLaunch> fseq;
-    BRC(batch_factor_schedule(bt, fseq));
-    AllWork A;
-    BRC(make_all_work(bt, A));
-    SParams prm{};
+    BRC(batch_factor_schedule(bt, step.fseq));
+    BRC(make_all_work(bt, step.A));
+    SParams &prm = step.prm;
     prm.grid = to.grid;
     prm.max_extend = to.max_extend;
     prm.newton = (to.newton && !ridders) ? 1 : 0;
@@ -1031,13 +1075,12 @@ int mag_tplus_batch(mag_ctx *c, int32_t B, const double *X, const int64_t *offs,
     prm.fixed = 0;
     prm.lo_factor = to.lo_factor;
     prm.rtol = to.rtol;
-    int *dcount = reinterpret_cast<int *>(bt.dstage + (size_t)B * 128);
-    const RefPlan rp = main_plan(o, restart);
-    RefPlan dp = rp;  // the Newton derivative: a shorter refinement suffices for a safeguarded step
-    dp.rounds = std::min(rp.rounds, 2);
-    dp.kcycle = std::min(rp.kcycle, 8);
-    BRC(build_step_graph(bt, fseq, A, Sd, prm, rp, dp, dcount));
-    const int steps = run_steps(bt, dcount, 1000);
+    step.dcount = reinterpret_cast<int *>(bt.dstage + (size_t)B * 128);
+    step.rp = step.dp = main_plan(o, restart);
+    // the Newton derivative: a shorter refinement suffices for a safeguarded step
+    step.dp.rounds = std::min(step.rp.rounds, 2);
+    step.dp.kcycle = std::min(step.rp.kcycle, 8);
+    const int steps = run_steps(bt, step, true, 1000);
     if (steps < 0) return steps;
     std::vector<SState> st(B);
     BCHK(hipMemcpyAsync(st.data(), Sd, sizeof(SState) * B, hipMemcpyDeviceToHost, bt.s));

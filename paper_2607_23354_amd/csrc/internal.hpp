@@ -101,6 +101,7 @@ enum : int { RC_RNORM = 0, RC_BEST, RC_PREV, RC_TOL, RC_BETA, RC_INNER, RC_KDONE
 // preconditioner counters sit below it).
 constexpr int kIntsPer = 2048;
 constexpr int kIntFlags = kIntsPer - 8;
+constexpr int kIntParked = kIntsPer - 7;  // the control word of a refinement left for the step's second part
 enum : int {
     F_SEARCH = 1 << 0,     // solved in this step
     F_REF = 1 << 1,        // refinement still running
@@ -272,8 +273,11 @@ void launch_search_select_b(hipStream_t s, BProb *P, SState *S, int B, SParams p
 void launch_breakdown_b(hipStream_t s, BProb *P, SState *S, int B);
 void launch_search_update_b(hipStream_t s, BProb *P, SState *S, int B, SParams prm);
 void launch_search_deriv_b(hipStream_t s, BProb *P, SState *S, int B);
-// out[0] = clouds still searching, out[1] = any error
-void launch_search_count_b(hipStream_t s, const SState *S, int B, int *out);
+// put aside / take up again the refinements of a phase (F_SEARCH or F_NEEDD) that go on
+void launch_park_b(hipStream_t s, BProb *P, int B, int phase);
+void launch_unpark_b(hipStream_t s, BProb *P, int B, int phase);
+// out[0] = clouds still searching, out[1] = any error, out[2] = refinements parked
+void launch_search_count_b(hipStream_t s, const BProb *P, const SState *S, int B, int *out);
 void launch_unpack_b(hipStream_t s, const BProb *P, const int *plist, int na, const int64_t *offs, int slot,
                      double *out, int64_t maxn);
 
@@ -378,6 +382,10 @@ void launch_tilegen64p(hipStream_t s, const double *X, int64_t n, int m, double 
 // Writes min squared distance partials; returns number of partials in *np.
 void launch_dmin2(hipStream_t s, const double *X, int64_t n, int m, double *partial,
                   int64_t *np, double *out_min2);
+// batched: per problem scal[SC_PICK] = ~bits of the smallest d^2 (0: no pair), [SC_PICK + 1] =
+// 1 if a coordinate is not finite; scal and the status words zero beforehand
+int64_t validate_b_units(int64_t n);
+void launch_validate_b(hipStream_t s, const BProb *P, int B, const BWork &w);
 void launch_check_finite(hipStream_t s, const double *X, int64_t count, int *status);
 
 // C - P Q^T into C, or P Q^T into C with its transpose (the GEMM kernels' modes)

@@ -195,20 +195,21 @@ k_tilegen64p(const double *__restrict__ X, int64_t n, int m, double t, double *_
     }
 }
 
-// Per-block minimum of d_jk^2 over j > k inside the block.
-__global__ void __launch_bounds__(kThreads)
-k_dmin2_partial(const double *__restrict__ X, int64_t n, int m, double *__restrict__ partial)
+// Minimum of d_jk^2 over j > k inside the block blk (in thread 0).  bad: as in stage, from
+// the blocks of the first columns.
+__device__ __forceinline__ double dmin2_block(const double *__restrict__ X, int64_t n, int m, int64_t blk,
+                                              int *bad = nullptr)
 {
     __shared__ double Sr[kLC * kRows];
     __shared__ double Sc[kLC * kCols];
     __shared__ double red[kThreads];
     int64_t I, Jc;
-    lower_block(blockIdx.x, I, Jc);
+    lower_block(blk, I, Jc);
     const int64_t row0 = I * kRows, col0 = Jc * kCols;
     double best = INFINITY;
     if (col0 < n) {  // uniform per block
         double s[kPerThread];
-        block_sqdist(s, X, n, m, row0, col0, Sr, Sc);
+        block_sqdist(s, X, n, m, row0, col0, Sr, Sc, Jc == 0 ? bad : nullptr);
         const int r = threadIdx.x & (kRows - 1);
         const int h = threadIdx.x >> 7;
         const int64_t j = row0 + r;
@@ -224,7 +225,35 @@ k_dmin2_partial(const double *__restrict__ X, int64_t n, int m, double *__restri
         if (threadIdx.x < w) red[threadIdx.x] = fmin(red[threadIdx.x], red[threadIdx.x + w]);
         __syncthreads();
     }
-    if (threadIdx.x == 0) partial[blockIdx.x] = red[0];
+    return red[0];
+}
+
+__global__ void __launch_bounds__(kThreads)
+k_dmin2_partial(const double *__restrict__ X, int64_t n, int m, double *__restrict__ partial)
+{
+    const double d = dmin2_block(X, n, m, blockIdx.x);
+    if (threadIdx.x == 0) partial[blockIdx.x] = d;
+}
+
+// Batched, one launch for all problems: the complement of the smallest d^2's bits by
+// an atomic maximum into scal[SC_PICK] (0 beforehand, and where there is no pair), and
+// the non-finite flag in the status words.
+__global__ void __launch_bounds__(kThreads)
+k_validate_b(const BProb *__restrict__ P, BWork w)
+{
+    const int i = bfind(w.pref, w.na, blockIdx.x);
+    const BProb &q = P[w.plist[i]];
+    const double d = dmin2_block(q.X, q.n, q.m, blockIdx.x - w.pref[i], q.ints);
+    if (threadIdx.x == 0 && d < INFINITY)
+        atomicMax(reinterpret_cast<unsigned long long *>(q.scal + SC_PICK),
+                  ~(unsigned long long)__double_as_longlong(d));
+}
+
+// the flag beside the distance: scal[SC_PICK + 1]
+__global__ void k_validate_done_b(const BProb *__restrict__ P, int B)
+{
+    const int b = blockIdx.x * blockDim.x + threadIdx.x;
+    if (b < B) P[b].scal[SC_PICK + 1] = P[b].ints[kStNonFinite] ? 1.0 : 0.0;
 }
 
 __global__ void __launch_bounds__(256)
@@ -299,6 +328,14 @@ void launch_dmin2(hipStream_t s, const double *X, int64_t n, int m, double *part
     hipLaunchKernelGGL(k_dmin2_partial, dim3((unsigned)nb), dim3(kThreads), 0, s, X, n, m, partial);
     hipLaunchKernelGGL(k_min_reduce, dim3(1), dim3(256), 0, s, partial, nb, out_min2);
     if (np) *np = nb;
+}
+
+int64_t validate_b_units(int64_t n) { return lower_blocks(n); }
+
+void launch_validate_b(hipStream_t s, const BProb *P, int B, const BWork &w)
+{
+    hipLaunchKernelGGL(k_validate_b, dim3((unsigned)w.total), dim3(kThreads), 0, s, P, w);
+    hipLaunchKernelGGL(k_validate_done_b, dim3((unsigned)((B + 63) / 64)), dim3(64), 0, s, P, B);
 }
 
 void launch_check_finite(hipStream_t s, const double *X, int64_t count, int *status)
