@@ -33,7 +33,7 @@ size_t ctx_held_bytes(const mag_ctx *c)
     size_t sum = 0;
     for (const DevBuf *b : {&c->factor, &c->dinv, &c->vecs, &c->partial, &c->ints, &c->aux, &c->bfactor,
                             &c->bdinv, &c->bvec, &c->bscal, &c->bpartial, &c->bints, &c->bdesc, &c->barena,
-                            &c->bstage, &c->hodlr, &c->eig, &c->hss, &c->split})
+                            &c->bstage, &c->hodlr, &c->eig, &c->hss, &c->split, &c->bpanel})
         sum += b->bytes;
     return sum;
 }
@@ -47,19 +47,20 @@ static void release(mag_ctx *ctx, DevBuf &b)
     b.bytes = 0;
 }
 
-// Give up the split image (the factor runs without it), so that it never takes
-// room from a buffer a call cannot do without.
-static bool drop_split(mag_ctx *ctx)
+// Give up what the factors run without (the split image, the batched panels'
+// exchanges), so that it never takes room from a buffer a call cannot do without.
+static bool drop_optional(mag_ctx *ctx)
 {
-    if (!ctx->split.p) return false;
+    if (!ctx->split.p && !ctx->bpanel.p) return false;
     release(ctx, ctx->split);
+    release(ctx, ctx->bpanel);
     return true;
 }
 
 int ctx_may_allocate(mag_ctx *c, size_t extra)
 {
     if (c->ws_limit == 0) return MAG_OK;
-    if (ctx_held_bytes(c) + extra > c->ws_limit) drop_split(c);
+    if (ctx_held_bytes(c) + extra > c->ws_limit) drop_optional(c);
     return ctx_held_bytes(c) + extra <= c->ws_limit ? MAG_OK : MAG_ENOMEM;
 }
 
@@ -68,7 +69,8 @@ int ensure(mag_ctx *ctx, DevBuf &b, size_t bytes)
     if (bytes <= b.bytes) return MAG_OK;
     // the cap counts the buffer at its new size in place of its old one
     const auto over = [&] { return ctx->ws_limit && ctx_held_bytes(ctx) - b.bytes + bytes > ctx->ws_limit; };
-    if (over() && (&b == &ctx->split || !drop_split(ctx) || over())) return MAG_ENOMEM;
+    const bool optional = &b == &ctx->split || &b == &ctx->bpanel;
+    if (over() && (optional || !drop_optional(ctx) || over())) return MAG_ENOMEM;
     if (b.p) {
         if (hipStreamSynchronize(ctx->stream) != hipSuccess) return MAG_EHIP;
         hipFree(b.p);
@@ -76,7 +78,7 @@ int ensure(mag_ctx *ctx, DevBuf &b, size_t bytes)
         b.bytes = 0;
     }
     hipError_t e = hipMalloc(&b.p, bytes);
-    if (e != hipSuccess && &b != &ctx->split && drop_split(ctx)) {
+    if (e != hipSuccess && !optional && drop_optional(ctx)) {
         (void)hipGetLastError();
         e = hipMalloc(&b.p, bytes);
     }
@@ -1426,7 +1428,7 @@ void mag_destroy(mag_ctx *c)
     if (c->stream) hipStreamSynchronize(c->stream);
     for (DevBuf *b : {&c->factor, &c->dinv, &c->vecs, &c->partial, &c->ints, &c->aux, &c->bfactor,
                       &c->bdinv, &c->bvec, &c->bscal, &c->bpartial, &c->bints, &c->bdesc, &c->barena,
-                      &c->bstage, &c->hodlr, &c->eig, &c->hss, &c->split})
+                      &c->bstage, &c->hodlr, &c->eig, &c->hss, &c->split, &c->bpanel})
         if (b->p) hipFree(b->p);
     if (c->panel) hipFree(c->panel);
     if (c->bhost) hipHostFree(c->bhost);

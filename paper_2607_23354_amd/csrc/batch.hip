@@ -231,6 +231,10 @@ int batch_setup(mag_ctx *c, Batch &bt, const std::vector<const double *> &Xs,
     size_t img = 0;
     for (int b = 0; b < B; ++b) img += image(np[b]);
     const bool split = img > 0 && ensure(c, c->split, img) == MAG_OK;
+    // and the panel kernel's exchanges, likewise
+    const bool fresh = c->bpanel.bytes < panel_work_bytes() * B;
+    const bool panels = ensure(c, c->bpanel, panel_work_bytes() * B) == MAG_OK;
+    if (panels && fresh) BCHK(hipMemsetAsync(c->bpanel.p, 0, c->bpanel.bytes, bt.s));  // the tickets, once
     char *ip = (char *)c->split.p;
     float *fp = (float *)c->bfactor.p;
     float *dp = (float *)c->bdinv.p;
@@ -257,6 +261,7 @@ int batch_setup(mag_ctx *c, Batch &bt, const std::vector<const double *> &Xs,
         q.active = 1;
         q.img = split ? ip : nullptr;
         ip += image(np[b]);
+        q.panel = panels ? (char *)c->bpanel.p + panel_work_bytes() * b : nullptr;
     }
     BCHK(hipMemsetAsync(c->bvec.p, 0, sizeof(double) * vec, bt.s));
     BCHK(hipMemsetAsync(c->bscal.p, 0, sizeof(double) * (size_t)B * SC_COUNT, bt.s));
@@ -271,7 +276,8 @@ int batch_setup(mag_ctx *c, Batch &bt, const std::vector<const double *> &Xs,
 // whose descriptor is inactive.
 struct FLaunch {
     // 0 trsm, 1 subupdate, 2 syrk (pair), 3 potrf, 4 tilegen, 5 zero status, 6 strip, 7 syrk
-    // (single); on the split image: 8 split, 9 syrk
+    // (single); on the split image: 8 split, 9 syrk; with an exchange: 10 its begin, 11 a panel
+    // of 512 columns
     int kind;
     int64_t kk;
     BWork w;
@@ -335,6 +341,17 @@ int batch_factor_schedule(Batch &bt, std::vector<FLaunch> &seq, int group = 0)
         }
         return MAG_OK;
     }
+    if (bt.h[0].panel) {
+        // panels of 2 kPanel columns in one launch each, then the trailing update
+        seq.push_back({10, 0, wall});
+        for (int64_t k = 0; k < bt.maxpad; k += 2 * kPanel) {
+            BWork w;
+            BRC(bt.make_work(all, [&](int p) { return panel_b_units(bt.h[p].npad, k); }, true, w));
+            seq.push_back({11, k, w});
+            BRC(schedule_trailing(bt, seq, all, k, 2 * kPanel));
+        }
+        return MAG_OK;
+    }
     // panels of kPanel columns in pairs: first panel, strip update of the second
     // panel by the first, second panel, then one trailing update by both
     for (int64_t k = 0; k < bt.maxpad; k += 2 * kPanel) {
@@ -376,6 +393,8 @@ void record_factor(Batch &bt, const std::vector<FLaunch> &seq)
         case 7: launch_gemm_b(bt.s, 4, bt.d, L.w, L.kk); break;
         case 8: launch_split_b(bt.s, bt.d, L.w, L.kk, L.K); break;
         case 9: launch_syrk_split_b(bt.s, bt.d, L.w, L.kk, L.K, L.tm); break;
+        case 10: launch_panel_begin_b(bt.s, bt.d, bt.B); break;
+        case 11: launch_panel_b(bt.s, bt.d, L.w, L.kk); break;
         default: launch_gemm_b(bt.s, L.kind, bt.d, L.w, L.kk); break;
         }
     }

@@ -68,6 +68,7 @@ struct BProb {
     int32_t m;
     int32_t active;   // 0: skip (finished)
     void *img;        // BF16 split image of a panel pair (NULL: FP32 trailing updates)
+    void *panel;      // exchange of the panel kernel (NULL: 128 columns at a time)
 };
 
 struct BWork {
@@ -299,6 +300,7 @@ struct mag_ctx {
     mag::DevBuf eig;       // Lanczos bases of the eigenvalue estimator
     mag::DevBuf hss;       // HSS approximation and ULV factor
     mag::DevBuf split;     // BF16 split image of a panel (optional: given up when memory runs short)
+    mag::DevBuf bpanel;    // exchanges of the batched panel kernel (optional likewise)
     void *panel = nullptr;   // exchange of the FP32 factor's panel kernel (panel_work_bytes)
     void *bhost = nullptr;   // pinned host staging for work lists and descriptors
     size_t bhost_bytes = 0;
@@ -433,6 +435,10 @@ size_t panel_work_bytes();
 void launch_panel_begin(hipStream_t s, void *work);
 void launch_panel(hipStream_t s, float *A, int64_t ld, int64_t k, int64_t nb, int64_t n, float *dinv, int *status,
                   void *work, int index);
+// batched: the panel of (up to) 512 columns at k of every active problem (BProb::panel)
+int64_t panel_b_units(int64_t npad, int64_t k);
+void launch_panel_begin_b(hipStream_t s, const BProb *P, int B);
+void launch_panel_b(hipStream_t s, const BProb *P, const BWork &w, int64_t k);
 
 // gemv64.hip: FP64 matrix-free products with Z regenerated from X.
 //   mode 0: y = Z v;  mode 1: y = b - Z v (b may be NULL meaning ones) and

@@ -665,8 +665,8 @@ __device__ __forceinline__ bool panel_step(const PanelArgs &a, PanelShared &sh, 
     return false;
 }
 
-__global__ void __launch_bounds__(NTP)
-k_panel(PanelArgs a)
+// blk, count: this workgroup's index among the panel's
+__device__ __forceinline__ void panel_body(const PanelArgs &a, int blk, int count)
 {
     __shared__ PanelShared sh;
     const int lane = threadIdx.x & 63, I = row_block();
@@ -674,11 +674,11 @@ k_panel(PanelArgs a)
     // line per thread and tile
     float warm = 0.0f;
     for (int t = 0; t < a.nsub; ++t)
-        warm += a.A[(a.k + NB * t + (threadIdx.x >> 2)) * a.ld + a.k + NB * (int64_t)blockIdx.x + 32 * (threadIdx.x & 3)];
+        warm += a.A[(a.k + NB * t + (threadIdx.x >> 2)) * a.ld + a.k + NB * (int64_t)blk + 32 * (threadIdx.x & 3)];
     if (threadIdx.x == 0) {
         // tickets: a workgroup waits only for earlier ones, which are running
         sh.ib = atomicAdd(a.ticket, 1);
-        if (sh.ib == (int)gridDim.x - 1) *a.ticket = 0;
+        if (sh.ib == count - 1) *a.ticket = 0;
         sh.bad = 0;
     }
     __syncthreads();
@@ -729,33 +729,17 @@ k_panel(PanelArgs a)
     }
 }
 
-__global__ void __launch_bounds__(256)
-k_unset(v4u *__restrict__ x)
+__global__ void __launch_bounds__(NTP)
+k_panel(PanelArgs a)
 {
-    v4u u;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) u[r] = kUnset;
-    x[blockIdx.x * 256 + threadIdx.x] = u;
-}
-
-}  // namespace
-
-void launch_potrf128_b(hipStream_t s, const BProb *P, const BWork &w, int64_t k0)
-{
-    if (w.na > 0) hipLaunchKernelGGL(k_potrf128_b, dim3(w.na), dim3(NTP), 0, s, P, w, k0);
+    panel_body(a, blockIdx.x, gridDim.x);
 }
 
 constexpr size_t kExchangeBytes = (size_t)kPanelBlocks * kBlockWords * 8;
 static_assert(kExchangeBytes % 4096 == 0, "whole workgroups of k_unset");
-size_t panel_work_bytes() { return 2 * kExchangeBytes + 64; }
 
-void launch_panel_begin(hipStream_t s, void *work)
-{
-    hipLaunchKernelGGL(k_unset, dim3(kExchangeBytes / 4096), dim3(256), 0, s, (v4u *)work);
-}
-
-void launch_panel(hipStream_t s, float *A, int64_t ld, int64_t k, int64_t nb, int64_t n, float *dinv, int *status,
-                  void *work, int index)
+__device__ __host__ inline PanelArgs panel_args(float *A, int64_t ld, int64_t k, int64_t nb, int64_t n, float *dinv,
+                                                int *status, void *work, int index)
 {
     char *w = (char *)work;
     PanelArgs a;
@@ -770,7 +754,76 @@ void launch_panel(hipStream_t s, float *A, int64_t ld, int64_t k, int64_t nb, in
     a.xch = (uint64_t *)(w + (index & 1) * kExchangeBytes);
     a.xnext = (uint64_t *)(w + (~index & 1) * kExchangeBytes);
     a.spin_limit = kPanelSpinLimit;
-    hipLaunchKernelGGL(k_panel, dim3((unsigned)((ld - k) / NB)), dim3(NTP), 0, s, a);
+    return a;
+}
+
+// Batched: the panel at k of every active problem, each with its own exchange and tickets;
+// a problem's workgroups are consecutive, so its first ones, which the others wait
+// for, are dispatched first.
+__global__ void __launch_bounds__(NTP)
+k_panel_b(const BProb *__restrict__ P, BWork w, int64_t k)
+{
+    const int i = bfind(w.pref, w.na, blockIdx.x);
+    const BProb &q = P[w.plist[i]];
+    if (!q.active) return;
+    const int64_t left = q.npad - k;
+    panel_body(panel_args(q.A, q.npad, k, left < NB * MT ? left : NB * MT, q.n, q.dinv, q.ints, q.panel,
+                          (int)(k / (NB * MT))),
+               (int)(blockIdx.x - w.pref[i]), (int)(left / NB));
+}
+
+__device__ __forceinline__ void unset(v4u *x, int64_t i)
+{
+    v4u u;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) u[r] = kUnset;
+    x[i] = u;
+}
+
+__global__ void __launch_bounds__(256)
+k_unset(v4u *__restrict__ x)
+{
+    unset(x, blockIdx.x * 256 + threadIdx.x);
+}
+
+__global__ void __launch_bounds__(256)
+k_unset_b(const BProb *__restrict__ P)
+{
+    const BProb &q = P[blockIdx.y];
+    if (q.active) unset((v4u *)q.panel, blockIdx.x * 256 + threadIdx.x);
+}
+
+}  // namespace
+
+void launch_potrf128_b(hipStream_t s, const BProb *P, const BWork &w, int64_t k0)
+{
+    if (w.na > 0) hipLaunchKernelGGL(k_potrf128_b, dim3(w.na), dim3(NTP), 0, s, P, w, k0);
+}
+
+size_t panel_work_bytes() { return 2 * kExchangeBytes + 64; }
+
+void launch_panel_begin(hipStream_t s, void *work)
+{
+    hipLaunchKernelGGL(k_unset, dim3(kExchangeBytes / 4096), dim3(256), 0, s, (v4u *)work);
+}
+
+void launch_panel(hipStream_t s, float *A, int64_t ld, int64_t k, int64_t nb, int64_t n, float *dinv, int *status,
+                  void *work, int index)
+{
+    hipLaunchKernelGGL(k_panel, dim3((unsigned)((ld - k) / NB)), dim3(NTP), 0, s,
+                       panel_args(A, ld, k, nb, n, dinv, status, work, index));
+}
+
+int64_t panel_b_units(int64_t npad, int64_t k) { return k < npad ? (npad - k) / NB : 0; }
+
+void launch_panel_begin_b(hipStream_t s, const BProb *P, int B)
+{
+    hipLaunchKernelGGL(k_unset_b, dim3(kExchangeBytes / 4096, (unsigned)B), dim3(256), 0, s, P);
+}
+
+void launch_panel_b(hipStream_t s, const BProb *P, const BWork &w, int64_t k)
+{
+    if (w.total > 0) hipLaunchKernelGGL(k_panel_b, dim3((unsigned)w.total), dim3(NTP), 0, s, P, w, k);
 }
 
 }  // namespace mag

@@ -66,3 +66,23 @@ def test_validation(mag, n):
         assert e.value.code == -2
         info = mag.tplus_batch(dev(Xp), offs)[2]
         assert info[1]["d_min"] == mag.dmin(dev(clouds[1]))
+
+
+@pytest.mark.parametrize("sizes", [(1, 256, 257, 511), (512, 513, 100, 769), (1300, 1025, 640)])
+def test_panels_and_the_path_without_room_for_them(mag, sizes):
+    clouds = [W.gaussian(n, 3, seed=n) for n in sizes]
+    Xp, offs = W.pack_clouds(clouds)
+    ts = [W.gaussian_cutoff_estimate(max(n, 2), 3) for n in sizes]
+    out = []
+    free, capped = mag.Context(0), mag.Context(0)
+    for _ in range(2):  # the second call finds the exchanges as the first left them
+        out.append(mag.weighting_batch(dev(Xp), offs, ts, ctx=free)[0].cpu().numpy())
+    capped.set_workspace_limit(free.workspace_bytes() - 1)  # the panels' exchanges come last
+    out.append(mag.weighting_batch(dev(Xp), offs, ts, ctx=capped)[0].cpu().numpy())
+    assert capped.workspace_bytes() < free.workspace_bytes()
+    assert np.array_equal(out[0], out[1])
+    for w in out:
+        for b, (X, t) in enumerate(zip(clouds, ts)):
+            assert np.abs(oracle.residual(X, t, w[offs[b]:offs[b + 1]])).max() <= 1.1e-12
+    free.close()
+    capped.close()
