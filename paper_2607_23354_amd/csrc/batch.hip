@@ -282,7 +282,6 @@ struct FLaunch {
     int64_t kk;
     BWork w;
     int64_t K = 0;
-    int tm = 0;
 };
 
 // The trailing update after the K columns at k.
@@ -296,13 +295,10 @@ int schedule_trailing(Batch &bt, std::vector<FLaunch> &seq, const std::vector<in
         seq.push_back({K == 2 * kPanel ? 2 : 7, k, w});
         return MAG_OK;
     }
-    int64_t tiles = 0;
-    for (int p : all) tiles += syrk_split_b_units(rows(p), 256);
-    const int tm = syrk_split_tile(tiles);
     BRC(bt.make_work(all, [&](int p) { return split_b_units(rows(p), K); }, true, w));
     seq.push_back({8, k, w, K});
-    BRC(bt.make_work(all, [&](int p) { return syrk_split_b_units(rows(p), tm); }, true, w));
-    seq.push_back({9, k, w, K, tm});
+    BRC(bt.make_work(all, [&](int p) { return syrk_split_b_units(rows(p)); }, true, w));
+    seq.push_back({9, k, w, K});
     return MAG_OK;
 }
 
@@ -403,7 +399,7 @@ void record_factor(Batch &bt, const std::vector<FLaunch> &seq)
         case 6: launch_gemm_b(bt.s, 3, bt.d, L.w, L.kk); break;
         case 7: launch_gemm_b(bt.s, 4, bt.d, L.w, L.kk); break;
         case 8: launch_split_b(bt.s, bt.d, L.w, L.kk, L.K); break;
-        case 9: launch_syrk_split_b(bt.s, bt.d, L.w, L.kk, L.K, L.tm); break;
+        case 9: launch_syrk_split_b(bt.s, bt.d, L.w, L.kk, L.K); break;
         case 12: launch_near_q_b(bt.s, bt.d, L.w); break;
         case 10: launch_panel_begin_b(bt.s, bt.d, bt.B); break;
         case 11: launch_panel_b(bt.s, bt.d, L.w, L.kk); break;

@@ -214,10 +214,9 @@ int64_t gemm_b_units(int kind, int64_t npad, int64_t kk);
 void launch_gemm_b(hipStream_t s, int kind, const BProb *P, const BWork &w, int64_t kk);
 // gemm_split.hip: the trailing updates on the BF16 matrix cores
 int64_t split_b_units(int64_t rows, int64_t K);
-int64_t syrk_split_b_units(int64_t rows, int tm);
-int syrk_split_tile(int64_t tiles256);
+int64_t syrk_split_b_units(int64_t rows);
 void launch_split_b(hipStream_t s, const BProb *P, const BWork &w, int64_t kk, int64_t K);
-void launch_syrk_split_b(hipStream_t s, const BProb *P, const BWork &w, int64_t kk, int64_t K, int tm);
+void launch_syrk_split_b(hipStream_t s, const BProb *P, const BWork &w, int64_t kk, int64_t K);
 // the factor's near tiles in place (after it, before the first prec_apply_b)
 int64_t near_q_b_units(int64_t npad);
 void launch_near_q_b(hipStream_t s, const BProb *P, const BWork &w);

@@ -28,8 +28,8 @@ def backward_error(mag, X, t, ctx):
     return float(E.norm() / Z.norm()), float(E.abs().max())
 
 
-# trailing rows 256, 512, 768 (one and two super-tiles of 128-row tiles, the odd
-# half), 4864 (the last size on them), 5120 and 5632 (256-row tiles); panels of
+# trailing rows 256, 512, 768 (one and two super-tiles, the odd
+# half), 4864, 5120 and 5632 (ten and eleven); panels of
 # 512 (K = 1024) and 256 columns (K = 512)
 @pytest.mark.parametrize("n,nb", [(1280, 512), (1281, 512), (1790, 512), (5888, 512), (6144, 512), (6500, 512),
                                   (700, 256), (2049, 256)])
