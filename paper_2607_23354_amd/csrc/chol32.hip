@@ -9,8 +9,9 @@
 // brings the second one's columns up to date; after the second, one trailing
 // update A22 -= L21 L21^T of both panels (K = 2 nb, lower tiles only) applies the
 // pair to the rest.  A deep K amortises the load and store of each C tile over more
-// matrix work; the strip runs on 64-row tiles (twice the workgroups of 128-row
-// ones, which keeps more CUs busy in the late panels).  The inverses of the diagonal
+// matrix work.  Both run on the BF16 split image of the panels (gemm_split.hip), late
+// strips on the FP32 instruction in 64-row tiles (twice the workgroups of 128-row
+// ones, which keeps more CUs busy).  The inverses of the diagonal
 // 128-blocks are kept (dinv) for the preconditioner's triangular solves.
 #include "internal.hpp"
 
@@ -18,6 +19,11 @@
 #include <vector>
 
 namespace mag {
+
+// Rows above which the strip takes the split image, whose first half is then formed before
+// it (5 us more in launches): up to 4096 rows the FP32 strip is one round of 64-row tiles,
+// 23 us against 24-26 us on the image; above, 38 against 25 us at 4608 rows, 42 against 31 at 7680.
+constexpr int64_t kSplitStrip = 4096;
 
 // Factor the padded npad x npad FP32 matrix A (column-major, ld = npad) in place.
 // timer (optional) records an event pair around every trailing update.
@@ -39,12 +45,19 @@ void chol32_factor(hipStream_t s, float *A, int64_t npad, int64_t n, float *dinv
         const int64_t k2 = k + nb;
         if (k2 >= npad) break;
         const int64_t nb2 = std::min<int64_t>(kNb, npad - k2);
+        const int64_t below = npad - k2;
+        const bool split = img && below > kSplitStrip;
         {
             // strip: panel p+1's columns (all rows from k2) by panel p; the tiles above
             // the 128-diagonal of its diagonal block are rewritten by its own panel launch
             float *C = A + k2 * npad + k2;
             const float *P = A + k * npad + k2;
-            launch_gemm_rows64(s, C, npad, P, npad, P, npad, npad - k2, nb2, nb);
+            if (split) {
+                launch_split(s, P, npad, below, nb, img, below, 0, 0);
+                launch_strip_split(s, C, npad, img, below, nb2, nb);
+            } else {
+                launch_gemm_rows64(s, C, npad, P, npad, P, npad, below, nb2, nb);
+            }
         }
         launch_panel(s, A, npad, k2, nb2, n, dinv, status, work, panels++);
         const int64_t k3 = k2 + nb2;
@@ -69,9 +82,12 @@ void chol32_factor(hipStream_t s, float *A, int64_t npad, int64_t n, float *dinv
                 timer->flops.push_back(nt > 0 ? (double)K * (double)nt * (double)(nt + 1) : 0.0);
                 hipEventRecord(e0, s);
             }
-            if (img) {
-                launch_split(s, P, npad, trail, K, img);
-                launch_syrk_split(s, C, npad, img, trail, K);
+            if (split) {
+                launch_split(s, P + nb * npad, npad, trail, nb2, img, below, nb2, nb);
+                launch_syrk_split(s, C, npad, img, below, nb2, trail, K);
+            } else if (img) {
+                launch_split(s, P, npad, trail, K, img, trail, 0, 0);
+                launch_syrk_split(s, C, npad, img, trail, 0, trail, K);
             } else {
                 launch_syrk_lower(s, C, npad, P, npad, trail, K);
             }
@@ -83,8 +99,8 @@ void chol32_factor(hipStream_t s, float *A, int64_t npad, int64_t n, float *dinv
 
 size_t chol32_image_bytes(int64_t npad, int nb)
 {
-    const int64_t K = 2 * ((nb == 256) ? 256 : 512);
-    return npad > K ? split_image_bytes(npad - K, K) : 0;
+    const int64_t w = (nb == 256) ? 256 : 512;
+    return npad > 2 * w ? split_image_bytes(npad - w, 2 * w) : 0;
 }
 
 int size_bucket(int64_t npad)

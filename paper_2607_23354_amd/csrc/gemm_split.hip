@@ -231,6 +231,19 @@ k_syrk_split(float *__restrict__ C, int64_t ldc, const v8bf *__restrict__ img, i
     split_tile_body(C, ldc, img, stride, i0, j0, rows, K);
 }
 
+// The first tilesN columns of tiles of C alone (lower tiles): the strip of a panel pair.  The
+// tiles of a row share its operand, so they go to one XCD.
+__global__ void __launch_bounds__(NT, 2)
+k_strip_split(float *__restrict__ C, int64_t ldc, const v8bf *__restrict__ img, int64_t stride, int64_t rows, int64_t K,
+              int tilesN)
+{
+    const int64_t b = blockIdx.x;
+    const int64_t xcd = b % kXcds, slot = b / kXcds;
+    const int64_t i0 = ((slot / tilesN) * kXcds + xcd) * TM, j0 = (slot % tilesN) * TM;
+    if (i0 >= rows || j0 > i0) return;
+    split_tile_body(C, ldc, img, stride, i0, j0, rows, K);
+}
+
 // Batched: the trailing rows of every active problem after the K columns at kk.
 // Units of the split: (rows / 256) x (K / 8); of the update, tiles by rows of
 // tiles.
@@ -260,11 +273,13 @@ k_syrk_split_b(const BProb *__restrict__ Pr, BWork w, int64_t kk, int64_t K)
 
 size_t split_image_bytes(int64_t rows, int64_t K) { return (size_t)round_up(rows, 256) * (size_t)(K / 8) * NS * 16; }
 
-void launch_split(hipStream_t s, const float *P, int64_t ldp, int64_t rows, int64_t K, void *img)
+void launch_split(hipStream_t s, const float *P, int64_t ldp, int64_t rows, int64_t K, void *img, int64_t img_rows,
+                  int64_t row0, int64_t col0)
 {
     if (rows <= 0 || K <= 0) return;
+    const int64_t stride = round_up(img_rows, 256);
     hipLaunchKernelGGL(k_split, dim3((unsigned)((rows + NT - 1) / NT), (unsigned)(K / 8)), dim3(NT), 0, s, P, ldp, rows,
-                       (v8bf *)img, round_up(rows, 256));
+                       (v8bf *)img + (col0 / 8) * NS * stride + row0, stride);
 }
 
 // Units of one problem of the batched split and update (rows: a multiple of 256).
@@ -285,14 +300,24 @@ void launch_syrk_split_b(hipStream_t s, const BProb *P, const BWork &w, int64_t 
     if (w.total > 0) hipLaunchKernelGGL(k_syrk_split_b, dim3((unsigned)w.total), dim3(NT), 0, s, P, w, kk, K);
 }
 
-void launch_syrk_split(hipStream_t s, float *C, int64_t ldc, const void *img, int64_t rows, int64_t K)
+void launch_syrk_split(hipStream_t s, float *C, int64_t ldc, const void *img, int64_t img_rows, int64_t row0,
+                       int64_t rows, int64_t K)
 {
     if (rows <= 0 || K <= 0) return;
     const int64_t st = (rows + kSup - 1) / kSup;
     const int64_t nsup = st * (st + 1) / 2;
     const int64_t blocks = (nsup + kXcds - 1) / kXcds * kXcds * (kSup / TM) * (kSup / TM);
-    hipLaunchKernelGGL(k_syrk_split, dim3((unsigned)blocks), dim3(NT), 0, s, C, ldc, (const v8bf *)img,
-                       round_up(rows, 256), rows, K);
+    hipLaunchKernelGGL(k_syrk_split, dim3((unsigned)blocks), dim3(NT), 0, s, C, ldc, (const v8bf *)img + row0,
+                       round_up(img_rows, 256), rows, K);
+}
+
+void launch_strip_split(hipStream_t s, float *C, int64_t ldc, const void *img, int64_t rows, int64_t N, int64_t K)
+{
+    const int64_t tm = rows / TM, tn = N / TM;
+    if (tm <= 0 || tn <= 0 || K <= 0) return;
+    const int64_t blocks = (tm + kXcds - 1) / kXcds * kXcds * tn;
+    hipLaunchKernelGGL(k_strip_split, dim3((unsigned)blocks), dim3(NT), 0, s, C, ldc, (const v8bf *)img,
+                       round_up(rows, 256), rows, K, (int)tn);
 }
 
 }  // namespace mag

@@ -406,9 +406,14 @@ void launch_syrk_lower(hipStream_t s, float *C, int64_t ldc, const float *P, int
 // split into three BF16 components.  The image of rows x K (column-major P)
 // takes split_image_bytes(rows, K); rows a multiple of 128, K of 16.
 size_t split_image_bytes(int64_t rows, int64_t K);
-void launch_split(hipStream_t s, const float *P, int64_t ldp, int64_t rows, int64_t K, void *img);
-// C (rows x rows, lower 128-tiles only) -= P P^T from the image of P
-void launch_syrk_split(hipStream_t s, float *C, int64_t ldc, const void *img, int64_t rows, int64_t K);
+// rows x K of the panel into rows row0.. and columns col0.. of an image of img_rows rows
+void launch_split(hipStream_t s, const float *P, int64_t ldp, int64_t rows, int64_t K, void *img, int64_t img_rows,
+                  int64_t row0, int64_t col0);
+// C (rows x rows, lower 128-tiles only) -= P P^T, P the rows row0.. of the image
+void launch_syrk_split(hipStream_t s, float *C, int64_t ldc, const void *img, int64_t img_rows, int64_t row0,
+                       int64_t rows, int64_t K);
+// the first N columns of the same for all rows of the image
+void launch_strip_split(hipStream_t s, float *C, int64_t ldc, const void *img, int64_t rows, int64_t N, int64_t K);
 
 // gemm64.hip: the FP64 factor's contractions, C (M x N) -= P Q^T (kGemmSub) or
 // C = P Q^T with C^T into CT (kGemmSetT); operands column-major as for
