@@ -2299,13 +2299,16 @@ int mag_weighting_vjp(mag_ctx *c, mag_factor *f, const double *X, int64_t n, int
     } else {
         launch_scale(s, wv, gM, lam, n, npad);  // lambda = gM w
     }
-    if (dt) {
+    if (dt && dX && m <= pair_fused_max_dim()) {
+        launch_gradx(s, X, n, m, t, wv, lam, dX, partial, u, rhs);
+        HIPCHK(hipMemcpyAsync(c->host_scalars + 43, rhs, sizeof(double), hipMemcpyDeviceToHost, s));
+    } else if (dt) {
         launch_dzmv(s, X, n, m, t, wv, u, partial);
         double *h = (double *)c->partial.p + blas1_partial_doubles(3) + 16;
         launch_multidot(s, u, npad, 1, lam, npad, partial, h);
         HIPCHK(hipMemcpyAsync(c->host_scalars + 43, h, sizeof(double), hipMemcpyDeviceToHost, s));
     }
-    if (dX) launch_gradx(s, X, n, m, t, wv, lam, dX, partial);
+    if (dX && !(dt && m <= pair_fused_max_dim())) launch_gradx(s, X, n, m, t, wv, lam, dX, partial);
     HIPCHK(hipStreamSynchronize(s));
     if (dt) *dt = c->host_scalars[43];
     return MAG_OK;

