@@ -834,26 +834,78 @@ k_node_small(const double *__restrict__ partial, int cmax, int k, const double *
     }
 }
 
-// x[r] -= Ph[r, :] tv[c/2][(c%2) k ...] for the rows of child c; one
-// workgroup per 64-row block, 4 threads per row.
+// The same in three launches, a workgroup per 64 rows of a matrix: with one per node the few
+// nodes of the upper levels pull their 3 k^2 entries through as many CUs (400 us a node at
+// k = 512, where these take about 6 us each).
+// STAGE 0: s2 and u = s1 - B s2 into tv[i] = [u; s2];  1: x1 = S^{-1} u into x1 (k per
+// node);  2: tv[i] = [x1; s2 - C x1].
+template <int STAGE>
+__global__ void __launch_bounds__(NT)
+k_node_mv(const double *partial, int cmax, int k, const double *__restrict__ W, double *__restrict__ tv, double *x1)
+{
+    __shared__ double v[KMAXC * SL];
+    __shared__ double red[NT / SL][SL];
+    const int i0 = blockIdx.x, r0 = blockIdx.y * SL, tid = threadIdx.x;
+    const int rl = tid & (SL - 1), g = tid / SL;
+    const int64_t kk = (int64_t)k * k;
+    const double *M = W + (int64_t)i0 * 3 * kk + (STAGE == 0 ? 0 : STAGE == 1 ? 2 * kk : kk);
+    double *o = tv + (int64_t)i0 * 2 * k, *xi = x1 + (int64_t)i0 * k;
+    const auto dots = [&](int child, int q) {
+        double a = 0.0;
+        for (int ch = 0; ch < cmax; ++ch) a += partial[((int64_t)(2 * i0 + child) * cmax + ch) * k + q];
+        return a;
+    };
+    for (int q = tid; q < k; q += NT) v[q] = STAGE == 0 ? dots(0, q) : STAGE == 1 ? o[q] : xi[q];
+    __syncthreads();
+    const int per = k / (NT / SL);
+    double acc = 0.0;
+#pragma unroll 8
+    for (int j = g * per; j < (g + 1) * per; ++j) acc = fma(M[(int64_t)j * k + r0 + rl], v[j], acc);
+    red[g][rl] = acc;
+    __syncthreads();
+    if (g != 0) return;
+#pragma unroll
+    for (int q = 1; q < NT / SL; ++q) acc += red[q][rl];
+    const int r = r0 + rl;
+    if (STAGE == 0) {
+        o[r] = dots(1, r) - acc;
+        o[k + r] = v[r];
+    } else if (STAGE == 1) {
+        xi[r] = acc;
+    } else {
+        o[r] = v[r];
+        o[k + r] -= acc;
+    }
+}
+
+// x[r] -= Ph[r, :] tv[c/2][(c%2) k ...] for the rows of child c; one workgroup per
+// 64-row block, a wave per row at a time, so a row's entries come in whole lines (bound
+// by reading Ph).
 __global__ void __launch_bounds__(NT)
 k_node_update(const double *__restrict__ Ph, int k, const int64_t *__restrict__ bnd, int rbmax,
               const double *__restrict__ tv, double *__restrict__ x)
 {
+    constexpr int RW = 64 / (NT / 64);  // rows of a wave
     const int c = blockIdx.x / rbmax, rb = blockIdx.x % rbmax;
     const int64_t lo = bnd[c], hi = bnd[c + 1];
-    const int64_t r = lo + (int64_t)rb * 64 + (threadIdx.x >> 2);
-    const int part = threadIdx.x & 3;
-    const int q = k / 4;
-    const double *tvec = tv + (int64_t)(c >> 1) * 2 * k + (c & 1) * k + part * q;
-    double acc = 0.0;
-    if (r < hi) {
-        const double *row = Ph + r * k + part * q;
-        for (int j = 0; j < q; ++j) acc = fma(row[j], tvec[j], acc);
+    const int lane = threadIdx.x & 63;
+    const int64_t r0 = lo + (int64_t)rb * 64 + RW * (threadIdx.x >> 6);
+    const double *tvec = tv + (int64_t)(c >> 1) * 2 * k + (c & 1) * k;
+    double acc[RW];
+#pragma unroll
+    for (int i = 0; i < RW; ++i) acc[i] = 0.0;
+    for (int j = lane; j < k; j += 64) {
+        const double t = tvec[j];
+#pragma unroll
+        for (int i = 0; i < RW; ++i)
+            if (r0 + i < hi) acc[i] = fma(Ph[(r0 + i) * k + j], t, acc[i]);
     }
-    acc += __shfl_xor(acc, 1);
-    acc += __shfl_xor(acc, 2);
-    if (r < hi && part == 0) x[r] -= acc;
+#pragma unroll
+    for (int i = 0; i < RW; ++i) {
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) acc[i] += __shfl_xor(acc[i], o);
+        if (r0 + i < hi && lane == 0) x[r0 + i] -= acc[i];
+    }
 }
 
 inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
@@ -1242,8 +1294,17 @@ void hodlr_apply(hipStream_t s, const HodlrFactor &H, const double *r, double *z
         const int64_t *bch = H.bnd + boff(l + 1);
         hipLaunchKernelGGL(k_node_dots, dim3((unsigned)(nch * H.cmax[l]), (unsigned)(k / SL)), dim3(NT), 0, s,
                            H.P + H.poff[l], k, H.xp, bch, H.crows[l], H.cmax[l], H.apart);
-        hipLaunchKernelGGL(k_node_small, dim3((unsigned)tasks), dim3(NT), 0, s, H.apart, H.cmax[l], k,
-                           H.W + H.woff[l], H.tv);
+        if (k >= 2 * SL) {
+            const dim3 g((unsigned)tasks, (unsigned)(k / SL));
+            const double *W = H.W + H.woff[l];
+            hipLaunchKernelGGL(k_node_mv<0>, g, dim3(NT), 0, s, H.apart, H.cmax[l], k, W, H.tv, H.apart);
+            // the dots are summed: their place takes x1
+            hipLaunchKernelGGL(k_node_mv<1>, g, dim3(NT), 0, s, H.apart, H.cmax[l], k, W, H.tv, H.apart);
+            hipLaunchKernelGGL(k_node_mv<2>, g, dim3(NT), 0, s, H.apart, H.cmax[l], k, W, H.tv, H.apart);
+        } else {
+            hipLaunchKernelGGL(k_node_small, dim3((unsigned)tasks), dim3(NT), 0, s, H.apart, H.cmax[l], k,
+                               H.W + H.woff[l], H.tv);
+        }
         hipLaunchKernelGGL(k_node_update, dim3((unsigned)(nch * rb)), dim3(NT), 0, s, H.Ph + H.poff[l], k, bch, rb,
                            H.tv, H.xp);
     }
