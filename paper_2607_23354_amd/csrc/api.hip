@@ -1000,11 +1000,11 @@ int solve_hss(mag_ctx *ctx, const double *X, int64_t n, int m, double t, double 
 // MAG_AUTO takes the HODLR preconditioner above this size.  Measured on the
 // MI355X, whole solves, dense FP32 factor + refinement against the HODLR with
 // max_rank 512 and one subspace iteration (noisy torus at t = 0.5, 2, 8; Gaussian
-// cloud at its cutoff scale; mixture of five Gaussians at t = 30, 100): n = 52000:
-// 274-316 ms against 365-402 ms; n = 57344: 357-405 against 389-508 (the torus at t = 0.5
-// alone 405 against 393); n = 60001: 410-461 against 408-466; n = 65536: 522-583
-// against 443-583.  Without the subspace iteration the HODLR solve of the mixture
-// at t = 30 stalls at n = 131072.
+// cloud at its cutoff scale; mixture of five Gaussians at t = 30, 100): n = 53248:
+// 285-323 ms against 329-423 ms; n = 57344: 351-395 against 345-432 (369 against 366 on
+// average); n = 60416: 411-459 against 363-452; n = 65536: 517-574 against 391-503.
+// Without the subspace iteration the HODLR solve of the mixture at t = 30 stalls at
+// n = 131072.
 constexpr int64_t kAutoHodlrMinN = 57344;
 // Up to here the dense factor is the only choice; between the two the HODLR still
 // takes what the dense path has no memory for or does not converge on.

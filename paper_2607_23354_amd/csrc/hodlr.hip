@@ -457,19 +457,6 @@ k_gram_shift(double *__restrict__ G, int k, const int64_t *__restrict__ bnd, int
     for (int i = threadIdx.x; i < k; i += NT) g[(int64_t)i * k + i] += s;
 }
 
-// Zero the strictly lower triangle of each k x k column-major block (the
-// Cholesky leaves it untouched), so the block is R^{-1} for the row products.
-__global__ void k_zero_lower(double *__restrict__ R, int k, int64_t count)
-{
-    const int64_t per = (int64_t)k * k;
-    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < count * per;
-         e += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t w = e % per;
-        const int col = (int)(w / k), row = (int)(w % k);
-        if (row > col) R[e] = 0.0;
-    }
-}
-
 // Row-block products: out[r, slab] = (sub ? out[r, slab] - : ) A[r, :] M[:, slab]
 // for the rows r of each task, M = Mb + task * mstride (lda x ldo,
 // column-major, leading dimension lda); grid (tasks * rbmax, ldo / 64).
@@ -1165,11 +1152,7 @@ int hodlr_factor(mag_ctx *ctx, const double *X, int64_t n, int m, double t, int 
             for (int pass = 0; pass < 3; ++pass) {
                 gram(src, k, src, k, bch, 2, side, tasks, l, G);
                 hipLaunchKernelGGL(k_gram_shift, dim3((unsigned)tasks), dim3(NT), 0, s, G, k, bch, 2, side);
-                RBCHK(rocsolver_dpotrf_strided_batched(bh, rocblas_fill_upper, k, G, k, (rocblas_stride)k * k,
-                                                       rinfo, (rocblas_int)tasks));
-                RBCHK(rocsolver_dtrtri_strided_batched(bh, rocblas_fill_upper, rocblas_diagonal_non_unit, k, G, k,
-                                                       (rocblas_stride)k * k, rinfo, (rocblas_int)tasks));
-                hipLaunchKernelGGL(k_zero_lower, dim3(1024), dim3(NT), 0, s, G, k, tasks);
+                launch_cholinv64_b(s, G, k, tasks, gpart);  // (the Gram partials are summed)
                 hipLaunchKernelGGL(k_rowmul, dim3((unsigned)(tasks * rb), (unsigned)(k / SL)), dim3(NT), 0, s, src,
                                    k, dst, k, G, (int64_t)k * k, bch, 2, side, rb, 0);
                 std::swap(src, dst);

@@ -429,6 +429,9 @@ void launch_syrk64_lower(hipStream_t s, double *C, int64_t ldc, const double *P,
 // place (L below and on the diagonal, L^T above) and write its inverse to Linv
 // (64 x 64 column-major).  Breakdown -> status.
 void launch_potrf64(hipStream_t s, double *A, int64_t ld, int64_t k0, double *Linv, int *status);
+// count matrices G = R^T R (k x k column-major, one after another; k a multiple of 64) into R^{-1}
+// (zeros below the diagonal); scratch: count * k * 64 doubles
+void launch_cholinv64_b(hipStream_t s, double *G, int k, int64_t count, double *scratch);
 // chol64.hip: FP64 factor of the padded npad x npad A (layout of the FP32
 // factor) in place; dinv receives the inverses of the 64-diagonal blocks
 // (npad / 64 blocks of 64 x 64).

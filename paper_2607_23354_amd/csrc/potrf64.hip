@@ -79,8 +79,9 @@ __device__ inline void blk16_store(double *dst, int ld, const v4d &acc, int q, i
     }
 }
 
-__global__ void __launch_bounds__(256)
-k_potrf64(double *__restrict__ A, int64_t ld, int64_t k0, double *__restrict__ Linv, int *__restrict__ status)
+// The block at Ablk, global pivot index k0; status may be NULL.
+__device__ __forceinline__ void potrf64_body(double *__restrict__ Ablk, int64_t ld, int64_t k0,
+                                             double *__restrict__ Linv, int *__restrict__ status)
 {
     __shared__ double S[NB * LD];   // A, then L: column-major S[c * LD + r], lower triangle
     __shared__ double V[NB * LD];   // L^{-1}, same layout
@@ -89,7 +90,6 @@ k_potrf64(double *__restrict__ A, int64_t ld, int64_t k0, double *__restrict__ L
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const int q = lane & 15, kq = lane >> 4;
-    double *Ablk = A + k0 * ld + k0;
 
     // the block: 8 loads of two entries per thread, all in flight before the
     // first LDS store (only the lower triangle is trusted)
@@ -231,10 +231,129 @@ k_potrf64(double *__restrict__ A, int64_t ld, int64_t k0, double *__restrict__ L
         *reinterpret_cast<double2 *>(Ablk + (int64_t)c * ld + r) = l;
         *reinterpret_cast<double2 *>(Linv + c * NB + r) = w;
     }
-    if (tid == 0 && bad != 0) atomicCAS(&status[kStBreakdown], 0, bad);
+    if (status && tid == 0 && bad != 0) atomicCAS(&status[kStBreakdown], 0, bad);
+}
+
+__global__ void __launch_bounds__(256)
+k_potrf64(double *__restrict__ A, int64_t ld, int64_t k0, double *__restrict__ Linv, int *__restrict__ status)
+{
+    potrf64_body(A + k0 * ld + k0, ld, k0, Linv, status);
+}
+
+// ---- inverse Cholesky factors of many small matrices -------------------------------
+// G = R^T R (k x k, k a multiple of 64) into R^{-1}, in 64-column steps on 64 x 64 blocks: step
+// j factors block (j, j) into D_j = L_jj^{-1}; block column j, L below the diagonal and
+// (L^{-1})^T above it, is multiplied by D_j^T; and every block (r, i), i > j, for the rows r >= i
+// of L and r <= j of the inverse, loses (r, j) L_ij^T.  One kind of product, X Y^T, and
+// three launches a step for all matrices, a workgroup per block: at the upper levels of a
+// tree, with few wide matrices, the library's factor and triangular inverse took
+// some 40 launches of a workgroup or two each.  81 matrix sets of a compression at
+// n = 60001: some 130 ms then, 22 ms now, bound by the chain of the diagonal blocks.
+__global__ void __launch_bounds__(256)
+k_cholinv_diag(double *__restrict__ G, int k, int j, double *__restrict__ D)
+{
+    const int64_t b = blockIdx.x;
+    potrf64_body(G + b * k * k + (int64_t)NB * j * k + NB * j, k, 0, D + (b * (k / NB) + j) * NB * NB, nullptr);
+}
+
+// C (64 x 64, column-major, ld) = X Y^T, or (SUB) C - X Y^T, or (NEG) -X Y^T; TX: X transposed.
+// C may be X.  Lanes run down C's rows, so its accesses are whole lines.
+enum { kProdSet, kProdSub, kProdNeg };
+__device__ __forceinline__ void block_product(double *C, int64_t ldc, const double *X, int64_t ldx, bool tx,
+                                              const double *Y, int64_t ldy, int mode)
+{
+    constexpr int LX = NB + 1;
+    __shared__ double Xs[NB * LX], Ys[NB * LX];  // (row, k) at [k LX + row]
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int q = lane & 15, kq = lane >> 4;
+    double xv[NB * NB / 256], yv[NB * NB / 256];
+#pragma unroll
+    for (int e = 0; e < NB * NB / 256; ++e) {
+        xv[e] = X[(int64_t)(wave + 4 * e) * ldx + lane];
+        yv[e] = Y[(int64_t)(wave + 4 * e) * ldy + lane];
+    }
+#pragma unroll
+    for (int e = 0; e < NB * NB / 256; ++e) {
+        const int c = wave + 4 * e;
+        Xs[tx ? lane * LX + c : c * LX + lane] = xv[e];
+        Ys[c * LX + lane] = yv[e];
+    }
+    __syncthreads();
+    v4d acc[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc[i] = v4d{0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+    for (int k = 0; k < NB; k += 4) {
+        const double x = Xs[(k + kq) * LX + 16 * wave + q];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            acc[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(Ys[(k + kq) * LX + 16 * i + q], x, acc[i], 0, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            double *c = C + (int64_t)(16 * i + kq + 4 * v) * ldc + 16 * wave + q;
+            *c = mode == kProdSub ? *c - acc[i][v] : mode == kProdNeg ? -acc[i][v] : acc[i][v];
+        }
+}
+
+// Block column j times D_j^T, the diagonal block aside; grid (matrices, k / 64 - 1).
+__global__ void __launch_bounds__(256)
+k_cholinv_column(double *__restrict__ G, int k, int j, const double *__restrict__ D)
+{
+    const int64_t b = blockIdx.x;
+    const int r = (int)blockIdx.y + ((int)blockIdx.y >= j ? 1 : 0);
+    double *C = G + b * k * k + (int64_t)NB * j * k + NB * r;
+    block_product(C, k, C, k, false, D + (b * (k / NB) + j) * NB * NB, NB, kProdSet);
+}
+
+// Block columns i = j + 1 + blockIdx.z less (r, j) L_ij^T; grid (matrices, k / 64, columns).
+__global__ void __launch_bounds__(256)
+k_cholinv_update(double *__restrict__ G, int k, int j, const double *__restrict__ D)
+{
+    const int64_t b = blockIdx.x;
+    const int r = (int)blockIdx.y, i = j + 1 + (int)blockIdx.z;
+    if (r > j && r < i) return;  // neither of L nor yet of the inverse
+    double *M = G + b * k * k;
+    const double *L = M + (int64_t)NB * j * k + NB * i;
+    double *C = M + (int64_t)NB * i * k + NB * r;
+    if (r == j) block_product(C, k, D + (b * (k / NB) + j) * NB * NB, NB, true, L, k, kProdNeg);
+    else block_product(C, k, M + (int64_t)NB * j * k + NB * r, k, false, L, k, kProdSub);
+}
+
+// The diagonal blocks D_j^T, zeros below; grid (matrices, k / 64).
+__global__ void __launch_bounds__(256)
+k_cholinv_finish(double *__restrict__ G, int k, const double *__restrict__ D)
+{
+    const int64_t b = blockIdx.x;
+    const int j = blockIdx.y;
+    double *C = G + b * k * k + (int64_t)NB * j * k;
+    const double *Dj = D + (b * (k / NB) + j) * NB * NB;
+    for (int e = threadIdx.x; e < NB * NB; e += 256) {
+        const int c = e / NB, r = e % NB;
+        C[(int64_t)c * k + NB * j + r] = Dj[r * NB + c];
+    }
+    for (int c = threadIdx.x >> 6; c < NB; c += 4)
+        for (int r = NB * (j + 1) + (threadIdx.x & 63); r < k; r += 64) C[(int64_t)c * k + r] = 0.0;
 }
 
 }  // namespace
+
+void launch_cholinv64_b(hipStream_t s, double *G, int k, int64_t count, double *scratch)
+{
+    const int nb = k / NB;
+    const unsigned B = (unsigned)count;
+    if (count <= 0) return;
+    for (int j = 0; j < nb; ++j) {
+        hipLaunchKernelGGL(k_cholinv_diag, dim3(B), dim3(256), 0, s, G, k, j, scratch);
+        if (nb > 1) hipLaunchKernelGGL(k_cholinv_column, dim3(B, (unsigned)(nb - 1)), dim3(256), 0, s, G, k, j, scratch);
+        if (j + 1 < nb)
+            hipLaunchKernelGGL(k_cholinv_update, dim3(B, (unsigned)nb, (unsigned)(nb - 1 - j)), dim3(256), 0, s, G, k, j,
+                               scratch);
+    }
+    hipLaunchKernelGGL(k_cholinv_finish, dim3(B, (unsigned)nb), dim3(256), 0, s, G, k, scratch);
+}
 
 void launch_potrf64(hipStream_t s, double *A, int64_t ld, int64_t k0, double *Linv, int *status)
 {
