@@ -78,17 +78,17 @@ int mag_set_stream(mag_ctx *ctx, void *hip_stream);
 
 /* ---- options and diagnostics --------------------------------------------- */
 enum {
-    MAG_AUTO = 0,        /* by measured cost: MAG_FP32_IR up to n = 57344 (its FP32      *
-                          * factor is the cheaper solve there: 0.27-0.32 s against      *
-                          * 0.37-0.40 s for HODLR at n = 52000), MAG_HODLR above        *
-                          * (max_rank 512, one subspace iteration, GMRES(100), up to    *
-                          * 400 inner iterations; 0.44-0.58 s against 0.52-0.58 s at    *
-                          * n = 65536, on tori, Gaussian and clustered clouds) when     *
+    MAG_AUTO = 0,        /* by measured cost: MAG_FP32_IR up to n = 49152 (its FP32      *
+                          * factor's n^3/3 flops on MFMA are the cheaper solve there:   *
+                          * 0.18-0.20 s against 0.19-0.21 s for HODLR at n = 45056,     *
+                          * 0.22-0.26 s against 0.21-0.27 s at n = 49152),              *
+                          * MAG_HODLR above (max_rank 512, one subspace iteration,      *
+                          * GMRES(100), up to 400 inner iterations; 0.29-0.39 s against *
+                          * 0.51-0.57 s at n = 65536,                                   *
+                          * on tori, Gaussian and clustered clouds) when                *
                           * m <= 16; if the HODLR solve does not converge, or m > 16,   *
                           * MAG_FP32_IR when its npad^2 factor fits in 3/4 of the       *
-                          * device memory, else MAG_ENOMEM.  From n = 49153 to 57344    *
-                          * MAG_HODLR stands in where the factor does not fit or its    *
-                          * solve does not converge                                     */
+                          * device memory, else MAG_ENOMEM                              */
     MAG_FP64_DENSE = 1,  /* FP64 Z in HBM + rocSOLVER dpotrf/dpotrs (dense comparator)   */
     MAG_FP32_IR = 2,     /* FP32 MFMA Cholesky + FP64 GMRES iterative refinement         */
     MAG_HODLR = 3,       /* HODLR preconditioner + FP64 GMRES (largest sizes, Sec. 3.2): *

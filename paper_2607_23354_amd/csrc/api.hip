@@ -1000,15 +1000,12 @@ int solve_hss(mag_ctx *ctx, const double *X, int64_t n, int m, double t, double 
 // MAG_AUTO takes the HODLR preconditioner above this size.  Measured on the
 // MI355X, whole solves, dense FP32 factor + refinement against the HODLR with
 // max_rank 512 and one subspace iteration (noisy torus at t = 0.5, 2, 8; Gaussian
-// cloud at its cutoff scale; mixture of five Gaussians at t = 30, 100): n = 53248:
-// 285-323 ms against 329-423 ms; n = 57344: 351-395 against 345-432 (369 against 366 on
-// average); n = 60416: 411-459 against 363-452; n = 65536: 517-574 against 391-503.
+// cloud at its cutoff scale; mixture of five Gaussians at t = 30, 100): n = 45056:
+// 176-201 ms against 193-211 ms; n = 49152: 224-257 against 207-270 (235 against 223 on
+// average); n = 53248: 281-319 against 226-315; n = 65536: 511-568 against 286-391.
 // Without the subspace iteration the HODLR solve of the mixture at t = 30 stalls at
 // n = 131072.
-constexpr int64_t kAutoHodlrMinN = 57344;
-// Up to here the dense factor is the only choice; between the two the HODLR still
-// takes what the dense path has no memory for or does not converge on.
-constexpr int64_t kAutoDenseOnlyN = 49152;
+constexpr int64_t kAutoHodlrMinN = 49152;
 
 // Whether the dense FP32 factor's npad^2 floats fit in three quarters of the
 // device memory (counting what this context already holds for it) and in the
@@ -1019,7 +1016,6 @@ bool auto_dense(mag_ctx *ctx, int64_t n)
     const double npad = (double)round_up(n, kPad);
     const double need = 4.0 * npad * npad;
     if (ctx->ws_limit && need > (double)ctx->ws_limit) return false;
-    if ((double)ctx->factor.bytes >= need) return true;
     if (hipMemGetInfo(&fr, &tot) != hipSuccess) return true;
     return need <= 0.75 * ((double)fr + (double)ctx->factor.bytes);
 }
@@ -1597,23 +1593,11 @@ int mag_weighting(mag_ctx *c, const double *X, int64_t n, int32_t m, double t, d
     CHK(ensure_common(c, n, std::max(1, o.gmres_restart)));
     // MAG_AUTO: the HODLR preconditioner above the measured crossover, the dense
     // FP32 factor below it or when the HODLR solve does not converge
-    const bool may_hodlr = o.solver == MAG_AUTO && n > kAutoDenseOnlyN && m <= 16;
-    const bool fits = o.solver == MAG_AUTO && auto_dense(c, n);
-    const bool auto_hodlr = may_hodlr && (n > kAutoHodlrMinN || !fits);
+    const bool auto_hodlr = o.solver == MAG_AUTO && n > kAutoHodlrMinN && m <= 16;
     // the FP32 path's tile generator checks the points itself (no pass and no round trip
     // of their own)
-    const bool fp32 = o.solver == MAG_FP32_IR || (o.solver == MAG_AUTO && !auto_hodlr && fits);
+    const bool fp32 = o.solver == MAG_FP32_IR || (o.solver == MAG_AUTO && !auto_hodlr && auto_dense(c, n));
     int rc = (fp32 && n > 1) ? MAG_OK : check_points(c, X, n, m, o.solver != MAG_AUTO || auto_hodlr);
-    const auto hodlr = [&]() -> int {
-        mag_opts oh = o;
-        oh.max_rank = std::max(oh.max_rank, 512);
-        oh.power_iters = std::max(oh.power_iters, 1);
-        oh.gmres_restart = std::max(oh.gmres_restart, 100);
-        oh.max_gmres = std::max(oh.max_gmres, 400);
-        oh.max_outer = std::max(oh.max_outer, 30);
-        CHK(ensure_common(c, n, oh.gmres_restart));
-        return solve_hodlr(c, X, n, m, t, w, oh, info);
-    };
     if (rc == MAG_OK && n == 1) {
         launch_fill(c->stream, w, 1, 1.0);
         HIPCHK(hipStreamSynchronize(c->stream));
@@ -1630,18 +1614,17 @@ int mag_weighting(mag_ctx *c, const double *X, int64_t n, int32_t m, double t, d
         case MAG_HSS: rc = solve_hss(c, X, n, m, t, w, o, info); break;
         case MAG_AUTO:
             if (auto_hodlr) {
-                rc = hodlr();
+                mag_opts oh = o;
+                oh.max_rank = std::max(oh.max_rank, 512);
+                oh.power_iters = std::max(oh.power_iters, 1);
+                oh.gmres_restart = std::max(oh.gmres_restart, 100);
+                oh.max_gmres = std::max(oh.max_gmres, 400);
+                oh.max_outer = std::max(oh.max_outer, 30);
+                CHK(ensure_common(c, n, oh.gmres_restart));
+                rc = solve_hodlr(c, X, n, m, t, w, oh, info);
                 if (rc == MAG_ENOCONV && auto_dense(c, n)) rc = solve_fp32_ir(c, X, n, m, t, w, o, info);
             } else if (fp32) {
                 rc = solve_fp32_ir(c, X, n, m, t, w, o, info);
-                // the HODLR takes what the factor cannot (a singular Z stays refused)
-                if (may_hodlr && (rc == MAG_ENOMEM || rc == MAG_ENOCONV ||
-                                  (rc == MAG_ENOTPD && check_points(c, X, n, m) == MAG_OK))) {
-                    // it needs less than the factor, whose memory it may need
-                    release(c, c->factor);
-                    release(c, c->dinv);
-                    rc = hodlr();
-                }
             } else {
                 rc = MAG_ENOMEM;
             }

@@ -116,31 +116,3 @@ def test_cap_without_room_for_small_tiles(mag):
         assert np.all(np.abs((y - y2).cpu().numpy()) <= 64 * U64 * scale)
     finally:
         ctx.close()
-
-
-@pytest.mark.parametrize("spare", [-(4 << 30), 1 << 23])
-def test_auto_without_room_for_the_factor_takes_hodlr(mag, spare):
-    # n just above 49152: AUTO takes the dense factor, and the HODLR where a workspace cap
-    # holds less than the factor (spare < 0) or the factor but not what it needs beside it
-    n = 49300
-    X = W.gaussian(n, 3, seed=12)
-    t = W.gaussian_cutoff_estimate(n, 3)
-    npad = -(-n // 256) * 256
-    ctx = mag.Context(0)
-    ctx.set_workspace_limit(4 * npad * npad + spare)
-    res = mag.weighting(dev(X), t, ctx=ctx)
-    assert ctx.workspace_bytes() <= 4 * npad * npad + spare
-    ctx.close()
-    rows = np.random.default_rng(1).choice(n, size=64, replace=False)
-    assert res.info["solver"] == mag.SOLVERS["hodlr"]
-    assert np.abs(oracle.residual(X, t, res.w.cpu().numpy(), rows)).max() <= 1e-12
-
-
-def test_auto_takes_the_factor_just_above_49152(mag):
-    n = 49300
-    X = W.gaussian(n, 3, seed=12)
-    t = W.gaussian_cutoff_estimate(n, 3)
-    res = mag.weighting(dev(X), t)
-    rows = np.random.default_rng(1).choice(n, size=64, replace=False)
-    assert res.info["solver"] == mag.SOLVERS["fp32_ir"]
-    assert np.abs(oracle.residual(X, t, res.w.cpu().numpy(), rows)).max() <= 1e-12
