@@ -8,7 +8,10 @@
 //
 // All operands are column-major FP32: P(i, p) = P[p * ldp + i],
 // Q(j, p) = Q[p * ldq + j], C(i, j) = C[j * ldc + i].  Accumulation is FP32
-// on v_mfma_f32_32x32x2_f32.
+// on v_mfma_f32_32x32x2_f32.  The trailing updates run here (128 TF/s at 20480 rows,
+// K = 1024) only where the workspace limit leaves no room for the BF16 split image that
+// gemm_split.hip reads (195 TF/s); so do the batched panels without their exchange.  The
+// single factor's strips of up to 4096 rows run here always (64-row tiles).
 //
 // Workgroup tile 128 x 128, 4 waves in a 2 x 2 arrangement, each wave a
 // 64 x 64 sub-tile held as 2 x 2 MFMA 32 x 32 accumulators (64 registers).
