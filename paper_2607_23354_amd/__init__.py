@@ -62,8 +62,9 @@ class Context:
         _lib.check(self.lib.mag_set_workspace_limit(self.handle, int(nbytes)), "mag_set_workspace_limit")
 
     def set_spin_limit(self, polls: int) -> None:
-        """Bound the sync-free triangular solves' waits (0 = the default); a
-        call whose waits run out fails with MAG_EINTERNAL."""
+        """Bound the waits between workgroups in the triangular solves and the
+        factor's panels (0 = the default); a call whose waits run out fails
+        with MAG_EINTERNAL."""
         _lib.check(self.lib.mag_set_spin_limit(self.handle, int(polls)), "mag_set_spin_limit")
 
     def workspace_bytes(self) -> int:

@@ -113,12 +113,6 @@ using namespace mag;
     } while (0)
 
 namespace mag {
-// Polls of one wait of the sync-free substitutions on this context.
-long spin_limit_of(const mag_ctx *ctx)
-{
-    return ctx->spin_limit > 0 ? (long)ctx->spin_limit : kSpinLimitDefault;
-}
-
 // Validate the coordinates: finite, and no duplicate points (Z would be
 // singular).  One host sync.
 int check_points(mag_ctx *ctx, const double *X, int64_t n, int m, bool pairs)
@@ -277,7 +271,7 @@ void enqueue_factor(mag_ctx *ctx, const double *X, int64_t n, int m, double t, F
         ft->used = 0;
         ft->flops.clear();
     }
-    chol32_factor(s, F.A, F.npad, n, F.dinv, status, ft, nb, img, ctx->panel);
+    chol32_factor(s, F.A, F.npad, n, F.dinv, status, ft, nb, img, ctx->panel, panel_spin_limit_of(ctx));
     launch_near_q(s, F.A, F.npad, F.dinv, F.nq);
 }
 
@@ -288,6 +282,7 @@ int factor_verdict(const int *st, int64_t n, int attempt, Factor32 &F)
 {
     if (st[kStNonFinite]) return MAG_EINVAL;
     if (st[kStDuplicate]) return MAG_ENOTPD;
+    if (st[kStSpinTimeout]) return MAG_EINTERNAL;  // its NaNs are no breakdown of Z
     if (st[kStBreakdown] == 0) return MAG_OK;
     if (attempt >= 6) return MAG_ENOTPD;
     F.shift = (F.shift == 0.0) ? 1e-6 * std::max<double>(1.0, std::sqrt((double)n)) : F.shift * 10.0;
@@ -381,8 +376,9 @@ int refine_core(mag_ctx *ctx, const double *X, int64_t n, int m, double t, int64
     HIPCHK(hipStreamSynchronize(s));
     const double r0 = spec ? rep[3] : rep[0], r1 = rep[4];
     std::memcpy(st.status, spec ? rep + 5 : rep + 1, sizeof(st.status));
-    if (st.status[kStNonFinite] || st.status[kStDuplicate] || st.status[kStBreakdown]) return kRetry;
+    if (st.status[kStNonFinite] || st.status[kStDuplicate]) return kRetry;
     if (st.status[kStSpinTimeout]) return MAG_EINTERNAL;
+    if (st.status[kStBreakdown]) return kRetry;
     st.have_sum = false;
 
     Gmres G;
@@ -1490,12 +1486,13 @@ int mag_autotune(mag_ctx *c, const double *X, int64_t n, int32_t m, double t, in
     HIPCHK(hipEventCreate(&e0));
     HIPCHK(hipEventCreate(&e1));
     int rc = MAG_OK;
+    launch_fill_ints(s, status, 8, 0);
     for (int rep = 0; rep < std::max(1, reps) && rc == MAG_OK; ++rep) {
         for (int q = 0; q < 2; ++q) {
-            launch_fill_ints(s, status, 8, 0);
             if (hipEventRecord(e0, s) != hipSuccess) { rc = MAG_EHIP; break; }
             launch_tilegen32(s, X, n, m, t, A, npad, 0.0f);
-            chol32_factor(s, A, npad, n, dinv, status, nullptr, widths[q], chol32_image(c, npad, widths[q]), c->panel);
+            chol32_factor(s, A, npad, n, dinv, status, nullptr, widths[q], chol32_image(c, npad, widths[q]), c->panel,
+                          panel_spin_limit_of(c));
             float ms = 0.0f;
             if (hipEventRecord(e1, s) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
                 hipEventElapsedTime(&ms, e0, e1) != hipSuccess) {
@@ -1508,6 +1505,9 @@ int mag_autotune(mag_ctx *c, const double *X, int64_t n, int32_t m, double t, in
     hipEventDestroy(e0);
     hipEventDestroy(e1);
     if (rc != MAG_OK) return rc;
+    HIPCHK(hipMemcpyAsync(c->host_scalars, status, 8 * sizeof(int), hipMemcpyDeviceToHost, s));
+    HIPCHK(hipStreamSynchronize(s));
+    if (((const int *)c->host_scalars)[kStSpinTimeout]) return MAG_EINTERNAL;
     const int pick = (best[0] < best[1]) ? 256 : 512;
     c->tune_panel[size_bucket(npad)] = pick;
     if (nb_out) *nb_out = pick;
@@ -1717,10 +1717,13 @@ int mag_factor32(mag_ctx *c, const double *X, int64_t n, int32_t m, double t, do
     launch_fill_ints(c->stream, status, 8, 0);
     launch_tilegen32(c->stream, X, n, m, t, L, npad, (float)shift);
     const int nb = panel_width(c, npad);
-    chol32_factor(c->stream, L, npad, n, dinv, status, nullptr, nb, chol32_image(c, npad, nb), c->panel);
+    chol32_factor(c->stream, L, npad, n, dinv, status, nullptr, nb, chol32_image(c, npad, nb), c->panel,
+                  panel_spin_limit_of(c));
     HIPCHK(hipMemcpyAsync(c->host_scalars, status, 8 * sizeof(int), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(hipStreamSynchronize(c->stream));
-    if (breakdown) *breakdown = ((const int *)c->host_scalars)[kStBreakdown];
+    const int *st = (const int *)c->host_scalars;
+    if (st[kStSpinTimeout]) return MAG_EINTERNAL;
+    if (breakdown) *breakdown = st[kStBreakdown];
     return MAG_OK;
 }
 

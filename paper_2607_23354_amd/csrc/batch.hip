@@ -402,7 +402,7 @@ void record_factor(Batch &bt, const std::vector<FLaunch> &seq)
         case 9: launch_syrk_split_b(bt.s, bt.d, L.w, L.kk, L.K); break;
         case 12: launch_near_q_b(bt.s, bt.d, L.w); break;
         case 10: launch_panel_begin_b(bt.s, bt.d, bt.B); break;
-        case 11: launch_panel_b(bt.s, bt.d, L.w, L.kk); break;
+        case 11: launch_panel_b(bt.s, bt.d, L.w, L.kk, panel_spin_limit_of(bt.c)); break;
         default: launch_gemm_b(bt.s, L.kind, bt.d, L.w, L.kk); break;
         }
     }
@@ -444,7 +444,7 @@ int batch_refine(Batch &bt, const std::vector<int> &ids, int rhs_slot, const std
     {
         BWork wp;
         BRC(bt.make_work(ids, prec_units, false, wp));
-        launch_prec_apply_b(bt.s, bt.d, wp, rhs_slot, S.Y, S.X);
+        launch_prec_apply_b(bt.s, bt.d, wp, rhs_slot, S.Y, S.X, spin_limit_of(bt.c));
     }
     std::vector<double> hv;
     for (int outer = 0; outer < std::max(1, o.max_outer); ++outer) {
@@ -521,7 +521,7 @@ int batch_refine(Batch &bt, const std::vector<int> &ids, int rhs_slot, const std
             BWork pp, p1;
             BRC(bt.make_work(plain, prec_units, false, pp));
             BRC(bt.make_work(plain, one, false, p1));
-            launch_prec_apply_b(bt.s, bt.d, pp, S.Rr, S.Y, S.Z);
+            launch_prec_apply_b(bt.s, bt.d, pp, S.Rr, S.Y, S.Z, spin_limit_of(bt.c));
             const double *ones = bt.put(std::vector<double>(plain.size(), 1.0), false);
             if (!ones) return MAG_ENOMEM;
             launch_multi_axpy_hb(bt.s, bt.d, p1.plist, p1.na, bt.maxpad, S.Z, 1, ones, S.X, 1.0);
@@ -535,7 +535,7 @@ int batch_refine(Batch &bt, const std::vector<int> &ids, int rhs_slot, const std
         BWork gp, g1;
         BRC(bt.make_work(run, prec_units, false, gp));
         BRC(bt.make_work(run, one, false, g1));
-        launch_prec_apply_b(bt.s, bt.d, gp, S.Rr, S.Y, S.Z);
+        launch_prec_apply_b(bt.s, bt.d, gp, S.Rr, S.Y, S.Z, spin_limit_of(bt.c));
         launch_nrm2_b(bt.s, bt.d, g1.plist, g1.na, S.Z, SC_BETA);
         BRC(bt.gather(g1.plist, g1.na, SC_BETA, 1, hv));
         std::vector<int> act;
@@ -565,7 +565,7 @@ int batch_refine(Batch &bt, const std::vector<int> &ids, int rhs_slot, const std
             BRC(bt.make_work(act, prec_units, false, ap));
             BRC(bt.make_work(act, one, false, a1));
             launch_zmv_b(bt.s, bt.m, bt.d, az, ar, S.V0 + k, S.U, -1, 0, 0, bt.ts);
-            launch_prec_apply_b(bt.s, bt.d, ap, S.U, S.Y, S.V0 + k + 1);
+            launch_prec_apply_b(bt.s, bt.d, ap, S.U, S.Y, S.V0 + k + 1, spin_limit_of(bt.c));
             launch_multidot_b(bt.s, bt.d, a1.plist, a1.na, S.V0, k + 1, S.V0 + k + 1, SC_H);
             launch_multi_axpy_b(bt.s, bt.d, a1.plist, a1.na, bt.maxpad, S.V0, k + 1, SC_H, S.V0 + k + 1, -1.0);
             launch_multidot_b(bt.s, bt.d, a1.plist, a1.na, S.V0, k + 1, S.V0 + k + 1, SC_H + k + 1);
@@ -674,7 +674,7 @@ void record_refine(Batch &bt, const AllWork &A, int rhs_slot, int64_t bnorm_off,
     if (!rest) {
         launch_ref_init_b(s, P, B, bnorm_off, rp.tol);
         launch_gate_b(s, P, B, F_REF);
-        launch_prec_apply_b(s, P, A.wp, rhs_slot, S.Y, S.X);  // x0 = M^{-1} b
+        launch_prec_apply_b(s, P, A.wp, rhs_slot, S.Y, S.X, spin_limit_of(bt.c));  // x0 = M^{-1} b
     }
     for (int round = rest ? 1 : 0; round <= rp.rounds; ++round) {
         const int final_round = round == rp.rounds ? 1 : 0;
@@ -691,13 +691,13 @@ void record_refine(Batch &bt, const AllWork &A, int rhs_slot, int64_t bnorm_off,
             launch_copy_b(s, P, A.all, B, mp, S.Best, S.X);
         }
         launch_gate_b(s, P, B, F_DOPLAIN);
-        launch_prec_apply_b(s, P, A.wp, S.Rr, S.Y, S.Z);
+        launch_prec_apply_b(s, P, A.wp, S.Rr, S.Y, S.Z, spin_limit_of(bt.c));
         launch_axpy_slot_b(s, P, B, mp, S.Z, S.X);
         // the first round's correction is always a plain step (plain mode starts
         // on, and a switch to GMRES needs a plain step that gained too little)
         if (round == 0) continue;
         launch_gate_b(s, P, B, F_DOGMRES);
-        launch_prec_apply_b(s, P, A.wp, S.Rr, S.Y, S.Z);
+        launch_prec_apply_b(s, P, A.wp, S.Rr, S.Y, S.Z, spin_limit_of(bt.c));
         launch_nrm2_b(s, P, A.all, B, S.Z, SC_BETA);
         launch_gmres_start_b(s, P, B);
         launch_gate_b(s, P, B, F_INNER);
@@ -705,7 +705,7 @@ void record_refine(Batch &bt, const AllWork &A, int rhs_slot, int64_t bnorm_off,
         for (int k = 0; k < rp.kcycle; ++k) {
             launch_gate_b(s, P, B, F_INNER);
             launch_zmv_b(s, bt.m, P, A.wz, A.wr, S.V0 + k, S.U, -1, 0, 0, bt.ts);
-            launch_prec_apply_b(s, P, A.wp, S.U, S.Y, S.V0 + k + 1);
+            launch_prec_apply_b(s, P, A.wp, S.U, S.Y, S.V0 + k + 1, spin_limit_of(bt.c));
             launch_arnoldi_b(s, P, B, k, S.V0, rp.kcycle, rp.inner_tol, rp.max_gmres);
         }
         launch_gmres_finish_b(s, P, B, rp.kcycle);
@@ -721,7 +721,7 @@ struct Step {
     SState *S = nullptr;
     SParams prm{};
     RefPlan rp, dp;         // the solve's refinement and the Newton derivative's
-    int *dcount = nullptr;  // clouds still searching, breakdown at every shift, refinements parked
+    int *dcount = nullptr;  // launch_search_count_b's three words
 };
 
 // min w, the bracket update and, for Newton steps, the first part of d(min w)/dt = (dw/dt) at
@@ -787,6 +787,24 @@ void record_rest(Batch &bt, const Step &st)
     launch_search_count_b(bt.s, bt.d, st.S, bt.B, st.dcount);
 }
 
+// launch_search_count_b's words to the host.
+int read_counts(Batch &bt, const int *dcount, int *hc)
+{
+    BCHK(hipMemcpyAsync(hc, dcount, 3 * sizeof(int), hipMemcpyDeviceToHost, bt.s));
+    BCHK(hipStreamSynchronize(bt.s));
+    return MAG_OK;
+}
+
+// MAG_EINTERNAL if a wait of the launches since the status words were zeroed gave up.
+int check_waits(Batch &bt)
+{
+    int *hc = reinterpret_cast<int *>(bt.c->host_scalars + 60);
+    int *dcount = reinterpret_cast<int *>(bt.dstage + (size_t)bt.B * 128);
+    launch_search_count_b(bt.s, bt.d, nullptr, bt.B, dcount);
+    BRC(read_counts(bt, dcount, hc));
+    return (hc[1] & kErrSpin) ? MAG_EINTERNAL : MAG_OK;
+}
+
 // Run steps until no cloud is searching (one count read per step, and one more if
 // refinements go on).  captured: as graphs, for searches that repeat the step some
 // thirty times; a fixed-scale batch takes it once, which a capture does not pay for.
@@ -808,14 +826,13 @@ int run_steps(Batch &bt, const Step &st, bool captured, int max_steps)
             }
             BCHK(hipGraphLaunch(bt.graph[which], bt.s));
         }
-        BCHK(hipMemcpyAsync(hc, st.dcount, 3 * sizeof(int), hipMemcpyDeviceToHost, bt.s));
-        BCHK(hipStreamSynchronize(bt.s));
-        return MAG_OK;
+        return read_counts(bt, st.dcount, hc);
     };
     for (int step = 0; step < max_steps; ++step) {
         BRC(part(0));
+        if (hc[1] == 0 && hc[2] > 0) BRC(part(1));
+        if (hc[1] & kErrSpin) return MAG_EINTERNAL;
         if (hc[1]) return MAG_ENOTPD;  // the FP32 factor broke down at every shift
-        if (hc[2] > 0) BRC(part(1));
         if (hc[0] == 0) return step + 1;
     }
     return MAG_ENOCONV;
@@ -927,6 +944,7 @@ int mag_weighting_batch(mag_ctx *c, int32_t B, const double *X, const int64_t *o
         launch_fill_b(bt.s, bt.d, wr.plist, wr.na, bt.maxpad, bt.sl.Rhs, 1.0, true);
         std::vector<double> bn(B, 1.0);
         BRC(batch_refine(bt, redo, bt.sl.Rhs, bn, o, fb));
+        BRC(check_waits(bt));
     }
     for (int b = 0; b < B; ++b) bt.h[b].active = 1;
     BRC(bt.upload_desc());
@@ -1032,6 +1050,7 @@ int mag_autotune_batch(mag_ctx *c, int32_t B, const double *X, const int64_t *of
     if (e0) hipEventDestroy(e0);
     if (e1) hipEventDestroy(e1);
     if (rc != MAG_OK) return rc;
+    BRC(check_waits(bt));
     const int pick = best[0] < best[1] ? 1 : 2;
     c->tune_bgroup[size_bucket(bt.maxpad)] = pick;
     if (group_out) *group_out = pick;

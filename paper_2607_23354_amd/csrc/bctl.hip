@@ -294,7 +294,7 @@ __global__ void k_search_select_b(BProb *__restrict__ P, SState *__restrict__ S,
         // the FP32 factor broke down at this scale: retake it with a larger diagonal shift
         q.shift = (q.shift == 0.0) ? 1e-6 * fmax(1.0, sqrt((double)p.n)) : q.shift * 10.0;
         if (++q.attempts > 6) {
-            q.err = 1;
+            q.err = kErrBreakdown;
             q.phase = 2;
             return;
         }
@@ -482,8 +482,11 @@ __global__ void __launch_bounds__(256) k_search_count_b(const BProb *__restrict_
     __shared__ int cnt[256], err[256], parked[256];
     int c = 0, e = 0, k = 0;
     for (int b = threadIdx.x; b < B; b += 256) {
-        c += (S[b].phase != 2) ? 1 : 0;
-        e |= S[b].err;
+        if (S) {
+            c += (S[b].phase != 2) ? 1 : 0;
+            e |= S[b].err;
+        }
+        if (P[b].ints[kStSpinTimeout]) e |= kErrSpin;
         k += P[b].ints[kIntParked] != 0 ? 1 : 0;
     }
     cnt[threadIdx.x] = c;

@@ -33,7 +33,7 @@ constexpr int64_t kSplitStrip = 4096;
 // update with K = 2 nb applies both panels to the rest.  Each tile of the large
 // trailing block is read and written once per two panels.
 void chol32_factor(hipStream_t s, float *A, int64_t npad, int64_t n, float *dinv, int *status,
-                   FactorTimer *timer, int nb_max, void *img, void *work)
+                   FactorTimer *timer, int nb_max, void *img, void *work, long spin_limit)
 {
     const int64_t kNb = (nb_max == 256) ? 256 : 512;
     int64_t k = 0;
@@ -41,7 +41,7 @@ void chol32_factor(hipStream_t s, float *A, int64_t npad, int64_t n, float *dinv
     launch_panel_begin(s, work);
     while (k < npad) {
         const int64_t nb = std::min<int64_t>(kNb, npad - k);
-        launch_panel(s, A, npad, k, nb, n, dinv, status, work, panels++);
+        launch_panel(s, A, npad, k, nb, n, dinv, status, work, panels++, spin_limit);
         const int64_t k2 = k + nb;
         if (k2 >= npad) break;
         const int64_t nb2 = std::min<int64_t>(kNb, npad - k2);
@@ -59,7 +59,7 @@ void chol32_factor(hipStream_t s, float *A, int64_t npad, int64_t n, float *dinv
                 launch_gemm_rows64(s, C, npad, P, npad, P, npad, below, nb2, nb);
             }
         }
-        launch_panel(s, A, npad, k2, nb2, n, dinv, status, work, panels++);
+        launch_panel(s, A, npad, k2, nb2, n, dinv, status, work, panels++, spin_limit);
         const int64_t k3 = k2 + nb2;
         const int64_t trail = npad - k3;
         if (trail > 0) {

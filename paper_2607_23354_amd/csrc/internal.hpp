@@ -225,7 +225,7 @@ int64_t prec_b_units(int64_t npad);
 // leaves them so; rhs_slot, tmp_slot and x_slot differ
 void launch_prec_begin_b(hipStream_t s, const BProb *P, int B, int tmp_slot);
 void launch_prec_apply_b(hipStream_t s, const BProb *P, const BWork &w, int rhs_slot, int tmp_slot,
-                         int x_slot);
+                         int x_slot, long spin_limit);
 int zmv_b_tile(int64_t tiles128);
 size_t zmv_b_partial_doubles(int64_t n, int ts);
 int64_t zmv_b_units(int64_t n, int m, int ts);
@@ -279,7 +279,9 @@ void launch_search_deriv_b(hipStream_t s, BProb *P, SState *S, int B);
 // put aside / take up again the refinements of a phase (F_SEARCH or F_NEEDD) that go on
 void launch_park_b(hipStream_t s, BProb *P, int B, int phase);
 void launch_unpark_b(hipStream_t s, BProb *P, int B, int phase);
-// out[0] = clouds still searching, out[1] = any error, out[2] = refinements parked
+// out[0] = clouds still searching (S not NULL), out[1] = kErr* of any cloud, out[2] =
+// refinements parked
+enum : int { kErrBreakdown = 1, kErrSpin = 2 };
 void launch_search_count_b(hipStream_t s, const BProb *P, const SState *S, int B, int *out);
 void launch_unpack_b(hipStream_t s, const BProb *P, const int *plist, int na, const int64_t *offs, int slot,
                      double *out, int64_t maxn);
@@ -320,7 +322,8 @@ struct mag_ctx {
     int tune_bgroup[64] = {};
     // cap on the device bytes held by the buffers above (0: none)
     size_t ws_limit = 0;
-    // polls of one substitution wait before MAG_EINTERNAL (0: kSpinLimitDefault)
+    // polls of one wait between workgroups before MAG_EINTERNAL (0: kSpinLimitDefault,
+    // kPanelSpinLimit)
     int64_t spin_limit = 0;
 };
 
@@ -348,9 +351,10 @@ struct FactorTimer {
 };
 // nb: panel width, 256 or 512 (npad is a multiple of 256).  img: room for
 // chol32_image_bytes(npad, nb) bytes, or NULL: the trailing updates then run on
-// the FP32 matrix instruction.  work: the context's panel buffer.
+// the FP32 matrix instruction.  work: the context's panel buffer; spin_limit: polls of
+// one of its waits.
 void chol32_factor(hipStream_t s, float *A, int64_t npad, int64_t n, float *dinv, int *status,
-                   FactorTimer *timer, int nb, void *img, void *work);
+                   FactorTimer *timer, int nb, void *img, void *work, long spin_limit);
 size_t chol32_image_bytes(int64_t npad, int nb);
 // The context's buffer for that image, or NULL when the context's cap or the
 // device has no room for it.
@@ -441,15 +445,16 @@ void chol64_factor(hipStream_t s, double *A, int64_t npad, int64_t n, double *di
 // place, L^T in the upper triangle, the inverses of its 128 x 128 diagonal blocks
 // (column-major) into dinv.  Rows from n on are identity padding.  Breakdown ->
 // status.  work: panel_work_bytes() of the context; launch_panel_begin before
-// the first panel of a factor, whose panels count index up from 0.
+// the first panel of a factor, whose panels count index up from 0.  A wait that gives
+// up after spin_limit polls sets status[kStSpinTimeout]; the kernel still finishes.
 size_t panel_work_bytes();
 void launch_panel_begin(hipStream_t s, void *work);
 void launch_panel(hipStream_t s, float *A, int64_t ld, int64_t k, int64_t nb, int64_t n, float *dinv, int *status,
-                  void *work, int index);
+                  void *work, int index, long spin_limit);
 // batched: the panel of (up to) 512 columns at k of every active problem (BProb::panel)
 int64_t panel_b_units(int64_t npad, int64_t k);
 void launch_panel_begin_b(hipStream_t s, const BProb *P, int B);
-void launch_panel_b(hipStream_t s, const BProb *P, const BWork &w, int64_t k);
+void launch_panel_b(hipStream_t s, const BProb *P, const BWork &w, int64_t k, long spin_limit);
 
 // gemv64.hip: FP64 matrix-free products with Z regenerated from X.
 //   mode 0: y = Z v;  mode 1: y = b - Z v (b may be NULL meaning ones) and
@@ -475,9 +480,11 @@ size_t zmv_split_partial_doubles(int64_t n);
 // once per device (with that device current) by mag_create.
 int noalloc_setup(int device);
 
-// Polls of one wait of the sync-free substitutions before they give up and
-// report MAG_EINTERNAL (mag_set_spin_limit overrides it per context).
-constexpr long kSpinLimitDefault = 1L << 26;
+// Polls of one wait of the sync-free substitutions, and of the panels, before they give
+// up and the call reports MAG_EINTERNAL (mag_set_spin_limit overrides both per context).
+constexpr long kSpinLimitDefault = 1L << 26, kPanelSpinLimit = 1L << 22;
+inline long spin_limit_of(const mag_ctx *c) { return c->spin_limit > 0 ? (long)c->spin_limit : kSpinLimitDefault; }
+inline long panel_spin_limit_of(const mag_ctx *c) { return c->spin_limit > 0 ? (long)c->spin_limit : kPanelSpinLimit; }
 // trsv.hip: z = L^{-T} L^{-1} r with the FP32 factor, FP64 arithmetic, by the
 // one-block-per-workgroup substitution with a composite near step.  Q: the near
 // tiles of launch_near_q for this factor (required).  r, y_tmp and z are three

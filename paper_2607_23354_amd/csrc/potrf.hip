@@ -57,7 +57,6 @@ constexpr int SB = 16;            // block edge
 constexpr int NBLK = NB / SB;     // blocks per row = waves
 constexpr int NTP = 64 * NBLK;    // threads
 constexpr int kPanelSteps = 32;   // 16-column steps of the widest panel (512 columns)
-constexpr long kPanelSpinLimit = 1L << 22;  // polls of one wait (seconds: never reached by a running panel)
 
 __device__ inline float bcast(float v, int src_lane)
 {
@@ -742,7 +741,7 @@ constexpr size_t kExchangeBytes = (size_t)kPanelBlocks * kBlockWords * 8;
 static_assert(kExchangeBytes % 4096 == 0, "whole workgroups of k_unset");
 
 __device__ __host__ inline PanelArgs panel_args(float *A, int64_t ld, int64_t k, int64_t nb, int64_t n, float *dinv,
-                                                int *status, void *work, int index)
+                                                int *status, void *work, int index, long spin_limit)
 {
     char *w = (char *)work;
     PanelArgs a;
@@ -756,7 +755,7 @@ __device__ __host__ inline PanelArgs panel_args(float *A, int64_t ld, int64_t k,
     a.ticket = (int *)(w + 2 * kExchangeBytes);
     a.xch = (uint64_t *)(w + (index & 1) * kExchangeBytes);
     a.xnext = (uint64_t *)(w + (~index & 1) * kExchangeBytes);
-    a.spin_limit = kPanelSpinLimit;
+    a.spin_limit = spin_limit;
     return a;
 }
 
@@ -764,14 +763,14 @@ __device__ __host__ inline PanelArgs panel_args(float *A, int64_t ld, int64_t k,
 // a problem's workgroups are consecutive, so its first ones, which the others wait
 // for, are dispatched first.
 __global__ void __launch_bounds__(NTP)
-k_panel_b(const BProb *__restrict__ P, BWork w, int64_t k)
+k_panel_b(const BProb *__restrict__ P, BWork w, int64_t k, long spin_limit)
 {
     const int i = bfind(w.pref, w.na, blockIdx.x);
     const BProb &q = P[w.plist[i]];
     if (!q.active) return;
     const int64_t left = q.npad - k;
     panel_body(panel_args(q.A, q.npad, k, left < NB * MT ? left : NB * MT, q.n, q.dinv, q.ints, q.panel,
-                          (int)(k / (NB * MT))),
+                          (int)(k / (NB * MT)), spin_limit),
                (int)(blockIdx.x - w.pref[i]), (int)(left / NB));
 }
 
@@ -811,10 +810,10 @@ void launch_panel_begin(hipStream_t s, void *work)
 }
 
 void launch_panel(hipStream_t s, float *A, int64_t ld, int64_t k, int64_t nb, int64_t n, float *dinv, int *status,
-                  void *work, int index)
+                  void *work, int index, long spin_limit)
 {
     hipLaunchKernelGGL(k_panel, dim3((unsigned)((ld - k) / NB)), dim3(NTP), 0, s,
-                       panel_args(A, ld, k, nb, n, dinv, status, work, index));
+                       panel_args(A, ld, k, nb, n, dinv, status, work, index, spin_limit));
 }
 
 int64_t panel_b_units(int64_t npad, int64_t k) { return k < npad ? (npad - k) / NB : 0; }
@@ -824,9 +823,9 @@ void launch_panel_begin_b(hipStream_t s, const BProb *P, int B)
     hipLaunchKernelGGL(k_unset_b, dim3(kExchangeBytes / 4096, (unsigned)B), dim3(256), 0, s, P);
 }
 
-void launch_panel_b(hipStream_t s, const BProb *P, const BWork &w, int64_t k)
+void launch_panel_b(hipStream_t s, const BProb *P, const BWork &w, int64_t k, long spin_limit)
 {
-    if (w.total > 0) hipLaunchKernelGGL(k_panel_b, dim3((unsigned)w.total), dim3(NTP), 0, s, P, w, k);
+    if (w.total > 0) hipLaunchKernelGGL(k_panel_b, dim3((unsigned)w.total), dim3(NTP), 0, s, P, w, k, spin_limit);
 }
 
 }  // namespace mag

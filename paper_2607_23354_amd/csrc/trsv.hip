@@ -682,14 +682,14 @@ k_near_q_b(const BProb *__restrict__ P, BWork w)
 // forward-progress argument holds per problem; problems never wait on each other.
 template <bool BWD>
 __global__ void __launch_bounds__(512)
-k_trsv_b(const BProb *__restrict__ P, BWork w, int rhs_slot, int x_slot, int z_slot)
+k_trsv_b(const BProb *__restrict__ P, BWork w, int rhs_slot, int x_slot, int z_slot, long spin_limit)
 {
     const int i = bfind(w.pref, w.na, blockIdx.x);
     const BProb &q = P[w.plist[i]];
     if (!q.active) return;
     trsv1_body<BWD, true>(q.A, q.npad, q.dinv, nullptr, q.vec + (int64_t)rhs_slot * q.npad,
                           q.vec + (int64_t)x_slot * q.npad, q.vec + (int64_t)z_slot * q.npad, q.ints + 64,
-                          (int)(q.npad / 128), q.ints, kSpinLimitDefault);
+                          (int)(q.npad / 128), q.ints, spin_limit);
 }
 
 // Tickets zero and the vector in `slot` unset, one workgroup per problem.
@@ -735,11 +735,13 @@ void launch_prec_begin_b(hipStream_t s, const BProb *P, int B, int tmp_slot)
 
 // x_slot = (L L^T)^{-1} rhs_slot for every problem of the work list (units = npad/128 each)
 void launch_prec_apply_b(hipStream_t s, const BProb *P, const BWork &w, int rhs_slot, int tmp_slot,
-                         int x_slot)
+                         int x_slot, long spin_limit)
 {
     if (w.na <= 0) return;
-    hipLaunchKernelGGL(k_trsv_b<false>, dim3((unsigned)w.total), dim3(512), 0, s, P, w, rhs_slot, tmp_slot, x_slot);
-    hipLaunchKernelGGL(k_trsv_b<true>, dim3((unsigned)w.total), dim3(512), 0, s, P, w, tmp_slot, x_slot, tmp_slot);
+    hipLaunchKernelGGL(k_trsv_b<false>, dim3((unsigned)w.total), dim3(512), 0, s, P, w, rhs_slot, tmp_slot, x_slot,
+                       spin_limit);
+    hipLaunchKernelGGL(k_trsv_b<true>, dim3((unsigned)w.total), dim3(512), 0, s, P, w, tmp_slot, x_slot, tmp_slot,
+                       spin_limit);
 }
 
 void launch_refine_begin(hipStream_t s, double *y_tmp, double *rhs, int64_t n, int64_t npad, int *counters,
