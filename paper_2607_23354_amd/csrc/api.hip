@@ -326,17 +326,21 @@ struct RefineStats {
 // ||b - Z x||_inf <= tol * max(1, ||b||_inf), on stagnation, or at the iteration
 // limits.
 //
-// x0 = M^{-1} b and one plain step x1 = x0 + M^{-1}(b - Z x0) are enqueued with
-// both residuals before the host looks at either: nearly every solve needs x1,
-// and most need no more, so such a solve is one round trip (the device writes
-// xout itself if x1 is the answer, launch_finish).  kRetry: the factor enqueued
-// before it (begun) broke down or saw bad points; see st.status.
-// prec(in, out, tmp): out = M^{-1} in for device npad vectors (tmp: npad scratch)
-using PrecFn = std::function<void(const double *, double *, double *)>;
+// x0 = M^{-1} b and, with an FP32 factor (gated), one plain step x1 = x0 +
+// M^{-1}(b - Z x0) are enqueued with both residuals before the host looks at either:
+// nearly every solve needs x1, and most need no more, so such a solve is one round trip
+// (the device writes xout itself if x1 is the answer, launch_finish).  The step's launches
+// stand behind a gate on x0's residual: a solve whose x0 meets a loose tol pays for empty
+// launches alone (tol 1e-4, n = 16384: refinement 0.80 ms, 1.49 ms with the step's pass,
+// 0.76 ms with nothing enqueued).  Hierarchical applies are many launches and take
+// the trip instead (0.85 against 1.70 ms for a loose tol at n = 16384).
+// kRetry: the factor enqueued before it (begun) broke down or saw bad points; see st.status.
+// prec(in, out, tmp, gate): out = M^{-1} in for device npad vectors (tmp: npad scratch)
+using PrecFn = std::function<void(const double *, double *, double *, const Gate &)>;
 
 int refine_core(mag_ctx *ctx, const double *X, int64_t n, int m, double t, int64_t npad,
                 const PrecFn &prec, const double *b, double bnorm, double *xout, int64_t xlen, const mag_opts &o,
-                RefineStats &st, int kernel = kKernExp, bool begun = false)
+                RefineStats &st, int kernel = kKernExp, bool begun = false, bool gated = false)
 {
     hipStream_t s = ctx->stream;
     const int restart = std::max(1, o.gmres_restart);
@@ -362,13 +366,14 @@ int refine_core(mag_ctx *ctx, const double *X, int64_t n, int m, double t, int64
     double *cur = v.x, *spare = v.best, *best = nullptr;
     double *r = v.r, *u = v.u;
     // x0 = M^{-1} b, and the plain step from it
-    prec(bb, cur, v.ytmp);
+    prec(bb, cur, v.ytmp, Gate());
     launch_zmv(s, X, n, m, t, cur, r, bb, 1, partial, cap, v.dsc, false, kernel);
-    const bool spec = max_outer >= 2;
+    const bool spec = gated && max_outer >= 2;
     if (spec) {
-        prec(r, v.z, v.ytmp);
+        const Gate gate{v.dsc, tol};
+        prec(r, v.z, v.ytmp, gate);
         launch_add(s, cur, v.z, spare, npad);
-        launch_zmv(s, X, n, m, t, spare, u, bb, 1, partial, cap, v.dsc + 1, false, kernel);
+        launch_zmv(s, X, n, m, t, spare, u, bb, 1, partial, cap, v.dsc + 1, false, kernel, gate);
         launch_finish(s, spare, n, v.dsc, status, tol, partial, xout, xlen, ctx->report_dev);
     } else {
         launch_norm_report(s, v.dsc, status, ctx->report_dev);
@@ -436,7 +441,7 @@ int refine_core(mag_ctx *ctx, const double *X, int64_t n, int m, double t, int64
             if (outer == 0 && spec) {
                 ahead = true;
             } else {
-                prec(r, v.z, v.ytmp);
+                prec(r, v.z, v.ytmp, Gate());
                 launch_add(s, cur, v.z, spare, npad);
             }
             std::swap(cur, spare);
@@ -455,7 +460,7 @@ int refine_core(mag_ctx *ctx, const double *X, int64_t n, int m, double t, int64
             G.hbuf.resize(2 * (restart + 2) + 2);
         }
         std::vector<double> &hbuf = G.hbuf;
-        prec(r, v.z, v.ytmp);
+        prec(r, v.z, v.ytmp, Gate());
         launch_nrm2(s, v.z, npad, partial, v.dsc + 1);
         HIPCHK(hipMemcpyAsync(ctx->host_scalars + 1, v.dsc + 1, sizeof(double), hipMemcpyDeviceToHost, s));
         HIPCHK(hipStreamSynchronize(s));
@@ -470,7 +475,7 @@ int refine_core(mag_ctx *ctx, const double *X, int64_t n, int m, double t, int64
             double *Vk = v.V + (size_t)k * npad;
             double *Vk1 = v.V + (size_t)(k + 1) * npad;
             launch_zmv(s, X, n, m, t, Vk, u, nullptr, 0, partial, cap, nullptr, f32_inner, kernel);
-            prec(u, Vk1, v.ytmp);
+            prec(u, Vk1, v.ytmp, Gate());
             // classical Gram-Schmidt, twice
             launch_multidot(s, v.V, npad, k + 1, Vk1, npad, partial, v.hdev);
             launch_multi_axpy(s, v.V, npad, k + 1, v.hdev, Vk1, Vk1, npad, -1.0);
@@ -535,10 +540,10 @@ int refine_solve(mag_ctx *ctx, const double *X, int64_t n, int m, double t, cons
     int *status = ints + kIntStatus;
     int *counters = ints + kIntCounters;
     hipStream_t s = ctx->stream;
-    const PrecFn prec = [&](const double *in, double *out, double *tmp) {
-        launch_prec_apply(s, F.A, F.npad, F.dinv, in, tmp, out, counters, status, F.nq, spin_limit_of(ctx));
+    const PrecFn prec = [&](const double *in, double *out, double *tmp, const Gate &gate) {
+        launch_prec_apply(s, F.A, F.npad, F.dinv, in, tmp, out, counters, status, F.nq, spin_limit_of(ctx), gate);
     };
-    const int rc = refine_core(ctx, X, n, m, t, F.npad, prec, b, bnorm, xout, xlen, o, st, kernel, begun);
+    const int rc = refine_core(ctx, X, n, m, t, F.npad, prec, b, bnorm, xout, xlen, o, st, kernel, begun, true);
     return (rc == kRetry && !begun) ? MAG_EINTERNAL : rc;
 }
 
@@ -891,7 +896,7 @@ int solve_hodlr(mag_ctx *ctx, const double *X, int64_t n, int m, double t, doubl
                      o.seed, H));
     tm.mark(1);
     tm.mark(2);
-    const PrecFn prec = [&](const double *in, double *out, double *) { hodlr_apply(s, H, in, out); };
+    const PrecFn prec = [&](const double *in, double *out, double *, const Gate &) { hodlr_apply(s, H, in, out); };
     RefineStats st;
     int rc = refine_core(ctx, X, n, m, t, H.npad, prec, nullptr, 1.0, w, n, o, st);
     if (rc != MAG_OK && rc != MAG_ENOCONV) return rc;
@@ -950,7 +955,7 @@ int solve_hss(mag_ctx *ctx, const double *X, int64_t n, int m, double t, double 
     tm.mark(1);
     tm.mark(2);
     int prc = MAG_OK;
-    const PrecFn prec = [&](const double *in, double *out, double *) {
+    const PrecFn prec = [&](const double *in, double *out, double *, const Gate &) {
         const int e = hss_apply(s, H, in, out);
         if (e != MAG_OK) prc = e;
     };

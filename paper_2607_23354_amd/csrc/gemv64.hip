@@ -338,8 +338,9 @@ __device__ __forceinline__ void zmv_sym_body(const double *__restrict__ X, int64
 template <int M, int TS, int ENT = kEntExp>
 __global__ void __launch_bounds__(256, (M >= 1 && M <= 3) ? 4 : 1)
 k_zmv_sym(const double *__restrict__ X, int64_t n, int m_rt, double t, const double *__restrict__ v,
-          double *__restrict__ part, double *__restrict__ norm)
+          double *__restrict__ part, double *__restrict__ norm, Gate gate)
 {
+    if (gate.closed()) return;
     if (norm && blockIdx.x == 0 && threadIdx.x == 0) *norm = 0.0;
     zmv_sym_body<M, TS, ENT>(X, n, m_rt, t, v, part, blockIdx.x);
 }
@@ -419,8 +420,9 @@ template <int M>
 __global__ void __launch_bounds__(RT)
 k_zmv_partial(const double *__restrict__ X, int64_t n, int m_rt, double t,
               const double *__restrict__ v, double *__restrict__ partial, int64_t cps,
-              int64_t npad, double *__restrict__ norm)
+              int64_t npad, double *__restrict__ norm, Gate gate)
 {
+    if (gate.closed()) return;
     if (norm && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *norm = 0.0;
     zmv_partial_body<M>(X, n, m_rt, t, v, partial, cps, npad, blockIdx.x, blockIdx.y);
 }
@@ -605,52 +607,54 @@ size_t zmv_split_partial_doubles(int64_t n)
 
 // Row-per-thread form (any m): (row blocks) x (column splits), then the split reduce.
 void launch_zmv_split(hipStream_t s, const double *X, int64_t n, int m, double t, const double *v,
-                             double *y, const double *b, int mode, double *partial, double *out_norm)
+                             double *y, const double *b, int mode, double *partial, double *out_norm, Gate gate)
 {
     Plan p = plan_for(n);
     dim3 grid((unsigned)p.rowblocks, (unsigned)p.splits);
     double *norm = mode == 1 ? out_norm : nullptr;
-    hipLaunchKernelGGL(k_zmv_partial<0>, grid, dim3(RT), 0, s, X, n, m, t, v, partial, p.cps, p.npad, norm);
+    hipLaunchKernelGGL(k_zmv_partial<0>, grid, dim3(RT), 0, s, X, n, m, t, v, partial, p.cps, p.npad, norm, gate);
     hipLaunchKernelGGL(k_zmv_reduce, dim3((unsigned)(p.npad / 256)), dim3(256), 0, s, partial, p.npad, n,
                        (int)p.splits, y, b, mode, norm);
 }
 
 template <int ENT, int TS>
 void zmv_sym(hipStream_t s, const double *X, int64_t n, int m, double t, const double *v, double *y, const double *b,
-             int mode, double *partial, double *norm)
+             int mode, double *partial, double *norm, Gate gate)
 {
     const int64_t npad = (n + kPad - 1) / kPad * kPad;
     const int64_t T = npad / TS;
     const dim3 grid((unsigned)(T * (T + 1) / 2));
     switch (m) {
-    case 1: hipLaunchKernelGGL((k_zmv_sym<1, TS, ENT>), grid, dim3(256), 0, s, X, n, m, t, v, partial, norm); break;
-    case 2: hipLaunchKernelGGL((k_zmv_sym<2, TS, ENT>), grid, dim3(256), 0, s, X, n, m, t, v, partial, norm); break;
-    case 3: hipLaunchKernelGGL((k_zmv_sym<3, TS, ENT>), grid, dim3(256), 0, s, X, n, m, t, v, partial, norm); break;
-    case 4: hipLaunchKernelGGL((k_zmv_sym<4, TS, ENT>), grid, dim3(256), 0, s, X, n, m, t, v, partial, norm); break;
-    case 8: hipLaunchKernelGGL((k_zmv_sym<8, TS, ENT>), grid, dim3(256), 0, s, X, n, m, t, v, partial, norm); break;
-    default: hipLaunchKernelGGL((k_zmv_sym<0, TS, ENT>), grid, dim3(256), 0, s, X, n, m, t, v, partial, norm); break;
+    case 1: hipLaunchKernelGGL((k_zmv_sym<1, TS, ENT>), grid, dim3(256), 0, s, X, n, m, t, v, partial, norm, gate); break;
+    case 2: hipLaunchKernelGGL((k_zmv_sym<2, TS, ENT>), grid, dim3(256), 0, s, X, n, m, t, v, partial, norm, gate); break;
+    case 3: hipLaunchKernelGGL((k_zmv_sym<3, TS, ENT>), grid, dim3(256), 0, s, X, n, m, t, v, partial, norm, gate); break;
+    case 4: hipLaunchKernelGGL((k_zmv_sym<4, TS, ENT>), grid, dim3(256), 0, s, X, n, m, t, v, partial, norm, gate); break;
+    case 8: hipLaunchKernelGGL((k_zmv_sym<8, TS, ENT>), grid, dim3(256), 0, s, X, n, m, t, v, partial, norm, gate); break;
+    default: hipLaunchKernelGGL((k_zmv_sym<0, TS, ENT>), grid, dim3(256), 0, s, X, n, m, t, v, partial, norm, gate); break;
     }
     hipLaunchKernelGGL(k_zmv_sym_reduce<TS>, dim3((unsigned)T), dim3(TS), 0, s, partial, T, n, npad, y, b, mode, norm);
 }
 
 template <int ENT>
 void zmv_sym_any(hipStream_t s, const double *X, int64_t n, int m, double t, const double *v, double *y,
-                 const double *b, int mode, double *partial, size_t cap, double *norm)
+                 const double *b, int mode, double *partial, size_t cap, double *norm, Gate gate)
 {
-    if (n <= kSmallTileN && cap >= sym_doubles(n, TSS)) zmv_sym<ENT, TSS>(s, X, n, m, t, v, y, b, mode, partial, norm);
-    else zmv_sym<ENT, TSB>(s, X, n, m, t, v, y, b, mode, partial, norm);
+    if (n <= kSmallTileN && cap >= sym_doubles(n, TSS))
+        zmv_sym<ENT, TSS>(s, X, n, m, t, v, y, b, mode, partial, norm, gate);
+    else
+        zmv_sym<ENT, TSB>(s, X, n, m, t, v, y, b, mode, partial, norm, gate);
 }
 
 void launch_zmv(hipStream_t s, const double *X, int64_t n, int m, double t, const double *v,
                 double *y, const double *b, int mode, double *partial, size_t cap, double *out_norm, bool f32_entries,
-                int kernel)
+                int kernel, Gate gate)
 {
     double *norm = mode == 1 ? out_norm : nullptr;
     // the scale-zero system has m <= 16 only (checked by the caller)
-    if (kernel == kKernShiftDist) zmv_sym_any<kEntShiftDist>(s, X, n, m, t, v, y, b, mode, partial, cap, norm);
-    else if (m > MMAX_SYM) launch_zmv_split(s, X, n, m, t, v, y, b, mode, partial, out_norm);
-    else if (f32_entries) zmv_sym_any<kEntExp32>(s, X, n, m, t, v, y, b, mode, partial, cap, norm);
-    else zmv_sym_any<kEntExp>(s, X, n, m, t, v, y, b, mode, partial, cap, norm);
+    if (kernel == kKernShiftDist) zmv_sym_any<kEntShiftDist>(s, X, n, m, t, v, y, b, mode, partial, cap, norm, gate);
+    else if (m > MMAX_SYM) launch_zmv_split(s, X, n, m, t, v, y, b, mode, partial, out_norm, gate);
+    else if (f32_entries) zmv_sym_any<kEntExp32>(s, X, n, m, t, v, y, b, mode, partial, cap, norm, gate);
+    else zmv_sym_any<kEntExp>(s, X, n, m, t, v, y, b, mode, partial, cap, norm, gate);
 }
 
 }  // namespace mag

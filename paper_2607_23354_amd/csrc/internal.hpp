@@ -135,6 +135,14 @@ struct SParams {
     double lo_factor, rtol;
 };
 
+// A launch enqueued before the host knows whether it is wanted: with norm set, it does
+// nothing if norm[0] <= tol (the iterate it would improve is the answer).
+struct Gate {
+    const double *norm = nullptr;
+    double tol = 0.0;
+    __device__ __forceinline__ bool closed() const { return norm && !(norm[0] > tol); }
+};
+
 // FP64 kernel entry exp(-t d), d = sqrt(s), for the matrix-free products.
 // sqrt_pos: square root of a normal s > 0 from the hardware reciprocal square
 // root estimate, one Goldschmidt step (g ~ sqrt(s), h ~ 1/(2 sqrt(s))) and two
@@ -465,7 +473,8 @@ void launch_panel_b(hipStream_t s, const BProb *P, const BWork &w, int64_t k, lo
 //   t - d of the scale-zero system c 1 1^T - d with c passed as t (m <= 16).
 void launch_zmv(hipStream_t s, const double *X, int64_t n, int m, double t,
                 const double *v, double *y, const double *b, int mode,
-                double *partial, size_t cap, double *out_norm, bool f32_entries = false, int kernel = kKernExp);
+                double *partial, size_t cap, double *out_norm, bool f32_entries = false, int kernel = kKernExp,
+                Gate gate = Gate());
 // partial holds cap doubles: zmv_partial_doubles(n), or zmv_min_partial_doubles(n)
 // where memory is short (128-edged tiles at every n).
 size_t zmv_partial_doubles(int64_t n);
@@ -474,7 +483,7 @@ size_t zmv_min_partial_doubles(int64_t n);
 // needs zmv_split_partial_doubles(n) doubles, y npad doubles; the max norm of
 // mode 1 goes to out_norm (may be NULL).
 void launch_zmv_split(hipStream_t s, const double *X, int64_t n, int m, double t, const double *v,
-                      double *y, const double *b, int mode, double *partial, double *out_norm);
+                      double *y, const double *b, int mode, double *partial, double *out_norm, Gate gate = Gate());
 size_t zmv_split_partial_doubles(int64_t n);
 // Per-device address of the no-allocation entry point's scratch array, taken
 // once per device (with that device current) by mag_create.
@@ -492,7 +501,7 @@ inline long panel_spin_limit_of(const mag_ctx *c) { return c->spin_limit > 0 ? (
 // apply restores.
 void launch_prec_apply(hipStream_t s, const float *L, int64_t npad, const float *dinv,
                        const double *r, double *y_tmp, double *z, int *counters, int *status,
-                       const float *Q, long spin_limit);
+                       const float *Q, long spin_limit, Gate gate = Gate());
 // The near tiles D_b T(b, b -/+ 1) of every 128-block of the FP32 factor, both
 // directions (near_q_floats(npad) floats), from the factor and its inverses.
 size_t near_q_floats(int64_t npad);

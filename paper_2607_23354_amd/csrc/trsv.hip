@@ -378,7 +378,7 @@ template <bool BWD, bool INPLACE>
 __device__ __forceinline__ void trsv1_body(const float *__restrict__ L, int64_t ld, const float *__restrict__ dinv,
                                            const float *__restrict__ Qb, double *__restrict__ rhs,
                                            double *__restrict__ x, double *__restrict__ z, int *counters, int nblk,
-                                           int *status, long spin_limit)
+                                           int *status, long spin_limit, const Gate &gate)
 {
     constexpr int BS = 128, NW = 8, NT = 64 * NW;
     constexpr int WC = BS / NW;          // columns of a wave
@@ -392,11 +392,13 @@ __device__ __forceinline__ void trsv1_body(const float *__restrict__ L, int64_t 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (tid == 0) {
+        // (the tickets are taken, and left for the next solve, behind a closed gate too)
         const int ticket = take_ticket<BWD>(counters);
-        s_blk = BWD ? nblk - 1 - ticket : ticket;
+        s_blk = gate.closed() ? -1 : BWD ? nblk - 1 - ticket : ticket;
     }
     __syncthreads();
     const int b = s_blk;
+    if (b < 0) return;
     const int rg = lane & 31, ch = lane >> 5;     // tile products: rows 4 rg .., columns TC ch .. of the wave's
     const int row = tid & (BS - 1), h = tid >> 7;  // block product: part h of row's sum
     using Tile = Quad<float>[TC];
@@ -537,9 +539,9 @@ template <bool BWD>
 __global__ void __launch_bounds__(512)
 k_trsv1(const float *__restrict__ L, int64_t ld, const float *__restrict__ dinv, const float *__restrict__ Qb,
         double *__restrict__ rhs, double *__restrict__ x, double *__restrict__ z, int *counters, int nblk, int *status,
-        long spin_limit)
+        long spin_limit, Gate gate)
 {
-    trsv1_body<BWD, false>(L, ld, dinv, Qb, rhs, x, z, counters, nblk, status, spin_limit);
+    trsv1_body<BWD, false>(L, ld, dinv, Qb, rhs, x, z, counters, nblk, status, spin_limit, gate);
 }
 
 // The near tiles of k_trsv1 for every 128-block of the FP32 factor, both
@@ -689,7 +691,7 @@ k_trsv_b(const BProb *__restrict__ P, BWork w, int rhs_slot, int x_slot, int z_s
     if (!q.active) return;
     trsv1_body<BWD, true>(q.A, q.npad, q.dinv, nullptr, q.vec + (int64_t)rhs_slot * q.npad,
                           q.vec + (int64_t)x_slot * q.npad, q.vec + (int64_t)z_slot * q.npad, q.ints + 64,
-                          (int)(q.npad / 128), q.ints, spin_limit);
+                          (int)(q.npad / 128), q.ints, spin_limit, Gate());
 }
 
 // Tickets zero and the vector in `slot` unset, one workgroup per problem.
@@ -765,15 +767,15 @@ void prec_apply(hipStream_t s, const T *L, int64_t npad, const T *dinv, const do
 
 void launch_prec_apply(hipStream_t s, const float *L, int64_t npad, const float *dinv,
                        const double *r, double *y_tmp, double *z, int *counters, int *status, const float *Q,
-                       long spin_limit)
+                       long spin_limit, Gate gate)
 {
     const int nblk = (int)(npad / 128);
     const float *Qb = Q + (int64_t)nblk * 128 * 128;  // the backward direction's tiles
     double *rhs = const_cast<double *>(r);  // the forward solve only reads it
     hipLaunchKernelGGL(k_trsv1<false>, dim3(nblk), dim3(512), 0, s, L, npad, dinv, Q, rhs, y_tmp, z, counters, nblk,
-                       status, spin_limit);
+                       status, spin_limit, gate);
     hipLaunchKernelGGL(k_trsv1<true>, dim3(nblk), dim3(512), 0, s, L, npad, dinv, Qb, y_tmp, z, (double *)nullptr,
-                       counters, nblk, status, spin_limit);
+                       counters, nblk, status, spin_limit, gate);
 }
 
 size_t near_q_floats(int64_t npad) { return (size_t)npad * 256; }
