@@ -57,6 +57,20 @@ static bool drop_optional(mag_ctx *ctx)
     return true;
 }
 
+// hipMalloc; where the device is full, what can be done without makes way (not for another
+// such buffer).
+static int device_alloc(mag_ctx *ctx, void **p, size_t bytes, bool optional = false)
+{
+    if (hipMalloc(p, bytes) == hipSuccess) return MAG_OK;
+    (void)hipGetLastError();
+    if (!optional && drop_optional(ctx)) {
+        if (hipMalloc(p, bytes) == hipSuccess) return MAG_OK;
+        (void)hipGetLastError();
+    }
+    *p = nullptr;
+    return MAG_ENOMEM;
+}
+
 int ctx_may_allocate(mag_ctx *c, size_t extra)
 {
     if (c->ws_limit == 0) return MAG_OK;
@@ -77,16 +91,7 @@ int ensure(mag_ctx *ctx, DevBuf &b, size_t bytes)
         b.p = nullptr;
         b.bytes = 0;
     }
-    hipError_t e = hipMalloc(&b.p, bytes);
-    if (e != hipSuccess && !optional && drop_optional(ctx)) {
-        (void)hipGetLastError();
-        e = hipMalloc(&b.p, bytes);
-    }
-    if (e != hipSuccess) {
-        (void)hipGetLastError();
-        b.p = nullptr;
-        return MAG_ENOMEM;
-    }
+    if (device_alloc(ctx, &b.p, bytes, optional) != MAG_OK) return MAG_ENOMEM;
     b.bytes = bytes;
     return MAG_OK;
 }
@@ -1654,7 +1659,7 @@ int mag_magnitude(mag_ctx *c, const double *X, int64_t n, int32_t m, double t, d
         if (!valid_args(X, n, m, t)) return MAG_EINVAL;
         HIPCHK(hipSetDevice(c->device));
         CHK(ctx_may_allocate(c, sizeof(double) * n));
-        if (hipMalloc(&tmp.p, sizeof(double) * n) != hipSuccess) return MAG_ENOMEM;
+        CHK(device_alloc(c, &tmp.p, sizeof(double) * n));
         wbuf = (double *)tmp.p;
     }
     int rc = mag_weighting(c, X, n, m, t, wbuf, opts, inf);
@@ -2225,10 +2230,9 @@ int mag_weighting_fwd(mag_ctx *c, const double *X, int64_t n, int32_t m, double 
     f->m = m;
     f->t = t;
     f->F.npad = round_up(n, kPad);
-    if (hipMalloc((void **)&f->F.A, sizeof(float) * (size_t)f->F.npad * f->F.npad) != hipSuccess ||
-        hipMalloc((void **)&f->F.dinv,
-                  sizeof(float) * ((size_t)f->F.npad * kTile + near_q_floats(f->F.npad))) != hipSuccess) {
-        (void)hipGetLastError();
+    if (device_alloc(c, (void **)&f->F.A, sizeof(float) * (size_t)f->F.npad * f->F.npad) != MAG_OK ||
+        device_alloc(c, (void **)&f->F.dinv,
+                     sizeof(float) * ((size_t)f->F.npad * kTile + near_q_floats(f->F.npad))) != MAG_OK) {
         mag_factor_free(f);
         return MAG_ENOMEM;
     }
