@@ -56,8 +56,9 @@ void mag_destroy(mag_ctx *ctx);
  * default unless the environment variable MAG_WORKSPACE_LIMIT holds a byte
  * count, optionally with a K, M or G suffix, when the context is created).
  * A call whose workspace would exceed the cap returns MAG_ENOMEM without
- * allocating; buffers already held are kept.  *held (HOST, may be NULL)
- * receives the bytes held now. */
+ * allocating; buffers already held are kept, but for scratch that only saves
+ * time, which makes way.  *held (HOST) receives the bytes held now.  Neither
+ * counts the 1.6 MB that mag_create allocates once for the factor's panels. */
 int mag_set_workspace_limit(mag_ctx *ctx, uint64_t bytes);
 int mag_workspace_bytes(const mag_ctx *ctx, uint64_t *held);
 

@@ -1414,11 +1414,6 @@ int mag_create(mag_ctx **out, int device)
         mag_destroy(c);
         return MAG_ENOMEM;
     }
-    launch_fill_ints(c->stream, (int *)c->panel, (int64_t)(panel_work_bytes() / sizeof(int)), 0);
-    if (hipStreamSynchronize(c->stream) != hipSuccess) {
-        mag_destroy(c);
-        return MAG_EHIP;
-    }
     *out = c;
     return MAG_OK;
 }

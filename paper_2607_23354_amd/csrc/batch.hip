@@ -169,7 +169,8 @@ size_t batch_partial_doubles(int64_t n, int restart, int ts)
 
 // Allocate every problem's buffers and the descriptors.  items: (X, n, t).
 int batch_setup(mag_ctx *c, Batch &bt, const std::vector<const double *> &Xs,
-                const std::vector<int64_t> &ns, int m, const std::vector<double> &ts, int restart)
+                const std::vector<int64_t> &ns, int m, const std::vector<double> &ts, int restart,
+                bool both_groups = false)
 {
     bt.c = c;
     bt.s = c->stream;
@@ -232,10 +233,12 @@ int batch_setup(mag_ctx *c, Batch &bt, const std::vector<const double *> &Xs,
     for (int b = 0; b < B; ++b) img += image(np[b]);
     const bool split = img > 0 && ensure(c, c->split, img) == MAG_OK;
     // and the panel kernel's exchanges, likewise
-    const bool fresh = c->bpanel.bytes < panel_work_bytes() * B;
-    const bool panels = ensure(c, c->bpanel, panel_work_bytes() * B) == MAG_OK;
-    if (panels && fresh) BCHK(hipMemsetAsync(c->bpanel.p, 0, c->bpanel.bytes, bt.s));  // the tickets, once
+    // (single panels, group 1, run without them)
+    size_t exch = 0;
+    for (int b = 0; b < B; ++b) exch += panel_b_work_bytes(np[b]);
+    const bool panels = (both_groups || c->tune_bgroup[size_bucket(bt.maxpad)] != 1) && ensure(c, c->bpanel, exch) == MAG_OK;
     char *ip = (char *)c->split.p;
+    char *xp = (char *)c->bpanel.p;
     float *fp = (float *)c->bfactor.p;
     float *dp = (float *)c->bdinv.p;
     double *vp = (double *)c->bvec.p;
@@ -261,7 +264,8 @@ int batch_setup(mag_ctx *c, Batch &bt, const std::vector<const double *> &Xs,
         q.active = 1;
         q.img = split ? ip : nullptr;
         ip += image(np[b]);
-        q.panel = panels ? (char *)c->bpanel.p + panel_work_bytes() * b : nullptr;
+        q.panel = panels ? xp : nullptr;
+        xp += panel_b_work_bytes(np[b]);
     }
     BCHK(hipMemsetAsync(c->bvec.p, 0, sizeof(double) * vec, bt.s));
     BCHK(hipMemsetAsync(c->bscal.p, 0, sizeof(double) * (size_t)B * SC_COUNT, bt.s));
@@ -401,7 +405,7 @@ void record_factor(Batch &bt, const std::vector<FLaunch> &seq)
         case 8: launch_split_b(bt.s, bt.d, L.w, L.kk, L.K); break;
         case 9: launch_syrk_split_b(bt.s, bt.d, L.w, L.kk, L.K); break;
         case 12: launch_near_q_b(bt.s, bt.d, L.w); break;
-        case 10: launch_panel_begin_b(bt.s, bt.d, bt.B); break;
+        case 10: launch_panel_begin_b(bt.s, bt.d, bt.B, bt.maxpad); break;
         case 11: launch_panel_b(bt.s, bt.d, L.w, L.kk, panel_spin_limit_of(bt.c)); break;
         default: launch_gemm_b(bt.s, L.kind, bt.d, L.w, L.kk); break;
         }
@@ -1007,7 +1011,7 @@ int mag_autotune_batch(mag_ctx *c, int32_t B, const double *X, const int64_t *of
         ts[b] = t[b];
     }
     Batch bt;
-    BRC(batch_setup(c, bt, Xs, ns, m, ts, 1));
+    BRC(batch_setup(c, bt, Xs, ns, m, ts, 1, true));
     std::vector<double> dmin2;
     BRC(batch_validate(bt, dmin2));
     // the two schedules' launch sequences, each captured into a graph of its own

@@ -38,7 +38,7 @@ void chol32_factor(hipStream_t s, float *A, int64_t npad, int64_t n, float *dinv
     const int64_t kNb = (nb_max == 256) ? 256 : 512;
     int64_t k = 0;
     int panels = 0;
-    launch_panel_begin(s, work);
+    launch_panel_begin(s, work, std::min<int64_t>(kNb, npad));
     while (k < npad) {
         const int64_t nb = std::min<int64_t>(kNb, npad - k);
         launch_panel(s, A, npad, k, nb, n, dinv, status, work, panels++, spin_limit);

@@ -452,16 +452,17 @@ void chol64_factor(hipStream_t s, double *A, int64_t npad, int64_t n, double *di
 // potrf.hip: the FP32 factor's panel of nb (256 or 512) columns at k in one launch: L in
 // place, L^T in the upper triangle, the inverses of its 128 x 128 diagonal blocks
 // (column-major) into dinv.  Rows from n on are identity padding.  Breakdown ->
-// status.  work: panel_work_bytes() of the context; launch_panel_begin before
-// the first panel of a factor, whose panels count index up from 0.  A wait that gives
+// status.  work: panel_work_bytes() of the context; launch_panel_begin (nb: the first
+// panel's) before the first panel of a factor, whose panels count index up from 0.  A wait that gives
 // up after spin_limit polls sets status[kStSpinTimeout]; the kernel still finishes.
 size_t panel_work_bytes();
-void launch_panel_begin(hipStream_t s, void *work);
+void launch_panel_begin(hipStream_t s, void *work, int64_t nb);
 void launch_panel(hipStream_t s, float *A, int64_t ld, int64_t k, int64_t nb, int64_t n, float *dinv, int *status,
                   void *work, int index, long spin_limit);
 // batched: the panel of (up to) 512 columns at k of every active problem (BProb::panel)
 int64_t panel_b_units(int64_t npad, int64_t k);
-void launch_panel_begin_b(hipStream_t s, const BProb *P, int B);
+size_t panel_b_work_bytes(int64_t npad);
+void launch_panel_begin_b(hipStream_t s, const BProb *P, int B, int64_t maxpad);
 void launch_panel_b(hipStream_t s, const BProb *P, const BWork &w, int64_t k, long spin_limit);
 
 // gemv64.hip: FP64 matrix-free products with Z regenerated from X.

@@ -47,6 +47,8 @@
 // the host then refactors with a diagonal shift.
 #include "internal.hpp"
 
+#include <algorithm>
+
 namespace mag {
 namespace {
 
@@ -265,13 +267,21 @@ __device__ __forceinline__ void four_blocks(v4f *acc, const SplitX &x, const Spl
 // there yet.
 constexpr uint32_t kUnset = 0x7fa5f00du;  // a signalling NaN, in BF16 too (arithmetic yields quiet ones)
 constexpr int kBlockWords = 192;          // 8-byte words
-constexpr int kPanelBlocks = kPanelSteps * (kPanelSteps + 1) / 2;
 
-// Block of 16-row block row R >= g at 16-column step g of the panel's top block.
-__device__ __forceinline__ uint64_t *xblock(uint64_t *xch, int g, int R)
+// Block of 16-row block row R >= g at 16-column step g of the top block of a panel of
+// 16 `steps` columns (a step's blocks stand together).
+__device__ __forceinline__ uint64_t *xblock(uint64_t *xch, int steps, int g, int R)
 {
-    return xch + (g * kPanelSteps - g * (g + 1) / 2 + R) * kBlockWords;
+    return xch + (g * steps - g * (g + 1) / 2 + R) * kBlockWords;
 }
+
+// Bytes of the exchange of a panel of `cols` columns.
+__host__ __device__ constexpr int64_t exchange_bytes(int64_t cols)
+{
+    const int64_t R = cols / SB;
+    return R * (R + 1) / 2 * kBlockWords * 8;
+}
+static_assert(exchange_bytes(256) % 4096 == 0 && exchange_bytes(512) % 4096 == 0, "whole workgroups of k_unset");
 
 __device__ __forceinline__ v2u ld_plane(const uint64_t *p, int c, int lane)
 {
@@ -299,7 +309,7 @@ __device__ __forceinline__ void st_split(uint64_t *p, int lane, const Split &s)
 template <bool PUB>
 __device__ __forceinline__ void factor128(v4f (&Q)[NBLK], const v4f &dg, float *__restrict__ Ab, int64_t ld, int64_t k0,
                                           float *__restrict__ Linv, int *__restrict__ status, v4f (*Lx)[64], float *Yd,
-                                          int &bad, int I, int lane, uint64_t *xch, int g0)
+                                          int &bad, int I, int lane, uint64_t *xch, int steps, int g0)
 {
     const int g = lane >> 4, i = lane & 15;
     v4f P = dg, P0, X;
@@ -322,7 +332,7 @@ __device__ __forceinline__ void factor128(v4f (&Q)[NBLK], const v4f &dg, float *
         if (I != j) {
             const v4f y = *reinterpret_cast<const v4f *>(Yd + i * SB + 4 * g);
             if (PUB && I == ((j + 2) & (NBLK - 1))) {
-                uint64_t *p = xblock(xch, g0 + j, g0 + j);
+                uint64_t *p = xblock(xch, steps, g0 + j, g0 + j);
                 st_plane(p, 0, lane, __builtin_bit_cast(v4u, y).xy);
                 st_plane(p, 1, lane, __builtin_bit_cast(v4u, y).zw);
             }
@@ -333,12 +343,12 @@ __device__ __forceinline__ void factor128(v4f (&Q)[NBLK], const v4f &dg, float *
         }
         if (I > j) {
             Lx[I][lane] = X;
-            if (PUB && I != j + 1) st_split(xblock(xch, g0 + j, g0 + I), lane, split_rows(X));
+            if (PUB && I != j + 1) st_split(xblock(xch, steps, g0 + j, g0 + I), lane, split_rows(X));
         }
         __syncthreads();
         // for wave j + 1, which goes on with the pivots
         if (PUB && j + 1 < NBLK && I == ((j + 3) & (NBLK - 1)))
-            st_split(xblock(xch, g0 + j, g0 + j + 1), lane, split_rows(Lx[j + 1][lane]));
+            st_split(xblock(xch, steps, g0 + j, g0 + j + 1), lane, split_rows(Lx[j + 1][lane]));
         // out: L and L^T of this block column, rows of the inverse
         if (I == j) {
             float d = 1.0f;
@@ -467,7 +477,7 @@ k_potrf128_b(const BProb *__restrict__ P, BWork w, int64_t k0)
         for (int r = 0; r < 4; ++r) Q[K][r] = K < I ? Q[K][r] : (K == I ? dg[r] : 0.0f);
     if (threadIdx.x == 0) bad = 0;
     __syncthreads();
-    factor128<false>(Q, dg, Ab, q.npad, k0, Linv, q.ints, Lx, Yd, bad, I, lane, nullptr, 0);
+    factor128<false>(Q, dg, Ab, q.npad, k0, Linv, q.ints, Lx, Yd, bad, I, lane, nullptr, 0, 0);
 }
 
 // ---- one panel in one launch -------------------------------------------------------
@@ -478,6 +488,7 @@ struct PanelArgs {
     float *dinv;      // inverse of the panel's first diagonal block, the others behind it
     int *status, *ticket;
     uint64_t *xch, *xnext;  // this launch's exchange and the next one's
+    int unset;              // 16-byte words that the next one takes
     long spin_limit;
 };
 
@@ -509,7 +520,7 @@ __device__ __forceinline__ void below(const PanelArgs &a, PanelShared &sh, v4f (
 #pragma unroll
         for (int q = 0; q < MT; ++q)
             if (need(g, q)) {
-                const uint64_t *p = xblock(a.xch, g, NBLK * ((g >> 3) + q) + wave);
+                const uint64_t *p = xblock(a.xch, NBLK * a.nsub, g, NBLK * ((g >> 3) + q) + wave);
 #pragma unroll
                 for (int c = 0; c < 3; ++c)
                     if (c < 2 || q > 0 || wave != (g & (NBLK - 1))) pf[q].c[c] = ld_plane(p, c, lane);
@@ -543,7 +554,7 @@ __device__ __forceinline__ void below(const PanelArgs &a, PanelShared &sh, v4f (
 #pragma unroll
                 for (int q = 1; q < MT; ++q)
                     if (lane == q) mine = need(g, q);
-                const uint64_t *e = xblock(a.xch, g, NBLK * (s + (lane & (MT - 1))) + wave) + 127;
+                const uint64_t *e = xblock(a.xch, NBLK * a.nsub, g, NBLK * (s + (lane & (MT - 1))) + wave) + 127;
                 for (;;) {
                     uint64_t v = 0;
                     if (mine) v = __hip_atomic_load(e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -583,7 +594,7 @@ __device__ __forceinline__ void below(const PanelArgs &a, PanelShared &sh, v4f (
             }
             const Split xs = split_rows(X);
             if (top) {
-                st_split(xblock(a.xch, g, NBLK * ib + I), lane, xs);
+                st_split(xblock(a.xch, NBLK * a.nsub, g, NBLK * ib + I), lane, xs);
                 sh.O[cur][I].put(lane, xs);
             }
             x = widen(xs);
@@ -719,7 +730,8 @@ __device__ __forceinline__ void panel_body(const PanelArgs &a, int blk, int coun
             for (int K = 0; K < NBLK; ++K)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) Q[K][r] = K < I ? Q[K][r] : (K == I ? dg[r] : 0.0f);
-            factor128<true>(Q, dg, Ab, a.ld, k0, Linv, a.status, reinterpret_cast<v4f (*)[64]>(sh.B), sh.Yd, sh.bad, I, lane, a.xch, NBLK * ib);
+            factor128<true>(Q, dg, Ab, a.ld, k0, Linv, a.status, reinterpret_cast<v4f (*)[64]>(sh.B), sh.Yd, sh.bad, I, lane, a.xch,
+                            NBLK * a.nsub, NBLK * ib);
         }
     }
     if (ib == 0) {
@@ -727,7 +739,7 @@ __device__ __forceinline__ void panel_body(const PanelArgs &a, int blk, int coun
         v4u u;
 #pragma unroll
         for (int r = 0; r < 4; ++r) u[r] = kUnset;
-        for (int e = threadIdx.x; e < kPanelBlocks * kBlockWords / 2; e += NTP) reinterpret_cast<v4u *>(a.xnext)[e] = u;
+        for (int e = threadIdx.x; e < a.unset; e += NTP) reinterpret_cast<v4u *>(a.xnext)[e] = u;
     }
 }
 
@@ -737,13 +749,16 @@ k_panel(PanelArgs a)
     panel_body(a, blockIdx.x, gridDim.x);
 }
 
-constexpr size_t kExchangeBytes = (size_t)kPanelBlocks * kBlockWords * 8;
-static_assert(kExchangeBytes % 4096 == 0, "whole workgroups of k_unset");
+// The exchange buffer: the ticket, then two banks that the panels take in turn, the second
+// behind the widest panel's (a matrix of one panel has no second one).
+constexpr int64_t kHeaderBytes = 256;  // the banks' planes on whole lines (off them a panel takes 1.5 us more)
+constexpr int64_t kBankBytes = exchange_bytes(NB * MT);
 
 __device__ __host__ inline PanelArgs panel_args(float *A, int64_t ld, int64_t k, int64_t nb, int64_t n, float *dinv,
                                                 int *status, void *work, int index, long spin_limit)
 {
     char *w = (char *)work;
+    const int64_t left = ld - k - nb;
     PanelArgs a;
     a.A = A;
     a.ld = ld;
@@ -752,9 +767,10 @@ __device__ __host__ inline PanelArgs panel_args(float *A, int64_t ld, int64_t k,
     a.nsub = (int)(nb / NB);
     a.dinv = dinv + (k / NB) * NB * NB;
     a.status = status;
-    a.ticket = (int *)(w + 2 * kExchangeBytes);
-    a.xch = (uint64_t *)(w + (index & 1) * kExchangeBytes);
-    a.xnext = (uint64_t *)(w + (~index & 1) * kExchangeBytes);
+    a.ticket = (int *)w;
+    a.xch = (uint64_t *)(w + kHeaderBytes + (index & 1) * kBankBytes);
+    a.xnext = (uint64_t *)(w + kHeaderBytes + (~index & 1) * kBankBytes);
+    a.unset = (int)(exchange_bytes(left < nb ? left : nb) / 16);
     a.spin_limit = spin_limit;
     return a;
 }
@@ -782,17 +798,24 @@ __device__ __forceinline__ void unset(v4u *x, int64_t i)
     x[i] = u;
 }
 
-__global__ void __launch_bounds__(256)
-k_unset(v4u *__restrict__ x)
+// Ticket zero and the first bank unset, 4096 bytes of it per workgroup.
+__device__ __forceinline__ void panel_begin(void *work)
 {
-    unset(x, blockIdx.x * 256 + threadIdx.x);
+    if (blockIdx.x == 0 && threadIdx.x == 0) *(int *)work = 0;
+    unset((v4u *)((char *)work + kHeaderBytes), blockIdx.x * 256 + threadIdx.x);
 }
 
 __global__ void __launch_bounds__(256)
-k_unset_b(const BProb *__restrict__ P)
+k_panel_begin(void *__restrict__ work)
+{
+    panel_begin(work);
+}
+
+__global__ void __launch_bounds__(256)
+k_panel_begin_b(const BProb *__restrict__ P)
 {
     const BProb &q = P[blockIdx.y];
-    if (q.active) unset((v4u *)q.panel, blockIdx.x * 256 + threadIdx.x);
+    if (q.active && 4096 * (int64_t)blockIdx.x < exchange_bytes(q.npad < NB * MT ? q.npad : NB * MT)) panel_begin(q.panel);
 }
 
 }  // namespace
@@ -802,11 +825,17 @@ void launch_potrf128_b(hipStream_t s, const BProb *P, const BWork &w, int64_t k0
     if (w.na > 0) hipLaunchKernelGGL(k_potrf128_b, dim3(w.na), dim3(NTP), 0, s, P, w, k0);
 }
 
-size_t panel_work_bytes() { return 2 * kExchangeBytes + 64; }
+size_t panel_work_bytes() { return kHeaderBytes + 2 * kBankBytes; }
 
-void launch_panel_begin(hipStream_t s, void *work)
+size_t panel_b_work_bytes(int64_t npad)
 {
-    hipLaunchKernelGGL(k_unset, dim3(kExchangeBytes / 4096), dim3(256), 0, s, (v4u *)work);
+    const int64_t w = NB * MT;
+    return kHeaderBytes + exchange_bytes(std::min(npad, w)) + exchange_bytes(std::min(std::max<int64_t>(npad - w, 0), w));
+}
+
+void launch_panel_begin(hipStream_t s, void *work, int64_t nb)
+{
+    hipLaunchKernelGGL(k_panel_begin, dim3((unsigned)(exchange_bytes(nb) / 4096)), dim3(256), 0, s, work);
 }
 
 void launch_panel(hipStream_t s, float *A, int64_t ld, int64_t k, int64_t nb, int64_t n, float *dinv, int *status,
@@ -818,9 +847,10 @@ void launch_panel(hipStream_t s, float *A, int64_t ld, int64_t k, int64_t nb, in
 
 int64_t panel_b_units(int64_t npad, int64_t k) { return k < npad ? (npad - k) / NB : 0; }
 
-void launch_panel_begin_b(hipStream_t s, const BProb *P, int B)
+void launch_panel_begin_b(hipStream_t s, const BProb *P, int B, int64_t maxpad)
 {
-    hipLaunchKernelGGL(k_unset_b, dim3(kExchangeBytes / 4096, (unsigned)B), dim3(256), 0, s, P);
+    const int64_t bytes = exchange_bytes(std::min<int64_t>(maxpad, NB * MT));
+    hipLaunchKernelGGL(k_panel_begin_b, dim3((unsigned)(bytes / 4096), (unsigned)B), dim3(256), 0, s, P);
 }
 
 void launch_panel_b(hipStream_t s, const BProb *P, const BWork &w, int64_t k, long spin_limit)
