@@ -1492,6 +1492,7 @@ int mag_autotune(mag_ctx *c, const double *X, int64_t n, int32_t m, double t, in
     HIPCHK(hipEventCreate(&e1));
     int rc = MAG_OK;
     launch_fill_ints(s, status, 8, 0);
+    for (int nb : widths) chol32_image(c, npad, nb);  // allocated before the first event, not between two
     for (int rep = 0; rep < std::max(1, reps) && rc == MAG_OK; ++rep) {
         for (int q = 0; q < 2; ++q) {
             if (hipEventRecord(e0, s) != hipSuccess) { rc = MAG_EHIP; break; }
