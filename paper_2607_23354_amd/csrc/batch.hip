@@ -281,7 +281,7 @@ int batch_setup(mag_ctx *c, Batch &bt, const std::vector<const double *> &Xs,
 struct FLaunch {
     // 0 trsm, 1 subupdate, 2 syrk (pair), 3 potrf, 4 tilegen, 5 zero status, 6 strip, 7 syrk
     // (single); on the split image: 8 split, 9 syrk; with an exchange: 10 its begin, 11 a panel
-    // of 512 columns; 12 the substitutions' near tiles
+    // of 512 columns
     int kind;
     int64_t kk;
     BWork w;
@@ -308,7 +308,7 @@ int schedule_trailing(Batch &bt, std::vector<FLaunch> &seq, const std::vector<in
 
 // group: 0 the context's tuned choice for this batch's largest npad, 1 single
 // panels, 2 pairs.
-int schedule_panels(Batch &bt, std::vector<FLaunch> &seq, int group)
+int batch_factor_schedule(Batch &bt, std::vector<FLaunch> &seq, int group = 0)
 {
     std::vector<int> all(bt.B);
     for (int b = 0; b < bt.B; ++b) all[b] = b;
@@ -382,17 +382,6 @@ int schedule_panels(Batch &bt, std::vector<FLaunch> &seq, int group)
     return MAG_OK;
 }
 
-int batch_factor_schedule(Batch &bt, std::vector<FLaunch> &seq, int group = 0)
-{
-    BRC(schedule_panels(bt, seq, group));
-    std::vector<int> all(bt.B);
-    for (int b = 0; b < bt.B; ++b) all[b] = b;
-    BWork w;
-    BRC(bt.make_work(all, [&](int p) { return near_q_b_units(bt.h[p].npad); }, true, w));
-    seq.push_back({12, 0, w});
-    return MAG_OK;
-}
-
 void record_factor(Batch &bt, const std::vector<FLaunch> &seq)
 {
     for (const FLaunch &L : seq) {
@@ -404,7 +393,6 @@ void record_factor(Batch &bt, const std::vector<FLaunch> &seq)
         case 7: launch_gemm_b(bt.s, 4, bt.d, L.w, L.kk); break;
         case 8: launch_split_b(bt.s, bt.d, L.w, L.kk, L.K); break;
         case 9: launch_syrk_split_b(bt.s, bt.d, L.w, L.kk, L.K); break;
-        case 12: launch_near_q_b(bt.s, bt.d, L.w); break;
         case 10: launch_panel_begin_b(bt.s, bt.d, bt.B, bt.maxpad); break;
         case 11: launch_panel_b(bt.s, bt.d, L.w, L.kk, panel_spin_limit_of(bt.c)); break;
         default: launch_gemm_b(bt.s, L.kind, bt.d, L.w, L.kk); break;

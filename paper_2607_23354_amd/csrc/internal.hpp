@@ -225,9 +225,6 @@ int64_t split_b_units(int64_t rows, int64_t K);
 int64_t syrk_split_b_units(int64_t rows);
 void launch_split_b(hipStream_t s, const BProb *P, const BWork &w, int64_t kk, int64_t K);
 void launch_syrk_split_b(hipStream_t s, const BProb *P, const BWork &w, int64_t kk, int64_t K);
-// the factor's near tiles in place (after it, before the first prec_apply_b)
-int64_t near_q_b_units(int64_t npad);
-void launch_near_q_b(hipStream_t s, const BProb *P, const BWork &w);
 int64_t prec_b_units(int64_t npad);
 // tickets zero and tmp_slot unset: once before the first launch_prec_apply_b, which
 // leaves them so; rhs_slot, tmp_slot and x_slot differ

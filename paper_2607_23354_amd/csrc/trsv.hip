@@ -11,8 +11,9 @@
 //     are those of an FP32 factor in 128 x 128 blocks at n = 32768;
 //   * trsv1_body (one workgroup per block, composite near step, further down)
 //     serves the FP32 factors: 0.52 ms per direction at n = 32768 against the band
-//     kernel's 0.97 ms, and batched (k_trsv_b) 0.48 ms against 0.70 ms for 64
-//     clouds of 1000 to 6000 points, 10 us against 41 us for 32 of 50 to 400.
+//     kernel's 0.97 ms, and batched (k_trsv_b, whose near step is not composite)
+//     0.47 ms against 0.70 ms for 64 clouds of 1000 to 6000 points, 11 us against
+//     41 us for 32 of 50 to 400.
 //
 // Each triangular solve is ONE launch and no host round trips ("sync-free"
 // substitution).  For the band kernel:
@@ -372,9 +373,11 @@ k_trsv(const T *__restrict__ L, int64_t ld, const T *__restrict__ dinv,
 // FP64 before the wait, and one barrier is left, at the sum over the waves.  With
 // one polling wave, two barriers and 256 threads a direction took 55 us at
 // n = 3001 and 0.58 ms at n = 32768, now 40 us and 0.52 ms.
-// INPLACE (the batched solves): each Q_b stands in the place of its T(b, n), else one after
-// another at Qb.
-template <bool BWD, bool INPLACE>
+// COMPOSITE false (the batched solves): x_b = D_b (rhs_b - sum T(b, j) x_j), T(b, n)
+// resident in the place of Q_b and D_b applied after the wait, so nothing but the factor's
+// own FP32 entries is multiplied by, and no near tiles are formed with every factor (0.36 ms
+// for 64 clouds of 1000 to 6000 points) for the two applications of its solve.
+template <bool BWD, bool COMPOSITE>
 __device__ __forceinline__ void trsv1_body(const float *__restrict__ L, int64_t ld, const float *__restrict__ dinv,
                                            const float *__restrict__ Qb, double *__restrict__ rhs,
                                            double *__restrict__ x, double *__restrict__ z, int *counters, int nblk,
@@ -459,7 +462,7 @@ __device__ __forceinline__ void trsv1_body(const float *__restrict__ L, int64_t 
         unset_after_read<BWD>(rhs, z, (int64_t)b * BS + tid);
     }
     Tile tq;
-    if (has_near) load(INPLACE ? tile(jof(nsteps - 1)) : Qb + (int64_t)b * BS * BS, INPLACE ? ld : BS, tq);
+    if (has_near) load(COMPOSITE ? Qb + (int64_t)b * BS * BS : tile(jof(nsteps - 1)), COMPOSITE ? BS : ld, tq);
     Tile ta, tb;
     if (nfar > 0) load(tile(jof(0)), ld, ta);
     if (nfar > 1) load(tile(jof(1)), ld, tb);
@@ -487,6 +490,17 @@ __device__ __forceinline__ void trsv1_body(const float *__restrict__ L, int64_t 
         if (st + 2 < nfar) load(tile(jof(st + 2)), ld, ta);
         if (st + 3 < nfar) load(tile(jof(st + 3)), ld, tb);
     }
+    // the predecessor's block through tq
+    auto near = [&](double (&a)[4]) {
+        wait(jof(nsteps - 1), 0, false, false);
+#pragma unroll
+        for (int c = 0; c < TC; ++c) {
+            const double xv = xs[wave][0][TC * ch + c];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) a[i] += q[c][i] * xv;
+        }
+    };
+    if (!COMPOSITE && has_near) near(acc);
     // y = D_b (rhs_b - acc)
     to_part(acc);
     __syncthreads();
@@ -511,20 +525,14 @@ __device__ __forceinline__ void trsv1_body(const float *__restrict__ L, int64_t 
 #pragma unroll
         for (int g = 0; g < NP; ++g) y += part[g][tid];
     }
-    if (!has_near) {
+    if (!COMPOSITE || !has_near) {
         if (tid < BS) st_entry(x, (int64_t)b * BS + tid, y);
         return;
     }
     __syncthreads();  // part is rewritten below
-    // the predecessor's block: x_b = y - Q_b x_n
-    wait(jof(nsteps - 1), 0, false, false);
+    // x_b = y - Q_b x_n
     double aq[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int c = 0; c < TC; ++c) {
-        const double xv = xs[wave][0][TC * ch + c];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) aq[i] += q[c][i] * xv;
-    }
+    near(aq);
     to_part(aq);
     __syncthreads();
     if (tid < BS) {
@@ -541,7 +549,7 @@ k_trsv1(const float *__restrict__ L, int64_t ld, const float *__restrict__ dinv,
         double *__restrict__ rhs, double *__restrict__ x, double *__restrict__ z, int *counters, int nblk, int *status,
         long spin_limit, Gate gate)
 {
-    trsv1_body<BWD, false>(L, ld, dinv, Qb, rhs, x, z, counters, nblk, status, spin_limit, gate);
+    trsv1_body<BWD, true>(L, ld, dinv, Qb, rhs, x, z, counters, nblk, status, spin_limit, gate);
 }
 
 // The near tiles of k_trsv1 for every 128-block of the FP32 factor, both
@@ -609,77 +617,6 @@ k_near_q(const float *__restrict__ A, int64_t npad, const float *__restrict__ di
         for (int v = 0; v < 4; ++v) dst[(j0 + 16 * t + kq + 4 * v) * B + i0 + 16 * wave + q] = (float)acc[t][v];
 }
 
-// Batched, in place: Q_b over T(b, n), which only the near step reads (no memory of its
-// own; 0.36 ms for 64 clouds of 1000 to 6000 points, four tile reads and writes of
-// which the card's copy rate allows 0.15).  A workgroup forms 64
-// whole columns of a tile, from their entries alone, all read before the first is written.
-__global__ void __launch_bounds__(256)
-k_near_q_b(const BProb *__restrict__ P, BWork w)
-{
-    typedef double v4d __attribute__((ext_vector_type(4)));
-    constexpr int B = 128, H = 64, SL = 80;
-    __shared__ float Xs[H * SL];     // a quadrant X(i, k) of the inverse at Xs[k SL + i]
-    __shared__ float Ys[2][H * SL];  // Y(k, j) of the two halves of K
-    const int p = bfind(w.pref, w.na, blockIdx.x);
-    const BProb &pr = P[w.plist[p]];
-    if (!pr.active) return;
-    const int u = (int)(blockIdx.x - w.pref[p]);
-    const bool bwd = (u & 1) != 0;
-    const int j0 = H * ((u >> 1) & 1), e0 = u >> 2;  // e0: the pair of neighbours (e0, e0 + 1)
-    const int b = bwd ? e0 : e0 + 1, jn = bwd ? e0 + 1 : e0;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int q = lane & 15, kq = lane >> 4;
-    const float *D = pr.dinv + (int64_t)b * B * B;
-    float *T = pr.A + ((int64_t)jn * B + j0) * pr.npad + (int64_t)b * B;
-    const int lo = tid & (H - 1), hi = tid >> 6;
-    float yv[2][H * H / 256];
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-        for (int e = 0; e < H * H / 256; ++e) yv[h][e] = T[(int64_t)(hi + 4 * e) * pr.npad + H * h + lo];
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-        for (int e = 0; e < H * H / 256; ++e) Ys[h][lo * SL + hi + 4 * e] = yv[h][e];
-#pragma unroll
-    for (int ih = 0; ih < 2; ++ih) {
-        v4d acc[4];
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) acc[t][v] = 0.0;
-        for (int kh = 0; kh < 2; ++kh) {
-            if (bwd ? (kh < ih) : (kh > ih)) continue;  // D(i, k) = 0 for k > i, D(k, i) for k < i
-            float xv[H * H / 256];
-#pragma unroll
-            for (int e = 0; e < H * H / 256; ++e) {
-                const int v = hi + 4 * e;
-                xv[e] = bwd ? D[(H * ih + v) * B + H * kh + lo] : D[(H * kh + v) * B + H * ih + lo];
-            }
-            __syncthreads();
-#pragma unroll
-            for (int e = 0; e < H * H / 256; ++e) {
-                const int v = hi + 4 * e;
-                Xs[bwd ? lo * SL + v : v * SL + lo] = xv[e];
-            }
-            __syncthreads();
-#pragma unroll 4
-            for (int k = 0; k < H; k += 4) {
-                const double x = (double)Xs[(k + kq) * SL + 16 * wave + q];
-#pragma unroll
-                for (int t = 0; t < 4; ++t)
-                    acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)Ys[kh][(k + kq) * SL + 16 * t + q], x, acc[t],
-                                                                  0, 0, 0);
-            }
-        }
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-            for (int v = 0; v < 4; ++v)
-                T[(int64_t)(16 * t + kq + 4 * v) * pr.npad + H * ih + 16 * wave + q] = (float)acc[t][v];
-    }
-}
-
 // Batched: workgroups of problem p take tickets from p's own counters, so the
 // forward-progress argument holds per problem; problems never wait on each other.
 template <bool BWD>
@@ -689,7 +626,7 @@ k_trsv_b(const BProb *__restrict__ P, BWork w, int rhs_slot, int x_slot, int z_s
     const int i = bfind(w.pref, w.na, blockIdx.x);
     const BProb &q = P[w.plist[i]];
     if (!q.active) return;
-    trsv1_body<BWD, true>(q.A, q.npad, q.dinv, nullptr, q.vec + (int64_t)rhs_slot * q.npad,
+    trsv1_body<BWD, false>(q.A, q.npad, q.dinv, nullptr, q.vec + (int64_t)rhs_slot * q.npad,
                           q.vec + (int64_t)x_slot * q.npad, q.vec + (int64_t)z_slot * q.npad, q.ints + 64,
                           (int)(q.npad / 128), q.ints, spin_limit, Gate());
 }
@@ -722,13 +659,6 @@ __global__ void k_refine_begin(double *__restrict__ y, double *__restrict__ rhs,
 size_t prec_counter_ints() { return kCounterInts; }
 
 int64_t prec_b_units(int64_t npad) { return npad / 128; }
-
-int64_t near_q_b_units(int64_t npad) { return 4 * (npad / 128 - 1); }
-
-void launch_near_q_b(hipStream_t s, const BProb *P, const BWork &w)
-{
-    if (w.total > 0) hipLaunchKernelGGL(k_near_q_b, dim3((unsigned)w.total), dim3(256), 0, s, P, w);
-}
 
 void launch_prec_begin_b(hipStream_t s, const BProb *P, int B, int tmp_slot)
 {
