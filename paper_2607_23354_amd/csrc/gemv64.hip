@@ -6,12 +6,12 @@
 // (exact differences, uncontracted squared sum in ascending l, sqrt, then
 // exp(-(t d))), in FP64.
 //
-// Single solves use the symmetry of Z: only the 128 x 128 tiles (I, J) with
-// J <= I are evaluated; each off-diagonal tile adds Z_IJ v_J to block I and
-// Z_IJ^T v_I to block J, so every entry is formed once.  Per-tile row and
-// column sums go to a tile-major buffer and a second kernel adds them per
+// Up to 16 dimensions, single and batched, the products use the symmetry of Z: only the
+// 128 x 128 (or 64 x 64) tiles (I, J) with J <= I are evaluated; each off-diagonal tile adds
+// Z_IJ v_J to block I and Z_IJ^T v_I to block J, so every entry is formed once.  Per-tile row
+// and column sums go to a tile-major buffer and a second kernel adds them per
 // block in a fixed order (deterministic), optionally forming b - Z v and its
-// max-norm.  The batched path keeps the row-per-thread form: (row blocks of
+// max-norm.  Above 16 dimensions they take the row-per-thread form: (row blocks of
 // 256 rows) x (column splits), partial row sums split-major.
 #include "internal.hpp"
 
@@ -25,7 +25,6 @@ namespace {
 
 constexpr int RT = 256;   // rows per block (threads)
 constexpr int CH = 256;   // columns per LDS chunk
-constexpr int MMAX_LDS = 8;   // compile-time dimensions up to 8 stage coordinates in LDS
 
 __device__ inline double sq_acc(double s, double e)
 {
@@ -34,60 +33,31 @@ __device__ inline double sq_acc(double s, double e)
     return s + p;
 }
 
-template <int M>
-__device__ __forceinline__ void zmv_partial_body(const double *__restrict__ X, int64_t n, int m_rt,
+// Row-per-thread form (any m): coordinates read directly (L1/L2 cached), v staged per chunk.
+__device__ __forceinline__ void zmv_partial_body(const double *__restrict__ X, int64_t n, int m,
                                                  double t, const double *__restrict__ v,
                                                  double *__restrict__ partial, int64_t cps,
                                                  int64_t npad, int64_t bx, int64_t by)
 {
-    __shared__ double Xc[MMAX_LDS * CH];
     __shared__ double vc[CH];
-    const int m = (M > 0) ? M : m_rt;
     const int64_t j = bx * RT + threadIdx.x;
     const int64_t c_lo = by * cps;
     const int64_t c_hi = min(n, c_lo + cps);
     const bool live = j < n;
     double acc = 0.0;
-
-    if (M > 0) {
-        double xr[M > 0 ? M : 1];
-#pragma unroll
-        for (int l = 0; l < (M > 0 ? M : 1); ++l) xr[l] = live ? X[j * M + l] : 0.0;
-        for (int64_t k0 = c_lo; k0 < c_hi; k0 += CH) {
-            const int cnt = (int)min((int64_t)CH, c_hi - k0);
-            __syncthreads();
-            for (int e = threadIdx.x; e < cnt * M; e += RT) {
-                const int p = e / M, l = e % M;
-                Xc[l * CH + p] = X[(k0 + p) * M + l];
-            }
-            if (threadIdx.x < cnt) vc[threadIdx.x] = v[k0 + threadIdx.x];
-            __syncthreads();
-            if (live) {
-                for (int c = 0; c < cnt; ++c) {
-                    double s = 0.0;
-#pragma unroll
-                    for (int l = 0; l < M; ++l) s = sq_acc(s, xr[l] - Xc[l * CH + c]);
-                    const double z = (k0 + c == j) ? 1.0 : zexp(t, s);
-                    acc = fma(z, vc[c], acc);
-                }
-            }
-        }
-    } else {
-        // runtime m: coordinates read directly (L1/L2 cached); v staged per chunk
-        for (int64_t k0 = c_lo; k0 < c_hi; k0 += CH) {
-            const int cnt = (int)min((int64_t)CH, c_hi - k0);
-            __syncthreads();
-            if (threadIdx.x < cnt) vc[threadIdx.x] = v[k0 + threadIdx.x];
-            __syncthreads();
-            if (live) {
-                const double *xj = X + j * m;
-                for (int c = 0; c < cnt; ++c) {
-                    const double *xk = X + (k0 + c) * m;
-                    double s = 0.0;
-                    for (int l = 0; l < m; ++l) s = sq_acc(s, xj[l] - xk[l]);
-                    const double z = (k0 + c == j) ? 1.0 : zexp(t, s);
-                    acc = fma(z, vc[c], acc);
-                }
+    for (int64_t k0 = c_lo; k0 < c_hi; k0 += CH) {
+        const int cnt = (int)min((int64_t)CH, c_hi - k0);
+        __syncthreads();
+        if (threadIdx.x < cnt) vc[threadIdx.x] = v[k0 + threadIdx.x];
+        __syncthreads();
+        if (live) {
+            const double *xj = X + j * m;
+            for (int c = 0; c < cnt; ++c) {
+                const double *xk = X + (k0 + c) * m;
+                double s = 0.0;
+                for (int l = 0; l < m; ++l) s = sq_acc(s, xj[l] - xk[l]);
+                const double z = (k0 + c == j) ? 1.0 : zexp(t, s);
+                acc = fma(z, vc[c], acc);
             }
         }
     }
@@ -416,15 +386,14 @@ k_zmv_sym_reduce_b(const BProb *__restrict__ P, BWork w, int y_slot, int b_slot,
                             norm_off >= 0 ? q.scal + norm_off : nullptr, blockIdx.x - w.pref[i]);
 }
 
-template <int M>
 __global__ void __launch_bounds__(RT)
-k_zmv_partial(const double *__restrict__ X, int64_t n, int m_rt, double t,
+k_zmv_partial(const double *__restrict__ X, int64_t n, int m, double t,
               const double *__restrict__ v, double *__restrict__ partial, int64_t cps,
               int64_t npad, double *__restrict__ norm, Gate gate)
 {
     if (gate.closed()) return;
     if (norm && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *norm = 0.0;
-    zmv_partial_body<M>(X, n, m_rt, t, v, partial, cps, npad, blockIdx.x, blockIdx.y);
+    zmv_partial_body(X, n, m, t, v, partial, cps, npad, blockIdx.x, blockIdx.y);
 }
 
 // mode 0: y = sum_s partial;  mode 1: y = b - sum_s partial (b == NULL: ones),
@@ -484,7 +453,6 @@ __host__ __device__ inline Plan plan_for(int64_t n)
 }
 
 // Batched Z v: work units of problem p = rowblocks * splits (row block major).
-template <int M>
 __global__ void __launch_bounds__(RT)
 k_zmv_partial_b(const BProb *__restrict__ P, BWork w, int v_slot, int64_t norm_off)
 {
@@ -494,7 +462,7 @@ k_zmv_partial_b(const BProb *__restrict__ P, BWork w, int v_slot, int64_t norm_o
     const Plan pl = plan_for(q.n);
     const int64_t u = blockIdx.x - w.pref[i];
     if (norm_off >= 0 && u == 0 && threadIdx.x == 0) q.scal[norm_off] = 0.0;
-    zmv_partial_body<M>(q.X, q.n, q.m, q.t, q.vec + (int64_t)v_slot * q.npad, q.partial, pl.cps,
+    zmv_partial_body(q.X, q.n, q.m, q.t, q.vec + (int64_t)v_slot * q.npad, q.partial, pl.cps,
                         q.npad, u / pl.splits, u % pl.splits);
 }
 
@@ -594,7 +562,7 @@ void launch_zmv_b(hipStream_t s, int m, const BProb *P, const BWork &wz, const B
         return;
     }
     // m > MMAX_SYM: the runtime-m row-per-thread form
-    hipLaunchKernelGGL(k_zmv_partial_b<0>, dim3((unsigned)wz.total), dim3(RT), 0, s, P, wz, v_slot, norm_off);
+    hipLaunchKernelGGL(k_zmv_partial_b, dim3((unsigned)wz.total), dim3(RT), 0, s, P, wz, v_slot, norm_off);
     hipLaunchKernelGGL(k_zmv_reduce_b, dim3((unsigned)wr.total), dim3(256), 0, s, P, wr, y_slot, b_slot, mode,
                        norm_off);
 }
@@ -612,7 +580,7 @@ void launch_zmv_split(hipStream_t s, const double *X, int64_t n, int m, double t
     Plan p = plan_for(n);
     dim3 grid((unsigned)p.rowblocks, (unsigned)p.splits);
     double *norm = mode == 1 ? out_norm : nullptr;
-    hipLaunchKernelGGL(k_zmv_partial<0>, grid, dim3(RT), 0, s, X, n, m, t, v, partial, p.cps, p.npad, norm, gate);
+    hipLaunchKernelGGL(k_zmv_partial, grid, dim3(RT), 0, s, X, n, m, t, v, partial, p.cps, p.npad, norm, gate);
     hipLaunchKernelGGL(k_zmv_reduce, dim3((unsigned)(p.npad / 256)), dim3(256), 0, s, partial, p.npad, n,
                        (int)p.splits, y, b, mode, norm);
 }

@@ -1,52 +1,44 @@
 // trsv.hip -- preconditioner apply z = L^{-T} L^{-1} r of the refinement, and
 // the substitution of the FP64 dense factor.
 //
-// L is the FP32 Cholesky factor (column-major, leading dimension npad, lower
-// triangle), r and z are FP64 and all arithmetic is FP64.  The diagonal
-// 128 x 128 blocks are applied through their explicit inverses (FP32, from the
-// factorisation), so a block step is a small matrix-vector product.  Two
+// L is a Cholesky factor (column-major, leading dimension npad, L in the lower
+// triangle and L^T in the upper one), FP32 or FP64; r and z are FP64 and all
+// arithmetic is FP64.  The diagonal blocks (128 x 128 of the FP32 factor, 64 x 64 of
+// the FP64 one) are applied through their explicit inverses (in the factor's type,
+// from the factorisation), so a block step is a small matrix-vector product.  Two
 // kernels share the hand-off protocol below:
-//   * the band kernel (trsv_body, one workgroup per two blocks) serves the FP64
-//     factor with its 64 x 64 blocks (whose FP64 inverses fit LDS); the figures below
-//     are those of an FP32 factor in 128 x 128 blocks at n = 32768;
-//   * trsv1_body (one workgroup per block, composite near step, further down)
-//     serves the FP32 factors: 0.52 ms per direction at n = 32768 against the band
-//     kernel's 0.97 ms, and batched (k_trsv_b, whose near step is not composite)
-//     0.47 ms against 0.70 ms for 64 clouds of 1000 to 6000 points, 11 us against
-//     41 us for 32 of 50 to 400.
+//   * trsv1_body (one workgroup per block, further down) serves the FP32 factors, with a
+//     composite near step in single solves: 0.52 ms per direction at n = 32768; batched
+//     (k_trsv_b, whose near step is not composite) 0.47 ms for 64 clouds of 1000 to
+//     6000 points and 11 us for 32 of 50 to 400;
+//   * the band kernel (trsv_body, one workgroup per two blocks) serves the FP64 factor,
+//     whose inverses of both blocks just fit LDS: 1.1 ms per direction at n = 32768,
+//     4.3 GB at 3.9 TB/s.
 //
 // Each triangular solve is ONE launch and no host round trips ("sync-free"
-// substitution).  For the band kernel:
-//   * a workgroup owns a band of two consecutive blocks and takes a ticket
-//     from an atomic counter; ticket order is the band order of the
-//     substitution, so every block a workgroup waits for belongs to a
+// substitution):
+//   * a workgroup takes a ticket from an atomic counter; ticket order is the
+//     order of the substitution, so every block a workgroup waits for belongs to a
 //     workgroup that is already running -- forward progress does not depend
 //     on how many workgroups fit on the device;
 //   * block b streams its off-diagonal tiles in order (forward: L(b, j) from
 //     the lower triangle; backward: L^T(b, j) from the upper triangle, where
-//     the factorisation keeps the transpose); the tiles of a pair of outside
-//     blocks are loaded into registers a whole pair-step ahead of the wait
-//     for the solution blocks they multiply, and the band's own right-hand
-//     side and inner tile before the first wait, so the HBM stream stays off
-//     the dependency chain.  What stays on it, per band (measured at
-//     n = 32768 with in-kernel clock stamps, 7.2 us per band): 2.9 us from a
-//     band's last store to the next band seeing it, 1.3 us for the four FP64
-//     tile products with the received blocks (FP64-FMA bound: 64 Ki products
-//     and conversions on one CU), 2.7 us for the two diagonal solves, the
-//     inner tile and the LDS reductions;
+//     the factorisation keeps the transpose); the tiles of a pair of blocks
+//     are loaded into registers a whole pair-step ahead of the wait
+//     for the solution blocks they multiply, and the workgroup's own right-hand
+//     side and resident tiles before the first wait, so the HBM stream stays off
+//     the dependency chain;
 //   * the solution vector is the flag: before a solve every entry holds an
-//     "unset" bit pattern (a signalling NaN no arithmetic produces); a band
+//     "unset" bit pattern (a signalling NaN no arithmetic produces); a workgroup
 //     writes its solution entries with relaxed agent-scope atomic stores, and
-//     a waiting band's wave 0 reads the entries it needs with relaxed
+//     a waiting wave reads the entries it needs with relaxed
 //     agent-scope atomic loads until none is unset.  Each entry is written
 //     once, so a value that is not the pattern is final: no counter, no
 //     release or acquire fence (each fence a wave executes costs microseconds
 //     of L2 write-back or invalidation) and no second read of the data;
-//   * wave 0 alone polls and copies the received blocks into LDS for the
-//     others;
 //   * spin-waits are bounded: on exhaustion the kernel sets a status word and
 //     finishes, and the host reports an error.
-// HBM traffic per apply: the lower triangle read twice (n^2 * 4 bytes).
+// HBM traffic per direction: one triangle of the factor, read once.
 #include "internal.hpp"
 
 namespace mag {
@@ -95,39 +87,27 @@ __device__ inline void unset_after_read(double *rhs, double *z, int64_t i)
     reinterpret_cast<uint64_t *>(BWD ? rhs : z)[i] = kUnset;
 }
 
-// Wave 0 (lanes 0..63): wait until the BS entries of block j0 (and j1 if two)
+// Wave 0 (lanes 0..63): wait until the 64 entries of block j0 (and j1 if two)
 // of x are set, and copy them to xs[0] (xs[1]).  Bounded: after spin_limit
 // polls the status word is set and whatever was read is used.
-template <int BS>
-__device__ inline void wait_blocks(const double *x, int64_t j0, int64_t j1, bool two, double (&xs)[2][BS],
+__device__ inline void wait_blocks(const double *x, int64_t j0, int64_t j1, bool two, double (&xs)[2][64],
                                    int *status, long spin_limit)
 {
-    static_assert(BS == 64 || BS == 128, "one or two entries per lane and block");
-    constexpr bool E2 = BS == 128;
     const int lane = threadIdx.x;
-    uint64_t a0, a1 = 0, c0 = 0, c1 = 0;
+    uint64_t a, c = 0;
     long spins = 0;
     for (;;) {
-        a0 = ld_entry(x, j0 * BS + lane);
-        if (E2) a1 = ld_entry(x, j0 * BS + lane + 64);
-        if (two) {
-            c0 = ld_entry(x, j1 * BS + lane);
-            if (E2) c1 = ld_entry(x, j1 * BS + lane + 64);
-        }
-        const bool miss = a0 == kUnset || (E2 && a1 == kUnset) || (two && (c0 == kUnset || (E2 && c1 == kUnset)));
-        if (__ballot(miss) == 0) break;
+        a = ld_entry(x, j0 * 64 + lane);
+        if (two) c = ld_entry(x, j1 * 64 + lane);
+        if (__ballot(a == kUnset || (two && c == kUnset)) == 0) break;
         if (++spins > spin_limit) {
             if (lane == 0) status[kStSpinTimeout] = 1;
             break;
         }
         __builtin_amdgcn_s_sleep(1);
     }
-    xs[0][lane] = __builtin_bit_cast(double, a0);
-    if (E2) xs[0][lane + 64] = __builtin_bit_cast(double, a1);
-    if (two) {
-        xs[1][lane] = __builtin_bit_cast(double, c0);
-        if (E2) xs[1][lane + 64] = __builtin_bit_cast(double, c1);
-    }
+    xs[0][lane] = __builtin_bit_cast(double, a);
+    if (two) xs[1][lane] = __builtin_bit_cast(double, c);
 }
 
 // Four consecutive factor entries (one row group of a tile column).
@@ -153,30 +133,29 @@ __device__ inline void load_quad(const double *p, Quad<double> &q)
     q.v[3] = b.y;
 }
 
-// One triangular solve.  Forward (BWD = false): y = L^{-1} r, block b pulls
-// tiles L(b, j), j < b, from the lower triangle.  Backward (BWD = true):
+// One triangular solve with the FP64 factor.  Forward (BWD = false): y = L^{-1} r, block b
+// pulls tiles L(b, j), j < b, from the lower triangle.  Backward (BWD = true):
 // z = L^{-T} y, block b pulls tiles L^T(b, j), j > b, from the upper
-// triangle, where the factorisation stored L^T.  Both read a BS-row band of
+// triangle, where the factorisation stored L^T.  Both read a 64-row band of
 // column segments per step, the same HBM access pattern.
 //
-// A workgroup owns two consecutive blocks (a 2 BS-row band): it streams both
+// A workgroup owns two consecutive blocks (a 128-row band): it streams both
 // blocks' tiles against every finished block outside the band, then solves
 // the first block, applies the band's inner tile and solves the second, so
-// the dependency chain crosses workgroups once per 2 BS rows.
-// T, BS: the FP32 factor with 128-blocks, or the FP64 factor with 64-blocks.
-template <bool BWD, typename T, int BS>
-__device__ __forceinline__ void trsv_body(const T *__restrict__ L, int64_t ld,
-                                          const T *__restrict__ dinv,
+// the dependency chain crosses workgroups once per 128 rows.
+template <bool BWD>
+__device__ __forceinline__ void trsv_body(const double *__restrict__ L, int64_t ld,
+                                          const double *__restrict__ dinv,
                                           double *__restrict__ rhs, double *__restrict__ x, double *__restrict__ z,
                                           int *counters, int nblk, int *status, long spin_limit)
 {
+    constexpr int BS = 64;
     constexpr int RG = BS / 4;      // row groups of a tile (4 rows each)
     constexpr int CG = 256 / RG;    // column groups
     constexpr int CPG = BS / CG;    // columns per group
     constexpr int H = 256 / BS;     // parts of a diagonal-block row's product
     constexpr int HC = BS / H;      // columns per part
-    static_assert(RG * CG == 256 && CG * CPG == BS && H <= CG, "tile mapping");
-    __shared__ T Dl[2][BS * (BS + 1)];  // Dinv of the two blocks, row-major, padded stride
+    __shared__ double Dl[2][BS * (BS + 1)];  // Dinv of the two blocks, row-major, padded stride
     __shared__ double xs[2][BS];
     __shared__ double part[CG][BS];     // per column group partial sums of a block's rows
     __shared__ int s_band;
@@ -200,9 +179,9 @@ __device__ __forceinline__ void trsv_body(const T *__restrict__ L, int64_t ld,
 
     // tile (b, j): element (r, c) at L[(j BS + c) ld + b BS + r] -- forward L(b, j)
     // from the lower triangle, backward L^T(b, j) from the upper triangle
-    using Tile = Quad<T>[CPG];
+    using Tile = Quad<double>[CPG];
     auto load = [&](int b, int j, Tile &t) {
-        const T *p = L + ((int64_t)j * BS + CPG * cg) * ld + (int64_t)b * BS + 4 * rg;
+        const double *p = L + ((int64_t)j * BS + CPG * cg) * ld + (int64_t)b * BS + 4 * rg;
 #pragma unroll
         for (int c = 0; c < CPG; ++c) load_quad(p + (int64_t)c * ld, t[c]);
     };
@@ -210,10 +189,8 @@ __device__ __forceinline__ void trsv_body(const T *__restrict__ L, int64_t ld,
 #pragma unroll
         for (int c = 0; c < CPG; ++c) {
             const double v = xv[CPG * cg + c];
-            acc[0] += (double)t[c].v[0] * v;
-            acc[1] += (double)t[c].v[1] * v;
-            acc[2] += (double)t[c].v[2] * v;
-            acc[3] += (double)t[c].v[3] * v;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[i] += t[c].v[i] * v;
         }
     };
 
@@ -231,7 +208,7 @@ __device__ __forceinline__ void trsv_body(const T *__restrict__ L, int64_t ld,
 
     // Dinv (column-major in memory) into row-major padded LDS
     for (int q = 0; q < 2; ++q) {
-        const T *src = dinv + (int64_t)(q == 0 ? b0 : b1) * BS * BS;
+        const double *src = dinv + (int64_t)(q == 0 ? b0 : b1) * BS * BS;
         for (int e = tid; e < BS * BS; e += 256) {
             const int rr = e % BS, cc = e / BS;
             Dl[q][rr * (BS + 1) + cc] = src[e];
@@ -246,7 +223,7 @@ __device__ __forceinline__ void trsv_body(const T *__restrict__ L, int64_t ld,
     // steps st and st + 1 (if any): wave 0 waits for both solution blocks (a
     // band writes its two blocks moments apart) and copies them to LDS
     auto consume2 = [&](int st, bool two) {
-        if (tid < 64) wait_blocks<BS>(x, jof(st), two ? jof(st + 1) : 0, two, xs, status, spin_limit);
+        if (tid < 64) wait_blocks(x, jof(st), two ? jof(st + 1) : 0, two, xs, status, spin_limit);
         __syncthreads();
         gemv(ta0, xs[0], acc0);
         gemv(ta1, xs[0], acc1);
@@ -295,8 +272,7 @@ __device__ __forceinline__ void trsv_body(const T *__restrict__ L, int64_t ld,
 #pragma unroll 16
     for (int c = 0; c < HC; ++c) {
         const int cc = h * HC + c;
-        const T d = BWD ? Dl[0][cc * (BS + 1) + row] : Dl[0][row * (BS + 1) + cc];
-        v += (double)d * xs[0][cc];
+        v += (BWD ? Dl[0][cc * (BS + 1) + row] : Dl[0][row * (BS + 1) + cc]) * xs[0][cc];
     }
     part[h][row] = v;
     __syncthreads();
@@ -308,10 +284,7 @@ __device__ __forceinline__ void trsv_body(const T *__restrict__ L, int64_t ld,
     }
     __syncthreads();
     // wave 0 writes the band's solution entries (each write releases that entry)
-    if (tid < 64) {
-#pragma unroll
-        for (int e = 0; e < BS / 64; ++e) st_entry(x, (int64_t)b0 * BS + tid + 64 * e, xs[1][tid + 64 * e]);
-    }
+    if (tid < 64) st_entry(x, (int64_t)b0 * BS + tid, xs[1][tid]);
     // second block: acc1 += L(b1, b0) x_b0, then x_b1 = Dinv_b1 (rhs_b1 - acc1)
     gemv(ti, xs[1], acc1);
 #pragma unroll
@@ -328,30 +301,25 @@ __device__ __forceinline__ void trsv_body(const T *__restrict__ L, int64_t ld,
 #pragma unroll 16
     for (int c = 0; c < HC; ++c) {
         const int cc = h * HC + c;
-        const T d = BWD ? Dl[1][cc * (BS + 1) + row] : Dl[1][row * (BS + 1) + cc];
-        v += (double)d * xs[0][cc];
+        v += (BWD ? Dl[1][cc * (BS + 1) + row] : Dl[1][row * (BS + 1) + cc]) * xs[0][cc];
     }
     part[h][row] = v;
     __syncthreads();
     if (tid < 64) {
+        double sv = part[0][tid];
 #pragma unroll
-        for (int e = 0; e < BS / 64; ++e) {
-            const int rr = tid + 64 * e;
-            double sv = part[0][rr];
-#pragma unroll
-            for (int g = 1; g < H; ++g) sv += part[g][rr];
-            st_entry(x, (int64_t)b1 * BS + rr, sv);
-        }
+        for (int g = 1; g < H; ++g) sv += part[g][tid];
+        st_entry(x, (int64_t)b1 * BS + tid, sv);
     }
 }
 
-template <bool BWD, typename T, int BS>
+template <bool BWD>
 __global__ void __launch_bounds__(256)
-k_trsv(const T *__restrict__ L, int64_t ld, const T *__restrict__ dinv,
+k_trsv(const double *__restrict__ L, int64_t ld, const double *__restrict__ dinv,
        double *__restrict__ rhs, double *__restrict__ x, double *__restrict__ z, int *counters, int nblk,
        int *status, long spin_limit)
 {
-    trsv_body<BWD, T, BS>(L, ld, dinv, rhs, x, z, counters, nblk, status, spin_limit);
+    trsv_body<BWD>(L, ld, dinv, rhs, x, z, counters, nblk, status, spin_limit);
 }
 
 // One triangular solve of the FP32 factor with one 128-row block per
@@ -683,18 +651,6 @@ void launch_refine_begin(hipStream_t s, double *y_tmp, double *rhs, int64_t n, i
                        counters, status);
 }
 
-template <typename T, int BS>
-void prec_apply(hipStream_t s, const T *L, int64_t npad, const T *dinv, const double *r, double *y_tmp, double *z,
-                int *counters, int *status, long spin_limit)
-{
-    const int nblk = (int)(npad / BS);  // even: npad is a multiple of 256
-    double *rhs = const_cast<double *>(r);  // the forward solve only reads it
-    hipLaunchKernelGGL((k_trsv<false, T, BS>), dim3(nblk / 2), dim3(256), 0, s, L, npad, dinv, rhs, y_tmp, z, counters,
-                       nblk, status, spin_limit);
-    hipLaunchKernelGGL((k_trsv<true, T, BS>), dim3(nblk / 2), dim3(256), 0, s, L, npad, dinv, y_tmp, z,
-                       (double *)nullptr, counters, nblk, status, spin_limit);
-}
-
 void launch_prec_apply(hipStream_t s, const float *L, int64_t npad, const float *dinv,
                        const double *r, double *y_tmp, double *z, int *counters, int *status, const float *Q,
                        long spin_limit, Gate gate)
@@ -721,7 +677,12 @@ void launch_chol64_solve(hipStream_t s, const double *L, int64_t npad, const dou
                          double *y_tmp, double *z, int *counters, int *status,
                         long spin_limit)
 {
-    prec_apply<double, 64>(s, L, npad, dinv, r, y_tmp, z, counters, status, spin_limit);
+    const int nblk = (int)(npad / 64);  // even: npad is a multiple of 256
+    double *rhs = const_cast<double *>(r);  // the forward solve only reads it
+    hipLaunchKernelGGL(k_trsv<false>, dim3(nblk / 2), dim3(256), 0, s, L, npad, dinv, rhs, y_tmp, z, counters, nblk,
+                       status, spin_limit);
+    hipLaunchKernelGGL(k_trsv<true>, dim3(nblk / 2), dim3(256), 0, s, L, npad, dinv, y_tmp, z, (double *)nullptr,
+                       counters, nblk, status, spin_limit);
 }
 
 }  // namespace mag
