@@ -140,7 +140,8 @@ struct SParams {
 struct Gate {
     const double *norm = nullptr;
     double tol = 0.0;
-    __device__ __forceinline__ bool closed() const { return norm && !(norm[0] > tol); }
+    __device__ __forceinline__ double value() const { return norm ? norm[0] : INFINITY; }
+    __device__ __forceinline__ bool closed() const { return !(value() > tol); }
 };
 
 // FP64 kernel entry exp(-t d), d = sqrt(s), for the matrix-free products.

@@ -364,8 +364,9 @@ __device__ __forceinline__ void trsv1_body(const float *__restrict__ L, int64_t 
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (tid == 0) {
         // (the tickets are taken, and left for the next solve, behind a closed gate too)
+        const double g = gate.value();  // on its way beside the ticket
         const int ticket = take_ticket<BWD>(counters);
-        s_blk = gate.closed() ? -1 : BWD ? nblk - 1 - ticket : ticket;
+        s_blk = !(g > gate.tol) ? -1 : BWD ? nblk - 1 - ticket : ticket;
     }
     __syncthreads();
     const int b = s_blk;
